@@ -560,6 +560,16 @@ struct SolveStats {
     double rel = 0.0;
 };
 
+// Whether a series' sweeps visit only their front (the nodes that can still change).  A sweep
+// over the front has a fixed cost of about 1 us over a whole one (its marks), which a sweep
+// of a small matrix does not earn back: whole against front solves measured 507 / 536 us at
+// 1.5 M nonzeros (FP64), 393 / 401 at 3.2 M, 660 / 667 at 12.6 M, 1171 / 1117 at 20 M,
+// 2338 / 2139 at 70 M, 19.98 / 13.00 ms at 424 M.  A matrix that lies mostly in nodes of more than 64
+// couplings takes whole sweeps: each of them has an input that moves until the end (the
+// 11.5 strongest couplings per voxel: 71.5 ms whole, 72.0 over the front).
+constexpr int64_t kFrontMinNnz = 16000000;
+bool front_pays(const Scene &s) { return s.nnz - s.nnz_big >= kFrontMinNnz && s.nnz_big <= s.nnz / 2; }
+
 // FP32/FP64 Neumann sweeps x <- rhs + K x from x = 0.  Every sweep yields two measures
 // of its update dx: the L1 norm, which shrinks at least by the factor max_a T_a rho < 1
 // per sweep and so gives the sweep ratio q, and the largest per-edge relative update
@@ -576,6 +586,8 @@ sg_status neumann(Scene &s, hipStream_t st, Exec &tm, const Real *rhs, Real *&xa
     const int grid = spmv_grid<Real>(s, st, rhs, xa, xb, tm.autotune);
     std::vector<double> l1, rel;  // measures of consecutive monitored sweeps
     int chunk = 2, first = 1;
+    const bool front = front_pays(s);
+    int t = 0;  // sweeps of this series so far (the copied first iterate is none)
     stalled = 0;
     double host[64];
     double *meas = s.scal + 128;  // [32][2] measures of the chunk's sweeps
@@ -593,27 +605,30 @@ sg_status neumann(Scene &s, hipStream_t st, Exec &tm, const Real *rhs, Real *&xa
                     launch_first<Real>(s, st, rhs, xb, out(c));
                 } else {
                     hipEvent_t e0 = tm.mark(), e1 = tm.fresh();
-                    launch_spmv<Real>(s, st, rhs, xa, xb, out(c), grid, e1);
+                    launch_spmv<Real>(s, st, rhs, xa, xb, out(c), grid, e1, true, front ? front_of(t + 1 + c - n_copy) : 0);
                     tm.spmv.push_back({e0, e1});
                     tm.monitored += out(c) != nullptr;
                 }
                 std::swap(xa, xb);
             }
         } else {
+            // a chunk's launches depend on t through the sweeps before the front's and the rotation of its marks
+            const int phase = !front ? 0 : (t < kFrontFirst ? t : kFrontFirst + t % 3);
             const GraphKey key{1, (uintptr_t)chunk, (uintptr_t)rhs, (uintptr_t)xa, (uintptr_t)xb, (uintptr_t)grid,
-                               sizeof(Real), (uintptr_t)first};
+                               sizeof(Real), (uintptr_t)(first + 2 * phase)};
             Real *a0 = xa, *b0 = xb;
             SG_TRY(run_chunk(s, st, key, tm.graphs, [&]() {
                 Real *a = a0, *b = b0;
                 for (int c = 0; c < chunk; ++c) {
                     if (c < n_copy) launch_first<Real>(s, st, rhs, b, out(c));
-                    else launch_spmv<Real>(s, st, rhs, a, b, out(c), grid, nullptr);
+                    else launch_spmv<Real>(s, st, rhs, a, b, out(c), grid, nullptr, true, front ? front_of(t + 1 + c - n_copy) : 0);
                     std::swap(a, b);
                 }
             }));
             if (chunk & 1) std::swap(xa, xb);
         }
         ss.sweeps += chunk - n_copy;
+        t += chunk - n_copy;
         SG_HIP(hipGetLastError());
         SG_TRY(read_scalars(s, st, meas, host, 2 * chunk));
         // the first chunk (two sweeps) is monitored whole; later ones in their last two
@@ -1329,7 +1344,7 @@ void free_scene_impl(Scene *s) {
                     s->tab, s->lut, s->hull, s->rev, s->nodeoff, s->row_ptr, s->col_idx, s->scan_tmp, s->tau_s, s->tau_a, s->tsun_s,
                     s->tsun_a, s->T, s->Tsun, s->rho, s->val, s->S, s->x, s->y, s->c_rhs, s->c_a, s->c_b, s->qsun,
                     s->q, s->bS, s->bx, s->by, s->brho, s->bsrc, s->lam_buf, s->x64, s->r64, s->gm_V, s->partial, s->meas, s->meas_part, s->scal, s->J, s->pix,
-                    s->gmu_s, s->gmu_a, s->gfrac, s->los_ptr, s->los_node, s->los_t};
+                    s->gmu_s, s->gmu_a, s->gfrac, s->los_ptr, s->los_node, s->los_t, s->front};
     if (s->ctx)
         for (void *p : ptrs) pool_free(s->ctx, p);
     s->bytes = 0;
@@ -1404,6 +1419,7 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
         const int64_t deg = d->adj_ptr[l + 1] - d->adj_ptr[l];
         if (deg > kMaxWaveDegree) {
             bigv.push_back((int)l);
+            s.nnz_big += deg * deg;
             // one direction per workgroup for the colouring, groups for the Voronoi cells
             const int64_t n_in = l < s.n_vol ? deg + 1 : 1;
             const int64_t G = s.sigma_mode == SG_SIGMA_COLOUR ? 1 : qbuild_group_big(s.n_fib);
@@ -1448,6 +1464,7 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
     SG_TRY(dalloc(s, &s.meas, (size_t)s.N * nl));
     SG_TRY(dalloc(s, &s.meas_part, (size_t)node_chunks(s.N, nl) * nl * 2));
     SG_TRY(dalloc(s, &s.scal, 256));
+    SG_TRY(dalloc(s, &s.front, 3 * front_marks(s.N)));
     SG_TRY(dalloc(s, &s.J, (size_t)s.N * nl));
     SG_TRY(dalloc(s, &s.pix, (size_t)s.npx * nl));
     if (nl == 1) {
@@ -1693,6 +1710,7 @@ uint64_t reservations(const sg_scene_desc *d, const sg_solve_opts *o, bool with_
     if (n_big) b += a(n_big, 4) + a(n_big + 1, 8) * 2 + a(n_rows, 16);
     b += a(e * nl, 8) * 2 + a(std::max<uint64_t>((n + 3) / 4, 65 * 1024), 8) +
          a(n * nl, 8) + a((uint64_t)node_chunks((int)n, (int)nl) * nl * 2, 8) + a(256, 8) +
+         a(3 * front_marks((int)n), 1) +
          a(n * nl, 8) + a(npx * nl, 8);
     if (nl == 1) {
         b += a(e, 4) * 9 + a(n, 4) * 4 + a(z, 4);

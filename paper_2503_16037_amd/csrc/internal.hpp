@@ -83,6 +83,7 @@ struct Scene {
     // nodes of degree above 64 (handled by their own kernels: one workgroup per node in the
     // sweeps, one per (node, incoming direction) in the phase cells)
     int n_big = 0;
+    int64_t nnz_big = 0;          // their share of nnz
     int *big = nullptr;           // [n_big] node ids, ascending
     long long *bigdir = nullptr;  // [n_big + 1] prefix of their groups of incoming directions
     long long n_bigdir = 0;
@@ -160,6 +161,10 @@ struct Scene {
     double *scal = nullptr;  // device scalars
     double *J = nullptr;     // [N * n_lambda] node radiance toward the sensor
     double *pix = nullptr;   // [n_lambda * npx] radiance staging for host outputs
+
+    // sweeps over the front (solve.hip): three arrays of front_marks(N) byte marks, the nodes
+    // that this sweep visits, those the next one will, and those of the one before
+    unsigned char *front = nullptr;
 
     std::map<GraphKey, SceneGraph> graphs;  // captured sweep chunks
     // a second stream for the sun march, which runs beside the structure pass and the edge
@@ -262,12 +267,25 @@ void launch_qbuild(Scene &s, hipStream_t st, int write_q);
 int qbuild_group(int NF);
 int qbuild_group_big(int NF);
 
+// Which nodes a sweep visits: its argument front is 0 (all), kFrontFirst (all, marking the
+// nodes the next sweep has to visit) or higher (the marked ones, marking those of the next).
+// Sweep t of a series (1: the first after the copied iterate) takes front_of(t): light reaches
+// nearly every node in the first two sweeps, so marking starts with the third.
+constexpr int kFrontFirst = 3;
+inline int front_of(int t) { return t >= kFrontFirst ? t : 0; }
+// marks per array: the nodes, rounded up to whole 8-byte words
+__host__ __device__ inline size_t front_marks(int N) { return ((size_t)N + 7) / 8 * 8; }
+// the marks of the nodes sweep t visits
+inline unsigned char *front_marks_of(const Scene &s, int t) { return s.front + front_marks(s.N) * (t % 3); }
+// the shift from row to row of a front's nodes over W wavefronts (front_node): 0.618 W
+inline int front_skew(int W) { return (int)(0.618 * W); }
+
 template <class Real>
 // one sweep y = S + K x; out[0..1] = measures of y - x (see launch_measures);
 // after: an event recorded right after the sweep kernel; with_big = false leaves out the
 // nodes of degree above 64 (the launch-shape tuner times the regular kernel alone)
 void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y, double *out, int grid = 0,
-                 hipEvent_t after = nullptr, bool with_big = true);
+                 hipEvent_t after = nullptr, bool with_big = true, int front = 0);
 // the first Neumann iterate from x = 0: x = rhs; out[0..1] = measures of that update
 template <class Real>
 void launch_first(Scene &s, hipStream_t st, const Real *rhs, Real *x, double *out);
@@ -278,7 +296,8 @@ void launch_apply_imk64(Scene &s, hipStream_t st, const double *v, double *w);
 int spmv_blocks(const Scene &s);
 // Convergence measures of the last sweep or residual, reduced over nodes:
 // out[2 lambda] = sum over edges of |change|, out[2 lambda + 1] = max over edges of
-// |change| / (|value| + 1e-30), for lambda < nl.
+// |change| / (|value| + 1e-30), for lambda < nl; only != NULL: over the marked nodes (the others
+// were not visited and changed nothing).
 // nodes per reduction chunk: 2048 for one wavelength; about sqrt(N) for several, which
 // balances the chunk pass (chunk length) against the final pass (number of chunks)
 inline int node_chunk(int N, int nl) {
@@ -288,7 +307,7 @@ inline int node_chunk(int N, int nl) {
     return c;
 }
 inline int node_chunks(int N, int nl) { return (N + node_chunk(N, nl) - 1) / node_chunk(N, nl); }
-void launch_measures(Scene &s, int nl, double *out, hipStream_t st);
+void launch_measures(Scene &s, int nl, double *out, hipStream_t st, const unsigned char *only = nullptr);
 void launch_dot_multi(const double *V, int64_t ld, int k, const double *w, int64_t n, double *partial, int nblk,
                       double *out, hipStream_t st);
 void launch_axpy_multi(double *w, const double *V, int64_t ld, int k, const double *h, int64_t n, hipStream_t st);

@@ -8,6 +8,11 @@
 // the d_l inputs x[rev(out(l))] once and never reads a column index.  Every reduction has a fixed order (wave
 // butterfly, then block, then one final block), so results are bit-identical
 // from run to run.
+//
+// Sweeps over the front.  From its third sweep on a series visits only the nodes that can
+// still change: a node whose gathered inputs and own rows are the bits of the sweep before
+// gives the same bits again, so skipping it leaves every iterate as a whole sweep leaves
+// it (k_spmv_front).
 #include <algorithm>
 
 #include "device.hpp"
@@ -27,12 +32,16 @@ constexpr int kVecThreads = 256;
 // consecutive nodes -> part[c][lambda][2], then over the chunks in a fixed order, so the
 // result does not depend on how the sweep kernel was launched.  With several wavelengths
 // the lanes run over wavelengths (coalesced rows) and the wavefronts over nodes.
+// only != NULL: a sweep over the front, which left the nodes without a mark as they were
+// (measures zero).
 __global__ __launch_bounds__(kSpmvThreads) void k_measure_chunks(const float2 *__restrict__ meas, int N, int nl,
-                                                                int cn, double *__restrict__ part) {
+                                                                int cn, const unsigned char *__restrict__ only,
+                                                                double *__restrict__ part) {
     const int c = blockIdx.x, n0 = c * cn, n1 = min(N, n0 + cn);
     if (nl == 1) {
         double t = 0.0, u = 0.0;
         for (int i = n0 + (int)threadIdx.x; i < n1; i += kSpmvThreads) {
+            if (only && !only[i]) continue;
             const float2 m = meas[i];
             t += (double)m.x;
             u = fmax(u, (double)m.y);
@@ -53,6 +62,7 @@ __global__ __launch_bounds__(kSpmvThreads) void k_measure_chunks(const float2 *_
     if (lam < nl)
 #pragma unroll 8
         for (int i = n0 + w; i < n1; i += kW) {
+            if (only && !only[i]) continue;
             const float2 m = meas[(long long)i * nl + lam];
             t += (double)m.x;
             u = fmax(u, (double)m.y);
@@ -202,15 +212,79 @@ __device__ __forceinline__ NodeMeta load_meta(const long long *__restrict__ adj_
     return m;
 }
 
-// y = S + K x, persistent over groups of four nodes, one wavefront per node.  With
-// monitor != 0, meas[node] = (sum, max relative) of the node's updates y - x.
-template <class Real>
-__global__ __launch_bounds__(kSpmvThreads) void k_spmv(int N, int groups, const long long *__restrict__ adj_ptr,
+// True when a sweep's new value yn keeps its edge's head (and tail) node in the next
+// sweep: its bits moved, or it is not finite (the measures of an overflowed iterate have to
+// stay non-finite in every later sweep).
+__device__ __forceinline__ bool moved(float yn, float xb) {
+    return __float_as_int(yn) != __float_as_int(xb) || !(fabsf(yn) < __builtin_inff());
+}
+__device__ __forceinline__ bool moved(double yn, double xb) {
+    return __double_as_longlong(yn) != __double_as_longlong(xb) || !(fabs(yn) < __builtin_inf());
+}
+
+// One node of y = S + K x by one wavefront.  With monitor != 0, meas[l] = (sum, max
+// relative) of the node's updates y - x.  With kMark, the nodes the next sweep has to visit
+// are marked: a row whose value moved marks its head node (it is an input there) and its own
+// node (the other buffer still holds the value before) with a byte store of 1, which any
+// number of wavefronts may repeat.
+template <class Real, bool kMark>
+__device__ __forceinline__ void sweep_node(int N, int l, const NodeMeta &cur, int lane,
+                                           const long long *__restrict__ adj_ptr,
+                                           const long long *__restrict__ nodeoff, const int *__restrict__ rev,
+                                           const Real *__restrict__ val, const Real *__restrict__ S,
+                                           const Real *__restrict__ x, Real *__restrict__ y,
+                                           float2 *__restrict__ meas, int monitor, int dmax, Real *blk,
+                                           const int *__restrict__ adj_idx, unsigned char *__restrict__ mark) {
+    const long long off = cur.off, base = cur.base;
+    const int d = cur.d;
+    if (d > kWave) return;  // a node of higher degree: k_spmv_big
+    if (d == 0) {
+        if (monitor && lane == 0) meas[l] = make_float2(0.f, 0.f);
+        return;
+    }
+    if (!SG_IN(base + (long long)d * d - 1, nodeoff[N], 0x301)) return;
+    const bool act = lane < d;
+    const long long b = off + min(lane, d - 1);  // lanes past d repeat the last row
+    // the index load first, so that the gather waits for it alone
+    const int rv0 = rev[b];
+    const int rv = SG_IN(rv0, adj_ptr[N], 0x302) ? rv0 : (int)b;
+    const Real sb = S[b];
+    const Real xb = kMark || monitor ? x[b] : (Real)0;  // the previous value only for the marks and measures
+    const Real xl = x[rv];
+    const int head = kMark ? adj_idx[b] : 0;
+    const Real acc = node_row<Real>(val + base, d <= dmax ? blk : nullptr, d, lane, xl);
+    double r = 0.0, u = 0.0;
+    bool mv = false;
+    if (act) {
+        const Real yn = sb + acc;
+        y[b] = yn;
+        if (kMark) mv = moved(yn, xb);
+        r = fabs((double)yn - (double)xb);
+        // a NaN here is dropped by the max below, but it also makes this sweep's L1 sum
+        // non-finite, which the solve policy checks first (guarding u as well would cost
+        // this kernel two registers and a wave per SIMD)
+        u = r / (fabs((double)yn) + kRelFloor);
+    }
+    if (kMark) {
+        if (mv && SG_IN(head, N, 0x307)) mark[head] = 1;
+        if (__ballot(mv) && lane == 0) mark[l] = 1;
+    }
+    if (monitor) {
+        r = wave_sum(r);
+        u = wave_max(u);
+        if (lane == 0) meas[l] = make_float2((float)r, (float)u);
+    }
+}
+
+// y = S + K x, persistent over groups of four nodes, one wavefront per node (see sweep_node)
+template <class Real, bool kMark>
+__global__ __launch_bounds__(kSpmvThreads) void k_spmv(int N, const long long *__restrict__ adj_ptr,
                                                       const long long *__restrict__ nodeoff,
                                                       const int *__restrict__ rev, const Real *__restrict__ val,
                                                       const Real *__restrict__ S, const Real *__restrict__ x,
                                                       Real *__restrict__ y, float2 *__restrict__ meas, int monitor,
-                                                      int dmax) {
+                                                      int dmax, const int *__restrict__ adj_idx,
+                                                      unsigned char *__restrict__ mark) {
     extern __shared__ unsigned char smem_raw[];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     Real *blk = dmax ? reinterpret_cast<Real *>(smem_raw) + (size_t)w * dmax * dmax : nullptr;
@@ -221,37 +295,52 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(int N, int groups, const 
     for (; l < N; l += step) {
         const NodeMeta cur = nm;
         nm = load_meta(adj_ptr, nodeoff, l + step, N);
-        const long long off = cur.off, base = cur.base;
-        const int d = cur.d;
-        if (d > kWave) continue;  // a node of higher degree: k_spmv_big
-        if (d == 0) {
-            if (monitor && lane == 0) meas[l] = make_float2(0.f, 0.f);
-            continue;
-        }
-        if (!SG_IN(base + (long long)d * d - 1, nodeoff[N], 0x301)) continue;
-        const bool act = lane < d;
-        const long long b = off + min(lane, d - 1);  // lanes past d repeat the last row
-        // the index load first, so that the gather waits for it alone
-        const int rv0 = rev[b];
-        const int rv = SG_IN(rv0, adj_ptr[N], 0x302) ? rv0 : (int)b;
-        const Real sb = S[b];
-        const Real xb = monitor ? x[b] : (Real)0;  // the previous value only for the measures
-        const Real xl = x[rv];
-        const Real acc = node_row<Real>(val + base, d <= dmax ? blk : nullptr, d, lane, xl);
-        double r = 0.0, u = 0.0;
-        if (act) {
-            const Real yn = sb + acc;
-            y[b] = yn;
-            r = fabs((double)yn - (double)xb);
-            // a NaN here is dropped by the max below, but it also makes this sweep's L1 sum
-            // non-finite, which the solve policy checks first (guarding u as well would cost
-            // this kernel two registers and a wave per SIMD)
-            u = r / (fabs((double)yn) + kRelFloor);
-        }
-        if (monitor) {
-            r = wave_sum(r);
-            u = wave_max(u);
-            if (lane == 0) meas[l] = make_float2((float)r, (float)u);
+        sweep_node<Real, kMark>(N, l, cur, lane, adj_ptr, nodeoff, rev, val, S, x, y, meas, monitor, dmax, blk, adj_idx,
+                                mark);
+    }
+}
+
+// The nodes of a sweep over the front, for both its kernels: wavefront w of W takes, of
+// every W consecutive nodes (row j), the one at (w + j (0.618 W)) mod W.  The nodes that
+// change lie together (a cloud, a plume), and this spreads them evenly over the wavefronts;
+// a wavefront then reads the marks of 64 of its nodes with one load.
+__device__ __forceinline__ int front_node(int w, int j, int W, int skew) {
+    return j * W + (int)(((unsigned)w + (unsigned)j * (unsigned)skew) % (unsigned)W);
+}
+
+// The same sweep over the marked nodes only.  y holds the iterate before x, so the rows of
+// an unmarked node, whose inputs and values did not move in the sweep before, are already
+// what this sweep would write; its measures are zero (k_measure_chunks reads the marks).
+// spent: the marks of the sweep before, cleared here for the sweep after the next.
+// Bound by the stream of the visited blocks, as a whole sweep, and for few marked nodes by
+// the latency of one round of marks; the metadata is loaded one node ahead.
+// 128x128x48 cloud, sweeps 4 to 20: 0.44 ms each, 7.5 ms in all -> 0.20 ms falling to 0.01,
+// 0.86 ms in all (a list of the marked nodes compacted by a kernel of its own: 0.72 and 0.11).
+template <class Real>
+__global__ __launch_bounds__(kSpmvThreads) void k_spmv_front(
+    int N, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff, const int *__restrict__ rev,
+    const Real *__restrict__ val, const Real *__restrict__ S, const Real *__restrict__ x, Real *__restrict__ y,
+    float2 *__restrict__ meas, int monitor, int dmax, const int *__restrict__ adj_idx,
+    const unsigned char *__restrict__ now, unsigned char *__restrict__ next, unsigned long long *__restrict__ spent,
+    int skew) {
+    extern __shared__ unsigned char smem_raw[];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    Real *blk = dmax ? reinterpret_cast<Real *>(smem_raw) + (size_t)w * dmax * dmax : nullptr;
+    const int W = gridDim.x * kNodesPerSpmvBlock, wv = blockIdx.x * kNodesPerSpmvBlock + w;
+    for (int t = blockIdx.x * kSpmvThreads + threadIdx.x; t < (N + 7) / 8; t += gridDim.x * kSpmvThreads) spent[t] = 0ull;
+    for (int j0 = 0; j0 * (long long)W < N; j0 += 64) {
+        const int mine = (j0 + lane) * (long long)W < N ? front_node(wv, j0 + lane, W, skew) : N;
+        unsigned long long todo = __ballot(mine < N && now[min(mine, N - 1)]);
+        int l = todo ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(todo)) : N;
+        NodeMeta nm = load_meta(adj_ptr, nodeoff, l, N);
+        while (todo) {
+            todo &= todo - 1;
+            const NodeMeta cur = nm;
+            const int lc = l;
+            l = todo ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(todo)) : N;
+            nm = load_meta(adj_ptr, nodeoff, l, N);
+            sweep_node<Real, true>(N, lc, cur, lane, adj_ptr, nodeoff, rev, val, S, x, y, meas, monitor, dmax, blk,
+                                   adj_idx, next);
         }
     }
 }
@@ -261,9 +350,12 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(int N, int groups, const 
 template <class Real>
 __global__ __launch_bounds__(kSpmvThreads) void k_first(int N, const long long *__restrict__ adj_ptr,
                                                        const Real *__restrict__ rhs, Real *__restrict__ x,
-                                                       float2 *__restrict__ meas) {
+                                                       float2 *__restrict__ meas, unsigned char *__restrict__ mark) {
     // two nodes per wavefront, one per 32-lane half (a node has ~24 rows)
     const int l = blockIdx.x * (2 * kNodesPerSpmvBlock) + (threadIdx.x >> 5), lane = threadIdx.x & 31;
+    // no node is marked yet: the three marks of this workgroup's eight nodes
+    if (threadIdx.x < 3)
+        *reinterpret_cast<unsigned long long *>(mark + threadIdx.x * front_marks(N) + (size_t)blockIdx.x * 8) = 0ull;
     if (l >= N) return;  // a half past the last node exits; the shuffles below stay within a half
     const long long off = adj_ptr[l];
     const int d = (int)(adj_ptr[l + 1] - off);
@@ -395,12 +487,17 @@ __global__ __launch_bounds__(256) void k_spmv_big(int nbig, const int *__restric
                                                  const long long *__restrict__ nodeoff, const int *__restrict__ rev,
                                                  const Real *__restrict__ val, const Real *__restrict__ S,
                                                  const Real *__restrict__ x, Real *__restrict__ y,
-                                                 double2 *__restrict__ part, int monitor) {
+                                                 double2 *__restrict__ part, int monitor,
+                                                 const int *__restrict__ adj_idx, unsigned char *__restrict__ mark,
+                                                 const unsigned char *__restrict__ only) {
     extern __shared__ unsigned char smem_raw[];
     Real *xin = reinterpret_cast<Real *>(smem_raw);
     const long long wg = blockIdx.x;
     const int b = big_locate(nbig, bigrow, wg);
     const int l = big[b];
+    // a sweep over the front (only: its marks) leaves out the nodes that cannot change, and
+    // mark != NULL marks the nodes of the next one (see k_spmv)
+    if (only && !only[l]) return;
     const long long off = adj_ptr[l], base = nodeoff[l];
     const int d = (int)(adj_ptr[l + 1] - off);
     for (int m = threadIdx.x; m < d; m += 256) xin[m] = x[rev[off + m]];
@@ -411,9 +508,14 @@ __global__ __launch_bounds__(256) void k_spmv_big(int nbig, const int *__restric
         const Real acc = big_row<Real>(val + base, xin, d, n);
         const Real yn = S[off + n] + acc;
         y[off + n] = yn;
-        if (monitor) {
-            r = fabs((double)yn - (double)x[off + n]);
+        if (mark || monitor) {
+            const Real xb = x[off + n];
+            r = fabs((double)yn - (double)xb);
             u = keep_nan(r / (fabs((double)yn) + kRelFloor));
+            if (mark && moved(yn, xb)) {
+                mark[adj_idx[off + n]] = 1;
+                mark[l] = 1;
+            }
         }
     }
     if (monitor) {
@@ -480,9 +582,10 @@ __global__ __launch_bounds__(256) void k_apply_imk64_big(int nbig, const int *__
 // meas[node] of the nodes of degree above 64: their chunks' (sum, max) folded in order.
 __global__ __launch_bounds__(256) void k_big_measures(int nbig, const int *__restrict__ big,
                                                      const long long *__restrict__ bigrow,
-                                                     const double2 *__restrict__ part, float2 *__restrict__ meas) {
+                                                     const double2 *__restrict__ part, float2 *__restrict__ meas,
+                                                     const unsigned char *__restrict__ only) {
     const int b = blockIdx.x * 256 + threadIdx.x;
-    if (b >= nbig) return;
+    if (b >= nbig || (only && !only[big[b]])) return;  // not visited: zero by its mark
     double r = 0.0, u = 0.0;
     for (long long c = bigrow[b]; c < bigrow[b + 1]; ++c) {
         r += part[c].x;
@@ -593,29 +696,46 @@ static int lds_dmax(const Scene &s) { return block_lds<Real>(s) ? std::min(s.dma
 // also run persistent over fewer workgroups; the tuner measures both)
 static int default_grid(const Scene &s) { return spmv_blocks(s); }
 
+// Workgroups of a sweep over the front: eight wavefronts per SIMD (the most that are resident)
+static int front_grid(const Scene &s) { return std::min(spmv_blocks(s), 2048); }
+
 template <class Real>
 void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y, double *out, int grid,
-                 hipEvent_t after, bool with_big) {
+                 hipEvent_t after, bool with_big, int front) {
     if (grid <= 0) grid = default_grid(s);
     grid = std::min(grid, spmv_blocks(s));
-    hipLaunchKernelGGL((k_spmv<Real>), dim3(grid), dim3(kSpmvThreads), block_lds<Real>(s), st, s.N, spmv_blocks(s),
-                       s.adj_ptr, s.nodeoff, s.rev, (const Real *)s.val, S, x, y, s.meas, out ? 1 : 0, lds_dmax<Real>(s));
+    const size_t lds = block_lds<Real>(s);
+    const int dl = lds_dmax<Real>(s), mon = out ? 1 : 0;
+    const Real *val = (const Real *)s.val;
+    unsigned char *next = front ? front_marks_of(s, front + 1) : nullptr;
+    const unsigned char *only = front > kFrontFirst ? front_marks_of(s, front) : nullptr;
+    if (only) {
+        const int g = front_grid(s);
+        hipLaunchKernelGGL((k_spmv_front<Real>), dim3(g), dim3(kSpmvThreads), lds, st, s.N, s.adj_ptr, s.nodeoff, s.rev,
+                           val, S, x, y, s.meas, mon, dl, s.adj_idx, only, next,
+                           (unsigned long long *)front_marks_of(s, front + 2), front_skew(g * kNodesPerSpmvBlock));
+    } else if (front) {
+        hipLaunchKernelGGL((k_spmv<Real, true>), dim3(grid), dim3(kSpmvThreads), lds, st, s.N, s.adj_ptr, s.nodeoff,
+                           s.rev, val, S, x, y, s.meas, mon, dl, s.adj_idx, next);
+    } else {
+        hipLaunchKernelGGL((k_spmv<Real, false>), dim3(grid), dim3(kSpmvThreads), lds, st, s.N, s.adj_ptr, s.nodeoff,
+                           s.rev, val, S, x, y, s.meas, mon, dl, s.adj_idx, next);
+    }
     if (s.n_big && with_big) {
         hipLaunchKernelGGL((k_spmv_big<Real>), dim3(s.n_bigrow), dim3(256), sizeof(Real) * s.dmax, st, s.n_big, s.big,
-                           s.bigrow, s.adj_ptr, s.nodeoff, s.rev, (const Real *)s.val, S, x, y, s.big_part,
-                           out ? 1 : 0);
+                           s.bigrow, s.adj_ptr, s.nodeoff, s.rev, val, S, x, y, s.big_part, mon, s.adj_idx, next, only);
         if (out)
             hipLaunchKernelGGL(k_big_measures, dim3((s.n_big + 255) / 256), dim3(256), 0, st, s.n_big, s.big, s.bigrow,
-                               s.big_part, s.meas);
+                               s.big_part, s.meas, only);
     }
     if (after) (void)hipEventRecord(after, st);
-    if (out) launch_measures(s, 1, out, st);
+    if (out) launch_measures(s, 1, out, st, only);
 }
 
 template <class Real>
 void launch_first(Scene &s, hipStream_t st, const Real *rhs, Real *x, double *out) {
     hipLaunchKernelGGL((k_first<Real>), dim3((s.N + 2 * kNodesPerSpmvBlock - 1) / (2 * kNodesPerSpmvBlock)),
-                       dim3(kSpmvThreads), 0, st, s.N, s.adj_ptr, rhs, x, s.meas);
+                       dim3(kSpmvThreads), 0, st, s.N, s.adj_ptr, rhs, x, s.meas, s.front);
     launch_measures(s, 1, out, st);
 }
 
@@ -628,7 +748,7 @@ void launch_residual64(Scene &s, hipStream_t st, const Real *S, const double *x6
         hipLaunchKernelGGL((k_residual64_big<Real>), dim3(s.n_bigrow), dim3(256), sizeof(double) * s.dmax, st, s.n_big,
                            s.big, s.bigrow, s.adj_ptr, s.nodeoff, s.rev, (const Real *)s.val, S, x64, r64, s.big_part);
         hipLaunchKernelGGL(k_big_measures, dim3((s.n_big + 255) / 256), dim3(256), 0, st, s.n_big, s.big, s.bigrow,
-                           s.big_part, s.meas);
+                           s.big_part, s.meas, (const unsigned char *)nullptr);
     }
     launch_measures(s, 1, out, st);
 }
@@ -642,11 +762,11 @@ void launch_apply_imk64(Scene &s, hipStream_t st, const double *v, double *w) {
                            s.n_big, s.big, s.bigrow, s.adj_ptr, s.nodeoff, s.rev, (const Real *)s.val, v, w);
 }
 
-void launch_measures(Scene &s, int nl, double *out, hipStream_t st) {
+void launch_measures(Scene &s, int nl, double *out, hipStream_t st, const unsigned char *only) {
     const int cn = node_chunk(s.N, nl), nc = (s.N + cn - 1) / cn;
     const int lt = (nl + 63) / 64;
     hipLaunchKernelGGL(k_measure_chunks, dim3(nc, nl == 1 ? 1 : lt), dim3(kSpmvThreads), 0, st,
-                       (const float2 *)s.meas, s.N, nl, cn, s.meas_part);
+                       (const float2 *)s.meas, s.N, nl, cn, only, s.meas_part);
     hipLaunchKernelGGL(k_measure_nodes, dim3(nl == 1 ? 1 : lt), dim3(kSpmvThreads), 0, st,
                        (const double *)s.meas_part, nc, nl, out);
 }
@@ -686,7 +806,7 @@ void launch_fill(Real *a, Real v, int64_t n, hipStream_t st) {
 }
 
 #define SG_INST(R)                                                                                           \
-    template void launch_spmv<R>(Scene &, hipStream_t, const R *, const R *, R *, double *, int, hipEvent_t, bool);               \
+    template void launch_spmv<R>(Scene &, hipStream_t, const R *, const R *, R *, double *, int, hipEvent_t, bool, int);          \
     template void launch_residual64<R>(Scene &, hipStream_t, const R *, const double *, double *, double *); \
     template void launch_first<R>(Scene &, hipStream_t, const R *, R *, double *);                          \
     template void launch_apply_imk64<R>(Scene &, hipStream_t, const double *, double *);                  \
