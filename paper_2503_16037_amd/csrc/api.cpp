@@ -570,6 +570,18 @@ struct SolveStats {
 constexpr int64_t kFrontMinNnz = 16000000;
 bool front_pays(const Scene &s) { return s.nnz - s.nnz_big >= kFrontMinNnz && s.nnz_big <= s.nnz / 2; }
 
+// The same for a batch, by the bytes of a sweep (the values, and the inputs and results of
+// every edge and wavelength): from 128 MB on, where a sweep takes about 30 us.  Half of that
+// made a stream of 8 x 8 x 8 to 48 x 48 x 24 scenes 5 % slower, 128 MB 2 % faster; 12 wavelengths
+// on a 71 x 53 x 29 cloud (0.6 GB) 10.3 -> 7.4 ms, 64 on a 96 x 96 x 32 plume (4.2 GB) 18.0 -> 14.7 ms.
+// (A 32-lane tile, which only a caller or the tuner asks for, takes whole sweeps.)
+bool front_pays_batched(const Scene &s) {
+    return batched_tile(s) != 32 && 4 * s.nnz + 8 * s.E * s.n_lambda >= 8 * kFrontMinNnz;
+}
+// what the launches of a chunk depend on t by: the sweeps before the front's, then the
+// rotation of its marks
+int front_phase(bool front, int t) { return !front ? 0 : (t < 4 ? t : 4 + t % 3); }
+
 // FP32/FP64 Neumann sweeps x <- rhs + K x from x = 0.  Every sweep yields two measures
 // of its update dx: the L1 norm, which shrinks at least by the factor max_a T_a rho < 1
 // per sweep and so gives the sweep ratio q, and the largest per-edge relative update
@@ -612,10 +624,8 @@ sg_status neumann(Scene &s, hipStream_t st, Exec &tm, const Real *rhs, Real *&xa
                 std::swap(xa, xb);
             }
         } else {
-            // a chunk's launches depend on t through the sweeps before the front's and the rotation of its marks
-            const int phase = !front ? 0 : (t < kFrontFirst ? t : kFrontFirst + t % 3);
             const GraphKey key{1, (uintptr_t)chunk, (uintptr_t)rhs, (uintptr_t)xa, (uintptr_t)xb, (uintptr_t)grid,
-                               sizeof(Real), (uintptr_t)(first + 2 * phase)};
+                               sizeof(Real), (uintptr_t)(first + 2 * front_phase(front, t))};
             Real *a0 = xa, *b0 = xb;
             SG_TRY(run_chunk(s, st, key, tm.graphs, [&]() {
                 Real *a = a0, *b = b0;
@@ -1004,6 +1014,8 @@ sg_status neumann_batched(Scene &s, hipStream_t st, Exec &tm, int grid, const fl
     std::vector<int> done(nl, 0);
     int chunk = 3, first = 1;  // the first iterate and the third: a ratio over two sweeps
     int at = 0, at_prev = 0;   // sweep index of the last measure and of the one before
+    const bool front = front_pays_batched(s);
+    int t = 0;  // sweeps of this series so far (the copied first iterate is none)
     stalled = 0;
     double *hist = s.lam_buf + 4 * nl;  // [2][nl][2]: the first iterate's and the chunk's last sweep's
     while (true) {
@@ -1013,9 +1025,14 @@ sg_status neumann_batched(Scene &s, hipStream_t st, Exec &tm, int grid, const fl
         auto sweep = [&](int c, const float *a, float *b, hipEvent_t after) {
             const int mon = (first && c == 0) || c == chunk - 1;
             if (c < n_copy) launch_bfirst(s, st, rhs, b);
-            else launch_spmm(s, st, grid, rhs, a, b, mon);
+            // a batch's nodes keep moving until the last of its wavelengths settles: marking
+            // starts one sweep later
+            const int f = front && c >= n_copy ? front_of(t + c - n_copy) : 0;
+            if (c >= n_copy) launch_spmm(s, st, grid, rhs, a, b, mon, f);
             if (after) (void)hipEventRecord(after, st);
-            if (mon) launch_measures(s, nl, hist + (size_t)(c == chunk - 1 ? 1 : 0) * nl * 2, st);
+            if (mon)
+                launch_measures(s, nl, hist + (size_t)(c == chunk - 1 ? 1 : 0) * nl * 2, st,
+                                f > kFrontFirst ? front_marks_of(s, f) : nullptr);
         };
         if (tm.on) {
             for (int c = 0; c < chunk; ++c) {
@@ -1031,7 +1048,7 @@ sg_status neumann_batched(Scene &s, hipStream_t st, Exec &tm, int grid, const fl
             }
         } else {
             const GraphKey key{2, (uintptr_t)chunk, (uintptr_t)rhs, (uintptr_t)xa, (uintptr_t)xb, (uintptr_t)grid,
-                               (uintptr_t)first, (uintptr_t)s.tile};
+                               (uintptr_t)(first + 2 * front_phase(front, t)), (uintptr_t)s.tile};
             float *a0 = xa, *b0 = xb;
             SG_TRY(run_chunk(s, st, key, tm.graphs, [&]() {
                 float *a = a0, *b = b0;
@@ -1043,6 +1060,7 @@ sg_status neumann_batched(Scene &s, hipStream_t st, Exec &tm, int grid, const fl
             if (chunk & 1) std::swap(xa, xb);
         }
         ss.sweeps += chunk - n_copy;
+        t += chunk - n_copy;
         SG_HIP(hipGetLastError());
         SG_TRY(read_scalars(s, st, hist, host.data(), 4 * nl));
         const double *last = host.data() + 2 * nl;  // [nl][2] of the chunk's last sweep

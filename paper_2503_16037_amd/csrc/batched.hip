@@ -12,8 +12,7 @@
 // wavelengths, column-major within the block) is read once per sweep for all
 // of them.  The grid is persistent: a fixed set of workgroups strides over node
 // groups.
-#include "device.hpp"
-#include "internal.hpp"
+#include "batched_sweep.hpp"
 
 namespace sg {
 
@@ -44,187 +43,18 @@ __global__ __launch_bounds__(256) void k_bnode_coef(int N, int nvol, int nl, con
     bsrc[i] = l < nvol ? ts : mu0 * ts;
 }
 
-// One node per wavefront, lanes = wavelengths (tiles of 64).  The node's phase-cell
-// block Q is staged, coalesced, in the wavefront's LDS slice and its entries are read
-// as broadcasts (measured: reading the columns through scalar loads instead exposes
-// their latency, 1.4x slower at 64 wavelengths); the in-edge list and optical depths
-// are loaded once, coalesced, and broadcast with readlane; eight input gathers are in
-// flight at a time; the node's rows are accumulated in registers, the row count
-// rounded up to a multiple of 8 (DB) so the column reads are unguarded (the LDS slice
-// is padded past the block by 64 floats).
-// kResidual: FP64 residual r = S - x + K x of an FP64 iterate instead of a sweep.
-// exp(-(tau_s + s tau_a)) as one hardware exp2; its relative error (~|tau| 1e-7) is
-// below that of the FP32 path integral itself.  The sweep and the FP64 residual use
-// the same function, so iterative refinement sees one matrix.
-__device__ __forceinline__ float edge_T(float ts, float ta, float s) {
-    return __builtin_amdgcn_exp2f(-(ts + s * ta) * 1.4426950408889634f);
-}
-
-// n passes of 64 consecutive block elements from t0 into the wavefront's LDS slice
-template <int n>
-__device__ __forceinline__ void stage_q(const float *__restrict__ qg, float *__restrict__ qs, int t0, int nq,
-                                        int lane) {
-    float v[n];
-#pragma unroll
-    for (int j = 0; j < n; ++j) v[j] = qg[min(t0 + j * 64 + lane, nq - 1)];
-#pragma unroll
-    for (int j = 0; j < n; ++j) qs[min(t0 + j * 64 + lane, nq - 1)] = v[j];
-}
-
-template <int DB, class XT, class YT, class AccT, bool kResidual>
-__device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, float s, int nl, int monitor,
-                                            float *__restrict__ qs, const long long *__restrict__ adj_ptr,
-                                            const long long *__restrict__ nodeoff, const int *__restrict__ rev,
-                                            const float *__restrict__ q, const float *__restrict__ qsun,
-                                            const float *__restrict__ tau_s, const float *__restrict__ tau_a,
-                                            const float *__restrict__ brho, const float *__restrict__ bsrc,
-                                            const float *__restrict__ rhs, const XT *__restrict__ x,
-                                            YT *__restrict__ y) {
-    constexpr int kU = 8;
-    const long long off = adj_ptr[l];
-    const int d = (int)(adj_ptr[l + 1] - off);
-    const long long base = nodeoff[l];
-    // per in-edge data in lane m (lanes past d repeat the last in-edge), then the node's
-    // phase-cell block into this wavefront's LDS slice: as many 64-element passes as the
-    // block needs, at most 16 at a time (a wave-uniform switch into straight-line copies,
-    // so the loads are issued back to back; out-of-range lanes reload and rewrite the last
-    // element)
-    const long long em = off + min(lane, d - 1);
-    const int rv = rev[em];
-    const float ts = tau_s[em], ta = tau_a[em];
-    {
-        const int nq = d * d;
-        for (int t0 = 0; t0 < nq; t0 += 64 * 16) {
-            switch (min(16, (nq - t0 + 63) >> 6)) {
-#define SG_STAGE_CASE(n) \
-    case n: stage_q<n>(q + base, qs, t0, nq, lane); break;
-                SG_STAGE_CASE(1) SG_STAGE_CASE(2) SG_STAGE_CASE(3) SG_STAGE_CASE(4) SG_STAGE_CASE(5)
-                SG_STAGE_CASE(6) SG_STAGE_CASE(7) SG_STAGE_CASE(8) SG_STAGE_CASE(9) SG_STAGE_CASE(10)
-                SG_STAGE_CASE(11) SG_STAGE_CASE(12) SG_STAGE_CASE(13) SG_STAGE_CASE(14) SG_STAGE_CASE(15)
-                default: stage_q<16>(q + base, qs, t0, nq, lane);
-#undef SG_STAGE_CASE
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-    }
-    AccT acc[DB];
-#pragma unroll
-    for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
-    for (int m0 = 0; m0 < d; m0 += kU) {
-        XT xv[kU];
-#pragma unroll
-        for (int j = 0; j < kU; ++j) {
-            const int m = min(m0 + j, 63);
-            const int r = __builtin_amdgcn_readlane(rv, m);
-            xv[j] = (m0 + j < d && lv) ? x[(long long)r * nl + lam] : (XT)0;
-        }
-#pragma unroll
-        for (int j = 0; j < kU; ++j) {
-            const int m = m0 + j;
-            if (m < d) {
-                const float tsm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ts), m));
-                const float tam = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ta), m));
-                const AccT xm = (AccT)edge_T(tsm, tam, s) * (AccT)xv[j];
-                const float *qm = qs + m * d;  // column m: Q[n][m], n contiguous (LDS, uniform address)
-#pragma unroll
-                for (int n = 0; n < DB; ++n) acc[n] += (AccT)qm[n] * xm;
-            }
-        }
-    }
-    double sum = 0.0, mrel = 0.0;  // convergence measures of this node's rows
-    if (lv) {
-        const float rl = brho[(long long)l * nl + lam];
-        const float sl = bsrc[(long long)l * nl + lam];
-#pragma unroll
-        for (int n = 0; n < DB; ++n) {
-            if (n < d) {
-                const long long b = off + n;
-                const long long bi = b * nl + lam;
-                if (kResidual) {
-                    const double Sb = (double)(rl * sl * qsun[b]);
-                    const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
-                    y[bi] = (YT)rb;
-                    sum += fabs(rb);
-                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
-                } else {
-                    const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
-                    const float yv = src + rl * (float)acc[n];
-                    y[bi] = (YT)yv;
-                    if (monitor) {
-                        const double du = fabs((double)yv - (double)x[bi]);
-                        sum += du;
-                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
-                    }
-                }
-            }
-        }
-    }
-    return make_float2((float)sum, (float)mrel);
-}
-
-// Occupancy hints: at the requested waves per SIMD the compiler fits each instantiation
-// without spilling (the FP32 sweep: 72 VGPRs at D = 40 instead of 98; the FP64 residual up
-// to D = 40: 122 instead of 144, four waves per SIMD instead of three, where five would
-// spill its accumulators; the larger FP64 residuals keep their natural allocation, since
-// their accumulators alone fill four waves' registers).
-template <int D, bool kResidual>
-constexpr int wide_waves_per_eu() { return kResidual ? (D <= 40 ? 4 : 1) : (D <= 40 ? 7 : 5); }
-
-template <int D, class XT, class YT, class AccT, bool kResidual>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wide_waves_per_eu<D, kResidual>()))) void k_spmm_wide(
-    int N, int nl, int groups, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff,
-    const int *__restrict__ rev, const float *__restrict__ q, const float *__restrict__ qsun,
-    const float *__restrict__ tau_s, const float *__restrict__ tau_a, const float *__restrict__ abs_scale,
-    const float *__restrict__ brho, const float *__restrict__ bsrc, const float *__restrict__ rhs,
-    const XT *__restrict__ x, YT *__restrict__ y, float2 *__restrict__ meas, int monitor, int dmax) {
-    extern __shared__ float qs_all[];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int lam = blockIdx.y * 64 + lane;
-    const bool lv = lam < nl;
-    const float s = lv ? abs_scale[lam] : 0.f;
-    float *qs = qs_all + (size_t)w * (dmax * dmax + 64);  // + padding: whole-column reads past d
-    const int waves = blockDim.x >> 6;
-    for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-        const int l = __builtin_amdgcn_readfirstlane(g * waves + w);
-        if (l >= N) break;
-        const int d = (int)(adj_ptr[l + 1] - adj_ptr[l]);
-        if (d == 0) {  // an isolated node: no rows
-            if (monitor && lv) meas[(long long)l * nl + lam] = make_float2(0.f, 0.f);
-            continue;
-        }
-#ifdef SG_DEBUG_BOUNDS
-        {  // the node's Q block and its in-edges' reverse ids
-            bool ok = SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x401);
-            if (lane < d) ok = SG_IN(rev[adj_ptr[l] + lane], adj_ptr[N], 0x402) && ok;
-            if (!__all(ok)) continue;
-        }
-#endif
-        const int bucket = (d + 7) >> 3;
-        float2 part = make_float2(0.f, 0.f);
-#define SG_NODE(DB)                                                                                              \
-    part = wide_node<DB, XT, YT, AccT, kResidual>(l, lane, lam, lv, s, nl, monitor, qs, adj_ptr, nodeoff, rev, q, \
-                                              qsun, tau_s, tau_a, brho, bsrc, rhs, x, y)
-        if (bucket <= 1) { SG_NODE(8); }
-        else if (bucket == 2) { if constexpr (D >= 16) SG_NODE(16); }
-        else if (bucket == 3) { if constexpr (D >= 24) SG_NODE(24); }
-        else if (bucket == 4) { if constexpr (D >= 32) SG_NODE(32); }
-        else if (bucket == 5) { if constexpr (D >= 40) SG_NODE(40); }
-        else if (bucket == 6) { if constexpr (D >= 48) SG_NODE(48); }
-        else if (bucket == 7) { if constexpr (D >= 56) SG_NODE(56); }
-        else { if constexpr (D >= 64) SG_NODE(64); }
-#undef SG_NODE
-        if (monitor && lv) meas[(long long)l * nl + lam] = part;  // per node and wavelength
-    }
-}
-
 // The first batched Neumann iterate from x = 0: x = rhs, or the solar source
 // rho_l s_l Qsun_b, computed as the sweep computes it (plus rho_l times a zero sum), so
 // it has the sweep's bits; measures per (node, wavelength).
 __global__ __launch_bounds__(256) void k_bfirst(int N, int nl, const long long *__restrict__ adj_ptr,
                                                 const float *__restrict__ qsun, const float *__restrict__ brho,
                                                 const float *__restrict__ bsrc, const float *__restrict__ rhs,
-                                                float *__restrict__ x, float2 *__restrict__ meas) {
+                                                float *__restrict__ x, float2 *__restrict__ meas,
+                                                unsigned char *__restrict__ mark) {
     const int lane = threadIdx.x & 63;
+    // no node is marked yet: the three marks of this workgroup's four nodes
+    if (blockIdx.y == 0 && threadIdx.x < 3)
+        *reinterpret_cast<unsigned *>(mark + threadIdx.x * front_marks(N) + (size_t)blockIdx.x * 4) = 0u;
     const int l = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)));
     const int lam = blockIdx.y * 64 + lane;
     if (l >= N || lam >= nl) return;
@@ -242,136 +72,6 @@ __global__ __launch_bounds__(256) void k_bfirst(int N, int nl, const long long *
         mrel = fmax(mrel, keep_nan(du / (du + kRelFloor)));
     }
     meas[(long long)l * nl + lam] = make_float2((float)sum, (float)mrel);
-}
-
-// ---- wavelength tiles narrower than a wavefront -------------------------------------
-// For n_lambda <= 32 a wavefront holds 64 / W node slots of W wavelength lanes each, so
-// a small wavelength count does not leave lanes idle.  Each slot's in-edge data (rev,
-// tau_s, tau_a) goes to a small LDS slice; the phase-cell columns are read straight
-// from memory with 16-byte loads (the lanes of a slot share the addresses, so each
-// load costs one request per slot).  Per lane the arithmetic is exactly that of the
-// full-wavefront kernel (same expressions, columns in the same order), so the two give
-// the same bits.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-
-template <int DB, class XT, class YT, class AccT, bool kResidual>
-__device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, int nl, int monitor, long long off,
-                                            int d, long long base, int dw, const int *__restrict__ srv,
-                                            const float *__restrict__ sts, const float *__restrict__ sta,
-                                            const float *__restrict__ q, const float *__restrict__ qsun,
-                                            const float *__restrict__ brho, const float *__restrict__ bsrc,
-                                            const float *__restrict__ rhs, const XT *__restrict__ x,
-                                            YT *__restrict__ y) {
-    AccT acc[DB];
-#pragma unroll
-    for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
-    for (int m = 0; m < dw; ++m) {
-        // slots with fewer in-edges repeat their last column with a zero input: adding
-        // Q * 0 leaves every valid row's sum unchanged
-        const bool mv = m < d;
-        const int mc = min(m, d - 1);
-        const XT xin = (mv && lv) ? x[(long long)srv[mc] * nl + lam] : (XT)0;
-        const AccT xm = (AccT)edge_T(sts[mc], sta[mc], s) * (AccT)xin;
-        const f4u *qm = reinterpret_cast<const f4u *>(q + base + (long long)mc * d);
-#pragma unroll
-        for (int c = 0; c < DB / 4; ++c) {
-            const f4u v = qm[c];
-            acc[4 * c] += (AccT)v.x * xm;
-            acc[4 * c + 1] += (AccT)v.y * xm;
-            acc[4 * c + 2] += (AccT)v.z * xm;
-            acc[4 * c + 3] += (AccT)v.w * xm;
-        }
-    }
-    double sum = 0.0, mrel = 0.0;
-    if (lv) {
-        const float rl = brho[(long long)l * nl + lam];
-        const float sl = bsrc[(long long)l * nl + lam];
-#pragma unroll
-        for (int n = 0; n < DB; ++n) {
-            if (n < d) {
-                const long long b = off + n;
-                const long long bi = b * nl + lam;
-                if (kResidual) {
-                    const double Sb = (double)(rl * sl * qsun[b]);
-                    const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
-                    y[bi] = (YT)rb;
-                    sum += fabs(rb);
-                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
-                } else {
-                    const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
-                    const float yv = src + rl * (float)acc[n];
-                    y[bi] = (YT)yv;
-                    if (monitor) {
-                        const double du = fabs((double)yv - (double)x[bi]);
-                        sum += du;
-                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
-                    }
-                }
-            }
-        }
-    }
-    return make_float2((float)sum, (float)mrel);
-}
-
-template <int W, int D, class XT, class YT, class AccT, bool kResidual>
-__global__ __launch_bounds__(256) void k_spmm_pack(
-    int N, int nl, int groups, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff,
-    const int *__restrict__ rev, const float *__restrict__ q, const float *__restrict__ qsun,
-    const float *__restrict__ tau_s, const float *__restrict__ tau_a, const float *__restrict__ abs_scale,
-    const float *__restrict__ brho, const float *__restrict__ bsrc, const float *__restrict__ rhs,
-    const XT *__restrict__ x, YT *__restrict__ y, float2 *__restrict__ meas, int monitor) {
-    constexpr int P = 64 / W;  // node slots per wavefront
-    __shared__ int srv_all[4][P][64];
-    __shared__ float sts_all[4][P][64], sta_all[4][P][64];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int k = lane / W, lam = lane - k * W;
-    const bool lam_ok = lam < nl;
-    const float s = lam_ok ? abs_scale[lam] : 0.f;
-    int *srv = srv_all[w][k];
-    float *sts = sts_all[w][k], *sta = sta_all[w][k];
-    for (int g = blockIdx.x; g < groups; g += gridDim.x) {
-        const int l0 = __builtin_amdgcn_readfirstlane((g * 4 + w) * P);
-        if (l0 >= N) break;
-        const int l = l0 + k;
-        const bool node_ok = l < N;
-        long long off = 0, base = 0;
-        int d = 0;
-        if (node_ok) {
-            off = adj_ptr[l];
-            d = (int)(adj_ptr[l + 1] - off);
-            base = nodeoff[l];
-        }
-        for (int m = lam; m < d; m += W) {
-            const long long e = off + m;
-            srv[m] = SG_IN(rev[e], adj_ptr[N], 0x403) ? rev[e] : (int)e;
-            sts[m] = tau_s[e];
-            sta[m] = tau_a[e];
-        }
-        __builtin_amdgcn_wave_barrier();
-        int dw = d;  // the wavefront's largest degree (uniform loop bound)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) dw = max(dw, __shfl_xor(dw, o, 64));
-        dw = __builtin_amdgcn_readfirstlane(dw);
-        const bool lv = node_ok && lam_ok && d > 0;
-        float2 part = make_float2(0.f, 0.f);
-        if (dw > 0) {
-            const int bucket = (dw + 7) >> 3;
-#define SG_PACK(DB)                                                                                        \
-    part = pack_node<DB, XT, YT, AccT, kResidual>(l, lam, lv, s, nl, monitor, off, max(d, 1), base, dw, srv, sts, \
-                                              sta, q, qsun, brho, bsrc, rhs, x, y)
-            if (bucket <= 1) { SG_PACK(8); }
-            else if (bucket == 2) { if constexpr (D >= 16) SG_PACK(16); }
-            else if (bucket == 3) { if constexpr (D >= 24) SG_PACK(24); }
-            else if (bucket == 4) { if constexpr (D >= 32) SG_PACK(32); }
-            else if (bucket == 5) { if constexpr (D >= 40) SG_PACK(40); }
-            else if (bucket == 6) { if constexpr (D >= 48) SG_PACK(48); }
-            else if (bucket == 7) { if constexpr (D >= 56) SG_PACK(56); }
-            else { if constexpr (D >= 64) SG_PACK(64); }
-#undef SG_PACK
-        }
-        if (monitor && node_ok && lam_ok) meas[(long long)l * nl + lam] = part;
-        __builtin_amdgcn_wave_barrier();  // the slices are rewritten by the next group
-    }
 }
 
 // One wavelength of a batched scene in FP64, for its GMRES fallback: one wavefront per node,
@@ -638,72 +338,23 @@ int wide_waves(const Scene &s) { return (size_t)4 * (s.dmax * s.dmax + 64) * siz
 int smallest_tile(int n_lambda) { return n_lambda <= 8 ? 8 : n_lambda <= 16 ? 16 : n_lambda <= 32 ? 32 : 64; }
 int default_tile(int n_lambda) { return smallest_tile(n_lambda) <= 16 ? smallest_tile(n_lambda) : 64; }
 
-static int lambda_tile(const Scene &s) { return s.tile >= smallest_tile(s.n_lambda) ? s.tile : 64; }
+int batched_tile(const Scene &s) { return s.tile >= smallest_tile(s.n_lambda) ? s.tile : 64; }
 
 int batched_groups(const Scene &s) {
-    const int W = lambda_tile(s);
+    const int W = batched_tile(s);
     if (W < 64) return (s.N + 4 * (64 / W) - 1) / (4 * (64 / W));
     return (s.N + wide_waves(s) - 1) / wide_waves(s);
 }
 
-template <int W, class XT, class YT, class AccT, bool kRes>
-static void launch_pack(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor) {
-    const int groups = batched_groups(s);
-#define SG_PK(DD)                                                                                                  \
-    hipLaunchKernelGGL((k_spmm_pack<W, DD, XT, YT, AccT, kRes>), dim3(grid), dim3(256), 0, st, s.N, s.n_lambda, groups, \
-                       s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a,      \
-                       s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor)
-    if (s.dmax <= 16) SG_PK(16);
-    else if (s.dmax <= 24) SG_PK(24);
-    else if (s.dmax <= 32) SG_PK(32);
-    else if (s.dmax <= 40) SG_PK(40);
-    else if (s.dmax <= 48) SG_PK(48);
-    else if (s.dmax <= 56) SG_PK(56);
-    else SG_PK(64);
-#undef SG_PK
-}
-
-template <class XT, class YT, class AccT, bool kRes>
-static void launch_wide(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor) {
-    const int W = lambda_tile(s);
-    grid = std::max(1, std::min(grid, batched_groups(s)));
-    if (W == 8) return launch_pack<8, XT, YT, AccT, kRes>(s, st, grid, rhs, x, y, monitor);
-    if (W == 16) return launch_pack<16, XT, YT, AccT, kRes>(s, st, grid, rhs, x, y, monitor);
-    if (W == 32) return launch_pack<32, XT, YT, AccT, kRes>(s, st, grid, rhs, x, y, monitor);
-    const int waves = wide_waves(s);
-    const int groups = batched_groups(s);
-    dim3 gr(grid, (s.n_lambda + 63) / 64);
-    const size_t shm = (size_t)waves * (s.dmax * s.dmax + 64) * sizeof(float);
-#define SG_WIDE(DD)                                                                                                 \
-    hipLaunchKernelGGL((k_spmm_wide<DD, XT, YT, AccT, kRes>), gr, dim3(64 * waves), shm, st, s.N, s.n_lambda, groups, \
-                       s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a,      \
-                       s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor, s.dmax)
-    if (s.dmax <= 16) SG_WIDE(16);
-    else if (s.dmax <= 24) SG_WIDE(24);
-    else if (s.dmax <= 32) SG_WIDE(32);
-    else if (s.dmax <= 40) SG_WIDE(40);
-    else if (s.dmax <= 48) SG_WIDE(48);
-    else if (s.dmax <= 56) SG_WIDE(56);
-    else SG_WIDE(64);
-#undef SG_WIDE
-}
-
-void launch_spmm(Scene &s, hipStream_t st, int grid, const float *rhs, const float *x, float *y, int monitor) {
-    launch_wide<float, float, float, false>(s, st, grid, rhs, x, y, monitor);
-}
-
-void launch_bresidual64(Scene &s, hipStream_t st, int grid, const double *x64, float *r32) {
-    launch_wide<double, float, double, true>(s, st, grid, nullptr, x64, r32, 1);
-}
-
-void launch_bresidual32(Scene &s, hipStream_t st, int grid, const float *x, float *r32) {
-    launch_wide<float, float, double, true>(s, st, grid, nullptr, x, r32, 1);
+void launch_spmm(Scene &s, hipStream_t st, int grid, const float *rhs, const float *x, float *y, int monitor, int front) {
+    if (front) launch_spmm_front(s, st, grid, rhs, x, y, monitor, front);
+    else launch_wide<float, float, float, false, 0>(s, st, grid, rhs, x, y, monitor, 0);
 }
 
 void launch_bfirst(Scene &s, hipStream_t st, const float *rhs, float *x) {
     dim3 gr((s.N + 3) / 4, (s.n_lambda + 63) / 64);
     hipLaunchKernelGGL(k_bfirst, gr, dim3(256), 0, st, s.N, s.n_lambda, s.adj_ptr, s.qsun, s.brho, s.bsrc, rhs, x,
-                       s.meas);
+                       s.meas, s.front);
 }
 
 void launch_blam_residual64(Scene &s, hipStream_t st, int lam, const double *x, double *r) {

@@ -1,0 +1,445 @@
+// The sweep and residual kernels of many wavelengths and their launches, instantiated by
+// three sources that compile side by side: the whole sweeps (batched.hip), the sweeps over
+// the front (batched_front.hip) and the FP64 residual (batched_residual.hip).
+#pragma once
+
+#include "device.hpp"
+#include "internal.hpp"
+
+namespace sg {
+
+namespace {
+
+// One node per wavefront, lanes = wavelengths (tiles of 64).  The node's phase-cell
+// block Q is staged, coalesced, in the wavefront's LDS slice and its entries are read
+// as broadcasts (measured: reading the columns through scalar loads instead exposes
+// their latency, 1.4x slower at 64 wavelengths); the in-edge list and optical depths
+// are loaded once, coalesced, and broadcast with readlane; eight input gathers are in
+// flight at a time; the node's rows are accumulated in registers, the row count
+// rounded up to a multiple of 8 (DB) so the column reads are unguarded (the LDS slice
+// is padded past the block by 64 floats).
+// kResidual: FP64 residual r = S - x + K x of an FP64 iterate instead of a sweep.
+// exp(-(tau_s + s tau_a)) as one hardware exp2; its relative error (~|tau| 1e-7) is
+// below that of the FP32 path integral itself.  The sweep and the FP64 residual use
+// the same function, so iterative refinement sees one matrix.
+__device__ __forceinline__ float edge_T(float ts, float ta, float s) {
+    return __builtin_amdgcn_exp2f(-(ts + s * ta) * 1.4426950408889634f);
+}
+
+// n passes of 64 consecutive block elements from t0 into the wavefront's LDS slice
+template <int n>
+__device__ __forceinline__ void stage_q(const float *__restrict__ qg, float *__restrict__ qs, int t0, int nq,
+                                        int lane) {
+    float v[n];
+#pragma unroll
+    for (int j = 0; j < n; ++j) v[j] = qg[min(t0 + j * 64 + lane, nq - 1)];
+#pragma unroll
+    for (int j = 0; j < n; ++j) qs[min(t0 + j * 64 + lane, nq - 1)] = v[j];
+}
+
+// kMark: the rows whose value moved for any wavelength mark their head node and this one for
+// the next sweep over the front (as the single-wavelength sweep does).
+template <int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
+__device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, float s, int nl, int monitor,
+                                            float *__restrict__ qs, const long long *__restrict__ adj_ptr,
+                                            const long long *__restrict__ nodeoff, const int *__restrict__ rev,
+                                            const float *__restrict__ q, const float *__restrict__ qsun,
+                                            const float *__restrict__ tau_s, const float *__restrict__ tau_a,
+                                            const float *__restrict__ brho, const float *__restrict__ bsrc,
+                                            const float *__restrict__ rhs, const XT *__restrict__ x,
+                                            YT *__restrict__ y, const int *__restrict__ adj_idx,
+                                            unsigned char *__restrict__ mark) {
+    constexpr int kU = 8;
+    const long long off = adj_ptr[l];
+    const int d = (int)(adj_ptr[l + 1] - off);
+    const long long base = nodeoff[l];
+    // per in-edge data in lane m (lanes past d repeat the last in-edge), then the node's
+    // phase-cell block into this wavefront's LDS slice: as many 64-element passes as the
+    // block needs, at most 16 at a time (a wave-uniform switch into straight-line copies,
+    // so the loads are issued back to back; out-of-range lanes reload and rewrite the last
+    // element)
+    const long long em = off + min(lane, d - 1);
+    const int rv = rev[em];
+    const float ts = tau_s[em], ta = tau_a[em];
+    {
+        const int nq = d * d;
+        for (int t0 = 0; t0 < nq; t0 += 64 * 16) {
+            switch (min(16, (nq - t0 + 63) >> 6)) {
+#define SG_STAGE_CASE(n) \
+    case n: stage_q<n>(q + base, qs, t0, nq, lane); break;
+                SG_STAGE_CASE(1) SG_STAGE_CASE(2) SG_STAGE_CASE(3) SG_STAGE_CASE(4) SG_STAGE_CASE(5)
+                SG_STAGE_CASE(6) SG_STAGE_CASE(7) SG_STAGE_CASE(8) SG_STAGE_CASE(9) SG_STAGE_CASE(10)
+                SG_STAGE_CASE(11) SG_STAGE_CASE(12) SG_STAGE_CASE(13) SG_STAGE_CASE(14) SG_STAGE_CASE(15)
+                default: stage_q<16>(q + base, qs, t0, nq, lane);
+#undef SG_STAGE_CASE
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    AccT acc[DB];
+#pragma unroll
+    for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
+    for (int m0 = 0; m0 < d; m0 += kU) {
+        XT xv[kU];
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const int m = min(m0 + j, 63);
+            const int r = __builtin_amdgcn_readlane(rv, m);
+            xv[j] = (m0 + j < d && lv) ? x[(long long)r * nl + lam] : (XT)0;
+        }
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const int m = m0 + j;
+            if (m < d) {
+                const float tsm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ts), m));
+                const float tam = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ta), m));
+                const AccT xm = (AccT)edge_T(tsm, tam, s) * (AccT)xv[j];
+                const float *qm = qs + m * d;  // column m: Q[n][m], n contiguous (LDS, uniform address)
+#pragma unroll
+                for (int n = 0; n < DB; ++n) acc[n] += (AccT)qm[n] * xm;
+            }
+        }
+    }
+    double sum = 0.0, mrel = 0.0;  // convergence measures of this node's rows
+    unsigned long long rows = 0ull;  // the rows that moved for any wavelength
+    if (lv) {
+        const float rl = brho[(long long)l * nl + lam];
+        const float sl = bsrc[(long long)l * nl + lam];
+#pragma unroll
+        for (int n = 0; n < DB; ++n) {
+            if (n < d) {
+                const long long b = off + n;
+                const long long bi = b * nl + lam;
+                if (kResidual) {
+                    const double Sb = (double)(rl * sl * qsun[b]);
+                    const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
+                    y[bi] = (YT)rb;
+                    sum += fabs(rb);
+                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
+                } else {
+                    const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
+                    const float yv = src + rl * (float)acc[n];
+                    y[bi] = (YT)yv;
+                    if (kMark && __ballot(moved(yv, (float)x[bi]))) rows |= 1ull << n;
+                    if (monitor) {
+                        const double du = fabs((double)yv - (double)x[bi]);
+                        sum += du;
+                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
+                    }
+                }
+            }
+        }
+    }
+    if (kMark) {  // every lane with a wavelength holds the same mask, and lane 0 has one
+        const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)rows);
+        const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(rows >> 32));
+        const unsigned long long m = ((unsigned long long)hi << 32) | lo;
+        if (lane < d && (m >> lane & 1ull)) mark[adj_idx[em]] = 1;
+        if (m && lane == 0) mark[l] = 1;
+    }
+    return make_float2((float)sum, (float)mrel);
+}
+
+// Occupancy hints: at the requested waves per SIMD the compiler fits each instantiation
+// without spilling (the FP32 sweep: 72 VGPRs at D = 40 instead of 98; the FP64 residual up
+// to D = 40: 122 instead of 144, four waves per SIMD instead of three, where five would
+// spill its accumulators; the larger FP64 residuals keep their natural allocation, since
+// their accumulators alone fill four waves' registers).  The marking sweeps hold the heads and
+// moved rows too and fit six.
+template <int D, bool kResidual, int kMode>
+constexpr int wide_waves_per_eu() {
+    return kResidual ? (D <= 40 ? 4 : 1) : (D <= 40 ? (kMode ? 6 : 7) : 5);
+}
+
+// kMode 0: every node; kFrontFirst: every node, marking the nodes of the next sweep;
+// kFrontOn: the nodes marked in `now` only, marking those of the next (see k_spmv_front:
+// the same marks, spread over the wavefronts by the same skewed stride; spent is cleared).
+// 96x96x32, 64 wavelengths: whole sweeps 1.11 to 1.45 ms, the last six of ten 0.61 falling
+// to 0.24 ms; a stream of the visited nodes' inputs and results, as a whole sweep.
+enum { kFrontOn = kFrontFirst + 1 };
+template <int D, class XT, class YT, class AccT, bool kResidual, int kMode>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wide_waves_per_eu<D, kResidual, kMode>()))) void k_spmm_wide(
+    int N, int nl, int groups, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff,
+    const int *__restrict__ rev, const float *__restrict__ q, const float *__restrict__ qsun,
+    const float *__restrict__ tau_s, const float *__restrict__ tau_a, const float *__restrict__ abs_scale,
+    const float *__restrict__ brho, const float *__restrict__ bsrc, const float *__restrict__ rhs,
+    const XT *__restrict__ x, YT *__restrict__ y, float2 *__restrict__ meas, int monitor, int dmax,
+    const int *__restrict__ adj_idx, const unsigned char *__restrict__ now, unsigned char *__restrict__ next,
+    unsigned long long *__restrict__ spent, int skew) {
+    extern __shared__ float qs_all[];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int lam = blockIdx.y * 64 + lane;
+    const bool lv = lam < nl;
+    const float s = lv ? abs_scale[lam] : 0.f;
+    float *qs = qs_all + (size_t)w * (dmax * dmax + 64);  // + padding: whole-column reads past d
+    const int waves = blockDim.x >> 6;
+    auto node = [&](int l) {
+        const int d = (int)(adj_ptr[l + 1] - adj_ptr[l]);
+        if (d == 0) {  // an isolated node: no rows
+            if (monitor && lv) meas[(long long)l * nl + lam] = make_float2(0.f, 0.f);
+            return;
+        }
+#ifdef SG_DEBUG_BOUNDS
+        {  // the node's Q block and its in-edges' reverse ids
+            bool ok = SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x401);
+            if (lane < d) ok = SG_IN(rev[adj_ptr[l] + lane], adj_ptr[N], 0x402) && ok;
+            if (!__all(ok)) return;
+        }
+#endif
+        const int bucket = (d + 7) >> 3;
+        float2 part = make_float2(0.f, 0.f);
+#define SG_NODE(DB)                                                                                               \
+    part = wide_node<DB, XT, YT, AccT, kResidual, kMode != 0>(l, lane, lam, lv, s, nl, monitor, qs, adj_ptr, nodeoff, \
+                                                              rev, q, qsun, tau_s, tau_a, brho, bsrc, rhs, x, y,   \
+                                                              adj_idx, next)
+        if (bucket <= 1) { SG_NODE(8); }
+        else if (bucket == 2) { if constexpr (D >= 16) SG_NODE(16); }
+        else if (bucket == 3) { if constexpr (D >= 24) SG_NODE(24); }
+        else if (bucket == 4) { if constexpr (D >= 32) SG_NODE(32); }
+        else if (bucket == 5) { if constexpr (D >= 40) SG_NODE(40); }
+        else if (bucket == 6) { if constexpr (D >= 48) SG_NODE(48); }
+        else if (bucket == 7) { if constexpr (D >= 56) SG_NODE(56); }
+        else { if constexpr (D >= 64) SG_NODE(64); }
+#undef SG_NODE
+        if (monitor && lv) meas[(long long)l * nl + lam] = part;  // per node and wavelength
+    };
+    if constexpr (kMode == kFrontOn) {
+        const int W = gridDim.x * waves, wv = blockIdx.x * waves + w;
+        if (blockIdx.y == 0)
+            for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < (N + 7) / 8; t += gridDim.x * blockDim.x) spent[t] = 0ull;
+        for (int j0 = 0; j0 * (long long)W < N; j0 += 64) {
+            const int mine = (j0 + lane) * (long long)W < N ? front_node(wv, j0 + lane, W, skew) : N;
+            unsigned long long todo = __ballot(mine < N && now[min(mine, N - 1)]);
+            for (; todo; todo &= todo - 1) node(__builtin_amdgcn_readlane(mine, __builtin_ctzll(todo)));
+        }
+    } else {
+        for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+            const int l = __builtin_amdgcn_readfirstlane(g * waves + w);
+            if (l >= N) break;
+            node(l);
+        }
+    }
+}
+
+// ---- wavelength tiles narrower than a wavefront -------------------------------------
+// For n_lambda <= 32 a wavefront holds 64 / W node slots of W wavelength lanes each, so
+// a small wavelength count does not leave lanes idle.  Each slot's in-edge data (rev,
+// tau_s, tau_a) goes to a small LDS slice; the phase-cell columns are read straight
+// from memory with 16-byte loads (the lanes of a slot share the addresses, so each
+// load costs one request per slot).  Per lane the arithmetic is exactly that of the
+// full-wavefront kernel (same expressions, columns in the same order), so the two give
+// the same bits.
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+
+template <int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
+__device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, int nl, int monitor, long long off,
+                                            int d, long long base, int dw, const int *__restrict__ srv,
+                                            const float *__restrict__ sts, const float *__restrict__ sta,
+                                            const float *__restrict__ q, const float *__restrict__ qsun,
+                                            const float *__restrict__ brho, const float *__restrict__ bsrc,
+                                            const float *__restrict__ rhs, const XT *__restrict__ x,
+                                            YT *__restrict__ y, unsigned long long &rows) {
+    AccT acc[DB];
+#pragma unroll
+    for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
+    for (int m = 0; m < dw; ++m) {
+        // slots with fewer in-edges repeat their last column with a zero input: adding
+        // Q * 0 leaves every valid row's sum unchanged
+        const bool mv = m < d;
+        const int mc = min(m, d - 1);
+        const XT xin = (mv && lv) ? x[(long long)srv[mc] * nl + lam] : (XT)0;
+        const AccT xm = (AccT)edge_T(sts[mc], sta[mc], s) * (AccT)xin;
+        const f4u *qm = reinterpret_cast<const f4u *>(q + base + (long long)mc * d);
+#pragma unroll
+        for (int c = 0; c < DB / 4; ++c) {
+            const f4u v = qm[c];
+            acc[4 * c] += (AccT)v.x * xm;
+            acc[4 * c + 1] += (AccT)v.y * xm;
+            acc[4 * c + 2] += (AccT)v.z * xm;
+            acc[4 * c + 3] += (AccT)v.w * xm;
+        }
+    }
+    double sum = 0.0, mrel = 0.0;
+    if (lv) {
+        const float rl = brho[(long long)l * nl + lam];
+        const float sl = bsrc[(long long)l * nl + lam];
+#pragma unroll
+        for (int n = 0; n < DB; ++n) {
+            if (n < d) {
+                const long long b = off + n;
+                const long long bi = b * nl + lam;
+                if (kResidual) {
+                    const double Sb = (double)(rl * sl * qsun[b]);
+                    const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
+                    y[bi] = (YT)rb;
+                    sum += fabs(rb);
+                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
+                } else {
+                    const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
+                    const float yv = src + rl * (float)acc[n];
+                    y[bi] = (YT)yv;
+                    if (kMark && moved(yv, (float)x[bi])) rows |= 1ull << n;
+                    if (monitor) {
+                        const double du = fabs((double)yv - (double)x[bi]);
+                        sum += du;
+                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
+                    }
+                }
+            }
+        }
+    }
+    return make_float2((float)sum, (float)mrel);
+}
+
+// kMode: as k_spmm_wide.  Over the front, each slot of the wavefront takes the next of its
+// marked nodes.  The marking sweeps are held to the whole ones' five waves per SIMD (the
+// compiler would hoist the previous values of all rows and leave four).
+template <int W, int D, class XT, class YT, class AccT, bool kResidual, int kMode>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMode ? 5 : 1))) void k_spmm_pack(
+    int N, int nl, int groups, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff,
+    const int *__restrict__ rev, const float *__restrict__ q, const float *__restrict__ qsun,
+    const float *__restrict__ tau_s, const float *__restrict__ tau_a, const float *__restrict__ abs_scale,
+    const float *__restrict__ brho, const float *__restrict__ bsrc, const float *__restrict__ rhs,
+    const XT *__restrict__ x, YT *__restrict__ y, float2 *__restrict__ meas, int monitor,
+    const int *__restrict__ adj_idx, const unsigned char *__restrict__ now, unsigned char *__restrict__ next,
+    unsigned long long *__restrict__ spent, int skew) {
+    constexpr int P = 64 / W;  // node slots per wavefront
+    __shared__ int srv_all[4][P][64];
+    __shared__ float sts_all[4][P][64], sta_all[4][P][64];
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int k = lane / W, lam = lane - k * W;
+    const bool lam_ok = lam < nl;
+    const float s = lam_ok ? abs_scale[lam] : 0.f;
+    int *srv = srv_all[w][k];
+    float *sts = sts_all[w][k], *sta = sta_all[w][k];
+    auto slot_nodes = [&](int l) {  // node l per slot (l >= N: none)
+        const bool node_ok = l < N;
+        long long off = 0, base = 0;
+        int d = 0;
+        if (node_ok) {
+            off = adj_ptr[l];
+            d = (int)(adj_ptr[l + 1] - off);
+            base = nodeoff[l];
+        }
+        for (int m = lam; m < d; m += W) {
+            const long long e = off + m;
+            srv[m] = SG_IN(rev[e], adj_ptr[N], 0x403) ? rev[e] : (int)e;
+            sts[m] = tau_s[e];
+            sta[m] = tau_a[e];
+        }
+        __builtin_amdgcn_wave_barrier();
+        int dw = d;  // the wavefront's largest degree (uniform loop bound)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) dw = max(dw, __shfl_xor(dw, o, 64));
+        dw = __builtin_amdgcn_readfirstlane(dw);
+        const bool lv = node_ok && lam_ok && d > 0;
+        float2 part = make_float2(0.f, 0.f);
+        unsigned long long rows = 0ull;  // this lane's rows that moved
+        if (dw > 0) {
+            const int bucket = (dw + 7) >> 3;
+#define SG_PACK(DB)                                                                                            \
+    part = pack_node<DB, XT, YT, AccT, kResidual, kMode != 0>(l, lam, lv, s, nl, monitor, off, max(d, 1), base, dw, \
+                                                              srv, sts, sta, q, qsun, brho, bsrc, rhs, x, y, rows)
+            if (bucket <= 1) { SG_PACK(8); }
+            else if (bucket == 2) { if constexpr (D >= 16) SG_PACK(16); }
+            else if (bucket == 3) { if constexpr (D >= 24) SG_PACK(24); }
+            else if (bucket == 4) { if constexpr (D >= 32) SG_PACK(32); }
+            else if (bucket == 5) { if constexpr (D >= 40) SG_PACK(40); }
+            else if (bucket == 6) { if constexpr (D >= 48) SG_PACK(48); }
+            else if (bucket == 7) { if constexpr (D >= 56) SG_PACK(56); }
+            else { if constexpr (D >= 64) SG_PACK(64); }
+#undef SG_PACK
+        }
+        if (kMode) {  // the rows that moved for any of the slot's wavelengths
+            unsigned lo = (unsigned)rows, hi = (unsigned)(rows >> 32);
+#pragma unroll
+            for (int o = W / 2; o > 0; o >>= 1) {
+                lo |= __shfl_xor(lo, o, 64);
+                hi |= __shfl_xor(hi, o, 64);
+            }
+            for (int m = lam; m < d; m += W)
+                if ((m < 32 ? lo >> m : hi >> (m - 32)) & 1u) next[adj_idx[off + m]] = 1;
+            if ((lo | hi) && lam == 0) next[l] = 1;
+        }
+        if (monitor && node_ok && lam_ok) meas[(long long)l * nl + lam] = part;
+        __builtin_amdgcn_wave_barrier();  // the slices are rewritten by the next nodes
+    };
+    if constexpr (kMode == kFrontOn) {
+        const int V = gridDim.x * 4, wv = blockIdx.x * 4 + w;
+        for (int t = blockIdx.x * 256 + threadIdx.x; t < (N + 7) / 8; t += gridDim.x * 256) spent[t] = 0ull;
+        for (int j0 = 0; j0 * (long long)V < N; j0 += 64) {
+            const int mine = (j0 + lane) * (long long)V < N ? front_node(wv, j0 + lane, V, skew) : N;
+            unsigned long long todo = __ballot(mine < N && now[min(mine, N - 1)]);
+            while (todo) {
+                unsigned long long m = todo;  // slot k: without its k lowest marks
+#pragma unroll
+                for (int i = 0; i < P; ++i) {
+                    m = i < k ? m & (m - 1) : m;
+                    todo &= todo - 1;
+                }
+                const int from = __shfl(mine, m ? __builtin_ctzll(m) : 0, 64);
+                slot_nodes(m ? from : N);
+            }
+        }
+    } else {
+        for (int g = blockIdx.x; g < groups; g += gridDim.x) {
+            const int l0 = __builtin_amdgcn_readfirstlane((g * 4 + w) * P);
+            if (l0 >= N) break;
+            slot_nodes(l0 + k);
+        }
+    }
+}
+
+}  // namespace
+
+// front: which nodes (see front_of); kMode is its kind, one of the kernels' modes
+template <int W, class XT, class YT, class AccT, bool kRes, int kMode>
+static void launch_pack(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor, int front) {
+    const int groups = batched_groups(s);
+#define SG_PK(DD)                                                                                                  \
+    hipLaunchKernelGGL((k_spmm_pack<W, DD, XT, YT, AccT, kRes, kMode>), dim3(grid), dim3(256), 0, st, s.N, s.n_lambda, \
+                       groups, s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a, \
+                       s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor, s.adj_idx, front_marks_of(s, front), \
+                       front_marks_of(s, front + 1), (unsigned long long *)front_marks_of(s, front + 2), front_skew(grid * 4))
+    if (s.dmax <= 16) SG_PK(16);
+    else if (s.dmax <= 24) SG_PK(24);
+    else if (s.dmax <= 32) SG_PK(32);
+    else if (s.dmax <= 40) SG_PK(40);
+    else if (s.dmax <= 48) SG_PK(48);
+    else if (s.dmax <= 56) SG_PK(56);
+    else SG_PK(64);
+#undef SG_PK
+}
+
+template <class XT, class YT, class AccT, bool kRes, int kMode>
+static void launch_wide(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor, int front) {
+    const int W = batched_tile(s);
+    const int waves = wide_waves(s);
+    // over the front, the wavefronts that are resident (six per SIMD, five of the narrow tiles):
+    // each takes its share of the marks, and a second round of them would start when the first ends
+    if (kMode == kFrontOn) grid = W < 64 ? 256 * 5 : 256 * 6 * 4 / waves;
+    grid = std::max(1, std::min(grid, batched_groups(s)));
+    if (W == 8) return launch_pack<8, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
+    if (W == 16) return launch_pack<16, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
+    if constexpr (kMode == 0)  // (a 32-lane tile takes whole sweeps)
+        if (W == 32) return launch_pack<32, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
+    const int groups = batched_groups(s);
+    dim3 gr(grid, (s.n_lambda + 63) / 64);
+    const size_t shm = (size_t)waves * (s.dmax * s.dmax + 64) * sizeof(float);
+#define SG_WIDE(DD)                                                                                                 \
+    hipLaunchKernelGGL((k_spmm_wide<DD, XT, YT, AccT, kRes, kMode>), gr, dim3(64 * waves), shm, st, s.N, s.n_lambda,  \
+                       groups, s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a, \
+                       s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor, s.dmax, s.adj_idx,                 \
+                       front_marks_of(s, front), front_marks_of(s, front + 1),                                      \
+                       (unsigned long long *)front_marks_of(s, front + 2), front_skew(grid * waves))
+    if (s.dmax <= 16) SG_WIDE(16);
+    else if (s.dmax <= 24) SG_WIDE(24);
+    else if (s.dmax <= 32) SG_WIDE(32);
+    else if (s.dmax <= 40) SG_WIDE(40);
+    else if (s.dmax <= 48) SG_WIDE(48);
+    else if (s.dmax <= 56) SG_WIDE(56);
+    else SG_WIDE(64);
+#undef SG_WIDE
+}
+
+}  // namespace sg

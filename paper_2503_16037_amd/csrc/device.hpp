@@ -209,6 +209,24 @@ constexpr double kRelFloor = 1e-30;
 // sees a non-finite measure instead of a zero.
 __device__ __forceinline__ double keep_nan(double v) { return v == v ? v : __builtin_huge_val(); }
 
+// True when a sweep's new value yn keeps its edge's head (and tail) node in the next
+// sweep: its bits moved, or it is not finite (the measures of an overflowed iterate have to
+// stay non-finite in every later sweep).
+__device__ __forceinline__ bool moved(float yn, float xb) {
+    return __float_as_int(yn) != __float_as_int(xb) || !(fabsf(yn) < __builtin_inff());
+}
+__device__ __forceinline__ bool moved(double yn, double xb) {
+    return __double_as_longlong(yn) != __double_as_longlong(xb) || !(fabs(yn) < __builtin_inf());
+}
+
+// The nodes of a sweep over the front: wavefront w of W takes, of
+// every W consecutive nodes (row j), the one at (w + j (0.618 W)) mod W.  The nodes that
+// change lie together (a cloud, a plume), and this spreads them evenly over the wavefronts;
+// a wavefront then reads the marks of 64 of its nodes with one load.
+__device__ __forceinline__ int front_node(int w, int j, int W, int skew) {
+    return j * W + (int)(((unsigned)w + (unsigned)j * (unsigned)skew) % (unsigned)W);
+}
+
 // Deterministic block sum; every thread must call it; returns the total in thread 0.
 template <int kThreads>
 __device__ __forceinline__ double block_sum(double v) {

@@ -338,7 +338,12 @@ void launch_bnode_coef(Scene &s, hipStream_t st);
 void launch_bfirst(Scene &s, hipStream_t st, const float *rhs, float *x);
 // one batched sweep y = rhs + K x for all wavelengths (rhs = NULL: the solar source);
 // monitor != 0: per-node measures of y - x to s.meas
-void launch_spmm(Scene &s, hipStream_t st, int grid, const float *rhs, const float *x, float *y, int monitor);
+void launch_spmm(Scene &s, hipStream_t st, int grid, const float *rhs, const float *x, float *y, int monitor,
+                 int front = 0);
+void launch_spmm_front(Scene &s, hipStream_t st, int grid, const float *rhs, const float *x, float *y, int monitor,
+                       int front);
+int wide_waves(const Scene &s);    // wavefronts per workgroup of the full-wavefront kernels
+int batched_tile(const Scene &s);  // the tile the sweeps use: s.tile if it holds the wavelengths
 // r = S + K x64 - x64 evaluated in FP64 for all wavelengths and stored in FP32 (the correction
 // solve takes it in FP32); per-node measures of r relative to x (from the FP64 values) to s.meas
 void launch_bresidual64(Scene &s, hipStream_t st, int grid, const double *x64, float *r32);

@@ -32,8 +32,9 @@ constexpr int kVecThreads = 256;
 // consecutive nodes -> part[c][lambda][2], then over the chunks in a fixed order, so the
 // result does not depend on how the sweep kernel was launched.  With several wavelengths
 // the lanes run over wavelengths (coalesced rows) and the wavefronts over nodes.
-// only != NULL: a sweep over the front, which left the nodes without a mark as they were
-// (measures zero).
+// kOnly: a sweep over the front, which left the nodes without a mark as they were (measures
+// zero; what meas holds for them is not used).
+template <bool kOnly>
 __global__ __launch_bounds__(kSpmvThreads) void k_measure_chunks(const float2 *__restrict__ meas, int N, int nl,
                                                                 int cn, const unsigned char *__restrict__ only,
                                                                 double *__restrict__ part) {
@@ -41,8 +42,8 @@ __global__ __launch_bounds__(kSpmvThreads) void k_measure_chunks(const float2 *_
     if (nl == 1) {
         double t = 0.0, u = 0.0;
         for (int i = n0 + (int)threadIdx.x; i < n1; i += kSpmvThreads) {
-            if (only && !only[i]) continue;
-            const float2 m = meas[i];
+            float2 m = meas[i];
+            if (kOnly && !only[i]) m = make_float2(0.f, 0.f);
             t += (double)m.x;
             u = fmax(u, (double)m.y);
         }
@@ -62,8 +63,8 @@ __global__ __launch_bounds__(kSpmvThreads) void k_measure_chunks(const float2 *_
     if (lam < nl)
 #pragma unroll 8
         for (int i = n0 + w; i < n1; i += kW) {
-            if (only && !only[i]) continue;
-            const float2 m = meas[(long long)i * nl + lam];
+            float2 m = meas[(long long)i * nl + lam];
+            if (kOnly && !only[i]) m = make_float2(0.f, 0.f);
             t += (double)m.x;
             u = fmax(u, (double)m.y);
         }
@@ -212,16 +213,6 @@ __device__ __forceinline__ NodeMeta load_meta(const long long *__restrict__ adj_
     return m;
 }
 
-// True when a sweep's new value yn keeps its edge's head (and tail) node in the next
-// sweep: its bits moved, or it is not finite (the measures of an overflowed iterate have to
-// stay non-finite in every later sweep).
-__device__ __forceinline__ bool moved(float yn, float xb) {
-    return __float_as_int(yn) != __float_as_int(xb) || !(fabsf(yn) < __builtin_inff());
-}
-__device__ __forceinline__ bool moved(double yn, double xb) {
-    return __double_as_longlong(yn) != __double_as_longlong(xb) || !(fabs(yn) < __builtin_inf());
-}
-
 // One node of y = S + K x by one wavefront.  With monitor != 0, meas[l] = (sum, max
 // relative) of the node's updates y - x.  With kMark, the nodes the next sweep has to visit
 // are marked: a row whose value moved marks its head node (it is an input there) and its own
@@ -298,14 +289,6 @@ __global__ __launch_bounds__(kSpmvThreads) void k_spmv(int N, const long long *_
         sweep_node<Real, kMark>(N, l, cur, lane, adj_ptr, nodeoff, rev, val, S, x, y, meas, monitor, dmax, blk, adj_idx,
                                 mark);
     }
-}
-
-// The nodes of a sweep over the front, for both its kernels: wavefront w of W takes, of
-// every W consecutive nodes (row j), the one at (w + j (0.618 W)) mod W.  The nodes that
-// change lie together (a cloud, a plume), and this spreads them evenly over the wavefronts;
-// a wavefront then reads the marks of 64 of its nodes with one load.
-__device__ __forceinline__ int front_node(int w, int j, int W, int skew) {
-    return j * W + (int)(((unsigned)w + (unsigned)j * (unsigned)skew) % (unsigned)W);
 }
 
 // The same sweep over the marked nodes only.  y holds the iterate before x, so the rows of
@@ -696,8 +679,10 @@ static int lds_dmax(const Scene &s) { return block_lds<Real>(s) ? std::min(s.dma
 // also run persistent over fewer workgroups; the tuner measures both)
 static int default_grid(const Scene &s) { return spmv_blocks(s); }
 
-// Workgroups of a sweep over the front: eight wavefronts per SIMD (the most that are resident)
-static int front_grid(const Scene &s) { return std::min(spmv_blocks(s), 2048); }
+// Workgroups of a sweep over the front: the wavefronts that are resident (eight per SIMD in
+// FP32, five in FP64); a second round of them would start when the first ends
+template <class Real>
+static int front_grid(const Scene &s) { return std::min(spmv_blocks(s), 256 * (sizeof(Real) == 4 ? 8 : 5)); }
 
 template <class Real>
 void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y, double *out, int grid,
@@ -710,7 +695,7 @@ void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y
     unsigned char *next = front ? front_marks_of(s, front + 1) : nullptr;
     const unsigned char *only = front > kFrontFirst ? front_marks_of(s, front) : nullptr;
     if (only) {
-        const int g = front_grid(s);
+        const int g = front_grid<Real>(s);
         hipLaunchKernelGGL((k_spmv_front<Real>), dim3(g), dim3(kSpmvThreads), lds, st, s.N, s.adj_ptr, s.nodeoff, s.rev,
                            val, S, x, y, s.meas, mon, dl, s.adj_idx, only, next,
                            (unsigned long long *)front_marks_of(s, front + 2), front_skew(g * kNodesPerSpmvBlock));
@@ -765,8 +750,8 @@ void launch_apply_imk64(Scene &s, hipStream_t st, const double *v, double *w) {
 void launch_measures(Scene &s, int nl, double *out, hipStream_t st, const unsigned char *only) {
     const int cn = node_chunk(s.N, nl), nc = (s.N + cn - 1) / cn;
     const int lt = (nl + 63) / 64;
-    hipLaunchKernelGGL(k_measure_chunks, dim3(nc, nl == 1 ? 1 : lt), dim3(kSpmvThreads), 0, st,
-                       (const float2 *)s.meas, s.N, nl, cn, only, s.meas_part);
+    const auto chunks = only ? k_measure_chunks<true> : k_measure_chunks<false>;
+    hipLaunchKernelGGL(chunks, dim3(nc, nl == 1 ? 1 : lt), dim3(kSpmvThreads), 0, st, (const float2 *)s.meas, s.N, nl, cn, only, s.meas_part);
     hipLaunchKernelGGL(k_measure_nodes, dim3(nl == 1 ? 1 : lt), dim3(kSpmvThreads), 0, st,
                        (const double *)s.meas_part, nc, nl, out);
 }

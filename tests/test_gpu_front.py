@@ -101,3 +101,40 @@ def test_front_overflow_is_seen(ctx):
             assert np.abs(rad - ref).max() <= 1e-4 * np.abs(ref).max()
         else:
             assert not info["rel_residual"] <= 1e-6, info
+
+
+@pytest.mark.parametrize("n_lambda", [7, 12, 31])
+def test_batched_front_has_whole_sweeps_bits(ctx, n_lambda):
+    """A 32-lane tile takes whole sweeps, the others go over to the front: every tile gives the
+    same bits, for every wavelength."""
+    from paper_2503_16037_amd import sgrt
+    sc = scenes.make_cloud(seed=9, nx=DIMS[0], ny=DIMS[1], nz=DIMS[2], n_lambda=n_lambda)
+    say("batched front", n_lambda, 4 * sc.nnz() + 8 * sc.n_edges * n_lambda)
+    assert 4 * sc.nnz() + 8 * sc.n_edges * n_lambda >= 128_000_000
+    with sgrt.Scene(ctx, sc) as g:
+        ref, info = g.solve(lambda_tile=32)
+        phi = g.export_vector("phi")
+        assert info["converged"] == 1
+        err = rel_err(ref[n_lambda // 2], oracle.run(sc, abs_scale=float(sc.abs_scale[n_lambda // 2]))["radiance"])
+        assert err.max() < 1e-4
+        tiles = [t for t in (8, 16, 64) if t >= n_lambda]
+        for opts in [dict(lambda_tile=t) for t in tiles] + [{}, dict(timing=True), {}]:
+            rad, again = g.solve(**opts)
+            assert again["sweeps"] == info["sweeps"], opts
+            assert np.array_equal(rad, ref), opts
+            assert np.array_equal(g.export_vector("phi"), phi), opts
+
+
+def test_batched_front_two_columns(ctx):
+    """More than 64 wavelengths: two columns of wavefronts mark and visit the same nodes."""
+    from paper_2503_16037_amd import sgrt
+    sc = scenes.make_plume(seed=8, nx=41, ny=29, nz=17, n_lambda=70)
+    say("batched front, two columns", 4 * sc.nnz() + 8 * sc.n_edges * 70)
+    assert 4 * sc.nnz() + 8 * sc.n_edges * 70 >= 128_000_000
+    with sgrt.Scene(ctx, sc) as g:
+        rad, info = g.solve()
+        assert info["converged"] == 1
+        for k in (0, 63, 64, 69):
+            assert rel_err(rad[k], oracle.run(sc, abs_scale=float(sc.abs_scale[k]))["radiance"]).max() < 1e-4
+        again, _ = g.solve()
+        assert np.array_equal(again, rad)
