@@ -13,31 +13,35 @@
 //
 // Pruning.  A pair with k >= t satisfies |q_i - q_j|^2 <= mu_i mu_max / t, so for a
 // threshold t every partner of node i lies in an axis-aligned box of voxels around
-// it (half-width sqrt(mu_i mu_max / t) standard deviations per axis).  Box sizes
+// it (half-width sqrt(mu_i mu_max / t) standard deviations per axis; partners of higher
+// id only, so its layers start at the node's own).  Box sizes
 // differ by orders of magnitude (a strongly scattering node reaches far), so the
 // cells of all boxes are flattened, node after node and within a box in increasing
 // partner id (x fastest, then y, z, then the surface row), and evaluated one per
 // thread; each thread finds its node by binary search in the prefix sum of the box
 // sizes.  k is computed for the partners of higher id and the qualifying pairs are
 // compacted in cell order (ballot and workgroup prefix, then the workgroups'
-// prefix sum), so the candidate list is ordered by (i, j).  A stable radix sort on
-// k (descending) then ranks them with equal couplings in (i, j) order.
+// prefix sum), so the candidate list is ordered by (i, j).
 //   threshold mode: t = c_min^2, keep k > t;
 //   top-n mode: t = the lowest threshold whose boxes hold at most a fixed budget
-//   of cells (bisection on the box volumes); if at least n pairs have k >= t, the
-//   n best of them are the answer; otherwise every pair is streamed in node chunks
-//   through a running best-n list.
-// General nodes (the path points of the lines of sight, Sec. 2) are not tied to voxels:
-// a volume node's partners are all nodes of higher id, and top-n requests go straight
-// to the streamed ranking of every pair.
-// The adjacency is assembled from the sorted directed pair codes (tail N + head).
+//   of cells; if at least n pairs have k >= t, the n best of them are the answer;
+//   otherwise every pair is evaluated against a threshold taken from a sample of the
+//   pairs (k_graph_all), so that only about n of them become candidates.
+// General nodes (the path points of the lines of sight, Sec. 2) are not tied to voxels
+// and always take the second way; its candidates are then sorted by (i, j).
+// The n best of the candidates are selected, not sorted: a radix selection finds the
+// n-th largest k, and a compaction in list order keeps the larger ones and the first of
+// the equal ones (equal couplings: the smaller pair first).  The selected pairs are the
+// forward half of the adjacency in row order; a stable sort by partner gives the other.
 // Scans, the evaluated-pair sum and the sorts are this file's own: a three-phase
-// exclusive scan, and a stable least-significant-digit radix sort (8-bit digits, one
-// wavefront per tile of 4096 keys, a key's rank among equal digits of its 64-key round
-// from eight ballots).
+// exclusive scan, and a stable least-significant-digit radix sort (8-bit digits of the
+// bits that node ids use, one wavefront per tile of 1024 keys, a key's rank among equal
+// digits of its 64-key round from eight ballots).  A pair's code is i << 32 | j.
 #include <chrono>
 #include <cmath>
 #include <cstdlib>
+#include <cstring>
+#include <limits>
 #include <memory>
 #include <string>
 #include <vector>
@@ -51,14 +55,24 @@ namespace sg {
 
 namespace {
 
-// box cells a candidate pass may visit: 2^26 first, then 2^28 and 2^30 when the fitted
-// threshold leaves fewer than n candidates (SG_GRAPH_CELL_BUDGET fixes a single budget,
-// e.g. to exercise the streamed path on small inputs)
-std::vector<unsigned long long> cell_budgets() {
+// Box cells a candidate pass may visit for the n strongest couplings: sixteen times n at
+// first (one to five in ten cells of a box hold a candidate, by how much mu varies), then four
+// times as many while the fitted threshold leaves fewer than n, up to 2^29
+// (SG_GRAPH_CELL_BUDGET fixes a single budget, e.g. to exercise the ranking of every pair on
+// small inputs).  64x64x32 plume, n = 1,507,328: 2^26 cells 0.60 ms of passes
+// (2^25 0.40, 10 n 0.20 but then only 9 % more candidates than asked for, 16 n 0.29).
+constexpr unsigned long long kMostBudget = 1ull << 29;
+// boxes of one voxel per node already beyond this are refused (with the default budgets)
+constexpr unsigned long long kMostCells = 1ull << 26;
+
+std::vector<unsigned long long> cell_budgets(unsigned long long n) {
     const char *v = std::getenv("SG_GRAPH_CELL_BUDGET");
-    const unsigned long long b = v ? std::strtoull(v, nullptr, 10) : 0ull;
-    if (b) return {b};
-    return {1ull << 26, 1ull << 28, 1ull << 30};
+    const unsigned long long fixed = v ? std::strtoull(v, nullptr, 10) : 0ull;
+    if (fixed) return {fixed};
+    std::vector<unsigned long long> b;
+    for (unsigned long long k = std::max(16ull * n, 1ull << 22); k < kMostBudget; k *= 4) b.push_back(k);
+    b.push_back(kMostBudget);
+    return b;
 }
 
 struct Geo {
@@ -88,12 +102,15 @@ sg_status gfail(sg_status st, const std::string &msg) {
         if (st_ != SG_OK) return st_;    \
     } while (0)
 
-// device blocks from the context pool, released on scope exit
+// device blocks from the context pool, released on scope exit once the stream that uses
+// them has drained (the pool serves other streams too)
 struct Dev {
     Ctx *ctx;
+    hipStream_t st;
     std::vector<void *> blocks;
-    explicit Dev(Ctx *c) : ctx(c) {}
+    Dev(Ctx *c, hipStream_t s) : ctx(c), st(s) {}
     ~Dev() {
+        if (!blocks.empty()) (void)hipStreamSynchronize(st);
         for (void *p : blocks) pool_free(ctx, p);
     }
     template <class T>
@@ -104,17 +121,97 @@ struct Dev {
         *p = static_cast<T *>(q);
         return SG_OK;
     }
-    void release(void *p) {  // one block back to the pool before scope exit
-        for (auto it = blocks.begin(); it != blocks.end(); ++it)
-            if (*it == p) {
-                pool_free(ctx, p);
-                blocks.erase(it);
-                return;
-            }
-    }
 };
 
 // ---- kernels ---------------------------------------------------------------------------
+
+// Checks and exact integer moments of the inputs, in one pass: sums of the positions and (in
+// two halves: they pass 64 bits) of their squares per axis over all nodes, the largest mu_s,
+// the first node outside its voxel (general nodes: outside the box; x = 0 and y = 0 allowed,
+// a periodic wrap puts nodes there), and whether a mu_s or an albedo is out of range.
+struct Moments {
+    unsigned long long s1[3], lo[3], hi[3], bad_node;
+    unsigned mu_max, bad_mu, bad_albedo, pad;
+};
+__global__ __launch_bounds__(256) void k_graph_moments(Geo g, const int *__restrict__ pos,
+                                                       const float *__restrict__ mu_s,
+                                                       const float *__restrict__ albedo, Moments *__restrict__ out) {
+    unsigned long long v[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, bad = ~0ull;
+    unsigned top = 0u, bad_mu = 0u, bad_albedo = 0u;
+    const long long n = max(g.N, g.nvox), stride = (long long)gridDim.x * 256;
+    for (long long l = blockIdx.x * 256ll + threadIdx.x; l < n; l += stride) {
+        if (l < g.nvox) {
+            const float a = mu_s[l];
+            if (a >= 0.0f && a < __builtin_inff()) top = max(top, __float_as_uint(a) & 0x7fffffffu);
+            else bad_mu = 1u;
+        }
+        if (l >= g.N) continue;
+        long long p[3];
+        if (l < g.nvol) {
+            const long long c[3] = {l % g.nx, (l / g.nx) % g.ny, l / ((long long)g.nx * g.ny)};
+            const long long w[3] = {g.nx * kFx, g.ny * kFx, g.nz * kFx};
+            bool in = true;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                p[a] = pos[3 * l + a];
+                const long long lo = g.general ? (a < 2 ? -1 : 0) : c[a] * kFx;
+                in = in && p[a] > lo && p[a] < (g.general ? w[a] : lo + kFx);
+            }
+            if (!in) bad = min(bad, (unsigned long long)l);
+        } else {
+            const long long c = l - g.nvol;
+            p[0] = (c % g.nx) * kFx + kFx / 2;
+            p[1] = (c / g.nx) * kFx + kFx / 2;
+            p[2] = 0;
+            const float a = albedo[c];
+            if (!(a >= 0.0f && a <= 1.0f)) bad_albedo = 1u;
+        }
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const unsigned long long sq = (unsigned long long)(p[a] * p[a]);
+            v[a] += (unsigned long long)p[a];
+            v[3 + a] += sq & 0xffffffffull;
+            v[6 + a] += sq >> 32;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) v[a] += __shfl_xor(v[a], o, 64);
+        bad = min(bad, __shfl_xor(bad, o, 64));
+        top = max(top, __shfl_xor(top, o, 64));
+        bad_mu |= __shfl_xor(bad_mu, o, 64);
+        bad_albedo |= __shfl_xor(bad_albedo, o, 64);
+    }
+    // the wavefronts meet in LDS, and one thread per value takes it out (same-address atomics
+    // from every wavefront took 0.2 ms)
+    __shared__ unsigned long long sv[4][9], sbad[4];
+    __shared__ unsigned stop[4], sflag[4];
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int a = 0; a < 9; ++a) sv[w][a] = v[a];
+        sbad[w] = bad;
+        stop[w] = top;
+        sflag[w] = bad_mu | bad_albedo << 1;
+    }
+    __syncthreads();
+    if (threadIdx.x < 9) {
+        unsigned long long t = 0ull;
+        for (int k = 0; k < 4; ++k) t += sv[k][threadIdx.x];
+        atomicAdd(&out->s1[0] + threadIdx.x, t);  // s1, lo and hi lie one after the other
+    } else if (threadIdx.x == 9) {
+        for (int k = 1; k < 4; ++k) {
+            bad = min(k == 1 ? sbad[0] : bad, sbad[k]);
+            top = max(k == 1 ? stop[0] : top, stop[k]);
+        }
+        const unsigned flag = sflag[0] | sflag[1] | sflag[2] | sflag[3];
+        if (bad != ~0ull) atomicMin(&out->bad_node, bad);
+        atomicMax(&out->mu_max, top);
+        if (flag & 1u) atomicOr(&out->bad_mu, 1u);
+        if (flag & 2u) atomicOr(&out->bad_albedo, 1u);
+    }
+}
 
 // fixed-point position, coupling coefficient and scaled coordinates of every node; a
 // general node couples with the mu_s of the voxel holding it
@@ -180,7 +277,9 @@ __device__ __forceinline__ Box node_box(const Geo &g, const long long *__restric
         const double r = g.sd[a] > 0.0 ? rho * g.sd[a] + 1.0 : __builtin_inf();  // fixed-point units
         const double pa = (double)P[3 * i + a];
         const double flo = floor((pa - r) / (double)kFx), fhi = floor((pa + r) / (double)kFx);
-        b.lo[a] = flo < 0.0 ? 0 : (flo > (double)(n[a] - 1) ? n[a] : (long long)flo);
+        // partners of higher id lie in the node's own layer (its voxel's) and above
+        if (a == 2) b.lo[a] = i / ((long long)g.nx * g.ny);
+        else b.lo[a] = flo < 0.0 ? 0 : (flo > (double)(n[a] - 1) ? n[a] : (long long)flo);
         b.hi[a] = fhi > (double)(n[a] - 1) ? n[a] - 1 : (fhi < 0.0 ? -1 : (long long)fhi);
         if (a == 2) low_z = pa - r <= 0.0;
     }
@@ -188,26 +287,53 @@ __device__ __forceinline__ Box node_box(const Geo &g, const long long *__restric
     return b;
 }
 
-__device__ __forceinline__ unsigned long long box_cells(const Box &b) {
-    unsigned long long v = 1;
-    for (int a = 0; a < 3; ++a) v *= b.hi[a] >= b.lo[a] ? (unsigned long long)(b.hi[a] - b.lo[a] + 1) : 0ull;
-    if (b.surf) v += (unsigned long long)(b.hi[0] >= b.lo[0] ? b.hi[0] - b.lo[0] + 1 : 0) *
-                     (unsigned long long)(b.hi[1] >= b.lo[1] ? b.hi[1] - b.lo[1] + 1 : 0);
-    return v;
-}
-
-// total box cells of all nodes at threshold t (one thread per node)
-__global__ void k_graph_cells(Geo g, const long long *__restrict__ P, const double *__restrict__ mu, double t,
-                              unsigned long long *__restrict__ total) {
+// Total box cells of all nodes at the thresholds 2^((h0 + s dh) / 2), s < tests (dh = 0: of
+// the unbounded boxes): one thread per node, a workgroup's sums in LDS and then one atomic per
+// threshold.  The radius is taken in FP32 (a box may come out a voxel wider or narrower): the
+// totals only choose the threshold, the boxes themselves are k_graph_boxes'.
+// (In FP64, as node_box computes it, the launch took 88 us on the 64x64x32 plume, here 46.)
+constexpr int kCellTests = 64;
+inline double cell_threshold(int h) { return std::ldexp((h & 1) ? 1.4142135623730951 : 1.0, (h - (h & 1)) / 2); }
+__global__ __launch_bounds__(256) void k_graph_cells(Geo g, const long long *__restrict__ P, const double *__restrict__ mu,
+                                                     int h0, int dh, int tests, unsigned long long *__restrict__ total) {
     const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    __shared__ unsigned long long wsum[4];
-    unsigned long long v = 0;
-    if (i < g.N) v = box_cells(node_box(g, P, mu, i, t));
-    // wavefront sums, then one atomic per workgroup
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = v;
+    __shared__ unsigned long long sum[kCellTests];
+    if (threadIdx.x < kCellTests) sum[threadIdx.x] = 0ull;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(total, wsum[0] + wsum[1] + wsum[2] + wsum[3]);
+    const bool on = i < g.nvol && mu[i] > 0.0;
+    const int n[3] = {g.nx, g.ny, g.nz};
+    int vox[3] = {0, 0, 0};
+    float f[3] = {0.f, 0.f, 0.f}, sd[3] = {0.f, 0.f, 0.f}, lg = 0.f;
+    if (on) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            vox[a] = (int)(P[3 * i + a] >> 16);
+            f[a] = (float)(P[3 * i + a] & 0xffff) * 0x1p-16f;
+            sd[a] = (float)(g.sd[a] * 0x1p-16);
+        }
+        lg = (float)log2(mu[i] * g.mu_max);
+    }
+    const float huge = 4096.0f;  // voxels: beyond every grid
+    for (int s = 0; s < tests; ++s) {
+        unsigned long long v = 0ull;
+        if (on) {
+            const float rho = dh ? exp2f(fminf(0.5f * (lg - 0.5f * (float)(h0 + s * dh)), 100.0f)) : 0x1p100f;
+            unsigned long long e[3];
+            bool low = false;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const float r = sd[a] > 0.0f ? fminf(rho * sd[a] + 0x1p-16f, huge) : huge;
+                const int lo = a == 2 ? vox[2] : max(0, vox[a] + (int)floorf(f[a] - r));
+                e[a] = (unsigned long long)(min(n[a] - 1, vox[a] + (int)floorf(f[a] + r)) - lo + 1);
+                if (a == 2) low = (float)vox[2] + f[2] <= r;
+            }
+            v = e[0] * e[1] * (e[2] + (g.surface && low ? 1ull : 0ull));
+        }
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if ((threadIdx.x & 63) == 0) atomicAdd(&sum[s], v);
+    }
+    __syncthreads();
+    if (threadIdx.x < tests && sum[threadIdx.x]) atomicAdd(&total[threadIdx.x], sum[threadIdx.x]);
 }
 
 // Boxes of nodes n0 + r (r < n) at threshold t, stored as (lo x, lo y, lo z, extent
@@ -219,13 +345,6 @@ __global__ void k_graph_boxes(Geo g, const long long *__restrict__ P, const doub
     if (r > n) return;
     if (r == n) {
         cells[n] = 0;
-        return;
-    }
-    if (g.general) {  // every partner of higher id: the range n0 + r + 1 .. N - 1
-        const long long i = n0 + r;
-        int *o = box + 8 * r;
-        for (int a = 0; a < 8; ++a) o[a] = 0;
-        cells[r] = i < g.nvol && mu[i] > 0.0 ? (unsigned long long)(g.N - 1 - i) : 0ull;
         return;
     }
     const Box b = node_box(g, P, mu, n0 + r, t);
@@ -314,9 +433,7 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
                 const unsigned nv = bx * by * bz;
                 const unsigned lc = (unsigned)(c - (staged ? scoff[r - fb] : coff[r]));
                 i = n0 + r;
-                if (g.general) {
-                    j = i + 1 + lc;
-                } else if (lc < nv) {
+                if (lc < nv) {
                     const unsigned yz = lc / bx, cx = lc - yz * bx, cz = yz / by, cy = yz - cz * by;
                     j = ((long long)o[0] + cx) + (long long)g.nx * (((long long)o[1] + cy) + (long long)g.ny * ((long long)o[2] + cz));
                 } else {
@@ -343,7 +460,7 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
             const unsigned long long at = run + before + __popcll(m & ((1ull << lane) - 1ull));
             if (SG_IN(at, boff[gridDim.x], 0x702)) {
                 keys[at] = k;
-                codes[at] = (unsigned long long)i * (unsigned long long)g.N + (unsigned long long)j;
+                codes[at] = (unsigned long long)i << 32 | (unsigned long long)j;
             }
         }
         run += total;
@@ -359,36 +476,265 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
     }
 }
 
-// directed pair codes (tail N + head) of the selected pairs, both directions
-__global__ void k_graph_directed(long long n, long long N, const unsigned long long *__restrict__ pair,
-                                 unsigned long long *__restrict__ dir) {
+// Every pair i < j (i a volume node) against threshold t: the candidates (k > 0 and k >= t,
+// strict: k > t) appended to keys / codes in no fixed order, counted in *count also beyond
+// cap.  A workgroup takes 512 nodes i, two per thread (each j read from LDS serves both), and
+// the nodes j of every gridDim.y-th span of kAllSpan, staged in LDS kAllTile at a time.  The
+// division is left to the pairs that mu_i mu_j >= t d2 (1 - 1e-9) lets through: the
+// products, the differences and this test, eleven FP64 operations a pair, bound the kernel.
+// Candidates are few: they collect in LDS and leave with one atomic per workgroup (a list
+// that overflows goes out by one atomic per wavefront and node j).
+// 119,958 nodes (7.2e9 pairs): 3.3 ms, 24 T lane-operations/s of the 30 that FP64 issues; its
+// build 1440 -> 5.6 ms (every pair written out, sorted and merged into a best-n list before).
+constexpr int kAllTile = 256, kAllSpan = 4096, kAllHits = 512;
+__global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restrict__ q, const double *__restrict__ mu,
+                                                   double t, int strict, unsigned long long cap,
+                                                   unsigned long long *__restrict__ count, double *__restrict__ keys,
+                                                   unsigned long long *__restrict__ codes) {
+#pragma clang fp contract(off)
+    __shared__ double2 jxy[kAllTile], jzm[kAllTile];
+    __shared__ double hkey[kAllHits];
+    __shared__ unsigned long long hcode[kAllHits], hbase;
+    __shared__ unsigned nhit;
+    const int lane = threadIdx.x & 63;
+    const long long i0 = (long long)blockIdx.x * 512;
+    double xi[2], yi[2], zi[2], mi[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const long long i = i0 + 256 * h + threadIdx.x, ic = min(i, g.N - 1);
+        xi[h] = q[3 * ic];
+        yi[h] = q[3 * ic + 1];
+        zi[h] = q[3 * ic + 2];
+        mi[h] = i < g.nvol ? mu[ic] : 0.0;
+    }
+    const double tl = t * (1.0 - 1e-9);
+    auto candidate = [&](long long i, long long j, double mm, double d2) {
+        const double k = mm / d2;
+        if (!(j > i && k > 0.0 && (strict ? k > t : k >= t))) return;
+        const unsigned long long code = (unsigned long long)i << 32 | (unsigned long long)j;
+        const unsigned at = atomicAdd(&nhit, 1u);
+        if (at < (unsigned)kAllHits) {
+            hkey[at] = k;
+            hcode[at] = code;
+            return;
+        }
+        const unsigned long long m = __ballot(true);  // the lanes that overflowed
+        const int lead = __builtin_ctzll(m);
+        unsigned long long b = 0ull;
+        if (lane == lead) b = atomicAdd(count, (unsigned long long)__popcll(m));
+        b = (unsigned long long)__shfl((long long)b, lead, 64) + __popcll(m & ((1ull << lane) - 1ull));
+        if (b < cap) {
+            keys[b] = k;
+            codes[b] = code;
+        }
+    };
+    if (threadIdx.x == 0) nhit = 0u;
+    for (long long jb = (long long)blockIdx.y * kAllSpan; jb < g.N; jb += (long long)gridDim.y * kAllSpan) {
+        const long long je = min(g.N, jb + kAllSpan);
+        for (long long j0 = max(jb, i0); j0 < je; j0 += kAllTile) {  // none below every i
+            const int nj = (int)min((long long)kAllTile, je - j0);
+            __syncthreads();
+            if ((int)threadIdx.x < nj) {
+                const long long j = j0 + threadIdx.x;
+                jxy[threadIdx.x] = make_double2(q[3 * j], q[3 * j + 1]);
+                jzm[threadIdx.x] = make_double2(q[3 * j + 2], mu[j]);
+            }
+            __syncthreads();
+            for (int a = 0; a < nj; ++a) {
+                const double2 p = jxy[a], r = jzm[a];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const double u = xi[h] - p.x, v = yi[h] - p.y, w = zi[h] - r.x;
+                    const double d2 = (u * u + v * v) + w * w;
+                    const double mm = mi[h] * r.y;
+                    if (mm > 0.0 && mm >= tl * d2) candidate(i0 + 256 * h + threadIdx.x, j0 + a, mm, d2);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    const unsigned n = min(nhit, (unsigned)kAllHits);
+    if (threadIdx.x == 0) hbase = n ? atomicAdd(count, (unsigned long long)n) : 0ull;
+    __syncthreads();
+    for (unsigned h = threadIdx.x; h < n; h += 256)
+        if (hbase + h < cap) {
+            keys[hbase + h] = hkey[h];
+            codes[hbase + h] = hcode[h];
+        }
+}
+
+// The couplings of M pairs spread over all of them (a fixed hash of the sample's number, so
+// a build is the same every time); 0 for a pair that cannot couple.
+__global__ void k_graph_sample(Geo g, const double *__restrict__ q, const double *__restrict__ mu, long long M,
+                               double *__restrict__ keys) {
+#pragma clang fp contract(off)
     const long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const unsigned long long c = pair[s];
-    const unsigned long long i = c / (unsigned long long)N, j = c % (unsigned long long)N;
-    dir[2 * s] = i * (unsigned long long)N + j;
-    dir[2 * s + 1] = j * (unsigned long long)N + i;
+    if (s >= M) return;
+    unsigned long long h = (unsigned long long)s * 0x9e3779b97f4a7c15ull;
+    h ^= h >> 32;
+    h *= 0xd6e8feb86659fd93ull;
+    h ^= h >> 32;
+    const long long i = (long long)(((h & 0xffffffffull) * (unsigned long long)g.N) >> 32);
+    const long long j = (long long)(((h >> 32) * (unsigned long long)g.N) >> 32);
+    double k = 0.0;
+    if (i != j && !(i >= g.nvol && j >= g.nvol)) k = i < j ? pair_key(q, mu, i, j) : pair_key(q, mu, j, i);
+    keys[s] = k > 0.0 ? k : 0.0;
 }
 
-__global__ void k_graph_heads(long long E, long long N, const unsigned long long *__restrict__ dir,
-                              int *__restrict__ head) {
-    const long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (e < E) head[e] = (int)(dir[e] % (unsigned long long)N);
+// ---- selection of the n largest keys ---------------------------------------------------
+// Keys are positive, so their bit patterns order like them.  sel: [0] the chosen top bits of
+// the n-th largest key, [1] how many keys with those top bits still belong to the n.
+constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6;  // 5 x 11 bits, then 9
+
+__device__ __forceinline__ int sel_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
+
+__global__ __launch_bounds__(256) void k_sel_hist(const unsigned long long *__restrict__ keys, long long n, int pass,
+                                                  const unsigned long long *__restrict__ sel,
+                                                  unsigned *__restrict__ hist) {
+    __shared__ unsigned h[kSelBins];
+    for (int b = threadIdx.x; b < kSelBins; b += 256) h[b] = 0u;
+    __syncthreads();
+    const int sh = sel_shift(pass), up = pass ? sel_shift(pass - 1) : 0;
+    const unsigned long long top = pass ? sel[0] >> up : 0ull;
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
+        const unsigned long long k = keys[i];
+        if (pass && k >> up != top) continue;
+        atomicAdd(&h[(unsigned)(k >> sh) & (pass < 5 ? kSelBins - 1u : 511u)], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kSelBins; b += 256)
+        if (h[b]) atomicAdd(&hist[b], h[b]);
 }
 
-// row pointers from the sorted directed codes: ptr[l] = first e with dir[e] >= l N
-__global__ void k_graph_rowptr(long long N, long long E, const unsigned long long *__restrict__ dir,
-                               long long *__restrict__ ptr) {
-    const long long l = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (l > N) return;
-    const unsigned long long key = (unsigned long long)l * (unsigned long long)N;
-    long long a = 0, b = E;  // dir[0, a) < key <= dir[b, E)
+// one workgroup: the bin that holds the sel[1]-th largest (the n-th in the first pass), and the
+// histogram cleared
+__global__ __launch_bounds__(256) void k_sel_pick(int pass, unsigned long long n, unsigned long long *__restrict__ sel,
+                                                  unsigned *__restrict__ hist) {
+    __shared__ unsigned long long above[256];
+    constexpr int kPer = kSelBins / 256;
+    unsigned c[kPer];
+    unsigned long long sum = 0ull;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        c[j] = hist[threadIdx.x * kPer + j];
+        hist[threadIdx.x * kPer + j] = 0u;
+        sum += c[j];
+    }
+    above[threadIdx.x] = sum;
+    __syncthreads();
+    for (int o = 1; o < 256; o <<= 1) {  // sums over this thread's bins and all above
+        const unsigned long long t = threadIdx.x + o < 256 ? above[threadIdx.x + o] : 0ull;
+        __syncthreads();
+        above[threadIdx.x] += t;
+        __syncthreads();
+    }
+    const unsigned long long want = pass ? sel[1] : n;
+    unsigned long long more = above[threadIdx.x] - sum;  // in the bins above this thread's
+    __syncthreads();
+    if (more < want && want <= above[threadIdx.x]) {
+        int j = kPer - 1;
+        while (more + c[j] < want) more += c[j--];
+        sel[0] = (pass ? sel[0] : 0ull) | (unsigned long long)(threadIdx.x * kPer + j) << sel_shift(pass);
+        sel[1] = want - more;
+    }
+}
+
+constexpr int kPickItems = 8, kPickBlock = 256 * kPickItems;
+
+// Counts of the keys above the n-th largest (low word) and equal to it (high word) per
+// workgroup; with kWrite, their compaction in list order: a larger key, and the first sel[1]
+// of the equal ones.
+template <bool kWrite>
+__global__ __launch_bounds__(256) void k_sel_take(const unsigned long long *__restrict__ keys,
+                                                  const unsigned long long *__restrict__ codes, long long n,
+                                                  const unsigned long long *__restrict__ sel,
+                                                  unsigned long long *__restrict__ cnt,
+                                                  const unsigned long long *__restrict__ off, long long n_sel,
+                                                  unsigned long long *__restrict__ out) {
+    __shared__ unsigned long long lds[4];
+    const long long i0 = blockIdx.x * (long long)kPickBlock + (long long)threadIdx.x * kPickItems;
+    const unsigned long long kn = sel[0], ties = sel[1];
+    unsigned long long mine = 0ull;
+    unsigned gt = 0u, eq = 0u;
+#pragma unroll
+    for (int j = 0; j < kPickItems; ++j) {
+        const unsigned long long k = i0 + j < n ? keys[i0 + j] : 0ull;
+        const bool in = i0 + j < n;
+        if (in && k > kn) gt |= 1u << j;
+        if (in && k == kn) eq |= 1u << j;
+    }
+    mine = (unsigned long long)__popc(gt) | (unsigned long long)__popc(eq) << 32;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    unsigned long long x = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    if (lane == 63) lds[w] = x;
+    __syncthreads();
+    unsigned long long before = 0ull, total = 0ull;
+    for (int k = 0; k < 4; ++k) {
+        if (k < w) before += lds[k];
+        total += lds[k];
+    }
+    if (!kWrite) {
+        if (threadIdx.x == 0) cnt[blockIdx.x] = total;
+        return;
+    }
+    const unsigned long long base = off[blockIdx.x] + before + x - mine;
+    unsigned long long g = base & 0xffffffffull, e = base >> 32;
+    for (int j = 0; j < kPickItems; ++j) {
+        const bool is_gt = gt >> j & 1u, is_eq = eq >> j & 1u;
+        if (is_gt || (is_eq && e < ties)) {
+            const unsigned long long at = g + (e < ties ? e : ties);
+            if (SG_IN(at, n_sel, 0x705)) out[at] = codes[i0 + j];
+        }
+        g += is_gt;
+        e += is_eq;
+    }
+}
+
+// the selected pairs with their ids swapped (j << 32 | i), to be sorted by j
+__global__ void k_graph_swap(long long n, const unsigned long long *__restrict__ pair,
+                             unsigned long long *__restrict__ rev) {
+    const long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (s < n) rev[s] = pair[s] << 32 | pair[s] >> 32;
+}
+
+// ptr[l] = first e with codes[e] >> 32 >= l
+__device__ __forceinline__ long long first_of(const unsigned long long *__restrict__ codes, long long n, long long l) {
+    const unsigned long long key = (unsigned long long)l << 32;
+    long long a = 0, b = n;  // codes[0, a) < key <= codes[b, n)
     while (a < b) {
         const long long m = (a + b) >> 1;
-        if (dir[m] < key) a = m + 1;
+        if (codes[m] < key) a = m + 1;
         else b = m;
     }
-    ptr[l] = a;
+    return a;
+}
+
+// Row pointers: node l's row holds its partners of lower id (its run of rev) and then
+// those of higher id (its run of pair), each ascending.
+__global__ void k_graph_rowptr(long long N, long long n, const unsigned long long *__restrict__ pair,
+                               const unsigned long long *__restrict__ rev, long long *__restrict__ up,
+                               long long *__restrict__ down, long long *__restrict__ ptr) {
+    const long long l = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (l > N) return;
+    const long long u = first_of(pair, n, l), d = first_of(rev, n, l);
+    up[l] = u;
+    down[l] = d;
+    ptr[l] = u + d;
+}
+
+__global__ void k_graph_heads(long long n, long long N, const unsigned long long *__restrict__ pair,
+                              const unsigned long long *__restrict__ rev, const long long *__restrict__ up,
+                              const long long *__restrict__ down, int *__restrict__ head) {
+    const long long s = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+    if (s >= n) return;
+    const unsigned long long f = pair[s], r = rev[s];
+    const long long i = (long long)(f >> 32), j = (long long)(r >> 32);
+    if (SG_IN(i, N, 0x706) && SG_IN(s + down[i + 1], 2 * n, 0x707)) head[s + down[i + 1]] = (int)(f & 0xffffffffull);
+    if (SG_IN(j, N, 0x708) && SG_IN(s + up[j], 2 * n, 0x709)) head[s + up[j]] = (int)(r & 0xffffffffull);
 }
 
 // ---- scans, sums and sorts of the builder -----------------------------------------------
@@ -561,12 +907,6 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const unsigned long long *__
     }
 }
 
-// descending doubles (all positive) as ascending integers, and back
-__global__ void k_desc_bits(unsigned long long *__restrict__ a, long long n) {
-    const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-    if (i < n) a[i] = ~a[i];
-}
-
 unsigned blocks_for(long long n, int threads) { return (unsigned)std::max<long long>(1, (n + threads - 1) / threads); }
 
 // ---- host driver ---------------------------------------------------------------------
@@ -575,27 +915,31 @@ struct Builder {
     Ctx *ctx;
     hipStream_t st;
     Geo g;
-    Dev dev;
+    Dev dev;  // everything the build allocates, released when it ends
     long long *P = nullptr;
     double *q = nullptr, *mu = nullptr;
-    unsigned long long *scal = nullptr;  // [0] cell total, [1] evaluated pairs
+    unsigned long long *scal = nullptr;  // [0 .. kCellTests) cell totals, counters; then the selection's state
+    unsigned *hist = nullptr;            // the selection's histogram (zero between passes)
     // build statistics: candidate passes, summed kernel times (HIP event pairs)
     int passes = 0;
-    unsigned long long evals = 0;  // pairs evaluated by the count passes
+    unsigned long long evals = 0;  // pairs evaluated by the candidate passes
     std::vector<std::pair<hipEvent_t, hipEvent_t>> ev_pairs, ev_sort;
-    Builder(Ctx *c, hipStream_t s) : ctx(c), st(s), dev(c) {}
+    Builder(Ctx *c, hipStream_t s) : ctx(c), st(s), dev(c, s) {}
     ~Builder() {
         for (auto &e : ev_pairs) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
         for (auto &e : ev_sort) { (void)hipEventDestroy(e.first); (void)hipEventDestroy(e.second); }
     }
-    // an event pair recording around whatever the caller enqueues next
-    std::pair<hipEvent_t, hipEvent_t> *mark(std::vector<std::pair<hipEvent_t, hipEvent_t>> &v) {
+    // an event pair recording around whatever the caller enqueues next (its index; -1: none)
+    int mark(std::vector<std::pair<hipEvent_t, hipEvent_t>> &v) {
         hipEvent_t a = nullptr, b = nullptr;
-        if (hipEventCreate(&a) != hipSuccess) return nullptr;
-        if (hipEventCreate(&b) != hipSuccess) { (void)hipEventDestroy(a); return nullptr; }
+        if (hipEventCreate(&a) != hipSuccess) return -1;
+        if (hipEventCreate(&b) != hipSuccess) { (void)hipEventDestroy(a); return -1; }
         v.push_back({a, b});
         (void)hipEventRecord(a, st);
-        return &v.back();
+        return (int)v.size() - 1;
+    }
+    void end(std::vector<std::pair<hipEvent_t, hipEvent_t>> &v, int e) {
+        if (e >= 0) (void)hipEventRecord(v[e].second, st);
     }
     static double total_ms(const std::vector<std::pair<hipEvent_t, hipEvent_t>> &v) {
         double t = 0.0;
@@ -606,29 +950,27 @@ struct Builder {
         return t;
     }
 
-    sg_status cells(double t, unsigned long long &out) {
-        GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
-        hipLaunchKernelGGL(k_graph_cells, dim3(blocks_for(g.N, 256)), dim3(256), 0, st, g, P, mu, t, scal);
+    // box cells at the thresholds 2^((h0 + s dh) / 2), s < tests (dh = 0: of the unbounded boxes)
+    sg_status cells(int h0, int dh, int tests, unsigned long long *out) {
+        GHIP(hipMemsetAsync(scal, 0, tests * sizeof(unsigned long long), st));
+        hipLaunchKernelGGL(k_graph_cells, dim3(blocks_for(g.N, 256)), dim3(256), 0, st, g, P, mu, h0, dh, tests, scal);
         GHIP(hipGetLastError());
-        GHIP(hipMemcpyAsync(&out, scal, sizeof(out), hipMemcpyDeviceToHost, st));
+        GHIP(hipMemcpyAsync(out, scal, tests * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
         GHIP(hipStreamSynchronize(st));
         return SG_OK;
     }
 
-    // candidates of nodes [n0, n1) at threshold t, appended after `have` entries of
-    // (keys, codes), which are reallocated to fit
-    sg_status pairs(double t, int strict, long long n0, long long n1, double *&keys, unsigned long long *&codes,
-                    unsigned long long &have) {
-        const long long n = n1 - n0;
-        if (n <= 0) return SG_OK;
-        Dev tmp(ctx);
+    // candidates of all nodes' boxes at threshold t, ordered by (i, j); only their number when
+    // there are fewer than `least`
+    sg_status pairs(double t, int strict, unsigned long long least, double *&keys, unsigned long long *&codes, unsigned long long &have) {
+        const long long n = g.N;
+        have = 0;
         int *box = nullptr;
         unsigned long long *cells = nullptr, *coff = nullptr;
-        GTRY(tmp.get(&box, 8 * n));
-        GTRY(tmp.get(&cells, n + 1));
-        GTRY(tmp.get(&coff, n + 1));
-        hipLaunchKernelGGL(k_graph_boxes, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, g, P, mu, t, n0, n, box,
-                           cells);
+        GTRY(dev.get(&box, 8 * n));
+        GTRY(dev.get(&cells, n + 1));
+        GTRY(dev.get(&coff, n + 1));
+        hipLaunchKernelGGL(k_graph_boxes, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, g, P, mu, t, 0ll, n, box, cells);
         GHIP(hipGetLastError());
         GTRY(scan<unsigned long long>(cells, coff, n + 1, 0ull));
         unsigned long long T = 0;
@@ -638,51 +980,120 @@ struct Builder {
         const unsigned long long per = (unsigned long long)kEvalRounds * 256;
         const unsigned long long nb = (T + per - 1) / per;
         if (nb >= (1ull << 31)) return gfail(SG_E_NOMEM, "coupling boxes too large");
-        unsigned long long *bcount = nullptr, *boff = nullptr, *bev = nullptr, *evsum = nullptr;
-        GTRY(tmp.get(&bcount, nb + 1));
-        GTRY(tmp.get(&boff, nb + 1));
-        GTRY(tmp.get(&bev, nb));
-        GTRY(tmp.get(&evsum, 1));
+        unsigned long long *bcount = nullptr, *boff = nullptr, *bev = nullptr;
+        GTRY(dev.get(&bcount, nb + 1));
+        GTRY(dev.get(&boff, nb + 1));
+        GTRY(dev.get(&bev, nb));
         GHIP(hipMemsetAsync(bcount + nb, 0, sizeof(unsigned long long), st));
+        GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
         ++passes;
-        auto *e0 = mark(ev_pairs);
-        hipLaunchKernelGGL((k_graph_eval<false>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, n0, n,
+        const int e0 = mark(ev_pairs);
+        hipLaunchKernelGGL((k_graph_eval<false>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, 0ll, n,
                            box, coff, T, bcount, nullptr, nullptr, nullptr, bev);
-        if (e0) (void)hipEventRecord(e0->second, st);
+        end(ev_pairs, e0);
         GHIP(hipGetLastError());
-        // boff = have + exclusive sum of the workgroup counts; boff[nb] = the new total
-        GTRY(scan<unsigned long long>(bcount, boff, (long long)nb + 1, (unsigned long long)have));
-        GHIP(hipMemsetAsync(evsum, 0, sizeof(unsigned long long), st));
+        // boff = exclusive sum of the workgroup counts; boff[nb] = their total
+        GTRY(scan<unsigned long long>(bcount, boff, (long long)nb + 1, 0ull));
         hipLaunchKernelGGL(k_sum_u64, dim3((unsigned)std::min<unsigned long long>((nb + 255) / 256, 1024)), dim3(256), 0,
-                           st, bev, (long long)nb, evsum);
+                           st, bev, (long long)nb, scal);
         GHIP(hipGetLastError());
         unsigned long long total = 0, ev = 0;
         GHIP(hipMemcpyAsync(&total, boff + nb, sizeof(total), hipMemcpyDeviceToHost, st));
-        GHIP(hipMemcpyAsync(&ev, evsum, sizeof(ev), hipMemcpyDeviceToHost, st));
+        GHIP(hipMemcpyAsync(&ev, scal, sizeof(ev), hipMemcpyDeviceToHost, st));
         GHIP(hipStreamSynchronize(st));
         evals += ev;
         if (total >= (1ull << 31)) return gfail(SG_E_NOMEM, "more than 2^31 coupling candidates");
-        if (total > have) {
-            double *nk = nullptr;
-            unsigned long long *nc = nullptr;
-            GTRY(dev.get(&nk, total));
-            GTRY(dev.get(&nc, total));
-            if (have) {
-                GHIP(hipMemcpyAsync(nk, keys, sizeof(double) * have, hipMemcpyDeviceToDevice, st));
-                GHIP(hipMemcpyAsync(nc, codes, sizeof(unsigned long long) * have, hipMemcpyDeviceToDevice, st));
-            }
-            auto *e1 = mark(ev_pairs);
-            hipLaunchKernelGGL((k_graph_eval<true>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, n0, n,
-                               box, coff, T, nullptr, boff, nk, nc, nullptr);
-            if (e1) (void)hipEventRecord(e1->second, st);
-            GHIP(hipGetLastError());
-            GHIP(hipStreamSynchronize(st));  // the scratch above is released at return
-            dev.release(keys);
-            dev.release(codes);
-            keys = nk;
-            codes = nc;
-        }
         have = total;
+        if (total && total >= least) {
+            GTRY(dev.get(&keys, total));
+            GTRY(dev.get(&codes, total));
+            const int e1 = mark(ev_pairs);
+            hipLaunchKernelGGL((k_graph_eval<true>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, 0ll, n,
+                               box, coff, T, nullptr, boff, keys, codes, nullptr);
+            end(ev_pairs, e1);
+            GHIP(hipGetLastError());
+        }
+        return SG_OK;
+    }
+
+    // candidates among all pairs at threshold t, ordered by (i, j); room for `expect` of them
+    // (more: a second pass)
+    sg_status all_pairs(double t, int strict, unsigned long long expect, double *&keys, unsigned long long *&codes,
+                        unsigned long long &have) {
+        unsigned long long cap = expect;
+        const dim3 grid((unsigned)((g.nvol + 511) / 512),
+                        (unsigned)std::min<long long>((g.N + kAllSpan - 1) / kAllSpan, 65535));
+        while (true) {
+            if (cap >= (1ull << 31)) return gfail(SG_E_NOMEM, "more than 2^31 coupling candidates");
+            GTRY(dev.get(&keys, cap));
+            GTRY(dev.get(&codes, cap));
+            GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
+            ++passes;
+            const int e0 = mark(ev_pairs);
+            hipLaunchKernelGGL(k_graph_all, grid, dim3(256), 0, st, g, q, mu, t, strict, cap, scal, keys, codes);
+            end(ev_pairs, e0);
+            GHIP(hipGetLastError());
+            GHIP(hipMemcpyAsync(&have, scal, sizeof(have), hipMemcpyDeviceToHost, st));
+            GHIP(hipStreamSynchronize(st));
+            evals += (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
+            if (have <= cap) break;
+            cap = have;
+        }
+        const int e1 = mark(ev_sort);
+        GTRY(sort_codes(codes, reinterpret_cast<unsigned long long *>(keys), (long long)have, true));
+        end(ev_sort, e1);
+        return SG_OK;
+    }
+
+    // a threshold that about `want` pairs reach, from a sample (0: every pair)
+    sg_status sampled_threshold(double want, double &t) {
+        t = 0.0;
+        const double pairs = 0.5 * (double)g.N * (double)(g.N - 1);
+        if (pairs <= (double)(1 << 22)) return SG_OK;
+        const long long M = want / pairs * (double)(1 << 21) < 1024.0 ? 1ll << 24 : 1ll << 21;
+        const double m = std::max(64.0, std::ceil(want / pairs * (double)M));
+        if (m >= (double)M) return SG_OK;
+        double *keys = nullptr;
+        GTRY(dev.get(&keys, M));
+        hipLaunchKernelGGL(k_graph_sample, dim3(blocks_for(M, 256)), dim3(256), 0, st, g, q, mu, M, keys);
+        GHIP(hipGetLastError());
+        GTRY(select(reinterpret_cast<unsigned long long *>(keys), M, (unsigned long long)m));
+        unsigned long long bits = 0;
+        GHIP(hipMemcpyAsync(&bits, scal + kCellTests, sizeof(bits), hipMemcpyDeviceToHost, st));
+        GHIP(hipStreamSynchronize(st));
+        std::memcpy(&t, &bits, sizeof(t));
+        if (std::isinf(t)) t = std::numeric_limits<double>::max();  // coincident nodes
+        return SG_OK;
+    }
+
+    // the n-th largest of have keys (n <= have) and the number of keys equal to it among the n
+    // largest, to scal[kCellTests] and scal[kCellTests + 1]
+    sg_status select(const unsigned long long *keys, long long have, unsigned long long n) {
+        const unsigned nb = (unsigned)std::min<long long>((have + 2047) / 2048, 1024);
+        for (int p = 0; p < kSelPasses; ++p) {
+            hipLaunchKernelGGL(k_sel_hist, dim3(nb), dim3(256), 0, st, keys, have, p, scal + kCellTests, hist);
+            hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, st, p, n, scal + kCellTests, hist);
+        }
+        GHIP(hipGetLastError());
+        return SG_OK;
+    }
+
+    // the codes of the n largest keys in list order (equal keys: the first ones)
+    sg_status take(const double *keys, const unsigned long long *codes, long long have, long long n,
+                   unsigned long long *&out) {
+        const auto *k = reinterpret_cast<const unsigned long long *>(keys);
+        GTRY(select(k, have, (unsigned long long)n));
+        const long long nb = (have + kPickBlock - 1) / kPickBlock;
+        unsigned long long *cnt = nullptr, *off = nullptr;
+        GTRY(dev.get(&cnt, nb));
+        GTRY(dev.get(&off, nb));
+        GTRY(dev.get(&out, n));
+        hipLaunchKernelGGL((k_sel_take<false>), dim3((unsigned)nb), dim3(256), 0, st, k, codes, have, scal + kCellTests,
+                           cnt, nullptr, n, nullptr);
+        GTRY(scan<unsigned long long>(cnt, off, nb, 0ull));
+        hipLaunchKernelGGL((k_sel_take<true>), dim3((unsigned)nb), dim3(256), 0, st, k, codes, have, scal + kCellTests,
+                           nullptr, off, n, out);
+        GHIP(hipGetLastError());
         return SG_OK;
     }
 
@@ -696,59 +1107,59 @@ struct Builder {
             GHIP(hipGetLastError());
             return SG_OK;
         }
-        Dev tmp(ctx);
         T *tsum = nullptr, *toff = nullptr;
-        GTRY(tmp.get(&tsum, nb));
-        GTRY(tmp.get(&toff, nb));
+        GTRY(dev.get(&tsum, nb));
+        GTRY(dev.get(&toff, nb));
+        return scan_with(in, out, n, init, tsum, toff);
+    }
+    template <class T>
+    sg_status scan_with(const T *in, T *out, long long n, T init, T *tsum, T *toff) {
+        const long long nb = (n + kScanBlock - 1) / kScanBlock;
         hipLaunchKernelGGL((k_scan_local<T>), dim3((unsigned)nb), dim3(256), 0, st, in, out, n, (T)0, tsum);
         GHIP(hipGetLastError());
         GTRY(scan<T>(tsum, toff, nb, init));
         hipLaunchKernelGGL((k_scan_add<T>), dim3(blocks_for(n, 256)), dim3(256), 0, st, out, n, (const T *)toff);
         GHIP(hipGetLastError());
-        GHIP(hipStreamSynchronize(st));  // the scratch above is released at return
         return SG_OK;
     }
 
-    // stable ascending sort of n 64-bit keys, with their values when vals is given, in place
-    // (eight passes of 8-bit digits through a second buffer)
-    sg_status sort_u64(unsigned long long *keys, unsigned long long *vals, long long n) {
+    // stable ascending sort of n codes (a << 32 | b, a and b node ids) by a, or by (a, b) with
+    // both, with their values when vals is given, in place: passes of 8-bit digits of the bits
+    // that ids use, through a second buffer
+    sg_status sort_codes(unsigned long long *&keys, unsigned long long *vals, long long n, bool both) {
         if (n < 2) return SG_OK;
-        Dev tmp(ctx);
-        const long long ntiles = (n + kRsTile - 1) / kRsTile;
+        int bits = 1;
+        while (bits < 32 && (1ll << bits) < g.N) ++bits;
+        std::vector<int> at;
+        for (int h = both ? 0 : 1; h < 2; ++h)
+            for (int b = 0; b < bits; b += 8) at.push_back(32 * h + b);
+        const long long ntiles = (n + kRsTile - 1) / kRsTile, nh = 256 * ntiles;
+        const long long sb = (nh + kScanBlock - 1) / kScanBlock;
         unsigned long long *k2 = nullptr, *v2 = nullptr;
-        unsigned *hist = nullptr, *off = nullptr;
-        GTRY(tmp.get(&k2, n));
-        if (vals) GTRY(tmp.get(&v2, n));
-        GTRY(tmp.get(&hist, 256 * ntiles));
-        GTRY(tmp.get(&off, 256 * ntiles));
+        unsigned *hs = nullptr, *off = nullptr, *tsum = nullptr, *toff = nullptr;
+        GTRY(dev.get(&k2, n));
+        if (vals) GTRY(dev.get(&v2, n));
+        GTRY(dev.get(&hs, nh));
+        GTRY(dev.get(&off, nh));
+        GTRY(dev.get(&tsum, sb));
+        GTRY(dev.get(&toff, sb));
         const unsigned nblk = (unsigned)((ntiles + 3) / 4);
         unsigned long long *ka = keys, *va = vals, *kb = k2, *vb = v2;
-        for (int bit = 0; bit < 64; bit += 8) {
-            hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(256), 0, st, ka, n, bit, ntiles, hist);
+        for (int bit : at) {
+            hipLaunchKernelGGL(k_rs_hist, dim3(nblk), dim3(256), 0, st, ka, n, bit, ntiles, hs);
             GHIP(hipGetLastError());
-            GTRY(scan<unsigned>(hist, off, 256 * ntiles, 0u));
+            if (sb == 1) GTRY(scan<unsigned>(hs, off, nh, 0u));
+            else GTRY(scan_with<unsigned>(hs, off, nh, 0u, tsum, toff));
             hipLaunchKernelGGL(k_rs_scatter, dim3(nblk), dim3(256), 0, st, ka, va, kb, vb, n, bit, ntiles,
-                               (const unsigned *)off, (const unsigned *)hist);
+                               (const unsigned *)off, (const unsigned *)hs);
             GHIP(hipGetLastError());
             std::swap(ka, kb);
             std::swap(va, vb);
         }
-        GHIP(hipStreamSynchronize(st));  // eight passes: the result is back in keys / vals
-        return SG_OK;
-    }
-
-    // stable sort by key, descending (equal keys keep their order), in place; the keys are
-    // positive, so their bit patterns complemented sort ascending in the same order
-    sg_status sort_desc(double *&keys, unsigned long long *&codes, unsigned long long n) {
-        if (n < 2) return SG_OK;
-        auto *k = reinterpret_cast<unsigned long long *>(keys);
-        auto *e = mark(ev_sort);
-        hipLaunchKernelGGL(k_desc_bits, dim3(blocks_for((long long)n, 256)), dim3(256), 0, st, k, (long long)n);
-        GTRY(sort_u64(k, codes, (long long)n));
-        hipLaunchKernelGGL(k_desc_bits, dim3(blocks_for((long long)n, 256)), dim3(256), 0, st, k, (long long)n);
-        if (e) (void)hipEventRecord(e->second, st);
-        GHIP(hipGetLastError());
-        GHIP(hipStreamSynchronize(st));
+        if (ka != keys) {  // an odd number of passes: the result is in the second buffer
+            if (vals) GHIP(hipMemcpyAsync(vals, va, sizeof(unsigned long long) * n, hipMemcpyDeviceToDevice, st));
+            keys = ka;
+        }
         return SG_OK;
     }
 };
@@ -774,43 +1185,6 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     const long long nvol = general ? (long long)d->n_nodes : nvox;
     const long long N = nvol + (d->surface_nodes ? (long long)d->nx * d->ny : 0);
     if (N >= (1LL << 31)) return gfail(SG_E_INVALID, "too many nodes");
-    float mmax = 0.0f;
-    for (long long v = 0; v < nvox; ++v) {
-        const float a = d->mu_s[v];
-        if (!(a >= 0.0f) || !std::isfinite(a)) return gfail(SG_E_INVALID, "mu_s must be finite and >= 0");
-        mmax = std::max(mmax, a);
-    }
-    if (d->surface_nodes)
-        for (long long c = 0; c < (long long)d->nx * d->ny; ++c)
-            if (!(d->surf_albedo[c] >= 0.0f) || !(d->surf_albedo[c] <= 1.0f))
-                return gfail(SG_E_INVALID, "surf_albedo must be in [0, 1]");
-    // exact integer moments of the positions, per axis
-    __int128 s1[3] = {0, 0, 0}, s2[3] = {0, 0, 0};
-    const long long W[3] = {(long long)d->nx * kFx, (long long)d->ny * kFx, (long long)d->nz * kFx};
-    for (long long v = 0; v < nvol; ++v) {
-        const long long c[3] = {v % d->nx, (v / d->nx) % d->ny, v / ((long long)d->nx * d->ny)};
-        for (int a = 0; a < 3; ++a) {
-            const long long p = general ? d->node_pos_fx[3 * v + a] : d->vol_pos_fx[3 * v + a];
-            // a general node lies in the box (x = 0 and y = 0 allowed: a periodic wrap puts
-            // nodes there), off the ground; a per-voxel node strictly inside its voxel
-            const bool in = general ? (a < 2 ? p >= 0 && p < W[a] : p > 0 && p < W[a])
-                                    : p > c[a] * kFx && p < (c[a] + 1) * kFx;
-            if (!in)
-                return gfail(SG_E_INVALID, std::string(general ? "node position outside the box"
-                                                               : "node position not strictly inside its voxel") +
-                                               " (node " + std::to_string(v) + ")");
-            s1[a] += p;
-            s2[a] += (__int128)p * p;
-        }
-    }
-    if (d->surface_nodes)
-        for (long long c = 0; c < (long long)d->nx * d->ny; ++c) {
-            const long long p[3] = {(c % d->nx) * kFx + kFx / 2, (c / d->nx) * kFx + kFx / 2, 0};
-            for (int a = 0; a < 3; ++a) {
-                s1[a] += p[a];
-                s2[a] += (__int128)p[a] * p[a];
-            }
-        }
     Builder B(ctx, st);
     Geo &g = B.g;
     g.nx = d->nx;
@@ -821,29 +1195,49 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     g.nvox = nvox;
     g.nvol = nvol;
     g.N = N;
-    g.mu_max = (double)mmax;
-    for (int a = 0; a < 3; ++a) {
-        g.mean[a] = (double)s1[a] / (double)N;
-        const double var = (double)((__int128)N * s2[a] - s1[a] * s1[a]) / ((double)N * (double)N);
-        g.sd[a] = var > 0.0 ? std::sqrt(var) : 0.0;
-    }
 
-    // node arrays
+    // the inputs, their checks and exact integer moments, then the node arrays
     int *pos = nullptr;
     float *mus = nullptr, *alb = nullptr;
+    Moments *mom = nullptr;
     GTRY(B.dev.get(&pos, 3 * nvol));
     GTRY(B.dev.get(&mus, nvox));
     GTRY(B.dev.get(&alb, (long long)d->nx * d->ny));
+    GTRY(B.dev.get(&mom, 1));
     GTRY(B.dev.get(&B.P, 3 * N));
     GTRY(B.dev.get(&B.q, 3 * N));
     GTRY(B.dev.get(&B.mu, N));
-    GTRY(B.dev.get(&B.scal, 4));
-    GHIP(hipMemsetAsync(B.scal, 0, 4 * sizeof(unsigned long long), st));
+    GTRY(B.dev.get(&B.scal, kCellTests + 2));
+    GTRY(B.dev.get(&B.hist, kSelBins));
+    GHIP(hipMemsetAsync(B.hist, 0, sizeof(unsigned) * kSelBins, st));
+    GHIP(hipMemsetAsync(mom, 0, sizeof(Moments), st));
+    GHIP(hipMemsetAsync(&mom->bad_node, 0xff, sizeof(mom->bad_node), st));
     GHIP(hipMemcpyAsync(pos, general ? d->node_pos_fx : d->vol_pos_fx, sizeof(int) * 3 * nvol, hipMemcpyHostToDevice,
                         st));
     GHIP(hipMemcpyAsync(mus, d->mu_s, sizeof(float) * nvox, hipMemcpyHostToDevice, st));
     if (d->surface_nodes)
         GHIP(hipMemcpyAsync(alb, d->surf_albedo, sizeof(float) * d->nx * d->ny, hipMemcpyHostToDevice, st));
+    hipLaunchKernelGGL(k_graph_moments, dim3(std::min(256u, blocks_for(std::max(N, nvox), 256))), dim3(256), 0, st, g,
+                       pos, mus, alb, mom);
+    GHIP(hipGetLastError());
+    Moments m;
+    GHIP(hipMemcpyAsync(&m, mom, sizeof(m), hipMemcpyDeviceToHost, st));
+    GHIP(hipStreamSynchronize(st));
+    if (m.bad_mu) return gfail(SG_E_INVALID, "mu_s must be finite and >= 0");
+    if (m.bad_albedo) return gfail(SG_E_INVALID, "surf_albedo must be in [0, 1]");
+    if (m.bad_node != ~0ull)
+        return gfail(SG_E_INVALID, std::string(general ? "node position outside the box"
+                                                       : "node position not strictly inside its voxel") +
+                                       " (node " + std::to_string(m.bad_node) + ")");
+    float mu_max;
+    std::memcpy(&mu_max, &m.mu_max, sizeof(mu_max));
+    g.mu_max = (double)mu_max;
+    for (int a = 0; a < 3; ++a) {
+        const __int128 s1 = (__int128)m.s1[a], s2 = ((__int128)m.hi[a] << 32) + (__int128)m.lo[a];
+        g.mean[a] = (double)s1 / (double)N;
+        const double var = (double)((__int128)N * s2 - s1 * s1) / ((double)N * (double)N);
+        g.sd[a] = var > 0.0 ? std::sqrt(var) : 0.0;
+    }
     hipLaunchKernelGGL(k_graph_nodes, dim3(blocks_for(N, 256)), dim3(256), 0, st, g, pos, mus, alb, B.P, B.q, B.mu);
     GHIP(hipGetLastError());
 
@@ -852,88 +1246,104 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     unsigned long long *codes = nullptr, have = 0, n_sel = 0, ranked = 0;
     double t_used = 0.0;
     int streamed = 0;
+    const unsigned long long n_want = (unsigned long long)d->n_pairs;
     if (d->n_pairs == 0) {
         t_used = d->c_min * d->c_min;
-        GTRY(B.pairs(t_used, 1, 0, N, keys, codes, have));
+        if (general) GTRY(B.all_pairs(t_used, 1, 1ull << 20, keys, codes, have));
+        else GTRY(B.pairs(t_used, 1, 0ull, keys, codes, have));
         n_sel = ranked = have;
     } else {
-        // the lowest threshold (bisection in the exponent) whose boxes fit the cell budget;
-        // a larger budget when that threshold leaves fewer than n candidates
-        const std::vector<unsigned long long> budgets = cell_budgets();
-        const unsigned long long budget = budgets.back();
+        // the lowest threshold whose boxes fit the cell budget, to a factor of sqrt 2 (any
+        // threshold within the budget gives the same selection, a tighter one only fewer
+        // candidates): 64 thresholds a launch, over all exponents and then over one of the
+        // 32-binade steps between; a larger budget when it leaves fewer than n candidates
         double t_fit = 0.0;
-        unsigned long long cells = 0;
-        if (!general) GTRY(B.cells(0.0, cells));
-        const unsigned long long all_cells = cells;
-        // general nodes have no voxel boxes: straight to the streamed ranking of every pair
-        for (size_t k = 0; k < budgets.size() && !general; ++k) {
-            const unsigned long long bk = budgets[k];
-            t_fit = 0.0;
-            if (all_cells > bk) {
-                double lo = 1e-300, hi = 1e300;
-                GTRY(B.cells(hi, cells));
-                if (cells > bk) return gfail(SG_E_NOMEM, "coupling candidates exceed the cell budget");
-                // geometric bisection to a factor of two: any threshold within the budget
-                // gives the same selection, a tighter one only fewer candidates
-                while (hi > 2.0 * lo) {
-                    const double mid = std::sqrt(lo) * std::sqrt(hi);
-                    if (!(mid > lo && mid < hi)) break;
-                    GTRY(B.cells(mid, cells));
-                    if (cells <= bk) hi = mid;
-                    else lo = mid;
+        bool enough = false;
+        if (!general) {
+            const std::vector<unsigned long long> budgets = cell_budgets(n_want);
+            unsigned long long all_cells = 0, coarse[kCellTests], fine[kCellTests];
+            GTRY(B.cells(0, 0, 1, &all_cells));
+            const int h_lo = -2016, h_step = 64;  // thresholds 2^-1008, 2^-976, ..., 2^1008
+            bool have_coarse = false;
+            for (size_t k = 0; k < budgets.size(); ++k) {
+                const unsigned long long bk = budgets[k];
+                t_fit = 0.0;
+                if (all_cells > bk) {
+                    if (!have_coarse) GTRY(B.cells(h_lo, h_step, kCellTests, coarse));
+                    have_coarse = true;
+                    const unsigned long long least = coarse[kCellTests - 1];
+                    if (least > bk) {
+                        if (k + 1 < budgets.size() && least <= kMostCells) continue;
+                        return gfail(SG_E_NOMEM, "coupling candidates exceed the cell budget");
+                    }
+                    int s = kCellTests - 1;
+                    while (s > 0 && coarse[s - 1] <= bk) --s;
+                    int h = h_lo + s * h_step;
+                    if (s > 0) {  // between the last threshold above the budget and this one
+                        GTRY(B.cells(h - h_step + 1, 1, kCellTests, fine));
+                        int f = kCellTests - 1;
+                        while (f > 0 && fine[f - 1] <= bk) --f;
+                        h = h - h_step + 1 + f;
+                    }
+                    t_fit = cell_threshold(h);
                 }
-                t_fit = hi;
+                GTRY(B.pairs(t_fit, 0, t_fit > 0.0 ? n_want : 0ull, keys, codes, have));
+                enough = have >= n_want || t_fit == 0.0;
+                if (enough) break;
             }
-            have = 0;  // a retry replaces the candidates of a smaller budget
-            GTRY(B.pairs(t_fit, 0, 0, N, keys, codes, have));
-            if (have >= (unsigned long long)d->n_pairs || t_fit == 0.0) break;
         }
         t_used = t_fit;
-        ranked = have;
-        if (!general && (have >= (unsigned long long)d->n_pairs || t_fit == 0.0)) {
-            GTRY(B.sort_desc(keys, codes, have));
-            n_sel = std::min<unsigned long long>(have, (unsigned long long)d->n_pairs);
-        } else {
-            // every pair, streamed in node chunks through a running best-n list
+        if (!enough) {
+            // every pair against a threshold from a sample, lower ones while too few reach it
             streamed = 1;
             t_used = 0.0;
             B.evals = 0;
-            have = 0;
-            const long long chunk = std::max<long long>(1, (long long)(budget / (unsigned long long)N));
-            for (long long n0 = 0; n0 < N; n0 += chunk) {
-                GTRY(B.pairs(0.0, 1, n0, std::min(N, n0 + chunk), keys, codes, have));
-                ranked += have;
-                GTRY(B.sort_desc(keys, codes, have));
-                have = std::min<unsigned long long>(have, (unsigned long long)d->n_pairs);
+            for (double more = 1.25;; more *= 4.0) {
+                const double want = more * (double)n_want;
+                double t = 0.0;
+                GTRY(B.sampled_threshold(want, t));
+                const unsigned long long all =
+                    (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
+                const double room = std::min({1.25 * want + 65536.0, (double)all, 2147483647.0});
+                GTRY(B.all_pairs(t, 0, (unsigned long long)room, keys, codes, have));
+                if (have >= n_want || !(t > 0.0)) break;
             }
-            n_sel = have;
         }
+        ranked = have;
+        n_sel = std::min(have, n_want);
     }
 
-    // adjacency: directed codes sorted ascending give the rows in order
+    // the selected pairs in (i, j) order: the forward half of the adjacency; the same pairs
+    // sorted by j are the other half
     const long long E = 2 * (long long)n_sel;
     *n_edges = E;
     if (E >= (1LL << 31) - 1) return gfail(SG_E_INVALID, "too many edges");
-    Dev tmp(ctx);
-    unsigned long long *dir = nullptr;
+    unsigned long long *rev = nullptr;
     int *head = nullptr;
-    long long *ptr = nullptr;
-    GTRY(tmp.get(&dir, E));
-    GTRY(tmp.get(&head, E));
-    GTRY(tmp.get(&ptr, N + 1));
+    long long *ptr = nullptr, *up = nullptr, *down = nullptr;
+    GTRY(B.dev.get(&rev, n_sel));
+    GTRY(B.dev.get(&head, E));
+    GTRY(B.dev.get(&ptr, N + 1));
+    GTRY(B.dev.get(&up, N + 1));
+    GTRY(B.dev.get(&down, N + 1));
+    const int es = B.mark(B.ev_sort);
+    if (n_sel < have) GTRY(B.take(keys, codes, (long long)have, (long long)n_sel, codes));
     if (n_sel) {
-        hipLaunchKernelGGL(k_graph_directed, dim3(blocks_for((long long)n_sel, 256)), dim3(256), 0, st,
-                           (long long)n_sel, N, codes, dir);
+        hipLaunchKernelGGL(k_graph_swap, dim3(blocks_for((long long)n_sel, 256)), dim3(256), 0, st, (long long)n_sel,
+                           (const unsigned long long *)codes, rev);
         GHIP(hipGetLastError());
-        auto *e = B.mark(B.ev_sort);
-        GTRY(B.sort_u64(dir, nullptr, E));
-        if (e) (void)hipEventRecord(e->second, st);
-        hipLaunchKernelGGL(k_graph_heads, dim3(blocks_for(E, 256)), dim3(256), 0, st, E, N, dir, head);
+        GTRY(B.sort_codes(rev, nullptr, (long long)n_sel, false));
+    }
+    B.end(B.ev_sort, es);
+    hipLaunchKernelGGL(k_graph_rowptr, dim3(blocks_for(N + 1, 256)), dim3(256), 0, st, N, (long long)n_sel,
+                       (const unsigned long long *)codes, (const unsigned long long *)rev, up, down, ptr);
+    GHIP(hipGetLastError());
+    if (n_sel) {
+        hipLaunchKernelGGL(k_graph_heads, dim3(blocks_for((long long)n_sel, 256)), dim3(256), 0, st, (long long)n_sel, N,
+                           (const unsigned long long *)codes, (const unsigned long long *)rev, (const long long *)up,
+                           (const long long *)down, head);
         GHIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_graph_rowptr, dim3(blocks_for(N + 1, 256)), dim3(256), 0, st, N, E,
-                       (const unsigned long long *)dir, ptr);
-    GHIP(hipGetLastError());
     if (adj_ptr) GHIP(hipMemcpyAsync(adj_ptr, ptr, sizeof(int64_t) * (N + 1), hipMemcpyDeviceToHost, st));
     if (adj_idx && cap >= E && E > 0)
         GHIP(hipMemcpyAsync(adj_idx, head, sizeof(int32_t) * E, hipMemcpyDeviceToHost, st));

@@ -497,7 +497,7 @@ def graph_build(ctx: Context, scene, n_pairs: int = 0, c_min: float = 0.0, strea
         adj_idx = np.zeros(ne.value, np.int32)
         _check(lib().sg_graph_build(ctx.handle, C.byref(d), _stream_ptr(stream), _ptr(adj_ptr), _ptr(adj_idx),
                                     ne.value, C.byref(ne), C.byref(gi)))
-    out = (adj_ptr, adj_idx[:ne.value].copy())
+    out = (adj_ptr, adj_idx if ne.value == adj_idx.size else adj_idx[:ne.value].copy())
     return out + (gi.as_dict(),) if info else out
 
 

@@ -115,3 +115,46 @@ def test_scene_solved_on_a_built_graph(ctx):
     assert info["converged"] == 1
     ref = oracle.run(g)["radiance"]
     assert (np.abs(rad - ref) / np.abs(ref)).max() < 1e-4
+
+
+# every pair against a sampled threshold (general nodes; above 2^22 pairs), and the selection of
+# the n largest: ragged counts, large sets of equal couplings, couplings that are zero or infinite
+
+def scattered(n, seed=3, zero=0.0, twins=0):
+    """n general nodes anywhere in a plume's box; a share of the voxels scatters nothing, and the
+    first `twins` nodes come twice (an infinite coupling)."""
+    sc = scenes.make_plume(seed=seed, nx=24, ny=20, nz=12)
+    rng = np.random.default_rng(seed)
+    pos = np.stack([rng.integers(1, w * FX, n) for w in (24, 20, 12)], 1).astype(np.int32)
+    pos[n - twins:] = pos[:twins]
+    mu = sc.mu_s.copy()
+    mu[rng.random(mu.shape) < zero] = 0.0
+    return sc.with_(node_pos_fx=pos, mu_s=mu, los_ptr=np.zeros(24 * 20 + 1, np.int64), los_node=np.zeros(0, np.int32),
+                    los_t=np.zeros(0))
+
+
+@pytest.mark.parametrize("kw", [dict(n_pairs=1), dict(n_pairs=513), dict(n_pairs=60_000), dict(n_pairs=4_000_000),
+                                dict(c_min=0.2)])
+def test_all_pairs_general_nodes(ctx, kw):
+    same(ctx, scattered(2999), **kw)
+
+
+@pytest.mark.parametrize("zero, twins", [(0.999, 0), (0.0, 70)])
+def test_all_pairs_zero_and_infinite_couplings(ctx, zero, twins):
+    sc = scattered(3100, zero=zero, twins=twins)
+    for n in (40, 30_000):
+        same(ctx, sc, n_pairs=n)
+
+
+@pytest.mark.parametrize("n_pairs", [1, 7777, 44_001])
+def test_selection_among_equal_couplings(ctx, n_pairs):
+    same(ctx, lattice_scene(17, 13, 11), n_pairs=n_pairs)
+
+
+def test_one_dominant_voxel(ctx):
+    """A voxel that scatters a million times more than the others widens every box: the cell
+    budgets run out and every pair is ranked."""
+    sc = scenes.make_plume(nx=24, ny=20, nz=12, seed=9)
+    mu = sc.mu_s.copy()
+    mu[3, 4, 5] = mu.max() * 1e6
+    same(ctx, sc.with_(mu_s=mu), n_pairs=20_000)
