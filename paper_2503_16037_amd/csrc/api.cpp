@@ -118,6 +118,36 @@ void host_lattice(int N, std::vector<double> &p) {
     }
 }
 
+// The lattice as the column operands of the phase cells' matrix products (qbuild.hip), four
+// tiles of 32 points: each component times 2^10 in two FP16 halves, as pairs of halves
+// (hx, hy) (hz, hx) (hy, hz) (lx, ly) for lanes 0..31 and (lz, lx) (ly, lz) (2^10, 0) (0, 0) for
+// lanes 32..63; zero past the last point.
+void host_lattice_halves(int N, const std::vector<double> &p, std::vector<unsigned> &out) {
+    out.assign(4 * 64 * 4, 0u);
+    auto pair = [](_Float16 a, _Float16 b) {
+        unsigned short x, y;
+        std::memcpy(&x, &a, 2);
+        std::memcpy(&y, &b, 2);
+        return (unsigned)x | (unsigned)y << 16;
+    };
+    for (int i = 0; i < N; ++i) {
+        _Float16 h[3], l[3];
+        for (int k = 0; k < 3; ++k) {
+            const float v = (float)(p[3 * i + k] * 1024.0);
+            h[k] = (_Float16)v;
+            l[k] = (_Float16)(v - (float)h[k]);
+        }
+        unsigned *a = &out[((i >> 5) * 64 + (i & 31)) * 4], *b = a + 32 * 4;
+        a[0] = pair(h[0], h[1]);
+        a[1] = pair(h[2], h[0]);
+        a[2] = pair(h[1], h[2]);
+        a[3] = pair(l[0], l[1]);
+        b[0] = pair(l[2], l[0]);
+        b[1] = pair(l[1], l[2]);
+        b[2] = pair((_Float16)1024.0f, (_Float16)0.0f);
+    }
+}
+
 // Per-component Henyey-Greenstein table normalised over the lattice, then the
 // Lambertian cosine weights max(0, z_i) / sum_j max(0, z_j).
 // Neighbour lists of the lattice along the edges of its convex hull (the adjacency the
@@ -1358,7 +1388,7 @@ void free_scene_impl(Scene *s) {
     if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
     if (s->ev_join) (void)hipEventDestroy(s->ev_join);
     s->ev_fork = s->ev_join = nullptr;
-    void *ptrs[] = {s->big, s->bigdir, s->bigrow, s->big_part, s->mu_s, s->mu_a, s->frac, s->albedo, s->abs_scale_d, s->pos, s->adj_ptr, s->adj_idx, s->lat,
+    void *ptrs[] = {s->big, s->bigdir, s->bigrow, s->big_part, s->mu_s, s->mu_a, s->frac, s->albedo, s->abs_scale_d, s->pos, s->adj_ptr, s->adj_idx, s->lat, s->lat_halves,
                     s->tab, s->lut, s->hull, s->rev, s->nodeoff, s->row_ptr, s->col_idx, s->scan_tmp, s->tau_s, s->tau_a, s->tsun_s,
                     s->tsun_a, s->T, s->Tsun, s->rho, s->val, s->S, s->x, s->y, s->c_rhs, s->c_a, s->c_b, s->qsun,
                     s->q, s->bS, s->bx, s->by, s->brho, s->bsrc, s->lam_buf, s->x64, s->r64, s->gm_V, s->partial, s->meas, s->meas_part, s->scal, s->J, s->pix,
@@ -1465,6 +1495,7 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
         SG_TRY(dalloc(s, &s.los_t, (size_t)n_el));
     }
     SG_TRY(dalloc(s, &s.lat, (size_t)3 * s.n_fib));
+    SG_TRY(dalloc(s, &s.lat_halves, (size_t)4 * 64 * 4));
     SG_TRY(dalloc(s, &s.tab, (size_t)(s.n_phase + 1) * s.n_fib));
     if (s.lut_n) SG_TRY(dalloc(s, &s.lut, (size_t)s.n_phase * s.lut_n));
     if (s.sigma_mode == SG_SIGMA_COLOUR) SG_TRY(dalloc(s, &s.hull, (size_t)s.n_fib * (kHullNb + 1)));
@@ -1577,6 +1608,9 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
         SG_TRY(upload(s, s.bigrow, bigrow.data(), sizeof(long long) * bigrow.size(), st));
     }
     SG_TRY(upload(s, s.lat, lat.data(), sizeof(double) * lat.size(), st));
+    std::vector<unsigned> halves;
+    host_lattice_halves(s.n_fib, lat, halves);
+    SG_TRY(upload(s, s.lat_halves, halves.data(), sizeof(unsigned) * halves.size(), st));
     SG_TRY(upload(s, s.tab, tab.data(), sizeof(double) * tab.size(), st));
     if (s.E) {
         unsigned *bad = reinterpret_cast<unsigned *>(s.scal);
@@ -1712,7 +1746,7 @@ uint64_t reservations(const sg_scene_desc *d, const sg_solve_opts *o, bool with_
     bool table = false;
     for (int k = 0; k < d->n_phase; ++k) table = table || (d->phase_kind && d->phase_kind[k] == SG_PHASE_TABLE);
     uint64_t b = a(nvox, 4) * 2 + (np > 1 ? a(np * nvox, 4) : 0) + a(npx, 4) + a(3 * n, 4) + a(n + 1, 8) +
-                 a(e, 4) + a(3 * nf, 8) + a((np + 1) * nf, 8) + (table ? a(np * (uint64_t)d->phase_lut_n, 8) : 0) +
+                 a(e, 4) + a(3 * nf, 8) + a(4 * 64 * 4, 4) + a((np + 1) * nf, 8) + (table ? a(np * (uint64_t)d->phase_lut_n, 8) : 0) +
                  (d->sigma_mode == SG_SIGMA_COLOUR ? a(nf * (kHullNb + 1), 4) : 0);
     if (d->n_nodes > 0)  // general nodes: their medium and the lines of sight's elements
         b += a(n_vol, 4) * 2 + (np > 1 ? a(np * n_vol, 4) : 0) + a(npx + 1, 8) + a(n_el, 4) + a(n_el, 8);

@@ -125,6 +125,7 @@ struct Scene {
     long long *adj_ptr = nullptr;
     int *adj_idx = nullptr;
     double *lat = nullptr;  // [n_fib][3]
+    unsigned *lat_halves = nullptr;  // [4][64][4]: the lattice as matrix operands of the phase cells (qbuild.hip)
     double *tab = nullptr;  // [n_phase + 1][n_fib]: HG tables, then the Lambertian cosine weights
 
     // structure

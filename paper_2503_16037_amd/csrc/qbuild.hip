@@ -8,11 +8,10 @@
 // fixed point with LDS integer atomics (exact, so the sum is independent of the
 // order).  Surface nodes use the unrotated lattice with cosine weights (Lambertian).
 //
-// The incoming directions are processed in groups of G; the G x N_fib (direction,
-// lattice point) pairs are spread over the lanes, up to eight per lane, so every
-// out-edge direction read from LDS serves eight dot products per lane: the kernel is
-// bound by FP64 issue, not by LDS broadcasts.  Each direction's column of the node
-// block (column-major) is one coalesced store.
+// The dot products of a direction are one contraction, R s_m (out-edges) by p_i (lattice
+// points), and run on the matrix cores in FP16 halves of FP32 (see "The screen");
+// the incoming directions are processed in groups of eight, two at a time.  Each
+// direction's column of the node block (column-major) is one coalesced store.
 //
 // The ownership decision is an argmax over double-precision dot products; it is
 // written with this exact operation sequence (also followed by the FP64 CPU
@@ -25,10 +24,9 @@
 //   v_im = fma(q_i2, s_m2, fma(q_i1, s_m1, q_i0 s_m0))      (= p_i . R s_m)
 // with no other contraction, hence the pragma below and -ffp-contract=off.
 //
-// The regular kernel finds that argmax through an FP32 screen with a proven error bound
-// (FP64 compares and maxima issue at about half the rate of FP32 and 32-bit integer
-// operations): every decision the screen cannot certify is taken by the FP64 sequence above,
-// so each owner is the one the FP64 sequence gives (see screen_owners).
+// The regular kernel finds that argmax through a screen with an error bound: every decision
+// the screen cannot certify is taken by the FP64 sequence above, so each owner is the one
+// the FP64 sequence gives.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -40,19 +38,155 @@ namespace {
 
 constexpr double kFix = 4503599627370496.0;  // 2^52
 constexpr double kUnfix = 1.0 / 4503599627370496.0;
-constexpr int kQSlots = 8;     // (direction, lattice point) pairs per lane in a group
+constexpr int kQSlots = 8;     // k_qbuild_big: (direction, lattice point) pairs per lane in a group
 constexpr int kQMaxGroup = 8;  // incoming directions per group
-
-// Dynamic LDS layout of a node in k_qbuild (in doubles), sized by the lattice and the group so
-// that four workgroups fit per SIMD: sites [3][64]; in FP32 as float4 (16-byte aligned): the
-// sites [64], the lattice [N_fib], the rotations' columns [group][3]; then lattice weights
-// [N_fib] (fixed point), rotations [group][9] (FP64), bins [group][64] (fixed point)
-__host__ __device__ constexpr int qbuild_lds_doubles(int NF, int group) { return 320 + 3 * NF + 79 * group; }
 
 // p / n for 0 <= p < 1024 and 1 <= n <= 128 with one FP32 multiply: (p + 1/2) / n is at
 // least 1/(2n) >= 2^-8 away from an integer, far above the rounding error of the
 // product (below 2^-12 here, also with a reciprocal a few ulp off)
 __device__ __forceinline__ int small_div(int p, float inv_n) { return (int)(((float)p + 0.5f) * inv_n); }
+
+// The screen.  The matrix cores multiply in FP16 and add in FP32, so each FP32 component
+// (scaled by 2^10, which keeps the low halves normal) is split into a high half and a low half
+// and the dot product takes 12 of the 16 products of v_mfma_f32_32x32x16_f16:
+//   k     0..2     3..5     6..8     9..11    12
+//   A     hi s     lo s     hi s     lo s     0, or -2^11 for a row past the last out-edge
+//   B     hi p     hi p     lo p     lo p     2^10
+// (lanes 0..31 hold k 0..7 of row or column lane, lanes 32..63 k 8..15 of row or column
+// lane - 32).  A result holds 2^20 v for 32 out-edges (rows) and 32 lattice points
+// (columns): lane l has column l mod 32 and the rows 8 (i / 4) + 4 (l / 32) + i mod 4 of its
+// registers i < 16.  That row holds out-edge 2 i + l / 32 (+ 32 in a second row tile), so d
+// out-edges fill about d / 2 registers and the others are left out.  The low bits of each
+// value are replaced by 2 i (5 bits, 6 with two row tiles), and the two largest of a lane's
+// values are kept; v_permlane32_swap brings the two halves of a column together, 64 columns
+// (two tiles) a step, and the half is the out-edge's low bit.
+// Error bound, in units of v (|v| <= 1): the rotation in FP32 (one multiply and two FMAs from
+// the FP32 roundings of R and s) is off by at most 5 2^-24 per component, the halves of s
+// (rounded toward zero) by 2^-22 and those of p by 1.5 2^-24, together below sqrt(3) 10.5 2^-24
+// < 2^-19.7 in the dot product; the products are exact, and 16 additions of partial sums below
+// 2 are off by at most one unit of 2^-23 each, 2^-19 (measured: 2^-22.3 in all); the index moves
+// a value by less than 64 units in the last place, 2^-17.  So a value lies within 2^-16.1 of the
+// FP64 sequence's, and if the largest exceeds the second by more than 2^-15 (kCertified), its
+// out-edge is the FP64 argmax, with no tie.  The other slots (a few pairs in 10,000 on
+// jittered grids) are queued, and the FP64 sequence decides them, one per lane.
+// What bounds the kernel: vector issue.  Per tile of 32 points and d = 23 out-edges: 12 index
+// inserts and 15 maxima and medians; the matrix product itself runs beside them (a probe: 32
+// vector instructions 150 clocks, with one product 169).  FP32 FMAs with an index insert and 1.5
+// maxima per product, the form before, took 9.1e8 vector instructions on plume 64x64x32 (now
+// 5.5e8; issuing 93 % of the time): 1.27 -> 1.00 ms, cloud 128x128x48 7.6 -> 6.1 ms, plume
+// 96x96x32 2.85 -> 2.22 ms.
+// A node with a zero-length out-edge (coincident nodes) has NaN directions: all of its slots
+// go to the FP64 sequence.
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float16v __attribute__((ext_vector_type(16)));
+constexpr float kCertified = 32.0f;  // 2^-15 in units of 2^-20
+constexpr float kHalfScale = 1024.0f;
+
+struct Operand {  // four packed pairs of halves of a matrix operand
+    unsigned w[4];
+};
+__device__ __forceinline__ float16v dot_tile(const Operand &a, const Operand &b) {
+    const float16v zero = {};
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, a), __builtin_bit_cast(half8, b), zero, 0, 0,
+                                                  0);
+}
+
+// (x, y, z), scaled, in halves rounded toward zero: (hi x, hi y), (hi z, lo x), (lo y, lo z)
+__device__ __forceinline__ void split_halves(float x, float y, float z, unsigned (&p)[3]) {
+    const auto h = __builtin_amdgcn_cvt_pkrtz(x, y);
+    const float lx = x - (float)h[0], ly = y - (float)h[1];
+    const auto m = __builtin_amdgcn_cvt_pkrtz(z, lx);
+    const float lz = z - (float)m[0];
+    p[0] = __builtin_bit_cast(unsigned, h);
+    p[1] = __builtin_bit_cast(unsigned, m);
+    p[2] = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(ly, lz));
+}
+
+// u's low half beside v's low half, and u's high half beside v's (lanes 0..31, 32..63)
+__device__ __forceinline__ void swap_halves(unsigned u, unsigned v, unsigned &low, unsigned &high) {
+    const auto r = __builtin_amdgcn_permlane32_swap(u, v, false, false);
+    low = r[0];
+    high = r[1];
+}
+__device__ __forceinline__ void swap_halves(float u, float v, float &low, float &high) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(u), __float_as_uint(v), false, false);
+    low = __uint_as_float(r[0]);
+    high = __uint_as_float(r[1]);
+}
+
+// The two largest of a lane's first R values of a tile, with 2 i (from tag0 on) in their low
+// bits, joined to (best, second) unless this is the first tile.  Three values a, b, c enter by
+// their largest and their median (the smallest cannot be among the two), two such triples at
+// a time: eight instructions for six values.
+template <int R, int kMask>
+__device__ __forceinline__ void fold_tile(const float16v &v, int tag0, bool first, float &best, float &second) {
+    auto at = [&](int i) {
+        return __uint_as_float((__float_as_uint(v[i]) & ~(unsigned)kMask) | (unsigned)(tag0 + 2 * i));
+    };
+    auto largest = [](float a, float b, float c) { return fmaxf(fmaxf(a, b), c); };
+    int i = 0;
+    if (first && R >= 3) {
+        const float a = at(0), b = at(1), c = at(2);
+        best = largest(a, b, c);
+        second = __builtin_amdgcn_fmed3f(a, b, c);
+        i = 3;
+    } else if (first) {
+        best = fmaxf(at(0), at(1));
+        second = fminf(at(0), at(1));
+        i = 2;
+    }
+#pragma unroll
+    for (; i + 6 <= R; i += 6) {
+        const float a = at(i), b = at(i + 1), c = at(i + 2), x = at(i + 3), y = at(i + 4), z = at(i + 5);
+        const float g = largest(a, b, c), h = largest(x, y, z);
+        const float mid = __builtin_amdgcn_fmed3f(best, g, h);
+        second = largest(second, __builtin_amdgcn_fmed3f(a, b, c), __builtin_amdgcn_fmed3f(x, y, z));
+        second = fmaxf(second, mid);
+        best = largest(best, g, h);
+    }
+    if (i + 3 <= R) {
+        const float a = at(i), b = at(i + 1), c = at(i + 2), g = largest(a, b, c);
+        second = largest(second, __builtin_amdgcn_fmed3f(a, b, c), fminf(best, g));
+        best = fmaxf(best, g);
+        i += 3;
+    }
+    if (i + 2 <= R) {
+        const float a = at(i), b = at(i + 1);
+        second = fmaxf(second, __builtin_amdgcn_fmed3f(best, a, b));
+        best = largest(best, a, b);
+        i += 2;
+    }
+    if (i < R) {
+        const float a = at(i);
+        second = __builtin_amdgcn_fmed3f(best, second, a);
+        best = fmaxf(best, a);
+    }
+}
+
+// RT row tiles; R registers of the last (the first of two takes all 16)
+template <int RT, int R>
+struct Rows {
+    static constexpr int kMask = RT == 1 ? 31 : 63;
+    // the two largest values of every column against this lane's rows
+    static __device__ __forceinline__ void column(const Operand (&a)[2], const Operand &b, float &best, float &second) {
+        if constexpr (RT == 2) {
+            fold_tile<16, kMask>(dot_tile(a[0], b), 0, true, best, second);
+            fold_tile<R, kMask>(dot_tile(a[1], b), 32, false, best, second);
+        } else {
+            fold_tile<R, kMask>(dot_tile(a[0], b), 0, true, best, second);
+        }
+    }
+    // Both halves of two tiles' columns: lanes 0..31 take tile X's columns, the others Y's.
+    // The owner's out-edge, and whether it is certified.
+    static __device__ __forceinline__ int owner(float bx, float sx, float by, float sy, bool &sure) {
+        float b0, b1, s0, s1;
+        swap_halves(bx, by, b0, b1);
+        swap_halves(sx, sy, s0, s1);
+        const float best = fmaxf(b0, b1), second = fmaxf(fmaxf(fminf(b0, b1), s0), s1);
+        sure = best - second > kCertified;
+        return (int)((__float_as_uint(best) & (unsigned)kMask) | (b1 > b0 ? 1u : 0u));
+    }
+};
 
 // q = R^T p for lattice point (x, y, z) (R row-major, 9 doubles)
 __device__ __forceinline__ void rotate_point(const double *R, double x, double y, double z, double &q0, double &q1,
@@ -63,117 +197,134 @@ __device__ __forceinline__ void rotate_point(const double *R, double x, double y
     q2 = fma(R[8], z, fma(R[5], y, R[2] * x));
 }
 
-// The FP32 screen.  For a slot with rotated point q and every out-edge m it forms
-//   t_m = fma(q2', s_m2', fma(q1', s_m1', fma(q0', s_m0', c))),  c = 1 + 2^-10,
-// where s' is s_m rounded to FP32 and q' = R'^T p' is the rotation done in FP32 (one multiply,
-// two FMAs per component) from the FP32 roundings R' and p'; it replaces the low six bits of
-// t_m's bit pattern by 63 - m (t_m is positive, so the patterns order like the values and the
-// packed maximum names its index) and keeps the largest packed value P_b and the second
-// largest P_2.  Error bound: with |p|, |s_m| and R's columns of norm <= 1 + 2^-49, every
-// component of q' is within 5 * 2^-24 of q (two input roundings and three operation roundings,
-// each at most 2^-24 times a magnitude <= 1), so q'.s' is within 5 sqrt(3) 2^-24 + 2^-23 <
-// 2^-20.5 of q.s; the three FMAs (results in [2^-11, 2.01]) round by at most 2^-23 each; and the
-// packing moves a value by less than 64 ulp <= 2^-17 P.  So every packed P_m lies within E_m =
-// 2^-17 P_m + 2^-19 of c + q.s_m, while the FP64 sequence lies within 2^-51 of q.s_m.  If
-// P_b - P_2 > 2^-16 P_b + 2^-17 (>= E_b + E_2 + 2^-50) then for every m != b the FP64 value of
-// m is strictly below that of b: b is the FP64 argmax, with no tie.  Other slots (near-ties:
-// a few pairs in 10,000 on jittered grids) rerun the FP64 sequence.
-constexpr float kScreenOff = 1.0f + 0x1p-10f;
-
-// one bitfield insert, (63 & k) | (~63 & t), under the inline constant 63 (written out: the
-// compiler splits the plain expression into an AND with a literal and an OR)
-__device__ __forceinline__ float screen_pack(float t, int k) {
-    float r;
-    asm("v_bfi_b32 %0, 63, %1, %2" : "=v"(r) : "s"(k), "v"(t));
-    return r;
-}
-
-// Owners of the lane's first S slots of (direction, lattice point) pairs (S covers the
-// group's pairs; slots past its last pair within them hold repeats and are scanned too).
-template <int S>
-__device__ __forceinline__ void screen_owners(int d, const float4 *s4, const double *sx, const double *sy,
-                                              const double *sz, const double *Rg, const double *__restrict__ lat,
-                                              int lane, int ng, int NF, float inv_nf, const float (&f0)[kQSlots],
-                                              const float (&f1)[kQSlots], const float (&f2)[kQSlots], bool screen,
-                                              int (&own)[kQSlots]) {
+// the rotation that takes direction u to the pole (row-major)
+__device__ __forceinline__ void pole_rotation(double ux, double uy, double uz, double (&R)[9]) {
 #pragma clang fp contract(off)
-    float best[S], second[S];
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-        best[j] = 0.0f;
-        second[j] = 0.0f;
-    }
-    // two out-edges per step: the top two of (best, second, p, w) are max3(best, p, w) and
-    // max(second, med3(best, p, w)) since second <= best
-    int m = 0;
-    for (; m + 1 < d; m += 2) {
-        const float4 t = s4[m], u = s4[m + 1];
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            const float pv = screen_pack(fmaf(f2[j], t.z, fmaf(f1[j], t.y, fmaf(f0[j], t.x, kScreenOff))), 63 - m);
-            const float pw = screen_pack(fmaf(f2[j], u.z, fmaf(f1[j], u.y, fmaf(f0[j], u.x, kScreenOff))), 62 - m);
-            second[j] = fmaxf(second[j], __builtin_amdgcn_fmed3f(best[j], pv, pw));
-            best[j] = fmaxf(fmaxf(best[j], pv), pw);
-        }
-    }
-    if (m < d) {
-        const float4 t = s4[m];
-#pragma unroll
-        for (int j = 0; j < S; ++j) {
-            const float pv = screen_pack(fmaf(f2[j], t.z, fmaf(f1[j], t.y, fmaf(f0[j], t.x, kScreenOff))), 63 - m);
-            second[j] = __builtin_amdgcn_fmed3f(best[j], second[j], pv);
-            best[j] = fmaxf(best[j], pv);
-        }
-    }
-    unsigned pending = 0;  // slots the screen does not certify
-#pragma unroll
-    for (int j = 0; j < S; ++j) {
-        own[j] = 63 - (int)(__float_as_uint(best[j]) & 63u);
-        if (!(screen && best[j] - second[j] > fmaf(best[j], 0x1p-16f, 0x1p-17f))) pending |= 1u << j;
-    }
-    // each lane decides its pending slots with the FP64 sequence (one slot per pass: lanes
-    // with different pending slots share the passes); ties go to the lowest index, the index
-    // moving only on a strict increase.  A slot past the group's last pair takes any valid
-    // direction (its owner is not used).
-    while (pending) {
-        const int j = __builtin_ctz(pending);
-        pending &= pending - 1;
-        const int p = j * 64 + lane;
-        const int al0 = small_div(p, inv_nf), i = p - al0 * NF, al = min(al0, ng - 1);
-        double q0, q1, q2;
-        rotate_point(Rg + 9 * al, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
-        double bb = -__builtin_inf();
-        int o = 0;
-        for (int k = 0; k < d; ++k) {
-            const double v = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
-            o = v > bb ? k : o;
-            bb = fmax(bb, v);
-        }
-#pragma unroll
-        for (int jj = 0; jj < S; ++jj) own[jj] = jj == j ? o : own[jj];
+    if (1.0 + uz < 1e-12) {
+        R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = -1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0; R[8] = -1.0;
+    } else {
+        const double h = 1.0 / (1.0 + uz);
+        const double xy = (ux * uy) * h;
+        R[0] = uz + (uy * uy) * h; R[1] = -xy; R[2] = -ux;
+        R[3] = -xy; R[4] = uz + (ux * ux) * h; R[5] = -uy;
+        R[6] = ux; R[7] = uy; R[8] = uz;
     }
 }
 
-// Five wavefronts per SIMD (96 VGPRs; its LDS allows about 4.75): the per-node setup
-// spills a few values that each group reloads, which costs less than the fifth wavefront
-// gains in hiding the loads and atomics around the screen
+// Dynamic LDS of a node in k_qbuild, for node degrees up to dm (a multiple of 8): the FP64
+// sites [3][dm], bins [8][dm] (fixed point) and lattice weights [128] (fixed point), the
+// rotations' rows in FP32 as float4 [dm + 1][3], and the queue of uncertified slots
+constexpr int kQueue = kQMaxGroup * 128;
+__host__ __device__ constexpr size_t qbuild_lds(int dm) {
+    return 8 * (size_t)(3 * dm + kQMaxGroup * dm + 128) + 48 * (size_t)(dm + 1) + 2 * (size_t)kQueue;
+}
+
+// One group of ng directions from a0: their owners' weights into the bins, and the slots
+// whose owner is not certified into the queue (point + 128 x direction of the group; returns
+// their number).  Full tiles of 32 lattice points are taken two directions at a time, the out-edges
+// rotated (A) against the lattice (B, the same for every direction); up to eight points past
+// the last full tile are taken for all directions of the group at once, as columns (point,
+// direction) with the points rotated instead (B) against the out-edges as they are (A).
+template <int RT, int R>
+__device__ __forceinline__ int group_owners(int a0, int ng, int n_in, int dm, int NF, int nt, int rest, bool screen,
+                                            int lane, const float (&site)[2][3], const unsigned (&past)[2],
+                                            const Operand (&fixed)[2], const Operand (&pts)[4], const float4 *rows,
+                                            const unsigned long long *wq, const double *__restrict__ lat,
+                                            unsigned long long *bins, unsigned short *queue) {
+    using T = Rows<RT, R>;
+    int nq = 0;
+    // lattice point pt's weight to its owner m for direction dl of the group, or the slot to the queue
+    auto settle = [&](bool valid, int dl, int pt, int m, bool sure) {
+        sure = sure && screen;
+        if (valid && sure && SG_IN(dl * dm + m, kQMaxGroup * dm, 0x203)) atomicAdd(&bins[dl * dm + m], wq[pt]);
+        const bool wait = valid && !sure;
+        const unsigned long long open = __ballot(wait);
+        if (open) {
+            if (wait) queue[nq + __popcll(open & ((1ull << lane) - 1ull))] = (unsigned short)(dl * 128 + pt);
+            nq += __popcll(open);
+        }
+    };
+    const int half = lane >> 5, col = lane & 31;
+    for (int dl = 0; dl < ng; dl += 2) {
+        const int a = min(a0 + dl + half, n_in - 1);  // past the last direction: a repeat, not counted
+        const float4 r0 = rows[3 * a], r1 = rows[3 * a + 1], r2 = rows[3 * a + 2];
+        Operand op[2][2];  // [direction][row tile]
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const float x = site[t][0], y = site[t][1], z = site[t][2];
+            unsigned p[3];
+            split_halves(fmaf(r0.z, z, fmaf(r0.y, y, r0.x * x)), fmaf(r1.z, z, fmaf(r1.y, y, r1.x * x)),
+                         fmaf(r2.z, z, fmaf(r2.y, y, r2.x * x)), p);
+            swap_halves(p[0], p[1], op[0][t].w[0], op[1][t].w[0]);
+            swap_halves(p[1], p[2], op[0][t].w[1], op[1][t].w[1]);
+            swap_halves(p[2], past[t], op[0][t].w[2], op[1][t].w[2]);
+            swap_halves(p[0], 0u, op[0][t].w[3], op[1][t].w[3]);
+        }
+        const bool two = dl + 1 < ng;
+#pragma unroll
+        for (int t = 0; t < 4; t += 2) {
+            float b[2], s[2];
+            bool sure;
+            if (t + 1 < nt) {  // two tiles of each direction
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (q == 1 && !two) break;
+                    T::column(op[q], pts[t], b[0], s[0]);
+                    T::column(op[q], pts[t + 1], b[1], s[1]);
+                    const int pt = 32 * t + lane, m = T::owner(b[0], s[0], b[1], s[1], sure);
+                    if (32 * t + 64 <= NF) settle(true, dl + q, pt, m, sure);
+                    else settle(pt < NF, dl + q, pt, m, sure);
+                }
+            } else if (t < nt) {  // the last tile of both directions
+                T::column(op[0], pts[t], b[0], s[0]);
+                T::column(op[1], pts[t], b[1], s[1]);
+                const int pt = 32 * t + col, m = T::owner(b[0], s[0], b[1], s[1], sure);
+                settle((half == 0 || two) && pt < NF, dl + half, pt, m, sure);
+            }
+        }
+    }
+    if (rest) {
+        const int n = ng * rest;  // columns, at most 64
+        const int dl = min(small_div(lane, 1.0f / (float)rest), ng - 1);
+        const int pt = 32 * nt + lane - rest * small_div(lane, 1.0f / (float)rest);
+        const float4 r0 = rows[3 * (a0 + dl)], r1 = rows[3 * (a0 + dl) + 1], r2 = rows[3 * (a0 + dl) + 2];
+        const float x = (float)lat[3 * pt] * kHalfScale, y = (float)lat[3 * pt + 1] * kHalfScale,
+                    z = (float)lat[3 * pt + 2] * kHalfScale;
+        unsigned p[3];  // q = R^T p
+        split_halves(fmaf(r2.x, z, fmaf(r1.x, y, r0.x * x)), fmaf(r2.y, z, fmaf(r1.y, y, r0.y * x)),
+                     fmaf(r2.z, z, fmaf(r1.z, y, r0.z * x)), p);
+        const unsigned one = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(kHalfScale, 0.0f));
+        Operand q[2];  // (hx, hy) (hz, hx) (hy, hz) (lx, ly) | (lz, lx) (ly, lz) (2^10, 0) 0
+        swap_halves(p[0], (p[2] >> 16) | (p[1] & 0xffff0000u), q[0].w[0], q[1].w[0]);
+        swap_halves((p[1] & 0xffffu) | (p[0] << 16), p[2], q[0].w[1], q[1].w[1]);
+        swap_halves((p[0] >> 16) | (p[1] << 16), one, q[0].w[2], q[1].w[2]);
+        swap_halves((p[1] >> 16) | (p[2] << 16), 0u, q[0].w[3], q[1].w[3]);
+        float b0, s0, b1, s1;
+        T::column(fixed, q[0], b0, s0);
+        if (n > 32) T::column(fixed, q[1], b1, s1);
+        else { b1 = b0; s1 = s0; }
+        bool sure;
+        const int m = T::owner(b0, s0, b1, s1, sure);
+        settle(lane < n, dl, pt, m, sure);
+    }
+    return nq;
+}
+
 template <class Real, class BlkT, bool kWriteQ>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_qbuild(
     int N, int nvol, const long long *__restrict__ adj_ptr, const int *__restrict__ adj_idx,
-    const int *__restrict__ pos, const double *__restrict__ lat, const double *__restrict__ tab, int NF, int n_phase,
-    const float *__restrict__ frac, double sun_x, double sun_y, double sun_z, Real mu0, const Real *__restrict__ T,
-    const Real *__restrict__ rho, const Real *__restrict__ Tsun, const long long *__restrict__ nodeoff,
-    BlkT *__restrict__ val, Real *__restrict__ S, float *__restrict__ qsun, int group, int per, long long wx,
-    long long wy, int screen) {
+    const int *__restrict__ pos, const double *__restrict__ lat, const uint4 *__restrict__ lat_halves,
+    const double *__restrict__ tab, int NF, int n_phase, const float *__restrict__ frac, double sun_x, double sun_y,
+    double sun_z, Real mu0, const Real *__restrict__ T, const Real *__restrict__ rho, const Real *__restrict__ Tsun,
+    const long long *__restrict__ nodeoff, BlkT *__restrict__ val, Real *__restrict__ S, float *__restrict__ qsun,
+    int dm, int per, long long wx, long long wy, int screen) {
 #pragma clang fp contract(off)
     extern __shared__ double qb_lds[];
-    double *sx = qb_lds, *sy = qb_lds + 64, *sz = qb_lds + 128;
-    float4 *s4 = reinterpret_cast<float4 *>(qb_lds + 192);
-    float4 *lt4 = reinterpret_cast<float4 *>(qb_lds + 320);
-    float4 *Rc4 = reinterpret_cast<float4 *>(qb_lds + 320 + 2 * NF);
-    unsigned long long *wq = reinterpret_cast<unsigned long long *>(qb_lds + 320 + 2 * NF + 6 * group);
-    double *Rg = qb_lds + 320 + 3 * NF + 6 * group;
-    unsigned long long *bins = reinterpret_cast<unsigned long long *>(Rg + 9 * group);
+    double *sx = qb_lds, *sy = qb_lds + dm, *sz = qb_lds + 2 * dm;
+    unsigned long long *bins = reinterpret_cast<unsigned long long *>(qb_lds + 3 * dm);
+    unsigned long long *wq = bins + kQMaxGroup * dm;
+    float4 *rows = reinterpret_cast<float4 *>(wq + 128);
+    unsigned short *queue = reinterpret_cast<unsigned short *>(rows + 3 * (dm + 1));
 
     const int l = blockIdx.x;
     const int lane = threadIdx.x;
@@ -183,6 +334,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const bool surf = l >= nvol;
     if (!SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x201)) return;
 
+    bool zero = false;
     if (lane < d) {
         const int j0 = adj_idx[off + lane];
         const int j = SG_IN(j0, N, 0x202) ? j0 : l;
@@ -190,24 +342,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
         const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
         const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-        const double ex = (double)Dx / nrm, ey = (double)Dy / nrm, ez = (double)Dz / nrm;
-        sx[lane] = ex;
-        sy[lane] = ey;
-        sz[lane] = ez;
-        s4[lane] = make_float4((float)ex, (float)ey, (float)ez, 0.0f);
+        zero = (Dx | Dy | Dz) == 0;
+        sx[lane] = (double)Dx / nrm;
+        sy[lane] = (double)Dy / nrm;
+        sz[lane] = (double)Dz / nrm;
     }
-    for (int i = lane; i < NF; i += 64)
-        lt4[i] = make_float4((float)lat[3 * i], (float)lat[3 * i + 1], (float)lat[3 * i + 2], 0.0f);
-    const float inv_nf = 1.0f / (float)NF, inv_d = 1.0f / (float)d;
-    // the lane's slots: slot j holds pair p = 64 j + lane of a group, direction p / N_fib of
-    // the group and lattice point p mod N_fib, kept as direction * 128 + point
-    int sai[kQSlots];
-#pragma unroll
-    for (int j = 0; j < kQSlots; ++j) {
-        const int p = j * 64 + lane;
-        const int al = small_div(p, inv_nf);
-        sai[j] = al * 128 + (p - al * NF);
-    }
+    const bool screened = screen != 0 && __ballot(zero) == 0;
     // phase weights of the lattice points in fixed point
     for (int i = lane; i < NF; i += 64) {
         double w;
@@ -222,73 +362,103 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         }
         wq[i] = (unsigned long long)llrint(w * kFix);
     }
+    __syncthreads();
+    // the rotations of all incoming directions, in FP32
+    const int n_in = surf ? 1 : d + 1;
+    for (int a = lane; a < n_in; a += 64) {
+        double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+        if (!surf) {
+            if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
+            else pole_rotation(sun_x, sun_y, sun_z, R);
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            rows[3 * a + k] = make_float4((float)R[3 * k], (float)R[3 * k + 1], (float)R[3 * k + 2], 0.0f);
+    }
+    // this lane's out-edge of each row tile, its halves as they are, and the lattice
+    const unsigned below = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(-2.0f * kHalfScale, 0.0f));
+    float site[2][3];
+    unsigned past[2];
+    Operand fixed[2], pts[4];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        const int r = lane & 31, m = 32 * t + 2 * (4 * (r >> 3) + (r & 3)) + (r >> 2 & 1);
+        const bool in = m < d;
+        site[t][0] = in ? (float)sx[m] * kHalfScale : 0.0f;
+        site[t][1] = in ? (float)sy[m] * kHalfScale : 0.0f;
+        site[t][2] = in ? (float)sz[m] * kHalfScale : 0.0f;
+        past[t] = in ? 0u : below;
+        unsigned p[3];
+        split_halves(site[t][0], site[t][1], site[t][2], p);
+        const bool low = lane < 32;
+        fixed[t].w[0] = low ? p[0] : p[1];
+        fixed[t].w[1] = low ? p[1] : p[2];
+        fixed[t].w[2] = low ? p[2] : past[t];
+        fixed[t].w[3] = low ? p[0] : 0u;
+    }
+    // full tiles of lattice points; up to eight points past them are columns of their own, more
+    // make another tile
+    int nt = NF >> 5, rest = NF & 31;
+    if (rest > 8) {
+        ++nt;
+        rest = 0;
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const uint4 v = lat_halves[64 * t + lane];
+        pts[t].w[0] = v.x;
+        pts[t].w[1] = v.y;
+        pts[t].w[2] = v.z;
+        pts[t].w[3] = v.w;
+    }
 
+    const float inv_d = 1.0f / (float)d;
     const Real rl = rho ? rho[l] : (Real)0;
     const Real tsun = Tsun ? Tsun[l] : (Real)0;
     BlkT *blk = val + nodeoff[l];  // column-major: element (row n, column m) at m d + n
-    const int n_in = surf ? 1 : d + 1;
-    for (int a0 = 0; a0 < n_in; a0 += group) {
-        const int ng = min(group, n_in - a0);
-        // rotations of this group's incoming directions (FP64, and their columns in FP32), and
-        // empty bins
-        if (lane < ng) {
-            const int a = a0 + lane;
-            double *R = Rg + 9 * lane;
-            if (surf) {
-                R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = 1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0;
-                R[8] = 1.0;
-            } else {
-                double ux, uy, uz;
-                if (a < d) { ux = -sx[a]; uy = -sy[a]; uz = -sz[a]; }
-                else { ux = sun_x; uy = sun_y; uz = sun_z; }
-                if (1.0 + uz < 1e-12) {
-                    R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = -1.0; R[5] = 0.0; R[6] = 0.0;
-                    R[7] = 0.0; R[8] = -1.0;
-                } else {
-                    const double h = 1.0 / (1.0 + uz);
-                    const double xy = (ux * uy) * h;
-                    R[0] = uz + (uy * uy) * h; R[1] = -xy; R[2] = -ux;
-                    R[3] = -xy; R[4] = uz + (ux * ux) * h; R[5] = -uy;
-                    R[6] = ux; R[7] = uy; R[8] = uz;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < 3; ++k)
-                Rc4[3 * lane + k] = make_float4((float)R[k], (float)R[3 + k], (float)R[6 + k], 0.0f);
-        }
-        for (int t = lane; t < ng * 64; t += 64) bins[t] = 0ull;
+    for (int a0 = 0; a0 < n_in; a0 += kQMaxGroup) {
+        const int ng = min(kQMaxGroup, n_in - a0);
+        for (int t = lane; t < ng * dm; t += 64) bins[t] = 0ull;
         __syncthreads();
-        // this lane's pairs: q' = R'^T p' in FP32 for each (a slot past the group's last pair
-        // takes the group's last direction: scanned, not counted), then the owners
-        const int np = ng * NF;  // pairs of this group
-        float f0[kQSlots], f1[kQSlots], f2[kQSlots];
-        int own[kQSlots];
-#pragma unroll
-        for (int j = 0; j < kQSlots; ++j) {
-            const int al = min(sai[j] >> 7, ng - 1);
-            const float4 pt = lt4[sai[j] & 127], c0 = Rc4[3 * al], c1 = Rc4[3 * al + 1], c2 = Rc4[3 * al + 2];
-            f0[j] = fmaf(c0.z, pt.z, fmaf(c0.y, pt.y, c0.x * pt.x));
-            f1[j] = fmaf(c1.z, pt.z, fmaf(c1.y, pt.y, c1.x * pt.x));
-            f2[j] = fmaf(c2.z, pt.z, fmaf(c2.y, pt.y, c2.x * pt.x));
-            own[j] = 0;
-        }
-        // slots per lane that this group's pairs need (a node's last group is often short)
-        const bool scr = screen != 0;
-        if (np <= 2 * 64) screen_owners<2>(d, s4, sx, sy, sz, Rg, lat, lane, ng, NF, inv_nf, f0, f1, f2, scr, own);
-        else if (np <= 4 * 64) screen_owners<4>(d, s4, sx, sy, sz, Rg, lat, lane, ng, NF, inv_nf, f0, f1, f2, scr, own);
-        else if (np <= 6 * 64) screen_owners<6>(d, s4, sx, sy, sz, Rg, lat, lane, ng, NF, inv_nf, f0, f1, f2, scr, own);
-        else screen_owners<kQSlots>(d, s4, sx, sy, sz, Rg, lat, lane, ng, NF, inv_nf, f0, f1, f2, scr, own);
-#pragma unroll
-        for (int j = 0; j < kQSlots; ++j) {
-            const int al = sai[j] >> 7;  // below ng exactly for the group's pairs
-            if (al < ng && SG_IN(al * 64 + own[j], group * 64, 0x203))
-                atomicAdd(&bins[al * 64 + own[j]], wq[sai[j] & 127]);
+        int nq;
+#define SG_GROUP(RT, R)                                                                                            \
+    nq = group_owners<RT, R>(a0, ng, n_in, dm, NF, nt, rest, screened, lane, site, past, fixed, pts, rows, wq, lat, \
+                             bins, queue)
+        if (d <= 8) SG_GROUP(1, 4);
+        else if (d <= 16) SG_GROUP(1, 8);
+        else if (d <= 20) SG_GROUP(1, 10);
+        else if (d <= 24) SG_GROUP(1, 12);
+        else if (d <= 28) SG_GROUP(1, 14);
+        else if (d <= 32) SG_GROUP(1, 16);
+        else if (d <= 48) SG_GROUP(2, 8);
+        else SG_GROUP(2, 16);
+#undef SG_GROUP
+        __syncthreads();
+        // the uncertified slots, one per lane, with the FP64 sequence; ties go to the lowest
+        // index, the index moving only on a strict increase
+        for (int t = lane; t < nq; t += 64) {
+            const int slot = queue[t], dl = slot >> 7, i = slot & 127, a = a0 + dl;
+            double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+            if (!surf) {
+                if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
+                else pole_rotation(sun_x, sun_y, sun_z, R);
+            }
+            double q0, q1, q2;
+            rotate_point(R, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
+            double best = -__builtin_inf();
+            int o = 0;
+            for (int k = 0; k < d; ++k) {
+                const double v = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
+                o = v > best ? k : o;
+                best = fmax(best, v);
+            }
+            if (SG_IN(dl * dm + o, kQMaxGroup * dm, 0x203)) atomicAdd(&bins[dl * dm + o], wq[i]);
         }
         __syncthreads();
         // this group's columns: pair t = (a - a0) d + m is column a, row m
         for (int t = lane; t < ng * d; t += 64) {
             const int al = small_div(t, inv_d), m = t - al * d, a = a0 + al;
-            const double Q = (double)(long long)bins[al * 64 + m] * kUnfix;
+            const double Q = (double)(long long)bins[al * dm + m] * kUnfix;
             const long long b = off + m;
             if (surf) {
                 for (int c = 0; c < d; ++c) {
@@ -972,8 +1142,8 @@ int qbuild_group_big(int NF) { return std::min(qbuild_group(NF), kBigGroup); }
 template <class Real>
 void launch_qbuild(Scene &s, hipStream_t st, int write_q) {
     const size_t shm = 0;
-    const int group = qbuild_group(s.n_fib);
-    const size_t qshm = sizeof(double) * (size_t)qbuild_lds_doubles(s.n_fib, group);
+    const int dm = (std::min(s.dmax, kWave) + 7) / 8 * 8;
+    const size_t qshm = qbuild_lds(dm);
     if (s.sigma_mode == SG_SIGMA_COLOUR) {
         if (write_q) {
             hipLaunchKernelGGL((k_qcolour<Real, float, true>), dim3(s.N), dim3(64), shm, st, s.N, s.n_vol, s.adj_ptr,
@@ -1024,15 +1194,15 @@ void launch_qbuild(Scene &s, hipStream_t st, int write_q) {
     }
     if (write_q) {
         hipLaunchKernelGGL((k_qbuild<Real, float, true>), dim3(s.N), dim3(64), qshm, st, s.N, s.n_vol, s.adj_ptr,
-                           s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
+                           s.adj_idx, s.pos, s.lat, (const uint4 *)s.lat_halves, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
                            s.sun_in[2], (Real)s.mu0, (const Real *)nullptr, (const Real *)nullptr,
-                           (const Real *)nullptr, s.nodeoff, s.q, (Real *)nullptr, s.qsun, group, s.periodic, (long long)s.nx * kFx,
-                           (long long)s.ny * kFx, s.qscreen);
+                           (const Real *)nullptr, s.nodeoff, s.q, (Real *)nullptr, s.qsun, dm, s.periodic,
+                           (long long)s.nx * kFx, (long long)s.ny * kFx, s.qscreen);
     } else {
         hipLaunchKernelGGL((k_qbuild<Real, Real, false>), dim3(s.N), dim3(64), qshm, st, s.N, s.n_vol, s.adj_ptr,
-                           s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
+                           s.adj_idx, s.pos, s.lat, (const uint4 *)s.lat_halves, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
                            s.sun_in[2], (Real)s.mu0, (const Real *)s.T, (const Real *)s.rho, (const Real *)s.Tsun,
-                           s.nodeoff, (Real *)s.val, (Real *)s.S, s.qsun, group, s.periodic, (long long)s.nx * kFx,
+                           s.nodeoff, (Real *)s.val, (Real *)s.S, s.qsun, dm, s.periodic, (long long)s.nx * kFx,
                            (long long)s.ny * kFx, s.qscreen);
     }
 }
