@@ -263,9 +263,8 @@ template <class Real>
 void launch_node_weights(Scene &s, hipStream_t st, float scale);
 template <class Real>
 void launch_qbuild(Scene &s, hipStream_t st, int write_q);
-// incoming directions the phase-cell kernels take per group (a lattice of NF points), and
-// per workgroup of the kernel for nodes of degree above 64
-int qbuild_group(int NF);
+// incoming directions per workgroup of the phase-cell kernel for nodes of degree above 64 (a
+// lattice of NF points)
 int qbuild_group_big(int NF);
 
 // Which nodes a sweep visits: its argument front is 0 (all), kFrontFirst (all, marking the

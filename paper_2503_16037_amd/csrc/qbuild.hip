@@ -38,7 +38,6 @@ namespace {
 
 constexpr double kFix = 4503599627370496.0;  // 2^52
 constexpr double kUnfix = 1.0 / 4503599627370496.0;
-constexpr int kQSlots = 8;     // k_qbuild_big: (direction, lattice point) pairs per lane in a group
 constexpr int kQMaxGroup = 8;  // incoming directions per group
 
 // p / n for 0 <= p < 1024 and 1 <= n <= 128 with one FP32 multiply: (p + 1/2) / n is at
@@ -479,41 +478,80 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     }
 }
 
-// Nodes of degree above 64 (graphs whose strongest couplings gather on the dense nodes):
-// one 64-lane workgroup per (node, group of `group` incoming directions), wg = bigdir[b] +
-// g.  The (direction, lattice point) pairs fill the lanes' eight slots as in k_qbuild, and
-// the node's out-edge directions are formed in LDS 64 at a time and scanned in ascending
-// order with k_qbuild's operation sequence and tie rule, so each direction read from LDS
-// serves eight dot products.  No FP32 screen here: with hundreds to thousands of out-edges
-// the top two of a pair are within the screen's bound far more often (percents of the
-// pairs), and deciding those again cost more than the screen saved.  A direction's lattice points have at most N_fib distinct
-// owners among the d out-edges, so its cell sums go to a 256-slot open-addressing table in
-// LDS (owner -> fixed-point sum, exact integer atomics) rather than d words; the column is
-// then written by looking every row up (absent: 0).
-constexpr int kCellHash = 256;  // above the most owners a direction can have (N_fib <= 128)
-constexpr int kBigGroup = 5;    // directions per workgroup (the tables' LDS)
+// Nodes of degree above 64 (graphs whose strongest couplings gather on the dense nodes): one
+// workgroup of four wavefronts per (node, group of `group` incoming directions), wg =
+// bigdir[b] + g.  The group's (direction, lattice point) pairs are the columns of the screen's
+// matrix products, up to 1024, the points rotated by their direction; a wavefront keeps its
+// pairs of column tiles in registers and the out-edges pass by as row tiles from LDS, so each
+// is split into its halves once per group and read once per wavefront.
+//
+// Every lane keeps the largest value of a tile's 16 rows it holds (8 instructions), and of
+// those the two largest with the largest one's tile (4 more): with hundreds of out-edges an
+// index in every value, as k_qbuild inserts it, would cost 38.  The 16 rows of the best tile
+// are then done again in FP32 with a 4-bit index.
+// Error bound, in units of v: rotated point 5 2^-24 per component in FP32, its halves and the
+// out-edge's 2^-22 each (rounded toward zero), the out-edge in FP32 from its integer offset 6
+// 2^-24 relative: together below (sqrt(3) 13 + 6) 2^-24 < 2^-19.1; the additions of the matrix
+// product 2^-19, or the FP32 ones 3 2^-24 with the index 2^-19.  Any two of these values
+// together are off by less than 2^-17 (kBigCertified), so a larger gap between the best row and
+// the largest of all others certifies the FP64 argmax.  The other columns (below a percent
+// on jittered positions) are queued, and the workgroup scans all out-edges for them with the FP64
+// sequence, several lanes per column while there are few.
+//
+// Bound: vector issue, 81 % of the time (plume 64x64x32 with its 11.5 strongest couplings per voxel,
+// 1.3e9 cells: 35.6 ms with FP64 dot products for all out-edges, now 9.4 ms; four tenths of the
+// vector instructions are the tiles', a sixth the best tiles' rows again).
+constexpr int kBigPairs = 4;                    // pairs of 32-column tiles per wavefront
+constexpr int kBigCols = 4 * kBigPairs * 64;    // columns per workgroup
+constexpr int kBigGroup = 16;                   // most directions per workgroup (their rotations in LDS)
+constexpr int kBigRows = 1024;                  // out-edges in LDS at a time, as halves
+constexpr int kScanEdges = 256;                 // out-edges in LDS at a time, in FP64
+constexpr int kBinRows = 512;                   // rows of a column summed at a time, per wavefront
+constexpr float kBigCertified = 8.0f;           // 2^-17 in units of 2^-20
 
-constexpr unsigned short kNoOwner = 0xffff;  // owners are below 4096
-
-__device__ __forceinline__ int cell_find(const unsigned short *keys, int m) {
-    int h = m & (kCellHash - 1);
-    while (keys[h] != m && keys[h] != kNoOwner) h = (h + 1) & (kCellHash - 1);
-    return keys[h] == m ? h : -1;
+// A wavefront's first C pairs of column tiles against nt row tiles: per lane and tile the
+// largest value of its rows, the second largest of the row tiles' largest, and the best's tile
+template <int C>
+__device__ __forceinline__ void pass_rows(const uint4 *rows, int nt, int col, const Operand (&pts)[2 * kBigPairs],
+                                          float (&best)[2 * kBigPairs], float (&second)[2 * kBigPairs],
+                                          int (&tile)[2 * kBigPairs]) {
+    uint4 next = rows[col];
+    for (int t = 0; t < nt; ++t) {
+        const Operand a = {{next.x, next.y, next.z, next.w}};
+        next = rows[32 * min(t + 1, nt - 1) + col];
+#pragma unroll
+        for (int j = 0; j < 2 * C; ++j) {
+            const float16v v = dot_tile(a, pts[j]);
+            auto largest = [](float x, float y, float z) { return fmaxf(fmaxf(x, y), z); };
+            const float x = largest(v[0], v[1], v[2]), y = largest(v[3], v[4], v[5]), z = largest(v[6], v[7], v[8]);
+            const float w = largest(v[9], v[10], v[11]), u = largest(v[12], v[13], v[14]);
+            const float top = fmaxf(largest(x, y, z), largest(w, u, v[15]));
+            second[j] = __builtin_amdgcn_fmed3f(best[j], second[j], top);
+            tile[j] = top > best[j] ? t : tile[j];
+            best[j] = fmaxf(best[j], top);
+        }
+    }
 }
 
 template <class Real, class BlkT, bool kWriteQ>
-__global__ __launch_bounds__(64) void k_qbuild_big(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_qbuild_big(
     int nbig, const int *__restrict__ big, const long long *__restrict__ bigdir, int nvol,
     const long long *__restrict__ adj_ptr, const int *__restrict__ adj_idx, const int *__restrict__ pos,
     const double *__restrict__ lat, const double *__restrict__ tab, int NF, int n_phase,
     const float *__restrict__ frac, double sun_x, double sun_y, double sun_z, Real mu0, const Real *__restrict__ T,
     const Real *__restrict__ rho, const Real *__restrict__ Tsun, const long long *__restrict__ nodeoff,
     BlkT *__restrict__ val, Real *__restrict__ S, float *__restrict__ qsun, int group, int per, long long wx,
-    long long wy) {
+    long long wy, int screen) {
 #pragma clang fp contract(off)
-    __shared__ double cx[64], cy[64], cz[64], Rg[kBigGroup * 9], lt[384];
-    __shared__ unsigned long long wq[128], hval[kBigGroup][kCellHash];
-    __shared__ unsigned short hkey[kBigGroup][kCellHash];
+    // out-edges as halves, then out-edges in FP64, then each wavefront's bins
+    __shared__ uint4 pool[kBigRows];
+    __shared__ float4 whole[kBigRows];  // the same out-edges in FP32
+    static_assert(sizeof(pool) >= 3 * kScanEdges * sizeof(double), "FP64 out-edges");
+    static_assert(sizeof(pool) >= 4 * kBinRows * sizeof(unsigned long long), "bins");
+    __shared__ double Rg[kBigGroup * 9];
+    __shared__ unsigned long long wq[128];
+    __shared__ unsigned short owner[kBigCols], queue[kBigCols];
+    __shared__ int queued;
     const long long wg = blockIdx.x;
     int lo = 0, hi = nbig;  // the node b with bigdir[b] <= wg < bigdir[b + 1]
     while (hi - lo > 1) {
@@ -521,148 +559,271 @@ __global__ __launch_bounds__(64) void k_qbuild_big(
         if (bigdir[mid] <= wg) lo = mid; else hi = mid;
     }
     const int l = big[lo];
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const long long off = adj_ptr[l];
     const int d = (int)(adj_ptr[l + 1] - off);
     const bool surf = l >= nvol;
     const int n_in = surf ? 1 : d + 1;
     const int a0 = (int)(wg - bigdir[lo]) * group;
     const int ng = min(group, n_in - a0);
+    auto edge_offset = [&](int m, long long &Dx, long long &Dy, long long &Dz) {
+        const int j = adj_idx[off + m];
+        Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
+        Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
+        Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
+    };
     // the unit direction of out-edge m (the operation sequence of k_qbuild)
     auto edge_dir = [&](int m, double &ex, double &ey, double &ez) {
-        const int j = adj_idx[off + m];
-        const long long Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
-        const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
-        const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
+        long long Dx, Dy, Dz;
+        edge_offset(m, Dx, Dy, Dz);
         const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
         ex = (double)Dx / nrm;
         ey = (double)Dy / nrm;
         ez = (double)Dz / nrm;
     };
-    for (int i = lane; i < NF; i += 64) {
-        lt[i] = lat[3 * i];
-        lt[128 + i] = lat[3 * i + 1];
-        lt[256 + i] = lat[3 * i + 2];
+    if (tid < NF) {
         double w;
         if (surf) {
-            w = tab[n_phase * NF + i];
+            w = tab[n_phase * NF + tid];
         } else {
             w = 0.0;
             for (int k = 0; k < n_phase; ++k) {
                 const double f = frac ? (double)frac[(long long)k * nvol + l] : 1.0;
-                w = w + f * tab[k * NF + i];
+                w = w + f * tab[k * NF + tid];
             }
         }
-        wq[i] = (unsigned long long)llrint(w * kFix);
+        wq[tid] = (unsigned long long)llrint(w * kFix);
     }
-    for (int t = lane; t < ng * kCellHash; t += 64) {
-        hkey[t / kCellHash][t % kCellHash] = kNoOwner;
-        hval[t / kCellHash][t % kCellHash] = 0ull;
-    }
+    if (tid == 0) queued = 0;
     // rotations of this group's incoming directions
-    if (lane < ng) {
-        const int a = a0 + lane;
-        double *R = Rg + 9 * lane;
-        if (surf) {
-            R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = 1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0; R[8] = 1.0;
-        } else {
-            double ux, uy, uz;
+    if (tid >= 192 && tid - 192 < ng) {
+        const int a = a0 + tid - 192;
+        double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+        if (!surf) {
+            double ux = sun_x, uy = sun_y, uz = sun_z;
             if (a < d) {
                 edge_dir(a, ux, uy, uz);
                 ux = -ux; uy = -uy; uz = -uz;
-            } else {
-                ux = sun_x; uy = sun_y; uz = sun_z;
             }
-            if (1.0 + uz < 1e-12) {
-                R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = -1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0;
-                R[8] = -1.0;
-            } else {
-                const double h = 1.0 / (1.0 + uz);
-                const double xy = (ux * uy) * h;
-                R[0] = uz + (uy * uy) * h; R[1] = -xy; R[2] = -ux;
-                R[3] = -xy; R[4] = uz + (ux * ux) * h; R[5] = -uy;
-                R[6] = ux; R[7] = uy; R[8] = uz;
-            }
+            pole_rotation(ux, uy, uz, R);
         }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) Rg[9 * (tid - 192) + k] = R[k];
     }
     __syncthreads();
-    // this lane's pairs: q = R^T p
     const int np = ng * NF;
     const float inv_nf = 1.0f / (float)NF;
-    double q0[kQSlots], q1[kQSlots], q2[kQSlots], best[kQSlots];
-    int own[kQSlots];
-#pragma unroll
-    for (int j = 0; j < kQSlots; ++j) {
-        const int p = min(j * 64 + lane, np - 1);  // past the last pair: a repeat, not counted
+    // column p's rotated point q = R^T p in FP32, scaled
+    auto column = [&](int p, float &x, float &y, float &z) {
         const int al = small_div(p, inv_nf), i = p - al * NF;
         const double *R = Rg + 9 * al;
-        const double x = lt[i], y = lt[128 + i], z = lt[256 + i];
-        q0[j] = fma(R[6], z, fma(R[3], y, R[0] * x));
-        q1[j] = fma(R[7], z, fma(R[4], y, R[1] * x));
-        q2[j] = fma(R[8], z, fma(R[5], y, R[2] * x));
-        best[j] = -__builtin_inf();
-        own[j] = 0;
-    }
-    for (int m0 = 0; m0 < d; m0 += 64) {
-        const int nm = min(64, d - m0);
-        if (lane < nm) edge_dir(m0 + lane, cx[lane], cy[lane], cz[lane]);
-        __syncthreads();
-        for (int mm = 0; mm < nm; ++mm) {
-            const double tx = cx[mm], ty = cy[mm], tz = cz[mm];
+        const float u = (float)lat[3 * i] * kHalfScale, v = (float)lat[3 * i + 1] * kHalfScale,
+                    w = (float)lat[3 * i + 2] * kHalfScale;
+        x = fmaf((float)R[6], w, fmaf((float)R[3], v, (float)R[0] * u));
+        y = fmaf((float)R[7], w, fmaf((float)R[4], v, (float)R[1] * u));
+        z = fmaf((float)R[8], w, fmaf((float)R[5], v, (float)R[2] * u));
+    };
+    // this wavefront's pair j holds the columns 64 (wave + 4 j) + lane
+    const int pairs = (np + 63) / 64;
+    const int mine = pairs > wave ? (pairs - wave + 3) / 4 : 0;
+    bool zero = false;  // a zero-length out-edge: no direction
+    float run_best[kBigPairs], run_second[kBigPairs];
+    int run_own[kBigPairs];
+    if (screen) {
+        Operand pts[2 * kBigPairs];
 #pragma unroll
-            for (int j = 0; j < kQSlots; ++j) {
-                const double v = fma(q2[j], tz, fma(q1[j], ty, q0[j] * tx));
-                own[j] = v > best[j] ? m0 + mm : own[j];
-                best[j] = fmax(best[j], v);
+        for (int j = 0; j < kBigPairs; ++j) {
+            float x, y, z;
+            column(min(64 * (wave + 4 * j) + lane, np - 1), x, y, z);  // past the last: a repeat, not counted
+            unsigned p[3];
+            split_halves(x, y, z, p);
+            // k 0..7 hi (x, y) (z, x) (y, z) (2^10, 0); k 8..15 lo (x, y) (z, x) (y, z) 0
+            const unsigned one = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(kHalfScale, 0.0f));
+            Operand &s = pts[2 * j], &t = pts[2 * j + 1];
+            swap_halves(p[0], (p[1] >> 16) | (p[2] << 16), s.w[0], t.w[0]);
+            swap_halves((p[1] & 0xffffu) | (p[0] << 16), (p[2] >> 16) | (p[1] & 0xffff0000u), s.w[1], t.w[1]);
+            swap_halves((p[0] >> 16) | (p[1] << 16), p[2], s.w[2], t.w[2]);
+            swap_halves(one, 0u, s.w[3], t.w[3]);
+            run_best[j] = -8.0f * 0x1p20f;
+            run_second[j] = -8.0f * 0x1p20f;
+            run_own[j] = 0;
+        }
+        for (int m0 = 0; m0 < d; m0 += kBigRows) {
+            const int nm = min(kBigRows, d - m0), nt = (nm + 31) / 32;
+            if (m0) __syncthreads();
+            // both k halves of a row read (hi x, y) (hi z, lo x) (lo y, z) (0 or -2^11 past the last, 0)
+            for (int r = tid; r < 32 * nt; r += 256) {
+                const float past = r < nm ? 0.0f : -2.0f * kHalfScale;
+                float4 site = make_float4(0.0f, 0.0f, 0.0f, kHalfScale * past);
+                if (r < nm) {
+                    long long Dx, Dy, Dz;
+                    edge_offset(m0 + r, Dx, Dy, Dz);
+                    zero = zero || (Dx | Dy | Dz) == 0;
+                    const float x = (float)Dx, y = (float)Dy, z = (float)Dz;
+                    const float inv = __builtin_amdgcn_rsqf(fmaf(z, z, fmaf(y, y, x * x))) * kHalfScale;
+                    site.x = x * inv;
+                    site.y = y * inv;
+                    site.z = z * inv;
+                }
+                unsigned p[3];
+                split_halves(site.x, site.y, site.z, p);
+                pool[r] = make_uint4(p[0], p[1], p[2],
+                                     __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(past, 0.0f)));
+                whole[r] = site;
+            }
+            __syncthreads();
+            float best[2 * kBigPairs], second[2 * kBigPairs];
+            int tile[2 * kBigPairs];
+#pragma unroll
+            for (int j = 0; j < 2 * kBigPairs; ++j) {
+                best[j] = -8.0f * 0x1p20f;
+                second[j] = -8.0f * 0x1p20f;
+                tile[j] = 0;
+            }
+            if (mine == 4) pass_rows<4>(pool, nt, lane & 31, pts, best, second, tile);
+            else if (mine == 3) pass_rows<3>(pool, nt, lane & 31, pts, best, second, tile);
+            else if (mine == 2) pass_rows<2>(pool, nt, lane & 31, pts, best, second, tile);
+            else if (mine == 1) pass_rows<1>(pool, nt, lane & 31, pts, best, second, tile);
+            // lanes take a column each (both halves of the rows), and its best tile's 16 rows again
+#pragma unroll
+            for (int j = 0; j < kBigPairs; ++j) {
+                if (j >= mine) continue;
+                float b0, b1, s0, s1;
+                unsigned t0, t1;
+                swap_halves(best[2 * j], best[2 * j + 1], b0, b1);
+                swap_halves(second[2 * j], second[2 * j + 1], s0, s1);
+                swap_halves((unsigned)tile[2 * j], (unsigned)tile[2 * j + 1], t0, t1);
+                const bool upper = b1 > b0;
+                const int r0 = 32 * (int)(upper ? t1 : t0) + (upper ? 4 : 0);
+                float x, y, z;
+                column(min(64 * (wave + 4 * j) + lane, np - 1), x, y, z);
+                float top = -8.0f * 0x1p20f, next = fmaxf(fmaxf(fminf(b0, b1), s0), s1);
+                auto again = [&](int i) {
+                    const float4 a = whole[r0 + 8 * (i >> 2) + (i & 3)];
+                    const float v = fmaf(a.z, z, fmaf(a.y, y, fmaf(a.x, x, a.w)));
+                    return __uint_as_float((__float_as_uint(v) & ~15u) | (unsigned)i);
+                };
+#pragma unroll
+                for (int i = 0; i < 16; i += 2) {
+                    const float v = again(i), w = again(i + 1);
+                    next = fmaxf(next, __builtin_amdgcn_fmed3f(top, v, w));
+                    top = fmaxf(fmaxf(top, v), w);
+                }
+                const int i = (int)(__float_as_uint(top) & 15u);
+                run_own[j] = top > run_best[j] ? m0 + r0 + 8 * (i >> 2) + (i & 3) : run_own[j];
+                run_second[j] = fmaxf(fmaxf(run_second[j], next), fminf(run_best[j], top));
+                run_best[j] = fmaxf(run_best[j], top);
             }
         }
-        __syncthreads();  // the next chunk rewrites the directions
     }
-    // cell sums: owner -> fixed-point sum in the direction's table
+    const bool sure = screen && !__syncthreads_or(zero);
 #pragma unroll
-    for (int j = 0; j < kQSlots; ++j) {
-        const int p = j * 64 + lane;
-        if (p < np) {
-            const int al = small_div(p, inv_nf);
-            unsigned short *keys = hkey[al];
-            const unsigned short key = (unsigned short)own[j];
-            int h = own[j] & (kCellHash - 1);
-            while (true) {
-                const unsigned short old = atomicCAS(&keys[h], kNoOwner, key);
-                if (old == kNoOwner || old == key) break;
-                h = (h + 1) & (kCellHash - 1);
-            }
-            atomicAdd(&hval[al][h], wq[p - al * NF]);
+    for (int j = 0; j < kBigPairs; ++j) {
+        const int p = 64 * (wave + 4 * j) + lane;
+        const bool certain = sure && run_best[j] - run_second[j] > kBigCertified;
+        if (p < np && certain) owner[p] = (unsigned short)run_own[j];
+        const bool wait = p < np && !certain;
+        const unsigned long long open = __ballot(wait);
+        if (open) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&queued, __popcll(open));
+            at = __shfl(at, 0);
+            if (wait) queue[at + __popcll(open & ((1ull << lane) - 1ull))] = (unsigned short)p;
         }
     }
     __syncthreads();
+    // the queued columns: 256 / parts at a time, the out-edges m = part (mod parts) in a lane, with
+    // the FP64 sequence; ties go to the lowest index
+    const int nq = queued;
+    int parts = 1;
+    while (parts < 64 && 2 * parts * nq <= 256) parts *= 2;
+    double *ex = reinterpret_cast<double *>(pool), *ey = ex + kScanEdges, *ez = ey + kScanEdges;
+    for (int c0 = 0; c0 < nq; c0 += 256 / parts) {
+        const int c = c0 + tid / parts, part = tid & (parts - 1);
+        const int p = queue[min(c, nq - 1)], al = small_div(p, inv_nf), i = p - al * NF;
+        double q0, q1, q2;
+        rotate_point(Rg + 9 * al, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
+        double best = -__builtin_inf();
+        int own = 0;
+        for (int m0 = 0; m0 < d; m0 += kScanEdges) {
+            const int nm = min(kScanEdges, d - m0);
+            if (tid < nm) edge_dir(m0 + tid, ex[tid], ey[tid], ez[tid]);
+            __syncthreads();
+            if (c < nq) {
+#pragma unroll 4
+                for (int k = part; k < nm; k += parts) {
+                    const double v = fma(q2, ez[k], fma(q1, ey[k], q0 * ex[k]));
+                    own = v > best ? m0 + k : own;
+                    best = fmax(best, v);
+                }
+            }
+            __syncthreads();  // the next edges overwrite these
+        }
+        for (int s = 1; s < parts; s <<= 1) {
+            const double v = __shfl_xor(best, s);
+            const int o = __shfl_xor(own, s);
+            own = v > best || (v == best && o < own) ? o : own;
+            best = fmax(best, v);
+        }
+        if (c < nq && part == 0) owner[p] = (unsigned short)own;
+    }
+    __syncthreads();
+    // a wavefront per direction, kBinRows rows at a time: the weights summed by owner, then the
+    // column filled with the value of an empty cell and the owners' rows written over it (at most
+    // N_fib of the hundreds of rows; a read of every row's sum took a seventh of the kernel).  A
+    // surface node has one direction, and its columns differ by T only: the wavefronts share them.
     const Real rl = rho ? rho[l] : (Real)0;
     const Real tsun = Tsun ? Tsun[l] : (Real)0;
     BlkT *blk = val + nodeoff[l];  // column-major: element (row n, column m) at m d + n
-    for (int al = 0; al < ng; ++al) {
+    unsigned long long *bins = reinterpret_cast<unsigned long long *>(pool) + kBinRows * wave;
+    for (int al = surf ? 0 : wave; al < ng; al += 4) {
         const int a = a0 + al;
-        for (int m = lane; m < d; m += 64) {
-            const int h = cell_find(hkey[al], m);
-            const double Q = h < 0 ? 0.0 : (double)(long long)hval[al][h] * kUnfix;
-            const long long b = off + m;
-            if (surf) {
-                for (int c = 0; c < d; ++c) {
-                    if (kWriteQ) blk[(long long)c * d + m] = (BlkT)Q;
-                    else blk[(long long)c * d + m] = (BlkT)(T[off + c] * rl * (Real)Q);
+        for (int r0 = 0; r0 < d; r0 += kBinRows) {
+            const int nr = min(kBinRows, d - r0);
+            unsigned row[2];  // the owners of this lane's points, from r0
+            double Q[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int i = lane + 64 * h;
+                row[h] = i < NF ? (unsigned)(owner[al * NF + i] - r0) : ~0u;
+                if (row[h] < (unsigned)nr) bins[row[h]] = 0ull;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (row[h] < (unsigned)nr) atomicAdd(&bins[row[h]], wq[lane + 64 * h]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int h = 0; h < 2; ++h) Q[h] = row[h] < (unsigned)nr ? (double)(long long)bins[row[h]] * kUnfix : 0.0;
+            // rows r0.. of a column: value(Q) for every cell
+            auto put = [&](auto *dst, auto value) {
+                const auto empty = value(0.0);
+                for (int r = lane; r < nr; r += 64) dst[r0 + r] = empty;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    if (row[h] < (unsigned)nr) dst[r0 + row[h]] = value(Q[h]);
+            };
+            auto put_column = [&](int c) {
+                if (kWriteQ) put(blk + (long long)c * d, [](double q) { return (BlkT)q; });
+                else {
+                    const Real f = T[off + c] * rl;
+                    put(blk + (long long)c * d, [f](double q) { return (BlkT)(f * (Real)q); });
                 }
-                if (!kWriteQ) S[b] = rl * mu0 * tsun * (Real)Q;
-                qsun[b] = (float)Q;
+            };
+            if (surf) {
+                for (int c = wave; c < d; c += 4) put_column(c);
             } else if (a < d) {
-                if (kWriteQ) blk[(long long)a * d + m] = (BlkT)Q;
-                else blk[(long long)a * d + m] = (BlkT)(T[off + a] * rl * (Real)Q);
-            } else {
-                if (!kWriteQ) S[b] = tsun * rl * (Real)Q;
-                qsun[b] = (float)Q;
+                put_column(a);
+            }
+            if ((surf && wave == 0) || a == d) {
+                const Real f = surf ? rl * mu0 * tsun : tsun * rl;
+                if (!kWriteQ) put(S + off, [f](double q) { return f * (Real)q; });
+                put(qsun + off, [](double q) { return (float)q; });
             }
         }
     }
 }
-
 
 // The paper's discretisation of Sigma (Sec. 3), for scenes that ask for it: per
 // incoming direction, every out-edge direction colours its closest lattice point and
@@ -886,6 +1047,19 @@ __global__ __launch_bounds__(64) void k_qcolour(
         }
         __syncthreads();
     }
+}
+
+// Cell sums by owner: a direction's lattice points have at most N_fib distinct owners among the d
+// out-edges, so they go to a 256-slot open-addressing table in LDS (exact integer atomics), and a
+// column is written by looking every row up (absent: 0).
+constexpr int kCellHash = 256;  // above the most owners a direction can have (N_fib <= 128)
+
+constexpr unsigned short kNoOwner = 0xffff;  // owners are below 4096
+
+__device__ __forceinline__ int cell_find(const unsigned short *keys, int m) {
+    int h = m & (kCellHash - 1);
+    while (keys[h] != m && keys[h] != kNoOwner) h = (h + 1) & (kCellHash - 1);
+    return keys[h] == m ? h : -1;
 }
 
 // The colouring for nodes of degree above 64: one 64-lane workgroup per (node, incoming
@@ -1135,9 +1309,8 @@ __global__ __launch_bounds__(64) void k_qcolour_big(
 
 }  // namespace
 
-// directions per group: as many as fill the lanes' pair slots
-int qbuild_group(int NF) { return std::max(1, std::min(kQMaxGroup, kQSlots * 64 / NF)); }
-int qbuild_group_big(int NF) { return std::min(qbuild_group(NF), kBigGroup); }
+// directions per workgroup of k_qbuild_big: as many as fill its columns
+int qbuild_group_big(int NF) { return std::min(kBigCols / NF, kBigGroup); }
 
 template <class Real>
 void launch_qbuild(Scene &s, hipStream_t st, int write_q) {
@@ -1178,19 +1351,19 @@ void launch_qbuild(Scene &s, hipStream_t st, int write_q) {
     }
     if (s.n_big) {  // nodes of degree above 64
         if (write_q)
-            hipLaunchKernelGGL((k_qbuild_big<Real, float, true>), dim3(s.n_bigdir), dim3(64), 0, st, s.n_big, s.big,
+            hipLaunchKernelGGL((k_qbuild_big<Real, float, true>), dim3(s.n_bigdir), dim3(256), 0, st, s.n_big, s.big,
                                s.bigdir, s.n_vol, s.adj_ptr, s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s),
                                s.sun_in[0], s.sun_in[1], s.sun_in[2], (Real)s.mu0, (const Real *)nullptr,
                                (const Real *)nullptr, (const Real *)nullptr, s.nodeoff, s.q, (Real *)nullptr, s.qsun,
                                qbuild_group_big(s.n_fib), s.periodic, (long long)s.nx * kFx,
-                               (long long)s.ny * kFx);
+                               (long long)s.ny * kFx, s.qscreen);
         else
-            hipLaunchKernelGGL((k_qbuild_big<Real, Real, false>), dim3(s.n_bigdir), dim3(64), 0, st, s.n_big, s.big,
+            hipLaunchKernelGGL((k_qbuild_big<Real, Real, false>), dim3(s.n_bigdir), dim3(256), 0, st, s.n_big, s.big,
                                s.bigdir, s.n_vol, s.adj_ptr, s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s),
                                s.sun_in[0], s.sun_in[1], s.sun_in[2], (Real)s.mu0, (const Real *)s.T,
                                (const Real *)s.rho, (const Real *)s.Tsun, s.nodeoff, (Real *)s.val, (Real *)s.S, s.qsun,
                                qbuild_group_big(s.n_fib), s.periodic, (long long)s.nx * kFx,
-                               (long long)s.ny * kFx);
+                               (long long)s.ny * kFx, s.qscreen);
     }
     if (write_q) {
         hipLaunchKernelGGL((k_qbuild<Real, float, true>), dim3(s.N), dim3(64), qshm, st, s.N, s.n_vol, s.adj_ptr,

@@ -76,7 +76,7 @@ def test_weights_of_a_direction_sum_to_one(ctx):
     assert np.abs(total[sc.degrees() > 0] - 1.0).max() < 1e-6
 
 
-@pytest.mark.parametrize("most", [8, 64])
+@pytest.mark.parametrize("most", [8, 64, 300])
 def test_zero_length_out_edges(ctx, most):
     """Coupled general nodes at one place: their direction is no number, and the FP64 sequence
     alone decides every cell of such a node."""
@@ -100,3 +100,46 @@ def test_zero_length_out_edges(ctx, most):
             got.append((g.export_csr()[2], g.export_vector("source"), g.export_vector("qsun")))
         for x, y in zip(*got):
             assert np.array_equal(x, y, equal_nan=True)
+
+
+def dense_scene(hubs, n_fib, centred):
+    """Nodes of the given degrees, above 64 and round the multiples of the row tiles (32), the
+    wavefronts' sums (512), the FP64 scans (256) and the resident out-edges (1024); the last hub is
+    a surface node."""
+    rng = np.random.default_rng(n_fib)
+    sc = scenes.make_random_small(6, nx=20, ny=18, nz=12, two_phase=True, kscale=0.3, surface=True)
+    if centred:
+        sc = sc.with_(vol_pos_fx=scenes.jittered_positions(rng, 20, 18, 12, jitter=0.0))
+    nvol = sc.n_vol
+    at = list(range(len(hubs) - 1)) + [nvol]
+    a, b = [], []
+    for h, d in zip(at, hubs):
+        a += [h] * d
+        b += list(rng.choice(np.arange(len(hubs), nvol), d, replace=False))
+    ap, ai = scenes.adjacency_from_pairs(sc.n_nodes, np.array(a), np.array(b))
+    assert [int(np.diff(ap)[h]) for h in at] == hubs
+    return sc.with_(adj_ptr=ap, adj_idx=ai, n_fib=n_fib)
+
+
+@pytest.mark.parametrize("hubs, n_fib, centred, against", [
+    ([65, 66, 95, 96, 97, 127, 128, 129, 255, 256, 257, 70], 100, False, "oracle"),
+    ([65, 511, 512, 513, 300], 100, True, "oracle"),
+    ([64, 65, 1023, 1024, 1025, 900], 31, False, "oracle"),
+    ([1056, 1055, 100], 128, True, "oracle"),
+    ([300, 77, 65], 2, False, "oracle"),
+    ([2049, 4096, 4095, 3000], 64, False, "scan"),
+])
+def test_cells_of_dense_nodes(ctx, hubs, n_fib, centred, against):
+    from paper_2503_16037_amd import sgrt
+    sc = dense_scene(hubs, n_fib, centred)
+    say("dense nodes", hubs, n_fib, "lattice points")
+    with sgrt.Scene(ctx, sc) as g:
+        got = []
+        for screen in (True, False):
+            g.solve(precision="fp64", screen=screen, scatter_order=1)
+            got.append((g.export_csr()[2], g.export_vector("source"), g.export_vector("qsun")))
+        for x, y in zip(*got):
+            assert np.array_equal(x, y)
+    if against == "oracle":
+        ora = oracle.run(sc, scatter_order=1)
+        assert np.abs(got[0][0] - ora["val"]).max() <= 1e-12 * np.abs(ora["val"]).max()
