@@ -61,17 +61,16 @@ __global__ __launch_bounds__(256) void k_bfirst(int N, int nl, const long long *
     const long long off = adj_ptr[l];
     const int d = (int)(adj_ptr[l + 1] - off);
     const float rl = brho[(long long)l * nl + lam], sl = bsrc[(long long)l * nl + lam];
-    double sum = 0.0, mrel = 0.0;
+    RowMeasures measures;
     for (int n = 0; n < d; ++n) {
         const long long bi = (off + n) * nl + lam;
         const float src = rhs ? rhs[bi] : rl * sl * qsun[off + n];
         const float yv = src + rl * 0.0f;
         x[bi] = yv;
         const double du = fabs((double)yv);
-        sum += du;
-        mrel = fmax(mrel, keep_nan(du / (du + kRelFloor)));
+        measures.add(du, du + kRelFloor);
     }
-    meas[(long long)l * nl + lam] = make_float2((float)sum, (float)mrel);
+    meas[(long long)l * nl + lam] = measures.value();
 }
 
 // One wavelength of a batched scene in FP64, for its GMRES fallback: one wavefront per node,

@@ -15,7 +15,9 @@ namespace {
 // as broadcasts (measured: reading the columns through scalar loads instead exposes
 // their latency, 1.4x slower at 64 wavelengths); the in-edge list and optical depths
 // are loaded once, coalesced, and broadcast with readlane; eight input gathers are in
-// flight at a time; the node's rows are accumulated in registers, the row count
+// flight at a time (the FP64 residual, at four wavefronts per SIMD, asks for the next eight before it uses
+// these: 2.69 -> 2.04 ms at 96x96x32, 64 wavelengths; the FP32 sweep at seven loses 5 % with the
+// registers this takes); the node's rows are accumulated in registers, the row count
 // rounded up to a multiple of 8 (DB) so the column reads are unguarded (the LDS slice
 // is padded past the block by 64 floats).
 // kResidual: FP64 residual r = S - x + K x of an FP64 iterate instead of a sweep.
@@ -25,6 +27,37 @@ namespace {
 __device__ __forceinline__ float edge_T(float ts, float ta, float s) {
     return __builtin_amdgcn_exp2f(-(ts + s * ta) * 1.4426950408889634f);
 }
+
+// acc + q x.  In FP64 the FP32 entry q >= 0 is taken as the double of the same bits, moved to the
+// double's places (two 32-bit shifts, its value 2^-896 q) and x carries 2^896: the product is
+// exact either way.  (Cloud 71x53x29, 12 wavelengths: the residual 400 -> 248 us with this, three
+// wavefronts per SIMD instead of spilled sums, and one division per node.)
+constexpr double kResidualScale = 0x1p896;
+__device__ __forceinline__ float add_q(float acc, float q, float x) { return acc + q * x; }
+__device__ __forceinline__ double add_q(double acc, float q, double x) {
+    const unsigned b = __float_as_uint(q);
+    return fma(__hiloint2double((int)(b >> 3), (int)(b << 29)), x, acc);
+}
+__device__ __forceinline__ float column_input(float T, float x) { return T * x; }
+__device__ __forceinline__ double column_input(double T, double x) { return T * x * kResidualScale; }
+
+// The sum and the largest quotient num / den of a node's rows (num >= 0, den > 0): the
+// quotients are compared across, so there is one division per node (one per row took 80 of
+// the 240 us of a sweep of cloud 71x53x29, 12 wavelengths).  A num that is not finite
+// makes the sum so, and the quotient infinite.
+struct RowMeasures {
+    double sum = 0.0, num = 0.0, den = 1.0;
+    __device__ __forceinline__ void add(double n, double d) {
+        sum += n;
+        const bool more = n * den > num * d;
+        num = more ? n : num;
+        den = more ? d : den;
+    }
+    __device__ __forceinline__ float2 value() const {
+        const double worst = sum < __builtin_huge_val() ? num / den : __builtin_huge_val();
+        return make_float2((float)sum, (float)worst);
+    }
+};
 
 // n passes of 64 consecutive block elements from t0 into the wavefront's LDS slice
 template <int n>
@@ -61,6 +94,17 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
     const long long em = off + min(lane, d - 1);
     const int rv = rev[em];
     const float ts = tau_s[em], ta = tau_a[em];
+    constexpr bool kAhead = sizeof(AccT) == 8;  // the next eight gathers before these are used
+    auto inputs = [&](int m0, XT(&xv)[kU]) {
+#pragma unroll
+        for (int j = 0; j < kU; ++j) {
+            const int m = min(m0 + j, 63);
+            const int r = __builtin_amdgcn_readlane(rv, m);
+            xv[j] = (m0 + j < d && lv) ? x[(long long)r * nl + lam] : (XT)0;
+        }
+    };
+    XT xv[kU];
+    if (kAhead) inputs(0, xv);
     {
         const int nq = d * d;
         for (int t0 = 0; t0 < nq; t0 += 64 * 16) {
@@ -80,27 +124,26 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
 #pragma unroll
     for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
     for (int m0 = 0; m0 < d; m0 += kU) {
-        XT xv[kU];
-#pragma unroll
-        for (int j = 0; j < kU; ++j) {
-            const int m = min(m0 + j, 63);
-            const int r = __builtin_amdgcn_readlane(rv, m);
-            xv[j] = (m0 + j < d && lv) ? x[(long long)r * nl + lam] : (XT)0;
-        }
+        XT next[kU];
+        if (!kAhead) inputs(m0, xv);
+        else if (m0 + kU < d) inputs(m0 + kU, next);
 #pragma unroll
         for (int j = 0; j < kU; ++j) {
             const int m = m0 + j;
             if (m < d) {
                 const float tsm = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ts), m));
                 const float tam = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(ta), m));
-                const AccT xm = (AccT)edge_T(tsm, tam, s) * (AccT)xv[j];
+                const AccT xm = column_input((AccT)edge_T(tsm, tam, s), (AccT)xv[j]);
                 const float *qm = qs + m * d;  // column m: Q[n][m], n contiguous (LDS, uniform address)
 #pragma unroll
-                for (int n = 0; n < DB; ++n) acc[n] += (AccT)qm[n] * xm;
+                for (int n = 0; n < DB; ++n) acc[n] = add_q(acc[n], qm[n], xm);
             }
         }
+        if (kAhead)
+#pragma unroll
+            for (int j = 0; j < kU; ++j) xv[j] = next[j];
     }
-    double sum = 0.0, mrel = 0.0;  // convergence measures of this node's rows
+    RowMeasures measures;
     unsigned long long rows = 0ull;  // the rows that moved for any wavelength
     if (lv) {
         const float rl = brho[(long long)l * nl + lam];
@@ -114,18 +157,13 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
                     const double Sb = (double)(rl * sl * qsun[b]);
                     const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
                     y[bi] = (YT)rb;
-                    sum += fabs(rb);
-                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
+                    measures.add(fabs(rb), fabs((double)x[bi]) + kRelFloor);
                 } else {
                     const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
                     const float yv = src + rl * (float)acc[n];
                     y[bi] = (YT)yv;
                     if (kMark && __ballot(moved(yv, (float)x[bi]))) rows |= 1ull << n;
-                    if (monitor) {
-                        const double du = fabs((double)yv - (double)x[bi]);
-                        sum += du;
-                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
-                    }
+                    if (monitor) measures.add(fabs((double)yv - (double)x[bi]), fabs((double)yv) + kRelFloor);
                 }
             }
         }
@@ -137,7 +175,7 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
         if (lane < d && (m >> lane & 1ull)) mark[adj_idx[em]] = 1;
         if (m && lane == 0) mark[l] = 1;
     }
-    return make_float2((float)sum, (float)mrel);
+    return measures.value();
 }
 
 // Occupancy hints: at the requested waves per SIMD the compiler fits each instantiation
@@ -224,42 +262,85 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wide_waves_
 // ---- wavelength tiles narrower than a wavefront -------------------------------------
 // For n_lambda <= 32 a wavefront holds 64 / W node slots of W wavelength lanes each, so
 // a small wavelength count does not leave lanes idle.  Each slot's in-edge data (rev,
-// tau_s, tau_a) goes to a small LDS slice; the phase-cell columns are read straight
-// from memory with 16-byte loads (the lanes of a slot share the addresses, so each
-// load costs one request per slot).  Per lane the arithmetic is exactly that of the
-// full-wavefront kernel (same expressions, columns in the same order), so the two give
-// the same bits.
-typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+// tau_s, tau_a) goes to a small LDS slice.  The phase-cell columns pass through LDS a few
+// at a time: a slot's lanes load them side by side, the next ones while these are used, and
+// read them as 16-byte broadcasts (the slots' slices four words apart, so that their
+// reads fall on different banks).  Read straight from memory with 16-byte loads, each lane of a
+// slot took the same sixteen bytes through the vector memory path, and that path bound the
+// sweep: cloud 71x53x29, 12 wavelengths, a whole sweep 331 -> 162 us, over the front 296 falling
+// to 82 -> 166 falling to 34 us, the FP64 residual 427 -> 248 us.
+// Per lane the arithmetic is exactly that of the full-wavefront kernel (same expressions,
+// columns in the same order), so the two give the same bits.
+typedef float f4u __attribute__((ext_vector_type(4)));
 
-template <int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
+template <int W, int DB>
+struct PackTile {
+    static constexpr int kLoads = (DB + W - 1) / W;              // per lane and column
+    static constexpr int kStride = kLoads * W;                   // rows of a staged column
+    static constexpr int kCols = 4;                               // columns staged at a time
+    static constexpr int kSlice = kCols * kStride + 4;           // words of a slot
+};
+template <int W, int D>
+constexpr int pack_slice() {  // the largest slice of the degree buckets up to D
+    if constexpr (D <= 8) return PackTile<W, 8>::kSlice;
+    else return PackTile<W, D>::kSlice > pack_slice<W, D - 8>() ? PackTile<W, D>::kSlice : pack_slice<W, D - 8>();
+}
+
+template <int W, int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
 __device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, int nl, int monitor, long long off,
                                             int d, long long base, int dw, const int *__restrict__ srv,
                                             const float *__restrict__ sts, const float *__restrict__ sta,
-                                            const float *__restrict__ q, const float *__restrict__ qsun,
-                                            const float *__restrict__ brho, const float *__restrict__ bsrc,
-                                            const float *__restrict__ rhs, const XT *__restrict__ x,
-                                            YT *__restrict__ y, unsigned long long &rows) {
+                                            float *__restrict__ qs, const float *__restrict__ q,
+                                            const float *__restrict__ qsun, const float *__restrict__ brho,
+                                            const float *__restrict__ bsrc, const float *__restrict__ rhs,
+                                            const XT *__restrict__ x, YT *__restrict__ y, unsigned long long &rows) {
+    using P = PackTile<W, DB>;
     AccT acc[DB];
 #pragma unroll
     for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
-    for (int m = 0; m < dw; ++m) {
-        // slots with fewer in-edges repeat their last column with a zero input: adding
-        // Q * 0 leaves every valid row's sum unchanged
-        const bool mv = m < d;
-        const int mc = min(m, d - 1);
-        const XT xin = (mv && lv) ? x[(long long)srv[mc] * nl + lam] : (XT)0;
-        const AccT xm = (AccT)edge_T(sts[mc], sta[mc], s) * (AccT)xin;
-        const f4u *qm = reinterpret_cast<const f4u *>(q + base + (long long)mc * d);
+    // columns m0.. of the block, rows lam, lam + W, .. in this lane, and their inputs.  Slots with
+    // fewer in-edges repeat their last column with a zero input: adding Q * 0 leaves every
+    // valid row's sum unchanged
+    float qv[P::kCols * P::kLoads];
+    XT xv[P::kCols];
+    auto load = [&](int m0) {
 #pragma unroll
-        for (int c = 0; c < DB / 4; ++c) {
-            const f4u v = qm[c];
-            acc[4 * c] += (AccT)v.x * xm;
-            acc[4 * c + 1] += (AccT)v.y * xm;
-            acc[4 * c + 2] += (AccT)v.z * xm;
-            acc[4 * c + 3] += (AccT)v.w * xm;
+        for (int j = 0; j < P::kCols; ++j) {
+            const int mc = min(m0 + j, d - 1);
+            const float *qm = q + base + mc * d;
+#pragma unroll
+            for (int k = 0; k < P::kLoads; ++k) qv[j * P::kLoads + k] = qm[lam + W * k];
+            xv[j] = (m0 + j < d && lv) ? x[(long long)srv[mc] * nl + lam] : (XT)0;
         }
+    };
+    load(0);
+    for (int m0 = 0; m0 < dw; m0 += P::kCols) {
+        AccT xm[P::kCols];
+#pragma unroll
+        for (int j = 0; j < P::kCols; ++j) {
+            const int mc = min(m0 + j, d - 1);
+#pragma unroll
+            for (int k = 0; k < P::kLoads; ++k) qs[j * P::kStride + lam + W * k] = qv[j * P::kLoads + k];
+            xm[j] = column_input((AccT)edge_T(sts[mc], sta[mc], s), (AccT)xv[j]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (m0 + P::kCols < dw) load(m0 + P::kCols);
+#pragma unroll
+        for (int j = 0; j < P::kCols; ++j) {
+            if (m0 + j >= dw) break;
+            const f4u *qm = reinterpret_cast<const f4u *>(qs + j * P::kStride);
+#pragma unroll
+            for (int c = 0; c < DB / 4; ++c) {
+                const f4u v = qm[c];
+                acc[4 * c] = add_q(acc[4 * c], v.x, xm[j]);
+                acc[4 * c + 1] = add_q(acc[4 * c + 1], v.y, xm[j]);
+                acc[4 * c + 2] = add_q(acc[4 * c + 2], v.z, xm[j]);
+                acc[4 * c + 3] = add_q(acc[4 * c + 3], v.w, xm[j]);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
-    double sum = 0.0, mrel = 0.0;
+    RowMeasures measures;
     if (lv) {
         const float rl = brho[(long long)l * nl + lam];
         const float sl = bsrc[(long long)l * nl + lam];
@@ -272,30 +353,32 @@ __device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, in
                     const double Sb = (double)(rl * sl * qsun[b]);
                     const double rb = (Sb - (double)x[bi]) + (double)rl * (double)acc[n];
                     y[bi] = (YT)rb;
-                    sum += fabs(rb);
-                    mrel = fmax(mrel, keep_nan(fabs(rb) / (fabs((double)x[bi]) + kRelFloor)));
+                    measures.add(fabs(rb), fabs((double)x[bi]) + kRelFloor);
                 } else {
                     const float src = rhs ? rhs[bi] : rl * sl * qsun[b];
                     const float yv = src + rl * (float)acc[n];
                     y[bi] = (YT)yv;
                     if (kMark && moved(yv, (float)x[bi])) rows |= 1ull << n;
-                    if (monitor) {
-                        const double du = fabs((double)yv - (double)x[bi]);
-                        sum += du;
-                        mrel = fmax(mrel, keep_nan(du / (fabs((double)yv) + kRelFloor)));
-                    }
+                    if (monitor) measures.add(fabs((double)yv - (double)x[bi]), fabs((double)yv) + kRelFloor);
                 }
             }
         }
     }
-    return make_float2((float)sum, (float)mrel);
+    return measures.value();
+}
+
+// Four waves per SIMD (the compiler would hoist the previous values of all rows and leave three);
+// the FP64 residual's accumulators fit three up to D = 40.  The rows beyond that keep the natural
+// allocation.
+template <int D, bool kResidual>
+constexpr int pack_waves_per_eu() {
+    return D > 40 ? 1 : kResidual && D > 24 ? 3 : 4;
 }
 
 // kMode: as k_spmm_wide.  Over the front, each slot of the wavefront takes the next of its
-// marked nodes.  The marking sweeps are held to the whole ones' five waves per SIMD (the
-// compiler would hoist the previous values of all rows and leave four).
+// marked nodes.
 template <int W, int D, class XT, class YT, class AccT, bool kResidual, int kMode>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMode ? 5 : 1))) void k_spmm_pack(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_per_eu<D, kResidual>()))) void k_spmm_pack(
     int N, int nl, int groups, const long long *__restrict__ adj_ptr, const long long *__restrict__ nodeoff,
     const int *__restrict__ rev, const float *__restrict__ q, const float *__restrict__ qsun,
     const float *__restrict__ tau_s, const float *__restrict__ tau_a, const float *__restrict__ abs_scale,
@@ -304,14 +387,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMode ? 5 :
     const int *__restrict__ adj_idx, const unsigned char *__restrict__ now, unsigned char *__restrict__ next,
     unsigned long long *__restrict__ spent, int skew) {
     constexpr int P = 64 / W;  // node slots per wavefront
-    __shared__ int srv_all[4][P][64];
-    __shared__ float sts_all[4][P][64], sta_all[4][P][64];
+    __shared__ int srv_all[4][P][D];
+    __shared__ float sts_all[4][P][D], sta_all[4][P][D];
+    __shared__ __align__(16) float qs_all[4][P][pack_slice<W, D>()];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int k = lane / W, lam = lane - k * W;
     const bool lam_ok = lam < nl;
     const float s = lam_ok ? abs_scale[lam] : 0.f;
     int *srv = srv_all[w][k];
-    float *sts = sts_all[w][k], *sta = sta_all[w][k];
+    float *sts = sts_all[w][k], *sta = sta_all[w][k], *qs = qs_all[w][k];
     auto slot_nodes = [&](int l) {  // node l per slot (l >= N: none)
         const bool node_ok = l < N;
         long long off = 0, base = 0;
@@ -338,8 +422,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMode ? 5 :
         if (dw > 0) {
             const int bucket = (dw + 7) >> 3;
 #define SG_PACK(DB)                                                                                            \
-    part = pack_node<DB, XT, YT, AccT, kResidual, kMode != 0>(l, lam, lv, s, nl, monitor, off, max(d, 1), base, dw, \
-                                                              srv, sts, sta, q, qsun, brho, bsrc, rhs, x, y, rows)
+    part = pack_node<W, DB, XT, YT, AccT, kResidual, kMode != 0>(l, lam, lv, s, nl, monitor, off, max(d, 1), base, \
+                                                                 dw, srv, sts, sta, qs, q, qsun, brho, bsrc, rhs, x, \
+                                                                 y, rows)
             if (bucket <= 1) { SG_PACK(8); }
             else if (bucket == 2) { if constexpr (D >= 16) SG_PACK(16); }
             else if (bucket == 3) { if constexpr (D >= 24) SG_PACK(24); }
@@ -415,9 +500,9 @@ template <class XT, class YT, class AccT, bool kRes, int kMode>
 static void launch_wide(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor, int front) {
     const int W = batched_tile(s);
     const int waves = wide_waves(s);
-    // over the front, the wavefronts that are resident (six per SIMD, five of the narrow tiles):
+    // over the front, the wavefronts that are resident (six per SIMD, four of the narrow tiles):
     // each takes its share of the marks, and a second round of them would start when the first ends
-    if (kMode == kFrontOn) grid = W < 64 ? 256 * 5 : 256 * 6 * 4 / waves;
+    if (kMode == kFrontOn) grid = W < 64 ? 256 * 4 : 256 * 6 * 4 / waves;
     grid = std::max(1, std::min(grid, batched_groups(s)));
     if (W == 8) return launch_pack<8, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
     if (W == 16) return launch_pack<16, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);

@@ -143,3 +143,23 @@ def test_cells_of_dense_nodes(ctx, hubs, n_fib, centred, against):
     if against == "oracle":
         ora = oracle.run(sc, scatter_order=1)
         assert np.abs(got[0][0] - ora["val"]).max() <= 1e-12 * np.abs(ora["val"]).max()
+
+
+@pytest.mark.parametrize("most", [5, 24, 40, 64])
+def test_wavelength_tiles_at_every_degree(ctx, most):
+    """The narrow wavelength tiles stage the cells' columns, the wide one whole blocks: nodes of
+    every degree give the same bits in all of them, and the oracle's radiances."""
+    from paper_2503_16037_amd import sgrt
+    sc = hub_scene(33, most)
+    sc = sc.with_(abs_scale=np.linspace(0.2, 3.0, 5).astype(np.float32))
+    say("wavelength tiles, degrees up to", int(sc.degrees().max()))
+    with sgrt.Scene(ctx, sc) as g:
+        ref, info = g.solve(lambda_tile=64)
+        phi = g.export_vector("phi")
+        for tile in (8, 16, 32):
+            rad, again = g.solve(lambda_tile=tile)
+            assert np.array_equal(rad, ref) and np.array_equal(g.export_vector("phi"), phi)
+            assert again["sweeps"] == info["sweeps"]
+    for k in (0, 4):
+        ora = oracle.run(sc, abs_scale=float(sc.abs_scale[k]))["radiance"]
+        assert np.abs(ref[k] - ora).max() <= 1e-4 * np.abs(ora).max()
