@@ -121,7 +121,8 @@ void host_lattice(int N, std::vector<double> &p) {
 // The lattice as the column operands of the phase cells' matrix products (qbuild.hip), four
 // tiles of 32 points: each component times 2^10 in two FP16 halves, as pairs of halves
 // (hx, hy) (hz, hx) (hy, hz) (lx, ly) for lanes 0..31 and (lz, lx) (ly, lz) (2^10, 0) (0, 0) for
-// lanes 32..63; zero past the last point.
+// lanes 32..63.  Points past the last are zero but for k = 13, -2^11, which the colouring's screen
+// multiplies by 2^10 (as rows they lose to every point) and the Voronoi cells' by zero.
 void host_lattice_halves(int N, const std::vector<double> &p, std::vector<unsigned> &out) {
     out.assign(4 * 64 * 4, 0u);
     auto pair = [](_Float16 a, _Float16 b) {
@@ -146,6 +147,7 @@ void host_lattice_halves(int N, const std::vector<double> &p, std::vector<unsign
         b[1] = pair(l[1], l[2]);
         b[2] = pair((_Float16)1024.0f, (_Float16)0.0f);
     }
+    for (int i = N; i < 128; ++i) out[((i >> 5) * 64 + 32 + (i & 31)) * 4 + 2] = pair((_Float16)0.0f, (_Float16)-2048.0f);
 }
 
 // Per-component Henyey-Greenstein table normalised over the lattice, then the

@@ -828,7 +828,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // The paper's discretisation of Sigma (Sec. 3), for scenes that ask for it: per
 // incoming direction, every out-edge direction colours its closest lattice point and
 // the colours spread over the lattice by flood fill along the edges of its convex
-// hull.  One 64-lane wavefront per node, lattice points i and i + 64 in lane i.
+// hull.  One 64-lane wavefront per node; two incoming directions at a time up to degree 32 (lane
+// 32 dl + m: direction dl's out-edge m), one above (lane m).
 //   seeds: for m = 0, 1, ...: the lattice point of largest v_im (the Voronoi
 //   ownership's dot products, same operation sequence; ties to the lowest i) takes
 //   colour m unless it was claimed with a value >= v_im by an earlier direction;
@@ -836,6 +837,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 //   coloured neighbour had at the start of the round, until all are coloured (the
 //   hull graph is connected and there is at least one seed).
 // Q(u -> m) is the fixed-point sum of the phase weights of colour m, as in k_qbuild.
+// The largest v_im comes from k_qbuild's screen with the operands changed over (lattice points
+// are the rows, out-edges the columns, 2^-15 certifies as there), its FP64 value from the FP64
+// sequence at that point; a lane without a certificate scans all points in FP64.  In the fill
+// the coloured points are two 64-bit masks and so are a point's neighbours (points lane and lane +
+// 64): the lowest coloured neighbour is the first bit of their intersection, and one read gives
+// its colour.
+// Bound: vector issue.  FP64 dot products over all points and a fill that read up to 16
+// neighbours' colours a round, the form before: plume 48x48x24 2.30 ms, now 1.04 ms.
 // order-preserving 64-bit keys of doubles (for integer atomic max in LDS)
 __device__ __forceinline__ unsigned long long order_key(double v) {
     const unsigned long long b = (unsigned long long)__double_as_longlong(v);
@@ -847,17 +856,18 @@ __device__ __forceinline__ double order_value(unsigned long long k) {
 }
 
 template <class Real, class BlkT, bool kWriteQ>
-__global__ __launch_bounds__(64) void k_qcolour(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_qcolour(
     int N, int nvol, const long long *__restrict__ adj_ptr, const int *__restrict__ adj_idx,
-    const int *__restrict__ pos, const double *__restrict__ lat, const double *__restrict__ tab, int NF, int n_phase,
-    const float *__restrict__ frac, double sun_x, double sun_y, double sun_z, Real mu0, const Real *__restrict__ T,
-    const Real *__restrict__ rho, const Real *__restrict__ Tsun, const long long *__restrict__ nodeoff,
-    BlkT *__restrict__ val, Real *__restrict__ S, float *__restrict__ qsun, const int *__restrict__ hull, int per,
-    long long wx, long long wy) {
+    const int *__restrict__ pos, const double *__restrict__ lat, const uint4 *__restrict__ lat_halves,
+    const double *__restrict__ tab, int NF, int n_phase, const float *__restrict__ frac, double sun_x, double sun_y,
+    double sun_z, Real mu0, const Real *__restrict__ T, const Real *__restrict__ rho, const Real *__restrict__ Tsun,
+    const long long *__restrict__ nodeoff, BlkT *__restrict__ val, Real *__restrict__ S, float *__restrict__ qsun,
+    const int *__restrict__ hull, int per, long long wx, long long wy, int screen) {
 #pragma clang fp contract(off)
-    __shared__ double sx[64], sy[64], sz[64], lq[3][128];  // sites; this direction's rotated lattice
-    __shared__ unsigned long long wq[128], bins[64], bkey[128], mkey[64];
-    __shared__ int col[128], snap[128], mi[64];
+    __shared__ double sx[64], sy[64], sz[64];
+    __shared__ unsigned long long wq[128], bins[2][64], bkey[2][128];
+    __shared__ int col[2][128];
+    constexpr int kNone = 0x7fffffff;
 
     const int l = blockIdx.x;
     const int lane = threadIdx.x;
@@ -866,6 +876,7 @@ __global__ __launch_bounds__(64) void k_qcolour(
     if (d == 0 || d > kWave) return;  // higher degree: k_qcolour_big
     const bool surf = l >= nvol;
     if (!SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x204)) return;
+    bool zero = false;  // a zero-length out-edge: no direction
     if (lane < d) {
         const int j0 = adj_idx[off + lane];
         const int j = SG_IN(j0, N, 0x205) ? j0 : l;
@@ -873,10 +884,12 @@ __global__ __launch_bounds__(64) void k_qcolour(
         const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
         const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
         const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
+        zero = (Dx | Dy | Dz) == 0;
         sx[lane] = (double)Dx / nrm;
         sy[lane] = (double)Dy / nrm;
         sz[lane] = (double)Dz / nrm;
     }
+    const bool screened = screen != 0 && __ballot(zero) == 0;
     for (int i = lane; i < NF; i += 64) {
         double w;
         if (surf) {
@@ -896,144 +909,160 @@ __global__ __launch_bounds__(64) void k_qcolour(
     const Real tsun = Tsun ? Tsun[l] : (Real)0;
     BlkT *blk = val + nodeoff[l];  // column-major: element (row n, column m) at m d + n
     const int n_in = surf ? 1 : d + 1;
-    const int i0 = lane, i1 = lane + 64;
-    const bool ok0 = i0 < NF, ok1 = i1 < NF;
-    const int P = min(4, kWave / d);             // lanes per out-direction in the seed scan
-    const int blk_pts = (NF + P - 1) / P;        // lattice points per lane
-    double px[2], py[2], pz[2];  // this lane's lattice points i0, i1
-    int nn[2];                    // and their hull neighbours, four indices (< 128) a word
-    unsigned nbw[2][kHullNb / 4];
+    const int nd = d <= 32 ? 2 : 1;  // directions at a time
+    const int dl = nd == 2 ? lane >> 5 : 0, m = nd == 2 ? lane & 31 : lane;
+    const double tx = m < d ? sx[m] : 0.0, ty = m < d ? sy[m] : 0.0, tz = m < d ? sz[m] : 0.0;
+    const int nt = (NF + 31) >> 5, last = NF - 32 * (nt - 1);  // row tiles of lattice points
+    Operand pts[4];
 #pragma unroll
-    for (int h2 = 0; h2 < 2; ++h2) {
-        const int i = min(h2 ? i1 : i0, NF - 1);
-        px[h2] = lat[3 * i];
-        py[h2] = lat[3 * i + 1];
-        pz[h2] = lat[3 * i + 2];
-        nn[h2] = hull[NF * kHullNb + i];
+    for (int t = 0; t < 4; ++t) {
+        const uint4 v = lat_halves[64 * t + lane];
+        pts[t].w[0] = v.x;
+        pts[t].w[1] = v.y;
+        pts[t].w[2] = v.z;
+        pts[t].w[3] = v.w;
+    }
+    unsigned long long near[2][2];  // the hull neighbours of points lane and lane + 64, as masks
 #pragma unroll
-        for (int w = 0; w < kHullNb / 4; ++w) {
-            unsigned v = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) v |= ((unsigned)hull[i * kHullNb + 4 * w + b] & 0xffu) << (8 * b);
-            nbw[h2][w] = v;
+    for (int h = 0; h < 2; ++h) {
+        const int i = lane + 64 * h;
+        near[h][0] = near[h][1] = 0ull;
+        if (i < NF) {
+            const int nn = hull[NF * kHullNb + i];
+            for (int t = 0; t < nn; ++t) {
+                const int j = hull[i * kHullNb + t];
+                near[h][0] |= j < 64 ? 1ull << j : 0ull;
+                near[h][1] |= j < 64 ? 0ull : 1ull << (j & 63);
+            }
         }
     }
-    for (int a = 0; a < n_in; ++a) {
-        // rotation of this incoming direction (every lane, the same values)
-        double R[9];
-        if (surf) {
-            R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = 1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0; R[8] = 1.0;
-        } else {
-            double ux, uy, uz;
-            if (a < d) { ux = -sx[a]; uy = -sy[a]; uz = -sz[a]; }
-            else { ux = sun_x; uy = sun_y; uz = sun_z; }
-            if (1.0 + uz < 1e-12) {
-                R[0] = 1.0; R[1] = 0.0; R[2] = 0.0; R[3] = 0.0; R[4] = -1.0; R[5] = 0.0; R[6] = 0.0; R[7] = 0.0;
-                R[8] = -1.0;
-            } else {
-                const double h = 1.0 / (1.0 + uz);
-                const double xy = (ux * uy) * h;
-                R[0] = uz + (uy * uy) * h; R[1] = -xy; R[2] = -ux;
-                R[3] = -xy; R[4] = uz + (ux * ux) * h; R[5] = -uy;
-                R[6] = ux; R[7] = uy; R[8] = uz;
-            }
+    for (int a0 = 0; a0 < n_in; a0 += nd) {
+        // the rotation of this lane's direction
+        double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+        const int a = min(a0 + dl, n_in - 1);  // past the last direction: a repeat, not counted
+        if (!surf) {
+            if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
+            else pole_rotation(sun_x, sun_y, sun_z, R);
         }
-        // the rotated lattice (q_i = R^T p_i), and cleared claims
-        for (int h2 = 0; h2 < 2; ++h2) {
-            const int i = h2 ? i1 : i0;
-            if (i >= NF) continue;
-            const double x = px[h2], y = py[h2], z = pz[h2];
-            lq[0][i] = fma(R[6], z, fma(R[3], y, R[0] * x));
-            lq[1][i] = fma(R[7], z, fma(R[4], y, R[1] * x));
-            lq[2][i] = fma(R[8], z, fma(R[5], y, R[2] * x));
-            bkey[i] = 0ull;
-            col[i] = 0x7fffffff;
-        }
-        if (lane < d) {
-            mkey[lane] = 0ull;
-            mi[lane] = 0x7fffffff;
-        }
-        __syncthreads();
-        // seeds: lane m scans the lattice points in ascending order (strict >) for the
-        // largest v_im, and raises that point's best value; then every m whose seed value
-        // equals its point's best offers its index: a point seeded by several directions
-        // goes to the largest value, ties to the lowest m (claiming in order of m)
-        // (with P = 64 / d > 1 lanes per direction, lane m + part d scans the part-th block
-        // of points and the blocks combine by value, ties to the lower point)
-        double bv = 0.0;
-        int bi = 0;
-        const int part = lane / d;
-        const bool scans = part < P && part * blk_pts < NF;  // a block can be empty for tiny N_fib
-        if (scans) {
-            const int m = lane - part * d;
-            const int ib = part * blk_pts, ie = min(NF, ib + blk_pts);
-            const double tx = sx[m], ty = sy[m], tz = sz[m];
-            bv = fma(lq[2][ib], tz, fma(lq[1][ib], ty, lq[0][ib] * tx));
-            bi = ib;
-#pragma unroll 4
-            for (int i = ib + 1; i < ie; ++i) {
-                const double v = fma(lq[2][i], tz, fma(lq[1][i], ty, lq[0][i] * tx));
-                bi = v > bv ? i : bi;
-                bv = fmax(bv, v);
-            }
-            if (P > 1) atomicMax(&mkey[m], order_key(bv));
-        }
-        if (P > 1) {
-            __syncthreads();
-            if (scans && bv == order_value(mkey[lane - part * d])) atomicMin(&mi[lane - part * d], bi);
-            __syncthreads();
-            if (lane < d) {
-                bi = mi[lane];
-                bv = order_value(mkey[lane]);
-            }
-        }
-        if (lane < d) atomicMax(&bkey[bi], order_key(bv));
-        __syncthreads();
-        if (lane < d && bv == order_value(bkey[bi])) atomicMin(&col[bi], lane);
-        __syncthreads();
-        if (ok0 && col[i0] == 0x7fffffff) col[i0] = -1;  // each lane its own points
-        if (ok1 && col[i1] == 0x7fffffff) col[i1] = -1;
-        // flood fill in rounds: an uncoloured point takes the colour of its lowest-index
-        // coloured neighbour (the lists ascend) in the snapshot of the round's start; the
-        // list's reads are independent, so they are issued together
-        for (int round = 0; round < NF; ++round) {
-            if (ok0) snap[i0] = col[i0];
-            if (ok1) snap[i1] = col[i1];
-            __syncthreads();
-            bool missing = false;
+        const bool mine = m < d && a0 + dl < n_in;
+        // seeds: the screen's largest value over the lattice points of every (direction, out-edge)
+        bool sure = false;
+        int pt = 0;
+        if (screened) {
+            const float x = (float)tx * kHalfScale, y = (float)ty * kHalfScale, z = (float)tz * kHalfScale;
+            unsigned p[3];
+            split_halves(fmaf((float)R[2], z, fmaf((float)R[1], y, (float)R[0] * x)),
+                         fmaf((float)R[5], z, fmaf((float)R[4], y, (float)R[3] * x)),
+                         fmaf((float)R[8], z, fmaf((float)R[7], y, (float)R[6] * x)), p);
+            // k 13: 2^10 against the -2^11 of the rows past the last point
+            const unsigned one = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(0.0f, kHalfScale));
+            Operand op[2];
+            swap_halves(p[0], p[1], op[0].w[0], op[1].w[0]);
+            swap_halves(p[1], p[2], op[0].w[1], op[1].w[1]);
+            swap_halves(p[2], one, op[0].w[2], op[1].w[2]);
+            swap_halves(p[0], 0u, op[0].w[3], op[1].w[3]);
+            float best[2], second[2];
 #pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2) {
-                const int i = h2 ? i1 : i0;
-                if (i >= NF || snap[i] >= 0) continue;
-                int c = -1;
+            for (int q = 0; q < 2; ++q) {
 #pragma unroll
-                for (int t = kHullNb - 1; t >= 0; --t) {
-                    if (t < nn[h2]) {
-                        const int ct = snap[(nbw[h2][t >> 2] >> (8 * (t & 3))) & 0xffu];
-                        c = ct >= 0 ? ct : c;
-                    }
+                for (int t = 0; t < 4; ++t) {  // register i of tile t: 2 i + t mod 2 + 32 (t / 2)
+                    if (t >= nt) break;
+                    const int tag = 32 * (t >> 1) + (t & 1);
+                    const float16v v = dot_tile(pts[t], op[q]);
+                    if (t == nt - 1 && last <= 8) fold_tile<4, 63>(v, tag, t == 0, best[q], second[q]);
+                    else fold_tile<16, 63>(v, tag, t == 0, best[q], second[q]);
                 }
-                col[i] = c;
-                missing = missing || c < 0;
             }
-            const bool any = __ballot(missing) != 0ull;
-            __syncthreads();
-            if (!any) break;
+            float b0, b1, s0, s1;
+            swap_halves(best[0], best[1], b0, b1);
+            swap_halves(second[0], second[1], s0, s1);
+            const float top = fmaxf(b0, b1);
+            sure = top - fmaxf(fmaxf(fminf(b0, b1), s0), s1) > kCertified;
+            const int tag = (int)(__float_as_uint(top) & 63u), i = (tag & 31) >> 1;
+            pt = 32 * (2 * (tag >> 5) + (tag & 1)) + 8 * (i >> 2) + (b1 > b0 ? 4 : 0) + (i & 3);
         }
-        // cells: fixed-point sums per colour, then this direction's column
-        if (lane < d) bins[lane] = 0ull;
+        double v = -__builtin_inf();
+        if (mine && sure) {
+            double q0, q1, q2;
+            rotate_point(R, lat[3 * pt], lat[3 * pt + 1], lat[3 * pt + 2], q0, q1, q2);
+            v = fma(q2, tz, fma(q1, ty, q0 * tx));
+        } else if (mine) {  // the lattice points in ascending order, strict >
+            pt = 0;
+            for (int i = 0; i < NF; ++i) {
+                double q0, q1, q2;
+                rotate_point(R, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
+                const double w = fma(q2, tz, fma(q1, ty, q0 * tx));
+                pt = w > v ? i : pt;
+                v = fmax(v, w);
+            }
+        }
+        // claims: a point seeded by several out-edges goes to the largest value, ties to the
+        // lowest m (claiming in order of m)
+        for (int t = lane; t < 256; t += 64) {
+            bkey[t >> 7][t & 127] = 0ull;
+            col[t >> 7][t & 127] = kNone;
+        }
+        for (int q = 0; q < 2; ++q) bins[q][lane] = 0ull;
         __syncthreads();
-        if (ok0 && col[i0] >= 0 && SG_IN(col[i0], d, 0x206)) atomicAdd(&bins[col[i0]], wq[i0]);
-        if (ok1 && col[i1] >= 0 && SG_IN(col[i1], d, 0x207)) atomicAdd(&bins[col[i1]], wq[i1]);
+        if (mine) atomicMax(&bkey[dl][pt], order_key(v));
         __syncthreads();
-        if (lane < d) {
-            const int m = lane;
-            const double Q = (double)(long long)bins[m] * kUnfix;
+        if (mine && v == order_value(bkey[dl][pt])) atomicMin(&col[dl][pt], m);
+        __syncthreads();
+        // the fill, of both directions at once
+        int c[2][2];
+        bool ok[2][2];
+        unsigned long long done[2][2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                ok[q][h] = lane + 64 * h < NF && q < nd && a0 + q < n_in;
+                c[q][h] = col[q][lane + 64 * h];
+                done[q][h] = __ballot(ok[q][h] && c[q][h] != kNone);
+            }
+        }
+        while (true) {
+            bool fresh[2][2];
+            unsigned long long news = 0ull;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const unsigned long long lo = near[h][0] & done[q][0], hi = near[h][1] & done[q][1];
+                    fresh[q][h] = ok[q][h] && c[q][h] == kNone && (lo | hi) != 0ull;
+                    const int from = lo ? __builtin_ctzll(lo) : 64 + __builtin_ctzll(hi | 1ull << 63);
+                    if (fresh[q][h]) c[q][h] = col[q][from];
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (fresh[q][h]) col[q][lane + 64 * h] = c[q][h];
+                    const unsigned long long b = __ballot(fresh[q][h]);
+                    done[q][h] |= b;
+                    news |= b;
+                }
+            }
+            __syncthreads();
+            if (!news) break;
+        }
+        // cells: fixed-point sums per colour, then the directions' columns
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (ok[q][h] && c[q][h] != kNone && SG_IN(c[q][h], d, 0x206))
+                    atomicAdd(&bins[q][c[q][h]], wq[lane + 64 * h]);
+        }
+        __syncthreads();
+        if (mine) {
+            const double Q = (double)(long long)bins[dl][m] * kUnfix;
             const long long b = off + m;
             if (surf) {
-                for (int c = 0; c < d; ++c) {
-                    if (kWriteQ) blk[c * d + m] = (BlkT)Q;
-                    else blk[c * d + m] = (BlkT)(T[off + c] * rl * (Real)Q);
+                for (int k = 0; k < d; ++k) {
+                    if (kWriteQ) blk[k * d + m] = (BlkT)Q;
+                    else blk[k * d + m] = (BlkT)(T[off + k] * rl * (Real)Q);
                 }
                 if (!kWriteQ) S[b] = rl * mu0 * tsun * (Real)Q;
                 qsun[b] = (float)Q;
@@ -1314,22 +1343,23 @@ int qbuild_group_big(int NF) { return std::min(kBigCols / NF, kBigGroup); }
 
 template <class Real>
 void launch_qbuild(Scene &s, hipStream_t st, int write_q) {
-    const size_t shm = 0;
     const int dm = (std::min(s.dmax, kWave) + 7) / 8 * 8;
     const size_t qshm = qbuild_lds(dm);
     if (s.sigma_mode == SG_SIGMA_COLOUR) {
         if (write_q) {
-            hipLaunchKernelGGL((k_qcolour<Real, float, true>), dim3(s.N), dim3(64), shm, st, s.N, s.n_vol, s.adj_ptr,
-                               s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
+            hipLaunchKernelGGL((k_qcolour<Real, float, true>), dim3(s.N), dim3(64), 0, st, s.N, s.n_vol, s.adj_ptr,
+                               s.adj_idx, s.pos, s.lat, (const uint4 *)s.lat_halves, s.tab, s.n_fib, s.n_phase,
+                               node_frac(s), s.sun_in[0], s.sun_in[1],
                                s.sun_in[2], (Real)s.mu0, (const Real *)nullptr, (const Real *)nullptr,
                                (const Real *)nullptr, s.nodeoff, s.q, (Real *)nullptr, s.qsun, s.hull, s.periodic,
-                               (long long)s.nx * kFx, (long long)s.ny * kFx);
+                               (long long)s.nx * kFx, (long long)s.ny * kFx, s.qscreen);
         } else {
-            hipLaunchKernelGGL((k_qcolour<Real, Real, false>), dim3(s.N), dim3(64), shm, st, s.N, s.n_vol, s.adj_ptr,
-                               s.adj_idx, s.pos, s.lat, s.tab, s.n_fib, s.n_phase, node_frac(s), s.sun_in[0], s.sun_in[1],
+            hipLaunchKernelGGL((k_qcolour<Real, Real, false>), dim3(s.N), dim3(64), 0, st, s.N, s.n_vol, s.adj_ptr,
+                               s.adj_idx, s.pos, s.lat, (const uint4 *)s.lat_halves, s.tab, s.n_fib, s.n_phase,
+                               node_frac(s), s.sun_in[0], s.sun_in[1],
                                s.sun_in[2], (Real)s.mu0, (const Real *)s.T, (const Real *)s.rho,
                                (const Real *)s.Tsun, s.nodeoff, (Real *)s.val, (Real *)s.S, s.qsun, s.hull, s.periodic,
-                               (long long)s.nx * kFx, (long long)s.ny * kFx);
+                               (long long)s.nx * kFx, (long long)s.ny * kFx, s.qscreen);
         }
         if (s.n_big) {  // nodes of degree above 64: one workgroup per (node, incoming direction)
             if (write_q)

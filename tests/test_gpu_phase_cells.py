@@ -163,3 +163,21 @@ def test_wavelength_tiles_at_every_degree(ctx, most):
     for k in (0, 4):
         ora = oracle.run(sc, abs_scale=float(sc.abs_scale[k]))["radiance"]
         assert np.abs(ref[k] - ora).max() <= 1e-4 * np.abs(ora).max()
+
+
+@pytest.mark.parametrize("n_fib", [2, 5, 8, 9, 31, 32, 33, 40, 41, 64, 72, 73, 100, 127, 128])
+@pytest.mark.parametrize("most, centred", [(64, False), (28, True)])
+def test_coloured_cells_are_exact(ctx, n_fib, most, centred):
+    """The colouring's seeds through the screen and by the FP64 scan alone, and the oracle's cells."""
+    from paper_2503_16037_amd import sgrt
+    sc = hub_scene(n_fib, most, centred).with_(sigma_mode=1)
+    say("coloured cells", n_fib, "lattice points")
+    with sgrt.Scene(ctx, sc) as g:
+        got = []
+        for screen in (True, False):
+            g.solve(precision="fp64", screen=screen, scatter_order=1)
+            got.append((g.export_csr()[2], g.export_vector("source"), g.export_vector("qsun")))
+        for x, y in zip(*got):
+            assert np.array_equal(x, y)
+    ora = oracle.run(sc, scatter_order=1)
+    assert np.abs(got[0][0] - ora["val"]).max() <= 1e-12 * np.abs(ora["val"]).max()
