@@ -866,9 +866,9 @@ sg_status solve_linear(Scene &s, const sg_solve_opts &o, hipStream_t st, Exec &t
     const int m = o.gmres_restart > 0 ? std::min(std::max(o.gmres_restart, 2), 64) : 32;
     Real *S = (Real *)s.S;
     // a zero source needs no special case: every measure is zero from the first sweep
-    launch_fill<double>(s.x64, 0.0, E, st);
     int use_gmres = o.solver == SG_SOLVER_GMRES;
     bool warm = false, have_r = false;
+    if (use_gmres && !o.warm_start) launch_fill<double>(s.x64, 0.0, E, st);
     if (o.warm_start) {
         SG_TRY(load_warm_start(s, o, st));
         launch_residual64<Real>(s, st, S, s.x64, s.r64, s.scal);
@@ -888,16 +888,19 @@ sg_status solve_linear(Scene &s, const sg_solve_opts &o, hipStream_t st, Exec &t
         int stalled = 0;
         // per-edge relative updates settle at a few units of rounding: never ask for less
         const double floor_rel = sizeof(Real) == 4 ? 4e-6 : 1e-14;
+        bool fresh = !warm;  // xa is the solution, and x64 not yet its copy
         if (!warm) {  // a kept warm start goes straight to the refinement below
             SG_TRY(neumann<Real>(s, st, tm, S, xa, xb, 1, std::max(0.3 * rtol, floor_rel), max_sweeps, ss, stalled));
-            launch_to64<Real>(xa, s.x64, E, st);
             nonfinite = stalled == 2;
         }
         if (stalled && o.solver == SG_SOLVER_AUTO) use_gmres = 1;
+        if (use_gmres) launch_to64<Real>(xa, s.x64, E, st);
         // FP64 residual and iterative refinement
         for (int it = 0; !use_gmres && it < 12; ++it) {
             if (!have_r) {
-                launch_residual64<Real>(s, st, S, s.x64, s.r64, s.scal);
+                if (fresh) launch_residual64_of<Real>(s, st, S, xa, s.x64, s.r64, s.scal);
+                else launch_residual64<Real>(s, st, S, s.x64, s.r64, s.scal);
+                fresh = false;
                 ++ss.sweeps;
                 ++ss.refinements;
                 double m2[2];

@@ -291,6 +291,10 @@ template <class Real>
 void launch_first(Scene &s, hipStream_t st, const Real *rhs, Real *x, double *out);
 template <class Real>
 void launch_residual64(Scene &s, hipStream_t st, const Real *S, const double *x64, double *r64, double *norm_out);
+// the same of the sweeps' iterate x, whose FP64 copy goes to x64
+template <class Real>
+void launch_residual64_of(Scene &s, hipStream_t st, const Real *S, const Real *x, double *x64, double *r64,
+                          double *norm_out);
 template <class Real>
 void launch_apply_imk64(Scene &s, hipStream_t st, const double *v, double *w);
 int spmv_blocks(const Scene &s);

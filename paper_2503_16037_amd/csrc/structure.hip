@@ -20,27 +20,20 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 8;  // elements per thread
 constexpr int kScanTile = kScanThreads * kScanItems;
 
-__global__ __launch_bounds__(256) void k_degree_sq(int N, const long long *__restrict__ adj_ptr,
-                                                  long long *__restrict__ out) {
-    const int l = blockIdx.x * blockDim.x + threadIdx.x;
-    if (l < N) {
-        const long long d = adj_ptr[l + 1] - adj_ptr[l];
-        out[l] = d * d;
-    }
-}
-
-// Exclusive scan, pass 1: each tile scanned locally in place, tile total to tsum.
-__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(long long *__restrict__ a, int n,
-                                                            long long *__restrict__ tsum) {
+// Exclusive scan of d_l^2, pass 1: each tile scanned locally, tile total to tsum (a scene of one
+// tile, up to 2048 nodes, is done with that, and its total goes to *grand).
+__global__ __launch_bounds__(kScanThreads) void k_scan_tiles(const long long *__restrict__ adj_ptr,
+                                                            long long *__restrict__ a, int n,
+                                                            long long *__restrict__ tsum, long long *__restrict__ grand) {
     __shared__ long long sh[kScanThreads];
     const int base = blockIdx.x * kScanTile + threadIdx.x * kScanItems;
     long long v[kScanItems];
     long long run = 0;
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i) {
-        const long long x = (base + i < n) ? a[base + i] : 0;
+        const long long d = (base + i < n) ? adj_ptr[base + i + 1] - adj_ptr[base + i] : 0;
         v[i] = run;
-        run += x;
+        run += d * d;
     }
     sh[threadIdx.x] = run;
     __syncthreads();
@@ -55,7 +48,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tiles(long long *__restri
 #pragma unroll
     for (int i = 0; i < kScanItems; ++i)
         if (base + i < n) a[base + i] = v[i] + excl;
-    if (threadIdx.x == kScanThreads - 1) tsum[blockIdx.x] = sh[kScanThreads - 1];
+    if (threadIdx.x == kScanThreads - 1) *(gridDim.x == 1 ? grand : tsum + blockIdx.x) = sh[kScanThreads - 1];
 }
 
 // Pass 2: exclusive scan of the tile totals by one block (serial over chunks).
@@ -90,18 +83,24 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_add(long long *__restrict
         if (base + i < n) a[base + i] += off;
 }
 
-// rev(e) for every edge: position of (head, tail) in the head's row.  Two nodes per
-// wavefront, one per 32-lane half (a node has ~24 edges, each a chain of dependent loads
-// through the binary search, so a resident wavefront advances two chains per node slot).
-__global__ __launch_bounds__(256) void k_rev(int N, const long long *__restrict__ adj_ptr,
-                                            const int *__restrict__ adj_idx, int *__restrict__ rev) {
+// rev(e) for every edge, the position of (head, tail) in the head's row, and the row pointers.  Two
+// nodes per wavefront, one per 32-lane half (a node has ~24 edges, each a chain of dependent loads
+// through the binary search, so a resident wavefront advances two chains per node slot).  The
+// chains bound it.  The row pointers in a pass of their own cost as much at cloud 128x128x48 (221 + 53 us,
+// here 272) and a launch more, 3 of the 40 us of this stage at 8x8x8.
+__global__ __launch_bounds__(256) void k_rev(int N, long long E, const long long *__restrict__ adj_ptr,
+                                            const int *__restrict__ adj_idx, const long long *__restrict__ nodeoff,
+                                            int *__restrict__ rev, long long *__restrict__ row_ptr) {
     const int l = blockIdx.x * 8 + (threadIdx.x >> 5);
     const int lane = threadIdx.x & 31;
     if (l >= N) return;
     const long long off = adj_ptr[l];
     const int d = (int)(adj_ptr[l + 1] - off);
+    const long long b0 = nodeoff[l];
+    if (l == N - 1 && lane == 0) row_ptr[E] = nodeoff[N];
     for (int m = lane; m < d; m += 32) {
         const int j = adj_idx[off + m];
+        row_ptr[off + m] = b0 + (long long)m * d;
         if (!SG_IN(j, N, 0x601)) continue;
         long long lo = adj_ptr[j], hi = adj_ptr[j + 1];
         while (lo < hi) {
@@ -134,19 +133,6 @@ __global__ __launch_bounds__(256) void k_check_symmetric(int N, const long long 
     }
 }
 
-__global__ __launch_bounds__(256) void k_row_ptr(int N, long long E, const long long *__restrict__ adj_ptr,
-                                                const long long *__restrict__ nodeoff,
-                                                long long *__restrict__ row_ptr) {
-    const int l = blockIdx.x * 8 + (threadIdx.x >> 5);  // two nodes per wavefront
-    const int lane = threadIdx.x & 31;
-    if (l >= N) return;
-    const long long off = adj_ptr[l];
-    const int d = (int)(adj_ptr[l + 1] - off);
-    const long long b0 = nodeoff[l];
-    for (int m = lane; m < d; m += 32) row_ptr[off + m] = b0 + (long long)m * d;
-    if (l == N - 1 && lane == 0) row_ptr[E] = nodeoff[N];
-}
-
 __global__ __launch_bounds__(256) void k_col_idx(int N, const long long *__restrict__ adj_ptr,
                                                 const long long *__restrict__ nodeoff, const int *__restrict__ rev,
                                                 int *__restrict__ col) {
@@ -164,14 +150,15 @@ __global__ __launch_bounds__(256) void k_col_idx(int N, const long long *__restr
 
 void launch_structure(Scene &s, hipStream_t st) {
     const int N = s.N;
-    hipLaunchKernelGGL(k_degree_sq, dim3((N + 255) / 256), dim3(256), 0, st, N, s.adj_ptr, s.nodeoff);
     const int nt = (N + kScanTile - 1) / kScanTile;
-    hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(kScanThreads), 0, st, s.nodeoff, N, s.scan_tmp);
-    hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kScanThreads), 0, st, s.scan_tmp, nt, s.nodeoff + N);
-    hipLaunchKernelGGL(k_scan_add, dim3(nt), dim3(kScanThreads), 0, st, s.nodeoff, N, s.scan_tmp);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(nt), dim3(kScanThreads), 0, st, s.adj_ptr, s.nodeoff, N, s.scan_tmp, s.nodeoff + N);
+    if (nt > 1) {
+        hipLaunchKernelGGL(k_scan_totals, dim3(1), dim3(kScanThreads), 0, st, s.scan_tmp, nt, s.nodeoff + N);
+        hipLaunchKernelGGL(k_scan_add, dim3(nt), dim3(kScanThreads), 0, st, s.nodeoff, N, s.scan_tmp);
+    }
     const int nb = (N + 7) / 8;  // two nodes per wavefront, eight per workgroup
-    hipLaunchKernelGGL(k_rev, dim3(nb), dim3(256), 0, st, N, s.adj_ptr, s.adj_idx, s.rev);
-    hipLaunchKernelGGL(k_row_ptr, dim3(nb), dim3(256), 0, st, N, (long long)s.E, s.adj_ptr, s.nodeoff, s.row_ptr);
+    hipLaunchKernelGGL(k_rev, dim3(nb), dim3(256), 0, st, N, (long long)s.E, s.adj_ptr, s.adj_idx, s.nodeoff, s.rev,
+                       s.row_ptr);
 }
 
 void launch_check_symmetric(Scene &s, unsigned *bad, hipStream_t st) {
