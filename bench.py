@@ -60,12 +60,21 @@ def spmv_bytes(n_nodes: int, n_edges: int, nnz: int, real_bytes: int = 4, n_lamb
 
 # Lane operations per (incoming direction, out-edge, lattice point) of the phase-cell ownership
 # (Eq. 7): the algorithmic count is 5 (a 3-term dot product as one multiply and two FMAs, then
-# a compare and a select of the running argmax).  The kernel issues 5.5 full-rate FP32 and
-# integer operations per triple instead (its exact screen: three FMAs and a bitfield insert per
-# triple, a three-way maximum, a median and a maximum per two out-edges), plus the FP64 scan of
-# the rare uncertified pairs; that count is reported beside it
+# a compare and a select of the running argmax).  The kernel takes the dot products from the
+# matrix cores; every vector instruction it issues (counted on plume 64x64x32, its set-up and its columns
+# included) is 4.7 lane operations per triple, reported beside it
 QBUILD_OPS_PER_PAIR = 5
-QBUILD_OPS_ISSUED_PER_PAIR = 5.5
+# The nodes that a sweep over the front visits are not counted, so such sweeps count no bytes
+SWEEP_BYTES = "those of the whole sweeps, a lower bound: later sweeps visit the nodes whose inputs still move"
+
+
+def whole_sweeps(sz, launches, n_lambda):
+    """Of a solve's sweep launches, those that visit every node: the first three (four of a batch) where the
+    library goes over to the front (from 16 M matrix values, or 128 MB per sweep of a batch, on)."""
+    if n_lambda == 1:
+        return min(launches, 3) if sz["nnz"] >= 16e6 else launches
+    return min(launches, 4) if 4 * sz["nnz"] + 8 * sz["n_edges"] * n_lambda >= 128e6 else launches
+QBUILD_OPS_ISSUED_PER_PAIR = 4.7
 
 
 def qbuild_pairs(scene) -> float:
@@ -87,8 +96,8 @@ def step_bytes(sz, nvox, infos_avg):
       matrix: K values (4 nnz), the source and the sun's cell weight (8 per edge), the optical
         depths read back (8 per edge);
       sweeps: spmv_bytes per sweep (the previous iterate of monitored sweeps included);
-      FP64 residual: K values (4 nnz), per edge S (4), x64 (8), gathered x64 (8), r (8), rev (4),
-        per node 16;
+      FP64 residual: K values (4 nnz), per edge S (4), x (4), gathered x (4), the FP64 copy of x (8),
+        r (8), rev (4), per node 16;
       gather: phi (8 per edge) and the node radiances (8 per node);
       structure (CSR pattern): the adjacency read (4 per edge, 8 per node), the reverse edge
         ids and row pointers written (4 + 8 per edge), the node offsets (8 per node)."""
@@ -145,7 +154,7 @@ def measured_traffic(kernel: str, workload: str):
     or None when the kernel's sources changed since the counters were taken."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "traffic.json")
-    srcs = {"k_qbuild": ["qbuild.hip"], "k_spmv": ["solve.hip"], "k_spmm_wide": ["batched.hip"]}[kernel]
+    srcs = {"k_qbuild": ["qbuild.hip"], "k_spmv": ["solve.hip"], "k_spmm_wide": ["batched_sweep.hpp", "batched.hip", "batched_front.hip"]}[kernel]
     try:
         rec = json.load(open(path))["kernels"][f"{kernel}@{workload}"]
     except (OSError, KeyError, ValueError):
@@ -580,8 +589,9 @@ def main():
     # a sweep that computes the convergence measures also reads the previous iterate
     # (4 bytes per edge and wavelength): average over the timed launches
     monitored = sum(i["spmv_monitored"] for i in infos) / max(spmv_launches, 1)
-    sbytes = spmv_bytes(sz["n_nodes"], sz["n_edges"], sz["nnz"], n_lambda=g.n_lambda) + \
-        monitored * 4 * sz["n_edges"] * g.n_lambda
+    whole = whole_sweeps(sz, spmv_launches / len(infos), g.n_lambda) / max(spmv_launches / len(infos), 1e-9)
+    sbytes = whole * (spmv_bytes(sz["n_nodes"], sz["n_edges"], sz["nnz"], n_lambda=g.n_lambda) +
+                      monitored * 4 * sz["n_edges"] * g.n_lambda)
     qpairs = qbuild_pairs(scene)
     qops = QBUILD_OPS_PER_PAIR * qpairs
     if stages["ms_qbuild"] >= spmv_per_step_ms and g.n_lambda == 1:
@@ -600,23 +610,22 @@ def main():
                 "bound": "hbm", "achieved": round(achieved, 1),
                 "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": measured_traffic("k_spmv" if g.n_lambda == 1 else "k_spmm_wide", args.workload),
-                "algorithmic_per_launch": sbytes, "avg_launch_ms": round(spmv_avg_ms, 5)}
+                "algorithmic_per_launch": sbytes, "avg_launch_ms": round(spmv_avg_ms, 5), "bytes_are": SWEEP_BYTES}
     # the phase cells against the ALU peak whichever kernel dominates the step
     cell_roof = {"kernel": "k_qcolour" if args.sigma == "colour" else "k_qbuild", "bound": "alu",
                  "avg_launch_ms": round(stages["ms_qbuild"], 4), "ops_per_pair": QBUILD_OPS_PER_PAIR,
                  "achieved": round(qops / (stages["ms_qbuild"] * 1e-3) / 1e12, 3), "unit": "T lane-op/s",
                  "frac": round(qops / (stages["ms_qbuild"] * 1e-3) / 1e12 / ALU_PEAK_TOPS, 4),
-                 "owners": "FP64 scan only" if args.exact_cells else "FP32 screen, FP64 scan where uncertified"}
+                 "owners": "FP64 scan only" if args.exact_cells else "matrix-core screen, FP64 scan where uncertified"}
     sweep_roof = {"kernel": "k_spmv", "avg_launch_ms": round(spmv_avg_ms, 5), "bytes_per_launch": round(sbytes),
                   "monitored_fraction": round(monitored, 4),
                   "achieved_GBs": round(sbytes / max(spmv_avg_ms, 1e-9) / 1e6, 1),
-                  "launches_per_step": spmv_launches / len(infos)}
+                  "launches_per_step": spmv_launches / len(infos), "bytes_are": SWEEP_BYTES}
 
     step_hbm = None
     if g.n_lambda == 1:
-        # bytes of the step: every timed sweep launch (monitored ones read the previous x too)
-        sweep_total = (spmv_bytes(sz["n_nodes"], sz["n_edges"], sz["nnz"]) * spmv_launches +
-                       4 * sz["n_edges"] * sum(i["spmv_monitored"] for i in infos)) / len(infos)
+        # bytes of the step: every whole sweep (monitored ones read the previous x too)
+        sweep_total = sbytes * spmv_launches / len(infos)
         sb = step_bytes(sz, scene.nvox, {"sweep_bytes_total": sweep_total, "refinements": avg("refinements")})
         # the same without the phase-cell kernel, whose time is ALU issue (reported against the ALU
         # peak in phase_cell_kernel): its K values and source are taken out of the bytes
@@ -638,7 +647,7 @@ def main():
                             "over the whole step's wall time; the phase cells are ALU-bound and count no bytes; "
                             "without_phase_cells: structure, march, sweeps, residuals and gather over the step's "
                             "time less the phase-cell kernel's; solve_stage: the first iterate, the sweeps and the "
-                            "FP64 residuals over the solve stage's time"}
+                            "FP64 residuals over the solve stage's time; sweeps: " + SWEEP_BYTES}
     out = {"metric": METRIC, "value": round(scenes_per_s, 3), "unit": "scenes/s", "n_gpus": 1,
            "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_step, 4),
            "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "f32",
