@@ -229,7 +229,8 @@ __global__ __launch_bounds__(64) void k_bnode_J(int N, int nvol, int nl, const l
 
 // One wavefront per pixel, lanes = wavelengths: the voxel walk is the same for all
 // lanes, each accumulates its own wavelength in FP64.
-__global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per, int nl, const float *__restrict__ mu_s,
+template <bool kPer>
+__global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per_arg, int nl, const float *__restrict__ mu_s,
                                                const float *__restrict__ mu_a, const float *__restrict__ abs_scale,
                                                double len_view, long long vdx, long long vdy, long long vdz,
                                                long long sdx, long long sdy, long long sdz, double len_sun,
@@ -237,6 +238,7 @@ __global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per,
                                                int surface, double mu0, int nvol,
                                                const long long *__restrict__ los_ptr, const int *__restrict__ los_node,
                                                const double *__restrict__ los_t, double *__restrict__ out) {
+    const int per = kPer ? per_arg : 0;
     const int p = blockIdx.x;
     const int lane = threadIdx.x;
     const long long ix = p % nx, iy = p / nx;
@@ -246,7 +248,7 @@ __global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per,
         const int lam = min(l0 + lane, nl - 1);
         const double s = (double)abs_scale[lam];
         double tau_tot = 0.0;
-        voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+        voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
             const long long v = x + (long long)nx * (y + (long long)ny * z);
             if (SG_IN(v, (long long)nx * ny * nz, 0x406))
                 tau_tot += ((double)mu_s[v] + s * (double)mu_a[v]) * ((double)num / (double)den * len_view);
@@ -254,7 +256,7 @@ __global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per,
         });
         double I = 0.0, cum = 0.0;
         if (!los_ptr) {
-            voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+            voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
                 const long long v = x + (long long)nx * (y + (long long)ny * z);
                 if (!SG_IN(v, (long long)nx * ny * nz, 0x407)) return true;
                 const double ms = (double)mu_s[v];
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per,
             const long long e1 = los_ptr[p + 1];
             long long e = los_ptr[p];
             double t = 0.0;
-            voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+            voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
                 const long long v = x + (long long)nx * (y + (long long)ny * z);
                 if (!SG_IN(v, (long long)nx * ny * nz, 0x408)) return true;
                 const double ms = (double)mu_s[v];
@@ -300,7 +302,7 @@ __global__ __launch_bounds__(64) void k_bpixels(int nx, int ny, int nz, int per,
             I += exp(-tau_tot) * a_pi * J[((long long)nvol + p) * nl + lam];
         } else {
             double ts = 0.0;
-            voxel_walk(nx, ny, nz, per, px, py, 0, sdx, sdy, sdz, true, [&](int x, int y, int z, long long num, long long den) {
+            voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, sdx, sdy, sdz, true, [&](int x, int y, int z, auto num, auto den) {
                 const long long v = x + (long long)nx * (y + (long long)ny * z);
                 if (SG_IN(v, (long long)nx * ny * nz, 0x40a))
                     ts += ((double)mu_s[v] + s * (double)mu_a[v]) * ((double)num / (double)den * len_sun);
@@ -407,7 +409,8 @@ static void batched_gather(Scene &s, hipStream_t st, const PhiT *phi, int scatte
     const double fx = s.voxel_m / 65536.0;
     const double lv = sqrt((double)s.view[0] * s.view[0] + (double)s.view[1] * s.view[1] + (double)s.view[2] * s.view[2]) * fx;
     const double ls = sqrt((double)s.sun[0] * s.sun[0] + (double)s.sun[1] * s.sun[1] + (double)s.sun[2] * s.sun[2]) * fx;
-    hipLaunchKernelGGL(k_bpixels, dim3(s.npx), dim3(64), 0, st, s.nx, s.ny, s.nz, s.periodic, s.n_lambda, s.mu_s,
+    const auto pixels = s.periodic ? k_bpixels<true> : k_bpixels<false>;
+    hipLaunchKernelGGL(pixels, dim3(s.npx), dim3(64), 0, st, s.nx, s.ny, s.nz, s.periodic, s.n_lambda, s.mu_s,
                        s.mu_a, s.abs_scale_d, lv, (long long)s.view[0], (long long)s.view[1], (long long)s.view[2],
                        (long long)s.sun[0], (long long)s.sun[1], (long long)s.sun[2], ls, s.albedo, s.J, s.surface,
                        s.mu0, s.n_vol, s.general ? s.los_ptr : (const long long *)nullptr, s.los_node, s.los_t,

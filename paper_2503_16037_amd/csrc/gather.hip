@@ -81,7 +81,8 @@ __global__ __launch_bounds__(256) void k_node_J(int N, int nvol, const long long
     if (lane == 0) J[l] = acc;
 }
 
-__global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per, const float *__restrict__ mu_s,
+template <bool kPer>
+__global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per_arg, const float *__restrict__ mu_s,
                                               const float *__restrict__ mu_a, double scale, double len_view,
                                               long long vdx, long long vdy, long long vdz, long long sdx,
                                               long long sdy, long long sdz, double len_sun,
@@ -89,13 +90,14 @@ __global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per, 
                                               int surface, double mu0, int nvol, const long long *__restrict__ los_ptr,
                                               const int *__restrict__ los_node, const double *__restrict__ los_t,
                                               double *__restrict__ out) {
+    const int per = kPer ? per_arg : 0;
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= nx * ny) return;
     const long long ix = p % nx, iy = p / nx;
     const long long px = ix * kFx + kFx / 2, py = iy * kFx + kFx / 2;
     // pass 1: optical depth of the whole line of sight
     double tau_tot = 0.0;
-    voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+    voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
         const long long v = x + (long long)nx * (y + (long long)ny * z);
         if (!SG_IN(v, (long long)nx * ny * nz, 0x503)) return true;
         const double me = (double)mu_s[v] + scale * (double)mu_a[v];
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per, 
     // pass 2: chords, each attenuated from its far end to the sensor
     double I = 0.0, cum = 0.0;
     if (!los_ptr) {
-        voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+        voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
             const long long v = x + (long long)nx * (y + (long long)ny * z);
             if (!SG_IN(v, (long long)nx * ny * nz, 0x504)) return true;
             const double ms = (double)mu_s[v];
@@ -124,7 +126,7 @@ __global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per, 
         const long long e1 = los_ptr[p + 1];
         long long e = los_ptr[p];
         double t = 0.0;
-        voxel_walk(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, long long num, long long den) {
+        voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, vdx, vdy, vdz, true, [&](int x, int y, int z, auto num, auto den) {
             const long long v = x + (long long)nx * (y + (long long)ny * z);
             if (!SG_IN(v, (long long)nx * ny * nz, 0x505)) return true;
             const double ms = (double)mu_s[v];
@@ -155,7 +157,7 @@ __global__ __launch_bounds__(64) void k_pixels(int nx, int ny, int nz, int per, 
         I += exp(-tau_tot) * a_pi * J[nvol + p];
     } else {
         double ts = 0.0;
-        voxel_walk(nx, ny, nz, per, px, py, 0, sdx, sdy, sdz, true, [&](int x, int y, int z, long long num, long long den) {
+        voxel_walk_t<WalkT<kPer>>(nx, ny, nz, per, px, py, 0, sdx, sdy, sdz, true, [&](int x, int y, int z, auto num, auto den) {
             const long long v = x + (long long)nx * (y + (long long)ny * z);
             if (SG_IN(v, (long long)nx * ny * nz, 0x507))
                 ts += ((double)mu_s[v] + scale * (double)mu_a[v]) * ((double)num / (double)den * len_sun);
@@ -180,7 +182,8 @@ void launch_gather(Scene &s, hipStream_t st, const double *phi, int scatter_orde
     const double lv = sqrt((double)s.view[0] * s.view[0] + (double)s.view[1] * s.view[1] + (double)s.view[2] * s.view[2]) * fx;
     const double ls = sqrt((double)s.sun[0] * s.sun[0] + (double)s.sun[1] * s.sun[1] + (double)s.sun[2] * s.sun[2]) * fx;
     const double scale = s.abs_scale.empty() ? 1.0 : (double)s.abs_scale[0];
-    hipLaunchKernelGGL(k_pixels, dim3((s.npx + 63) / 64), dim3(64), 0, st, s.nx, s.ny, s.nz, s.periodic, s.mu_s, s.mu_a, scale,
+    const auto pixels = s.periodic ? k_pixels<true> : k_pixels<false>;
+    hipLaunchKernelGGL(pixels, dim3((s.npx + 63) / 64), dim3(64), 0, st, s.nx, s.ny, s.nz, s.periodic, s.mu_s, s.mu_a, scale,
                        lv,
                        (long long)s.view[0], (long long)s.view[1], (long long)s.view[2], (long long)s.sun[0],
                        (long long)s.sun[1], (long long)s.sun[2], ls, s.albedo, s.J, s.surface, s.mu0, s.n_vol,

@@ -24,11 +24,6 @@ constexpr int kMarchThreads = 256;
 constexpr int kNodesPerBlock = 32;
 constexpr int kBrickCap = 1024;  // voxels staged per workgroup (2 channels x 4 KB)
 
-// Crossing-time arithmetic of the marches: FP64 on a bounded grid (exact there, and one
-// multiply per product), 64-bit integers on periodic axes (walks long enough to pass 2^53)
-template <bool kPer>
-using WalkT = typename std::conditional<kPer, long long, double>::type;
-
 __device__ __forceinline__ void node_voxel(const int *__restrict__ pos, int l, int &vx, int &vy, int &vz) {
     vx = pos[3 * l] >> 16;
     vy = pos[3 * l + 1] >> 16;
