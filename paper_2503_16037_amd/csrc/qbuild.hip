@@ -16,13 +16,17 @@
 // The ownership decision is an argmax over double-precision dot products; it is
 // written with this exact operation sequence (also followed by the FP64 CPU
 // reference):
-//   s_m  = D_m / sqrt(Dx^2 + Dy^2 + Dz^2)             (exact integer sum)
+//   s_m  = D_m / sqrt(Dx^2 + Dy^2 + Dz^2)             (exact integer sum; D_m = 0: below)
 //   h    = 1 / (1 + u_z);  xy = (u_x u_y) h
 //   R    = [[u_z + (u_y u_y) h, -xy, -u_x], [-xy, u_z + (u_x u_x) h, -u_y], [u_x, u_y, u_z]]
 //          (R = diag(1, -1, -1) when 1 + u_z < 1e-12; the identity on the surface)
 //   q_ik = fma(R_2k, p_i2, fma(R_1k, p_i1, R_0k p_i0))      (q_i = R^T p_i)
 //   v_im = fma(q_i2, s_m2, fma(q_i1, s_m1, q_i0 s_m0))      (= p_i . R s_m)
 // with no other contraction, hence the pragma below and -ffp-contract=off.
+// Coupled nodes at one place (D_m = 0, an integer test) have no direction between them.  Such an
+// out-edge owns nothing, unless no out-edge of the node has a direction (the first then owns
+// all); as an incoming direction it counts as straight down (s_m = (0, 0, 1), u = -s_m).  No NaN
+// arises, and this file is compiled as if there were none.
 //
 // The regular kernel finds that argmax through a screen with an error bound: every decision
 // the screen cannot certify is taken by the FP64 sequence above, so each owner is the one
@@ -74,8 +78,7 @@ __device__ __forceinline__ int small_div(int p, float inv_n) { return (int)(((fl
 // maxima per product, the form before, took 9.1e8 vector instructions on plume 64x64x32 (now
 // 5.5e8; issuing 93 % of the time): 1.27 -> 1.00 ms, cloud 128x128x48 7.6 -> 6.1 ms, plume
 // 96x96x32 2.85 -> 2.22 ms.
-// A node with a zero-length out-edge (coincident nodes) has NaN directions: all of its slots
-// go to the FP64 sequence.
+// A node with an out-edge of no direction leaves all of its slots to the FP64 sequence.
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 constexpr float kCertified = 32.0f;  // 2^-15 in units of 2^-20
@@ -186,6 +189,16 @@ struct Rows {
         return (int)((__float_as_uint(best) & (unsigned)kMask) | (b1 > b0 ? 1u : 0u));
     }
 };
+
+// The unit vector of displacement (Dx, Dy, Dz); false (and straight up) where it is zero
+__device__ __forceinline__ bool unit_vector(long long Dx, long long Dy, long long Dz, double &x, double &y, double &z) {
+    const bool has = (Dx | Dy | Dz) != 0;
+    const double nrm = has ? sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz)) : 1.0;
+    x = (double)Dx / nrm;
+    y = (double)Dy / nrm;
+    z = has ? (double)Dz / nrm : 1.0;
+    return has;
+}
 
 // q = R^T p for lattice point (x, y, z) (R row-major, 9 doubles)
 __device__ __forceinline__ void rotate_point(const double *R, double x, double y, double z, double &q0, double &q1,
@@ -333,20 +346,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const bool surf = l >= nvol;
     if (!SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x201)) return;
 
-    bool zero = false;
+    bool none = false;
     if (lane < d) {
         const int j0 = adj_idx[off + lane];
         const int j = SG_IN(j0, N, 0x202) ? j0 : l;
         const long long Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
         const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
         const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
-        const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-        zero = (Dx | Dy | Dz) == 0;
-        sx[lane] = (double)Dx / nrm;
-        sy[lane] = (double)Dy / nrm;
-        sz[lane] = (double)Dz / nrm;
+        none = !unit_vector(Dx, Dy, Dz, sx[lane], sy[lane], sz[lane]);
     }
-    const bool screened = screen != 0 && __ballot(zero) == 0;
+    const unsigned long long without = __ballot(none);  // the out-edges of no direction
+    const bool screened = screen != 0 && without == 0ull;
     // phase weights of the lattice points in fixed point
     for (int i = lane; i < NF; i += 64) {
         double w;
@@ -447,7 +457,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             double best = -__builtin_inf();
             int o = 0;
             for (int k = 0; k < d; ++k) {
-                const double v = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
+                const double dot = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
+                const double v = without >> k & 1ull ? -__builtin_inf() : dot;
                 o = v > best ? k : o;
                 best = fmax(best, v);
             }
@@ -508,6 +519,7 @@ constexpr int kBigRows = 1024;                  // out-edges in LDS at a time, a
 constexpr int kScanEdges = 256;                 // out-edges in LDS at a time, in FP64
 constexpr int kBinRows = 512;                   // rows of a column summed at a time, per wavefront
 constexpr float kBigCertified = 8.0f;           // 2^-17 in units of 2^-20
+constexpr double kNoDirection = 2.0;            // x component, in LDS, of an out-edge of no direction
 
 // A wavefront's first C pairs of column tiles against nt row tiles: per lane and tile the
 // largest value of its rows, the second largest of the row tiles' largest, and the best's tile
@@ -576,10 +588,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     auto edge_dir = [&](int m, double &ex, double &ey, double &ez) {
         long long Dx, Dy, Dz;
         edge_offset(m, Dx, Dy, Dz);
-        const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-        ex = (double)Dx / nrm;
-        ey = (double)Dy / nrm;
-        ez = (double)Dz / nrm;
+        return unit_vector(Dx, Dy, Dz, ex, ey, ez);
     };
     if (tid < NF) {
         double w;
@@ -626,7 +635,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     // this wavefront's pair j holds the columns 64 (wave + 4 j) + lane
     const int pairs = (np + 63) / 64;
     const int mine = pairs > wave ? (pairs - wave + 3) / 4 : 0;
-    bool zero = false;  // a zero-length out-edge: no direction
+    bool none = false;  // an out-edge of no direction
     float run_best[kBigPairs], run_second[kBigPairs];
     int run_own[kBigPairs];
     if (screen) {
@@ -658,9 +667,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 if (r < nm) {
                     long long Dx, Dy, Dz;
                     edge_offset(m0 + r, Dx, Dy, Dz);
-                    zero = zero || (Dx | Dy | Dz) == 0;
-                    const float x = (float)Dx, y = (float)Dy, z = (float)Dz;
-                    const float inv = __builtin_amdgcn_rsqf(fmaf(z, z, fmaf(y, y, x * x))) * kHalfScale;
+                    none = none || (Dx | Dy | Dz) == 0;
+                    const float x = (float)Dx, y = (float)Dy, z = (float)Dz;  // whole: below 1 only if all zero
+                    const float inv = __builtin_amdgcn_rsqf(fmaxf(fmaf(z, z, fmaf(y, y, x * x)), 1.0f)) * kHalfScale;
                     site.x = x * inv;
                     site.y = y * inv;
                     site.z = z * inv;
@@ -716,7 +725,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
         }
     }
-    const bool sure = screen && !__syncthreads_or(zero);
+    const bool sure = screen && !__syncthreads_or(none);
 #pragma unroll
     for (int j = 0; j < kBigPairs; ++j) {
         const int p = 64 * (wave + 4 * j) + lane;
@@ -747,12 +756,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         int own = 0;
         for (int m0 = 0; m0 < d; m0 += kScanEdges) {
             const int nm = min(kScanEdges, d - m0);
-            if (tid < nm) edge_dir(m0 + tid, ex[tid], ey[tid], ez[tid]);
-            __syncthreads();
-            if (c < nq) {
+            bool has = true;
+            if (tid < nm) {
+                has = edge_dir(m0 + tid, ex[tid], ey[tid], ez[tid]);
+                if (!has) ex[tid] = kNoDirection;
+            }
+            const bool some = __syncthreads_or(!has);
+            if (c < nq && !some) {
 #pragma unroll 4
                 for (int k = part; k < nm; k += parts) {
                     const double v = fma(q2, ez[k], fma(q1, ey[k], q0 * ex[k]));
+                    own = v > best ? m0 + k : own;
+                    best = fmax(best, v);
+                }
+            } else if (c < nq) {
+                for (int k = part; k < nm; k += parts) {
+                    const double x = ex[k], dot = fma(q2, ez[k], fma(q1, ey[k], q0 * x));
+                    const double v = x == kNoDirection ? -__builtin_inf() : dot;
                     own = v > best ? m0 + k : own;
                     best = fmax(best, v);
                 }
@@ -876,20 +896,17 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     if (d == 0 || d > kWave) return;  // higher degree: k_qcolour_big
     const bool surf = l >= nvol;
     if (!SG_IN(nodeoff[l] + (long long)d * d - 1, nodeoff[N], 0x204)) return;
-    bool zero = false;  // a zero-length out-edge: no direction
+    bool none = false;
     if (lane < d) {
         const int j0 = adj_idx[off + lane];
         const int j = SG_IN(j0, N, 0x205) ? j0 : l;
         const long long Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
         const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
         const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
-        const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-        zero = (Dx | Dy | Dz) == 0;
-        sx[lane] = (double)Dx / nrm;
-        sy[lane] = (double)Dy / nrm;
-        sz[lane] = (double)Dz / nrm;
+        none = !unit_vector(Dx, Dy, Dz, sx[lane], sy[lane], sz[lane]);
     }
-    const bool screened = screen != 0 && __ballot(zero) == 0;
+    const unsigned long long without = __ballot(none);  // the out-edges of no direction
+    const bool screened = screen != 0 && without == 0ull;
     for (int i = lane; i < NF; i += 64) {
         double w;
         if (surf) {
@@ -944,7 +961,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
             else pole_rotation(sun_x, sun_y, sun_z, R);
         }
-        const bool mine = m < d && a0 + dl < n_in;
+        const bool mine = m < d && a0 + dl < n_in, seeds = mine && !(without >> m & 1ull);
         // seeds: the screen's largest value over the lattice points of every (direction, out-edge)
         bool sure = false;
         int pt = 0;
@@ -982,11 +999,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             pt = 32 * (2 * (tag >> 5) + (tag & 1)) + 8 * (i >> 2) + (b1 > b0 ? 4 : 0) + (i & 3);
         }
         double v = -__builtin_inf();
-        if (mine && sure) {
+        if (seeds && sure) {
             double q0, q1, q2;
             rotate_point(R, lat[3 * pt], lat[3 * pt + 1], lat[3 * pt + 2], q0, q1, q2);
             v = fma(q2, tz, fma(q1, ty, q0 * tx));
-        } else if (mine) {  // the lattice points in ascending order, strict >
+        } else if (seeds) {  // the lattice points in ascending order, strict >
             pt = 0;
             for (int i = 0; i < NF; ++i) {
                 double q0, q1, q2;
@@ -1004,20 +1021,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         }
         for (int q = 0; q < 2; ++q) bins[q][lane] = 0ull;
         __syncthreads();
-        if (mine) atomicMax(&bkey[dl][pt], order_key(v));
+        if (seeds) atomicMax(&bkey[dl][pt], order_key(v));
         __syncthreads();
-        if (mine && v == order_value(bkey[dl][pt])) atomicMin(&col[dl][pt], m);
+        if (seeds && v == order_value(bkey[dl][pt])) atomicMin(&col[dl][pt], m);
         __syncthreads();
         // the fill, of both directions at once
         int c[2][2];
         bool ok[2][2];
         unsigned long long done[2][2];
+        const bool unseeded = __popcll(without) == d;  // the first out-edge takes all
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 ok[q][h] = lane + 64 * h < NF && q < nd && a0 + q < n_in;
-                c[q][h] = col[q][lane + 64 * h];
+                c[q][h] = unseeded ? 0 : col[q][lane + 64 * h];
                 done[q][h] = __ballot(ok[q][h] && c[q][h] != kNone);
             }
         }
@@ -1084,6 +1102,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
 constexpr int kCellHash = 256;  // above the most owners a direction can have (N_fib <= 128)
 
 constexpr unsigned short kNoOwner = 0xffff;  // owners are below 4096
+constexpr unsigned char kNoSeed = 0xff;      // lattice points are below 128
 
 __device__ __forceinline__ int cell_find(const unsigned short *keys, int m) {
     int h = m & (kCellHash - 1);
@@ -1101,18 +1120,15 @@ __device__ __forceinline__ int cell_find(const unsigned short *keys, int m) {
 //   fill and cells as in k_qcolour, the colours' sums in a hash table (at most N_fib
 //   colours among the d out-edges), the column written by looking up every row.
 
-// unit vector of node l's out-edge m (the shortest periodic image)
-__device__ __forceinline__ void edge_unit(const long long *__restrict__ adj_ptr, const int *__restrict__ adj_idx,
+// unit vector of node l's out-edge m (the shortest periodic image); false: it has none
+__device__ __forceinline__ bool edge_unit(const long long *__restrict__ adj_ptr, const int *__restrict__ adj_idx,
                                           const int *__restrict__ pos, int l, int m, int per, long long wx,
                                           long long wy, double &ex, double &ey, double &ez) {
     const int j = adj_idx[adj_ptr[l] + m];
     const long long Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
     const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
     const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
-    const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-    ex = (double)Dx / nrm;
-    ey = (double)Dy / nrm;
-    ez = (double)Dz / nrm;
+    return unit_vector(Dx, Dy, Dz, ex, ey, ez);
 }
 
 // seeds of S out-directions per lane (m0 + 64 s + lane, s < S): each scans the lattice
@@ -1127,10 +1143,11 @@ __device__ __forceinline__ void colour_seeds(int m0, int d, int NF, const double
 #pragma clang fp contract(off)
     double tx[S], ty[S], tz[S], bv[S];
     int bi[S];
+    bool has[S];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         const int m = min(m0 + 64 * s + (int)threadIdx.x, d - 1);
-        edge_unit(adj_ptr, adj_idx, pos, l, m, per, wx, wy, tx[s], ty[s], tz[s]);
+        has[s] = edge_unit(adj_ptr, adj_idx, pos, l, m, per, wx, wy, tx[s], ty[s], tz[s]);
         bv[s] = fma(lq[2][0], tz[s], fma(lq[1][0], ty[s], lq[0][0] * tx[s]));
         bi[s] = 0;
     }
@@ -1147,8 +1164,8 @@ __device__ __forceinline__ void colour_seeds(int m0, int d, int NF, const double
     for (int s = 0; s < S; ++s) {
         const int m = m0 + 64 * s + (int)threadIdx.x;
         if (m < d) {
-            seed_pt[m] = (unsigned char)bi[s];
-            atomicMax(&bkey[bi[s]], order_key(bv[s]));
+            seed_pt[m] = has[s] ? (unsigned char)bi[s] : kNoSeed;
+            if (has[s]) atomicMax(&bkey[bi[s]], order_key(bv[s]));
         }
     }
 }
@@ -1183,14 +1200,7 @@ __global__ __launch_bounds__(64) void k_qcolour_big(
     const int d = (int)(adj_ptr[l + 1] - off);
     const bool surf = l >= nvol;
     auto edge_dir = [&](int m, double &ex, double &ey, double &ez) {
-        const int j = adj_idx[off + m];
-        const long long Dx = min_image((long long)pos[3 * j] - pos[3 * l], wx, per & 1);
-        const long long Dy = min_image((long long)pos[3 * j + 1] - pos[3 * l + 1], wy, per & 2);
-        const long long Dz = (long long)pos[3 * j + 2] - pos[3 * l + 2];
-        const double nrm = sqrt((double)(Dx * Dx + Dy * Dy + Dz * Dz));
-        ex = (double)Dx / nrm;
-        ey = (double)Dy / nrm;
-        ez = (double)Dz / nrm;
+        (void)edge_unit(adj_ptr, adj_idx, pos, l, m, per, wx, wy, ex, ey, ez);
     };
     double R[9];
     if (surf) {
@@ -1258,9 +1268,10 @@ __global__ __launch_bounds__(64) void k_qcolour_big(
     }
     __syncthreads();
     for (int m = lane; m < d; m += 64) {
+        const int bi = seed_pt[m];
+        if (bi == kNoSeed) continue;
         double tx, ty, tz;
         edge_dir(m, tx, ty, tz);
-        const int bi = seed_pt[m];
         const double v = fma(lq[2][bi], tz, fma(lq[1][bi], ty, lq[0][bi] * tx));
         if (v == order_value(bkey[bi])) atomicMin(&col[bi], m);
     }
@@ -1271,8 +1282,9 @@ __global__ __launch_bounds__(64) void k_qcolour_big(
     }
     const int i0 = lane, i1 = lane + 64;
     const bool ok0 = i0 < NF, ok1 = i1 < NF;
-    if (ok0 && col[i0] == 0x7fffffff) col[i0] = -1;  // each lane its own points
-    if (ok1 && col[i1] == 0x7fffffff) col[i1] = -1;
+    const bool unseeded = __ballot((ok0 && col[i0] != 0x7fffffff) || (ok1 && col[i1] != 0x7fffffff)) == 0ull;
+    if (ok0 && col[i0] == 0x7fffffff) col[i0] = unseeded ? 0 : -1;  // each lane its own points
+    if (ok1 && col[i1] == 0x7fffffff) col[i1] = unseeded ? 0 : -1;
     for (int round = 0; round < NF; ++round) {
         if (ok0) snap[i0] = col[i0];
         if (ok1) snap[i1] = col[i1];
