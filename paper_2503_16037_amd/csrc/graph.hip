@@ -62,6 +62,11 @@ namespace {
 // small inputs).  64x64x32 plume, n = 1,507,328: 2^26 cells 0.60 ms of passes
 // (2^25 0.40, 10 n 0.20 but then only 9 % more candidates than asked for, 16 n 0.29).
 constexpr unsigned long long kMostBudget = 1ull << 29;
+// candidates of all pairs that are listed, beyond four times as many as were expected, before the
+// selection over all pairs takes over (a list costs a second pass, its sort and 32 bytes a pair, the
+// selection thirteen passes: 16.2 M couplings equal, 13 ms by a list, 17.4 M 31 ms and 72 M 44 ms by
+// selection; 2.2 G 0.5 s, which no list holds)
+constexpr unsigned long long kMostListed = 1ull << 25;
 // boxes of one voxel per node already beyond this are refused (with the default budgets)
 constexpr unsigned long long kMostCells = 1ull << 26;
 
@@ -119,6 +124,12 @@ struct Dev {
         GTRY(pool_alloc(ctx, std::max<size_t>(n, 1) * sizeof(T), &q));
         blocks.push_back(q);
         *p = static_cast<T *>(q);
+        return SG_OK;
+    }
+    // the blocks taken since there were `level` of them go back before the others, once the stream drained
+    sg_status drop(size_t level) {
+        GHIP(hipStreamSynchronize(st));
+        for (; blocks.size() > level; blocks.pop_back()) pool_free(ctx, blocks.back());
         return SG_OK;
     }
 };
@@ -476,6 +487,20 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
     }
 }
 
+// Radix selection of the n largest of 64-bit keys (couplings are positive, so their bit patterns
+// order like them).  sel: [0] the chosen top bits of the n-th largest key, [1] how many keys with
+// those top bits still belong to the n.
+constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6;  // 5 x 11 bits, then 9
+
+__device__ __forceinline__ int sel_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
+
+// key k into a pass's bins, if its top bits are the chosen ones
+__device__ __forceinline__ void sel_count(unsigned *bins, unsigned long long k, int pass, unsigned long long chosen) {
+    const int up = pass ? sel_shift(pass - 1) : 0;
+    if (pass && k >> up != chosen >> up) return;
+    atomicAdd(&bins[(unsigned)(k >> sel_shift(pass)) & (pass < 5 ? kSelBins - 1u : 511u)], 1u);
+}
+
 // Every pair i < j (i a volume node) against threshold t: the candidates (k > 0 and k >= t,
 // strict: k > t) appended to keys / codes in no fixed order, counted in *count also beyond
 // cap.  A workgroup takes 512 nodes i, two per thread (each j read from LDS serves both), and
@@ -486,16 +511,27 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
 // that overflows goes out by one atomic per wavefront and node j).
 // 119,958 nodes (7.2e9 pairs): 3.3 ms, 24 T lane-operations/s of the 30 that FP64 issues; its
 // build 1440 -> 5.6 ms (every pair written out, sorted and merged into a best-n list before).
+// Where far more pairs reach the threshold than are asked for (equal couplings), none is written:
+// kAllKeys and kAllCodes count them for a pass of the radix selection (select_hist), by the coupling
+// and then, among those equal to the n-th (kn), by the complement of the code, so that the n best are
+// known in the order of their ids; kAllTake lists just these.
 constexpr int kAllTile = 256, kAllSpan = 4096, kAllHits = 512;
+enum AllMode { kAllList, kAllKeys, kAllCodes, kAllTake };
+template <AllMode kMode>
 __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restrict__ q, const double *__restrict__ mu,
                                                    double t, int strict, unsigned long long cap,
                                                    unsigned long long *__restrict__ count, double *__restrict__ keys,
-                                                   unsigned long long *__restrict__ codes) {
+                                                   unsigned long long *__restrict__ codes, int pass,
+                                                   const unsigned long long *__restrict__ sel, unsigned long long kn) {
 #pragma clang fp contract(off)
+    constexpr bool kCount = kMode == kAllKeys || kMode == kAllCodes;
     __shared__ double2 jxy[kAllTile], jzm[kAllTile];
-    __shared__ double hkey[kAllHits];
-    __shared__ unsigned long long hcode[kAllHits], hbase;
-    __shared__ unsigned nhit;
+    __shared__ double hkey[kCount ? 1 : kAllHits];
+    __shared__ unsigned long long hcode[kCount ? 1 : kAllHits], hbase;
+    __shared__ unsigned nhit, bins[kCount ? kSelBins : 1];
+    if (kCount)
+        for (int b = threadIdx.x; b < kSelBins; b += 256) bins[b] = 0u;  // published by the loop's barriers
+    const unsigned long long chosen = pass || kMode == kAllTake ? sel[0] : 0ull;
     const int lane = threadIdx.x & 63;
     const long long i0 = (long long)blockIdx.x * 512;
     double xi[2], yi[2], zi[2], mi[2];
@@ -512,6 +548,13 @@ __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restri
         const double k = mm / d2;
         if (!(j > i && k > 0.0 && (strict ? k > t : k >= t))) return;
         const unsigned long long code = (unsigned long long)i << 32 | (unsigned long long)j;
+        const unsigned long long bits = (unsigned long long)__double_as_longlong(k);
+        if (kCount) {
+            if (kMode == kAllCodes && bits != kn) return;
+            sel_count(bins, kMode == kAllKeys ? bits : ~code, pass, chosen);
+            return;
+        }
+        if (kMode == kAllTake && (bits < kn || (bits == kn && ~code < chosen))) return;
         const unsigned at = atomicAdd(&nhit, 1u);
         if (at < (unsigned)kAllHits) {
             hkey[at] = k;
@@ -553,6 +596,11 @@ __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restri
         }
     }
     __syncthreads();
+    if (kCount) {
+        for (int b = threadIdx.x; b < kSelBins; b += 256)
+            if (bins[b]) atomicAdd(&count[b], (unsigned long long)bins[b]);
+        return;
+    }
     const unsigned n = min(nhit, (unsigned)kAllHits);
     if (threadIdx.x == 0) hbase = n ? atomicAdd(count, (unsigned long long)n) : 0ull;
     __syncthreads();
@@ -582,42 +630,32 @@ __global__ void k_graph_sample(Geo g, const double *__restrict__ q, const double
 }
 
 // ---- selection of the n largest keys ---------------------------------------------------
-// Keys are positive, so their bit patterns order like them.  sel: [0] the chosen top bits of
-// the n-th largest key, [1] how many keys with those top bits still belong to the n.
-constexpr int kSelBits = 11, kSelBins = 1 << kSelBits, kSelPasses = 6;  // 5 x 11 bits, then 9
-
-__device__ __forceinline__ int sel_shift(int pass) { return pass < 5 ? 64 - kSelBits * (pass + 1) : 0; }
 
 __global__ __launch_bounds__(256) void k_sel_hist(const unsigned long long *__restrict__ keys, long long n, int pass,
                                                   const unsigned long long *__restrict__ sel,
-                                                  unsigned *__restrict__ hist) {
+                                                  unsigned long long *__restrict__ hist) {
     __shared__ unsigned h[kSelBins];
     for (int b = threadIdx.x; b < kSelBins; b += 256) h[b] = 0u;
     __syncthreads();
-    const int sh = sel_shift(pass), up = pass ? sel_shift(pass - 1) : 0;
-    const unsigned long long top = pass ? sel[0] >> up : 0ull;
-    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) {
-        const unsigned long long k = keys[i];
-        if (pass && k >> up != top) continue;
-        atomicAdd(&h[(unsigned)(k >> sh) & (pass < 5 ? kSelBins - 1u : 511u)], 1u);
-    }
+    const unsigned long long chosen = pass ? sel[0] : 0ull;
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < n; i += gridDim.x * 256ll) sel_count(h, keys[i], pass, chosen);
     __syncthreads();
     for (int b = threadIdx.x; b < kSelBins; b += 256)
-        if (h[b]) atomicAdd(&hist[b], h[b]);
+        if (h[b]) atomicAdd(&hist[b], (unsigned long long)h[b]);
 }
 
 // one workgroup: the bin that holds the sel[1]-th largest (the n-th in the first pass), and the
 // histogram cleared
 __global__ __launch_bounds__(256) void k_sel_pick(int pass, unsigned long long n, unsigned long long *__restrict__ sel,
-                                                  unsigned *__restrict__ hist) {
+                                                  unsigned long long *__restrict__ hist) {
     __shared__ unsigned long long above[256];
     constexpr int kPer = kSelBins / 256;
-    unsigned c[kPer];
+    unsigned long long c[kPer];
     unsigned long long sum = 0ull;
 #pragma unroll
     for (int j = 0; j < kPer; ++j) {
         c[j] = hist[threadIdx.x * kPer + j];
-        hist[threadIdx.x * kPer + j] = 0u;
+        hist[threadIdx.x * kPer + j] = 0ull;
         sum += c[j];
     }
     above[threadIdx.x] = sum;
@@ -919,7 +957,7 @@ struct Builder {
     long long *P = nullptr;
     double *q = nullptr, *mu = nullptr;
     unsigned long long *scal = nullptr;  // [0 .. kCellTests) cell totals, counters; then the selection's state
-    unsigned *hist = nullptr;            // the selection's histogram (zero between passes)
+    unsigned long long *hist = nullptr;  // the selection's histogram (zero between passes)
     // build statistics: candidate passes, summed kernel times (HIP event pairs)
     int passes = 0;
     unsigned long long evals = 0;  // pairs evaluated by the candidate passes
@@ -1016,33 +1054,69 @@ struct Builder {
         return SG_OK;
     }
 
-    // candidates among all pairs at threshold t, ordered by (i, j); room for `expect` of them
-    // (more: a second pass)
-    sg_status all_pairs(double t, int strict, unsigned long long expect, double *&keys, unsigned long long *&codes,
-                        unsigned long long &have) {
+    // candidates among all pairs at threshold t, ordered by (i, j); room for `expect` of them (more:
+    // a second pass, or, when the `best` strongest of them are asked for and the list would be
+    // long, these alone).  reached: the pairs at the threshold.
+    sg_status all_pairs(double t, int strict, unsigned long long expect, unsigned long long best, double *&keys,
+                        unsigned long long *&codes, unsigned long long &have, unsigned long long &reached) {
         unsigned long long cap = expect;
-        const dim3 grid((unsigned)((g.nvol + 511) / 512),
-                        (unsigned)std::min<long long>((g.N + kAllSpan - 1) / kAllSpan, 65535));
         while (true) {
             if (cap >= (1ull << 31)) return gfail(SG_E_NOMEM, "more than 2^31 coupling candidates");
+            const size_t level = dev.blocks.size();
             GTRY(dev.get(&keys, cap));
             GTRY(dev.get(&codes, cap));
-            GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
-            ++passes;
-            const int e0 = mark(ev_pairs);
-            hipLaunchKernelGGL(k_graph_all, grid, dim3(256), 0, st, g, q, mu, t, strict, cap, scal, keys, codes);
-            end(ev_pairs, e0);
-            GHIP(hipGetLastError());
+            GTRY(all_pass<kAllList>(t, strict, cap, scal, keys, codes, 0, 0ull));
             GHIP(hipMemcpyAsync(&have, scal, sizeof(have), hipMemcpyDeviceToHost, st));
             GHIP(hipStreamSynchronize(st));
-            evals += (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
+            reached = have;
             if (have <= cap) break;
+            GTRY(dev.drop(level));
+            if (best && have > std::max(4 * cap, kMostListed)) {
+                GTRY(best_pairs(t, strict, best, keys, codes));
+                have = best;
+                break;
+            }
             cap = have;
         }
         const int e1 = mark(ev_sort);
         GTRY(sort_codes(codes, reinterpret_cast<unsigned long long *>(keys), (long long)have, true));
         end(ev_sort, e1);
         return SG_OK;
+    }
+
+    // one pass over all pairs (k_graph_all); out: the counter (cleared first) or the histogram
+    template <AllMode kMode>
+    sg_status all_pass(double t, int strict, unsigned long long cap, unsigned long long *out, double *keys,
+                       unsigned long long *codes, int pass, unsigned long long kn) {
+        const dim3 grid((unsigned)((g.nvol + 511) / 512),
+                        (unsigned)std::min<long long>((g.N + kAllSpan - 1) / kAllSpan, 65535));
+        if (out == scal) GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
+        ++passes;
+        const int e0 = mark(ev_pairs);
+        hipLaunchKernelGGL(k_graph_all<kMode>, grid, dim3(256), 0, st, g, q, mu, t, strict, cap, out, keys, codes, pass,
+                           scal + kCellTests, kn);
+        end(ev_pairs, e0);
+        GHIP(hipGetLastError());
+        evals += (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
+        return SG_OK;
+    }
+
+    // the `best` strongest of more pairs than that at threshold t, by selection over all pairs; in no order
+    sg_status best_pairs(double t, int strict, unsigned long long best, double *&keys, unsigned long long *&codes) {
+        unsigned long long sel[2];
+        for (int p = 0; p < kSelPasses; ++p) {
+            GTRY(all_pass<kAllKeys>(t, strict, 0, hist, nullptr, nullptr, p, 0ull));
+            hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, st, p, best, scal + kCellTests, hist);
+        }
+        GHIP(hipMemcpyAsync(sel, scal + kCellTests, sizeof(sel), hipMemcpyDeviceToHost, st));
+        GHIP(hipStreamSynchronize(st));
+        for (int p = 0; p < kSelPasses; ++p) {
+            GTRY(all_pass<kAllCodes>(t, strict, 0, hist, nullptr, nullptr, p, sel[0]));
+            hipLaunchKernelGGL(k_sel_pick, dim3(1), dim3(256), 0, st, p, sel[1], scal + kCellTests, hist);
+        }
+        GTRY(dev.get(&keys, best));
+        GTRY(dev.get(&codes, best));
+        return all_pass<kAllTake>(t, strict, best, scal, keys, codes, 0, sel[0]);
     }
 
     // a threshold that about `want` pairs reach, from a sample (0: every pair)
@@ -1053,6 +1127,7 @@ struct Builder {
         const long long M = want / pairs * (double)(1 << 21) < 1024.0 ? 1ll << 24 : 1ll << 21;
         const double m = std::max(64.0, std::ceil(want / pairs * (double)M));
         if (m >= (double)M) return SG_OK;
+        const size_t level = dev.blocks.size();
         double *keys = nullptr;
         GTRY(dev.get(&keys, M));
         hipLaunchKernelGGL(k_graph_sample, dim3(blocks_for(M, 256)), dim3(256), 0, st, g, q, mu, M, keys);
@@ -1063,7 +1138,7 @@ struct Builder {
         GHIP(hipStreamSynchronize(st));
         std::memcpy(&t, &bits, sizeof(t));
         if (std::isinf(t)) t = std::numeric_limits<double>::max();  // coincident nodes
-        return SG_OK;
+        return dev.drop(level);
     }
 
     // the n-th largest of have keys (n <= have) and the number of keys equal to it among the n
@@ -1209,7 +1284,7 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     GTRY(B.dev.get(&B.mu, N));
     GTRY(B.dev.get(&B.scal, kCellTests + 2));
     GTRY(B.dev.get(&B.hist, kSelBins));
-    GHIP(hipMemsetAsync(B.hist, 0, sizeof(unsigned) * kSelBins, st));
+    GHIP(hipMemsetAsync(B.hist, 0, sizeof(unsigned long long) * kSelBins, st));
     GHIP(hipMemsetAsync(mom, 0, sizeof(Moments), st));
     GHIP(hipMemsetAsync(&mom->bad_node, 0xff, sizeof(mom->bad_node), st));
     GHIP(hipMemcpyAsync(pos, general ? d->node_pos_fx : d->vol_pos_fx, sizeof(int) * 3 * nvol, hipMemcpyHostToDevice,
@@ -1249,7 +1324,7 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     const unsigned long long n_want = (unsigned long long)d->n_pairs;
     if (d->n_pairs == 0) {
         t_used = d->c_min * d->c_min;
-        if (general) GTRY(B.all_pairs(t_used, 1, 1ull << 20, keys, codes, have));
+        if (general) GTRY(B.all_pairs(t_used, 1, 1ull << 20, 0ull, keys, codes, have, ranked));
         else GTRY(B.pairs(t_used, 1, 0ull, keys, codes, have));
         n_sel = ranked = have;
     } else {
@@ -1287,12 +1362,15 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
                     }
                     t_fit = cell_threshold(h);
                 }
+                const size_t level = B.dev.blocks.size();
                 GTRY(B.pairs(t_fit, 0, t_fit > 0.0 ? n_want : 0ull, keys, codes, have));
                 enough = have >= n_want || t_fit == 0.0;
                 if (enough) break;
+                GTRY(B.dev.drop(level));
             }
         }
         t_used = t_fit;
+        ranked = have;
         if (!enough) {
             // every pair against a threshold from a sample, lower ones while too few reach it
             streamed = 1;
@@ -1305,11 +1383,12 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
                 const unsigned long long all =
                     (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
                 const double room = std::min({1.25 * want + 65536.0, (double)all, 2147483647.0});
-                GTRY(B.all_pairs(t, 0, (unsigned long long)room, keys, codes, have));
+                const size_t level = B.dev.blocks.size();
+                GTRY(B.all_pairs(t, 0, (unsigned long long)room, n_want, keys, codes, have, ranked));
                 if (have >= n_want || !(t > 0.0)) break;
+                GTRY(B.dev.drop(level));
             }
         }
-        ranked = have;
         n_sel = std::min(have, n_want);
     }
 
