@@ -15,9 +15,9 @@ namespace {
 // as broadcasts (measured: reading the columns through scalar loads instead exposes
 // their latency, 1.4x slower at 64 wavelengths); the in-edge list and optical depths
 // are loaded once, coalesced, and broadcast with readlane; eight input gathers are in
-// flight at a time (the FP64 residual, at four wavefronts per SIMD, asks for the next eight before it uses
-// these: 2.69 -> 2.04 ms at 96x96x32, 64 wavelengths; the FP32 sweep at seven loses 5 % with the
-// registers this takes); the node's rows are accumulated in registers, the row count
+// flight at a time (the FP64 residual of an FP32 iterate, at four wavefronts per SIMD, asks for the next
+// eight before it uses these: 2.69 -> 2.04 ms at 96x96x32, 64 wavelengths; the FP32 sweep at seven loses
+// 5 % with the registers this takes, and an FP64 iterate's do not fit); the node's rows are accumulated in registers, the row count
 // rounded up to a multiple of 8 (DB) so the column reads are unguarded (the LDS slice
 // is padded past the block by 64 floats).
 // kResidual: FP64 residual r = S - x + K x of an FP64 iterate instead of a sweep.
@@ -94,7 +94,7 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
     const long long em = off + min(lane, d - 1);
     const int rv = rev[em];
     const float ts = tau_s[em], ta = tau_a[em];
-    constexpr bool kAhead = sizeof(AccT) == 8;  // the next eight gathers before these are used
+    constexpr bool kAhead = sizeof(AccT) == 8 && sizeof(XT) == 4;  // the next eight gathers before these are used
     auto inputs = [&](int m0, XT(&xv)[kU]) {
 #pragma unroll
         for (int j = 0; j < kU; ++j) {
@@ -180,13 +180,16 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
 
 // Occupancy hints: at the requested waves per SIMD the compiler fits each instantiation
 // without spilling (the FP32 sweep: 72 VGPRs at D = 40 instead of 98; the FP64 residual up
-// to D = 40: 122 instead of 144, four waves per SIMD instead of three, where five would
-// spill its accumulators; the larger FP64 residuals keep their natural allocation, since
-// their accumulators alone fill four waves' registers).  The marking sweeps hold the heads and
-// moved rows too and fit six.
+// to D = 40: 124 of an FP32 iterate instead of 144, four waves per SIMD instead of three, where five
+// would spill its accumulators, and 122 of an FP64 iterate, which leaves no room for the next gathers;
+// the larger FP64 residuals keep their natural allocation, since their accumulators alone fill four
+// waves' registers).  The marking sweeps hold the heads and moved rows too and fit six; the largest
+// degrees fit four (64, and 56 over the front).
 template <int D, bool kResidual, int kMode>
 constexpr int wide_waves_per_eu() {
-    return kResidual ? (D <= 40 ? 4 : 1) : (D <= 40 ? (kMode ? 6 : 7) : 5);
+    if (kResidual) return D <= 40 ? 4 : 1;
+    if (D <= 40) return kMode ? 6 : 7;
+    return D <= 48 || (D <= 56 && kMode <= kFrontFirst) ? 5 : 4;
 }
 
 // kMode 0: every node; kFrontFirst: every node, marking the nodes of the next sweep;
@@ -280,6 +283,12 @@ struct PackTile {
     static constexpr int kCols = 4;                               // columns staged at a time
     static constexpr int kSlice = kCols * kStride + 4;           // words of a slot
 };
+// this lane's own row of the node's in-edges, read again after the columns (the empty statement keeps the
+// compiler from holding it, two registers, through them)
+__device__ __forceinline__ long long edges_from(const long long *__restrict__ adj_ptr, int l) {
+    asm volatile("" : "+v"(l));
+    return adj_ptr[l];
+}
 template <int W, int D>
 constexpr int pack_slice() {  // the largest slice of the degree buckets up to D
     if constexpr (D <= 8) return PackTile<W, 8>::kSlice;
@@ -287,25 +296,27 @@ constexpr int pack_slice() {  // the largest slice of the degree buckets up to D
 }
 
 template <int W, int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
-__device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, int nl, int monitor, long long off,
+__device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, int nl, int monitor, 
                                             int d, long long base, int dw, const int *__restrict__ srv,
                                             const float *__restrict__ sts, const float *__restrict__ sta,
-                                            float *__restrict__ qs, const float *__restrict__ q,
+                                            float *__restrict__ qs, const long long *__restrict__ adj_ptr, const float *__restrict__ q,
                                             const float *__restrict__ qsun, const float *__restrict__ brho,
                                             const float *__restrict__ bsrc, const float *__restrict__ rhs,
                                             const XT *__restrict__ x, YT *__restrict__ y, unsigned long long &rows) {
     using P = PackTile<W, DB>;
+    // one staged column less where four do not fit the registers
+    constexpr int kCols = P::kCols - (W == 8 && (sizeof(XT) == 8 || (kMark && DB == 40)));
     AccT acc[DB];
 #pragma unroll
     for (int n = 0; n < DB; ++n) acc[n] = (AccT)0;
     // columns m0.. of the block, rows lam, lam + W, .. in this lane, and their inputs.  Slots with
     // fewer in-edges repeat their last column with a zero input: adding Q * 0 leaves every
     // valid row's sum unchanged
-    float qv[P::kCols * P::kLoads];
-    XT xv[P::kCols];
+    float qv[kCols * P::kLoads];
+    XT xv[kCols];
     auto load = [&](int m0) {
 #pragma unroll
-        for (int j = 0; j < P::kCols; ++j) {
+        for (int j = 0; j < kCols; ++j) {
             const int mc = min(m0 + j, d - 1);
             const float *qm = q + base + mc * d;
 #pragma unroll
@@ -314,19 +325,19 @@ __device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, in
         }
     };
     load(0);
-    for (int m0 = 0; m0 < dw; m0 += P::kCols) {
-        AccT xm[P::kCols];
+    for (int m0 = 0; m0 < dw; m0 += kCols) {
+        AccT xm[kCols];
 #pragma unroll
-        for (int j = 0; j < P::kCols; ++j) {
+        for (int j = 0; j < kCols; ++j) {
             const int mc = min(m0 + j, d - 1);
 #pragma unroll
             for (int k = 0; k < P::kLoads; ++k) qs[j * P::kStride + lam + W * k] = qv[j * P::kLoads + k];
             xm[j] = column_input((AccT)edge_T(sts[mc], sta[mc], s), (AccT)xv[j]);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (m0 + P::kCols < dw) load(m0 + P::kCols);
+        if (m0 + kCols < dw) load(m0 + kCols);
 #pragma unroll
-        for (int j = 0; j < P::kCols; ++j) {
+        for (int j = 0; j < kCols; ++j) {
             if (m0 + j >= dw) break;
             const f4u *qm = reinterpret_cast<const f4u *>(qs + j * P::kStride);
 #pragma unroll
@@ -342,6 +353,7 @@ __device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, in
     }
     RowMeasures measures;
     if (lv) {
+        const long long off = edges_from(adj_ptr, l);
         const float rl = brho[(long long)l * nl + lam];
         const float sl = bsrc[(long long)l * nl + lam];
 #pragma unroll
@@ -368,8 +380,10 @@ __device__ __forceinline__ float2 pack_node(int l, int lam, bool lv, float s, in
 }
 
 // Four waves per SIMD (the compiler would hoist the previous values of all rows and leave three);
-// the FP64 residual's accumulators fit three up to D = 40.  The rows beyond that keep the natural
-// allocation.
+// the FP64 residual's accumulators fit three from D = 32 to 40.  The rows beyond that keep the natural
+// allocation.  No instantiation spills: the node's first edge is read again after the columns
+// (edges_from), a slot's arrays lie behind one LDS address, and the sweep over the front recomputes its node.
+// (Before, 2 to 10 spilled values; a wave less instead made 12 wavelengths on 71x53x29 7 % slower.)
 template <int D, bool kResidual>
 constexpr int pack_waves_per_eu() {
     return D > 40 ? 1 : kResidual && D > 24 ? 3 : 4;
@@ -387,15 +401,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
     const int *__restrict__ adj_idx, const unsigned char *__restrict__ now, unsigned char *__restrict__ next,
     unsigned long long *__restrict__ spent, int skew) {
     constexpr int P = 64 / W;  // node slots per wavefront
-    __shared__ int srv_all[4][P][D];
-    __shared__ float sts_all[4][P][D], sta_all[4][P][D];
-    __shared__ __align__(16) float qs_all[4][P][pack_slice<W, D>()];
+    struct __align__(16) Slot {  // of one LDS address
+        float qs[pack_slice<W, D>()];
+        int rv[D];
+        float ts[D], ta[D];
+    };
+    __shared__ Slot slots[4][P];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int k = lane / W, lam = lane - k * W;
     const bool lam_ok = lam < nl;
     const float s = lam_ok ? abs_scale[lam] : 0.f;
-    int *srv = srv_all[w][k];
-    float *sts = sts_all[w][k], *sta = sta_all[w][k], *qs = qs_all[w][k];
+    Slot &slot = slots[w][k];
+    int *srv = slot.rv;
+    float *sts = slot.ts, *sta = slot.ta, *qs = slot.qs;
     auto slot_nodes = [&](int l) {  // node l per slot (l >= N: none)
         const bool node_ok = l < N;
         long long off = 0, base = 0;
@@ -422,8 +440,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
         if (dw > 0) {
             const int bucket = (dw + 7) >> 3;
 #define SG_PACK(DB)                                                                                            \
-    part = pack_node<W, DB, XT, YT, AccT, kResidual, kMode != 0>(l, lam, lv, s, nl, monitor, off, max(d, 1), base, \
-                                                                 dw, srv, sts, sta, qs, q, qsun, brho, bsrc, rhs, x, \
+    part = pack_node<W, DB, XT, YT, AccT, kResidual, kMode != 0>(l, lam, lv, s, nl, monitor, max(d, 1), base, dw,  \
+                                                                 srv, sts, sta, qs, adj_ptr, q, qsun, brho, bsrc, rhs, x, \
                                                                  y, rows)
             if (bucket <= 1) { SG_PACK(8); }
             else if (bucket == 2) { if constexpr (D >= 16) SG_PACK(16); }
@@ -442,8 +460,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
                 lo |= __shfl_xor(lo, o, 64);
                 hi |= __shfl_xor(hi, o, 64);
             }
+            const long long from = node_ok ? edges_from(adj_ptr, l) : 0;
             for (int m = lam; m < d; m += W)
-                if ((m < 32 ? lo >> m : hi >> (m - 32)) & 1u) next[adj_idx[off + m]] = 1;
+                if ((m < 32 ? lo >> m : hi >> (m - 32)) & 1u) next[adj_idx[from + m]] = 1;
             if ((lo | hi) && lam == 0) next[l] = 1;
         }
         if (monitor && node_ok && lam_ok) meas[(long long)l * nl + lam] = part;
@@ -462,8 +481,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
                     m = i < k ? m & (m - 1) : m;
                     todo &= todo - 1;
                 }
-                const int from = __shfl(mine, m ? __builtin_ctzll(m) : 0, 64);
-                slot_nodes(m ? from : N);
+                slot_nodes(m ? front_node(wv, j0 + __builtin_ctzll(m), V, skew) : N);
             }
         }
     } else {

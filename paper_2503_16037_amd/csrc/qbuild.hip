@@ -231,6 +231,12 @@ __host__ __device__ constexpr size_t qbuild_lds(int dm) {
     return 8 * (size_t)(3 * dm + kQMaxGroup * dm + 128) + 48 * (size_t)(dm + 1) + 2 * (size_t)kQueue;
 }
 
+// this lane's operand of lattice tile t
+__device__ __forceinline__ Operand lattice_tile(const uint4 *__restrict__ lat_halves, int t, int lane) {
+    const uint4 v = lat_halves[64 * t + lane];
+    return {{v.x, v.y, v.z, v.w}};
+}
+
 // One group of ng directions from a0: their owners' weights into the bins, and the slots
 // whose owner is not certified into the queue (point + 128 x direction of the group; returns
 // their number).  Full tiles of 32 lattice points are taken two directions at a time, the out-edges
@@ -240,7 +246,7 @@ __host__ __device__ constexpr size_t qbuild_lds(int dm) {
 template <int RT, int R>
 __device__ __forceinline__ int group_owners(int a0, int ng, int n_in, int dm, int NF, int nt, int rest, bool screen,
                                             int lane, const float (&site)[2][3], const unsigned (&past)[2],
-                                            const Operand (&fixed)[2], const Operand (&pts)[4], const float4 *rows,
+                                            const Operand (&pts)[4], const float4 *rows,
                                             const unsigned long long *wq, const double *__restrict__ lat,
                                             unsigned long long *bins, unsigned short *queue) {
     using T = Rows<RT, R>;
@@ -311,6 +317,19 @@ __device__ __forceinline__ int group_owners(int a0, int ng, int n_in, int dm, in
         swap_halves((p[1] & 0xffffu) | (p[0] << 16), p[2], q[0].w[1], q[1].w[1]);
         swap_halves((p[0] >> 16) | (p[1] << 16), one, q[0].w[2], q[1].w[2]);
         swap_halves((p[1] >> 16) | (p[2] << 16), 0u, q[0].w[3], q[1].w[3]);
+        // the out-edges as they are; the second row tile's halves do not fit the registers and are made
+        // group by group (the empty statement keeps the compiler from making them once and spilling them)
+        Operand fixed[2];
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            float sx = site[t][0];
+            if (t == 1) asm volatile("" : "+v"(sx));
+            split_halves(sx, site[t][1], site[t][2], p);
+            fixed[t].w[0] = half ? p[1] : p[0];
+            fixed[t].w[1] = half ? p[2] : p[1];
+            fixed[t].w[2] = half ? past[t] : p[2];
+            fixed[t].w[3] = half ? 0u : p[0];
+        }
         float b0, s0, b1, s1;
         T::column(fixed, q[0], b0, s0);
         if (n > 32) T::column(fixed, q[1], b1, s1);
@@ -384,11 +403,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         for (int k = 0; k < 3; ++k)
             rows[3 * a + k] = make_float4((float)R[3 * k], (float)R[3 * k + 1], (float)R[3 * k + 2], 0.0f);
     }
-    // this lane's out-edge of each row tile, its halves as they are, and the lattice
+    // this lane's out-edge of each row tile, and the lattice
     const unsigned below = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(-2.0f * kHalfScale, 0.0f));
     float site[2][3];
     unsigned past[2];
-    Operand fixed[2], pts[4];
+    Operand pts[4];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
         const int r = lane & 31, m = 32 * t + 2 * (4 * (r >> 3) + (r & 3)) + (r >> 2 & 1);
@@ -397,13 +416,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         site[t][1] = in ? (float)sy[m] * kHalfScale : 0.0f;
         site[t][2] = in ? (float)sz[m] * kHalfScale : 0.0f;
         past[t] = in ? 0u : below;
-        unsigned p[3];
-        split_halves(site[t][0], site[t][1], site[t][2], p);
-        const bool low = lane < 32;
-        fixed[t].w[0] = low ? p[0] : p[1];
-        fixed[t].w[1] = low ? p[1] : p[2];
-        fixed[t].w[2] = low ? p[2] : past[t];
-        fixed[t].w[3] = low ? p[0] : 0u;
     }
     // full tiles of lattice points; up to eight points past them are columns of their own, more
     // make another tile
@@ -413,13 +425,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         rest = 0;
     }
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const uint4 v = lat_halves[64 * t + lane];
-        pts[t].w[0] = v.x;
-        pts[t].w[1] = v.y;
-        pts[t].w[2] = v.z;
-        pts[t].w[3] = v.w;
-    }
+    for (int t = 0; t < 4; ++t) pts[t] = lattice_tile(lat_halves, t, lane);
 
     const float inv_d = 1.0f / (float)d;
     const Real rl = rho ? rho[l] : (Real)0;
@@ -431,7 +437,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         __syncthreads();
         int nq;
 #define SG_GROUP(RT, R)                                                                                            \
-    nq = group_owners<RT, R>(a0, ng, n_in, dm, NF, nt, rest, screened, lane, site, past, fixed, pts, rows, wq, lat, \
+    nq = group_owners<RT, R>(a0, ng, n_in, dm, NF, nt, rest, screened, lane, site, past, pts, rows, wq, lat, \
                              bins, queue)
         if (d <= 8) SG_GROUP(1, 4);
         else if (d <= 16) SG_GROUP(1, 8);
@@ -456,11 +462,16 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             rotate_point(R, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
             double best = -__builtin_inf();
             int o = 0;
-            for (int k = 0; k < d; ++k) {
-                const double dot = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
-                const double v = without >> k & 1ull ? -__builtin_inf() : dot;
+            auto take = [&](int k) {
+                const double v = fma(q2, sz[k], fma(q1, sy[k], q0 * sx[k]));
                 o = v > best ? k : o;
                 best = fmax(best, v);
+            };
+            if (without == 0ull) {
+                for (int k = 0; k < d; ++k) take(k);
+            } else {
+                for (int k = 0; k < d; ++k)
+                    if (!(without >> k & 1ull)) take(k);
             }
             if (SG_IN(dl * dm + o, kQMaxGroup * dm, 0x203)) atomicAdd(&bins[dl * dm + o], wq[i]);
         }
@@ -563,7 +574,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     __shared__ double Rg[kBigGroup * 9];
     __shared__ unsigned long long wq[128];
     __shared__ unsigned short owner[kBigCols], queue[kBigCols];
-    __shared__ int queued;
+    // (flags in LDS, not __syncthreads_or: that keeps all three thread indices in a register through the
+    // passes, the one that did not fit)
+    __shared__ int queued, lost;  // columns without a certificate; whether an out-edge has no direction
     const long long wg = blockIdx.x;
     int lo = 0, hi = nbig;  // the node b with bigdir[b] <= wg < bigdir[b + 1]
     while (hi - lo > 1) {
@@ -603,7 +616,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         }
         wq[tid] = (unsigned long long)llrint(w * kFix);
     }
-    if (tid == 0) queued = 0;
+    if (tid == 0) queued = lost = 0;
     // rotations of this group's incoming directions
     if (tid >= 192 && tid - 192 < ng) {
         const int a = a0 + tid - 192;
@@ -635,7 +648,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     // this wavefront's pair j holds the columns 64 (wave + 4 j) + lane
     const int pairs = (np + 63) / 64;
     const int mine = pairs > wave ? (pairs - wave + 3) / 4 : 0;
-    bool none = false;  // an out-edge of no direction
     float run_best[kBigPairs], run_second[kBigPairs];
     int run_own[kBigPairs];
     if (screen) {
@@ -667,7 +679,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
                 if (r < nm) {
                     long long Dx, Dy, Dz;
                     edge_offset(m0 + r, Dx, Dy, Dz);
-                    none = none || (Dx | Dy | Dz) == 0;
+                    if ((Dx | Dy | Dz) == 0) lost = 1;
                     const float x = (float)Dx, y = (float)Dy, z = (float)Dz;  // whole: below 1 only if all zero
                     const float inv = __builtin_amdgcn_rsqf(fmaxf(fmaf(z, z, fmaf(y, y, x * x)), 1.0f)) * kHalfScale;
                     site.x = x * inv;
@@ -725,7 +737,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
             }
         }
     }
-    const bool sure = screen && !__syncthreads_or(none);
+    __syncthreads();
+    const bool sure = screen && !lost;
 #pragma unroll
     for (int j = 0; j < kBigPairs; ++j) {
         const int p = 64 * (wave + 4 * j) + lane;
@@ -756,13 +769,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
         int own = 0;
         for (int m0 = 0; m0 < d; m0 += kScanEdges) {
             const int nm = min(kScanEdges, d - m0);
-            bool has = true;
-            if (tid < nm) {
-                has = edge_dir(m0 + tid, ex[tid], ey[tid], ez[tid]);
-                if (!has) ex[tid] = kNoDirection;
+            if (tid < nm && !edge_dir(m0 + tid, ex[tid], ey[tid], ez[tid])) {
+                ex[tid] = kNoDirection;
+                lost = 1;
             }
-            const bool some = __syncthreads_or(!has);
-            if (c < nq && !some) {
+            __syncthreads();
+            if (c < nq && !lost) {
 #pragma unroll 4
                 for (int k = part; k < nm; k += parts) {
                     const double v = fma(q2, ez[k], fma(q1, ey[k], q0 * ex[k]));
@@ -887,6 +899,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     __shared__ double sx[64], sy[64], sz[64];
     __shared__ unsigned long long wq[128], bins[2][64], bkey[2][128];
     __shared__ int col[2][128];
+    __shared__ double rot[2][9];
     constexpr int kNone = 0x7fffffff;
 
     const int l = blockIdx.x;
@@ -928,17 +941,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
     const int n_in = surf ? 1 : d + 1;
     const int nd = d <= 32 ? 2 : 1;  // directions at a time
     const int dl = nd == 2 ? lane >> 5 : 0, m = nd == 2 ? lane & 31 : lane;
-    const double tx = m < d ? sx[m] : 0.0, ty = m < d ? sy[m] : 0.0, tz = m < d ? sz[m] : 0.0;
+    const int mc = min(m, d - 1);  // lanes past d repeat the last out-edge, not counted
     const int nt = (NF + 31) >> 5, last = NF - 32 * (nt - 1);  // row tiles of lattice points
-    Operand pts[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const uint4 v = lat_halves[64 * t + lane];
-        pts[t].w[0] = v.x;
-        pts[t].w[1] = v.y;
-        pts[t].w[2] = v.z;
-        pts[t].w[3] = v.w;
-    }
     unsigned long long near[2][2];  // the hull neighbours of points lane and lane + 64, as masks
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -954,26 +958,40 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
         }
     }
     for (int a0 = 0; a0 < n_in; a0 += nd) {
-        // the rotation of this lane's direction
-        double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+        // the rotation of this lane's direction, in LDS
         const int a = min(a0 + dl, n_in - 1);  // past the last direction: a repeat, not counted
-        if (!surf) {
-            if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
-            else pole_rotation(sun_x, sun_y, sun_z, R);
+        {
+            double R[9] = {1.0, 0.0, 0.0, 0.0, 1.0, 0.0, 0.0, 0.0, 1.0};
+            if (!surf) {
+                if (a < d) pole_rotation(-sx[a], -sy[a], -sz[a], R);
+                else pole_rotation(sun_x, sun_y, sun_z, R);
+            }
+            if (m == 0) {
+#pragma unroll
+                for (int k = 0; k < 9; ++k) rot[dl][k] = R[k];
+            }
         }
+        __syncthreads();
+        const double *R = rot[dl];
         const bool mine = m < d && a0 + dl < n_in, seeds = mine && !(without >> m & 1ull);
         // seeds: the screen's largest value over the lattice points of every (direction, out-edge)
         bool sure = false;
         int pt = 0;
         if (screened) {
-            const float x = (float)tx * kHalfScale, y = (float)ty * kHalfScale, z = (float)tz * kHalfScale;
+            const float x = (float)sx[mc] * kHalfScale, y = (float)sy[mc] * kHalfScale, z = (float)sz[mc] * kHalfScale;
             unsigned p[3];
             split_halves(fmaf((float)R[2], z, fmaf((float)R[1], y, (float)R[0] * x)),
                          fmaf((float)R[5], z, fmaf((float)R[4], y, (float)R[3] * x)),
                          fmaf((float)R[8], z, fmaf((float)R[7], y, (float)R[6] * x)), p);
             // k 13: 2^10 against the -2^11 of the rows past the last point
             const unsigned one = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(0.0f, kHalfScale));
-            Operand op[2];
+            Operand op[2], pts[4];
+            // the lattice's operands are read anew (held from pair to pair they do not fit five wavefronts'
+            // registers, and hoisted, which the empty statement prevents, they would be spilled)
+            int at = lane;
+            asm volatile("" : "+v"(at));
+#pragma unroll
+            for (int t = 0; t < 4; ++t) pts[t] = lattice_tile(lat_halves, t, at);
             swap_halves(p[0], p[1], op[0].w[0], op[1].w[0]);
             swap_halves(p[1], p[2], op[0].w[1], op[1].w[1]);
             swap_halves(p[2], one, op[0].w[2], op[1].w[2]);
@@ -998,17 +1016,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
             const int tag = (int)(__float_as_uint(top) & 63u), i = (tag & 31) >> 1;
             pt = 32 * (2 * (tag >> 5) + (tag & 1)) + 8 * (i >> 2) + (b1 > b0 ? 4 : 0) + (i & 3);
         }
+        asm volatile("" ::: "memory");  // rotation and out-edge are read again: 24 registers less in the products
         double v = -__builtin_inf();
         if (seeds && sure) {
             double q0, q1, q2;
             rotate_point(R, lat[3 * pt], lat[3 * pt + 1], lat[3 * pt + 2], q0, q1, q2);
-            v = fma(q2, tz, fma(q1, ty, q0 * tx));
+            v = fma(q2, sz[m], fma(q1, sy[m], q0 * sx[m]));
         } else if (seeds) {  // the lattice points in ascending order, strict >
             pt = 0;
             for (int i = 0; i < NF; ++i) {
                 double q0, q1, q2;
                 rotate_point(R, lat[3 * i], lat[3 * i + 1], lat[3 * i + 2], q0, q1, q2);
-                const double w = fma(q2, tz, fma(q1, ty, q0 * tx));
+                const double w = fma(q2, sz[m], fma(q1, sy[m], q0 * sx[m]));
                 pt = w > v ? i : pt;
                 v = fmax(v, w);
             }
@@ -1088,7 +1107,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(5))) void k_
                 if (kWriteQ) blk[a * d + m] = (BlkT)Q;
                 else blk[a * d + m] = (BlkT)(T[off + a] * rl * (Real)Q);
             } else {
-                if (!kWriteQ) S[b] = tsun * rl * (Real)Q;
+                Real f = tsun;
+                asm volatile("" : "+v"(f));  // keeps the product below from being held through the directions
+                if (!kWriteQ) S[b] = f * rl * (Real)Q;
                 qsun[b] = (float)Q;
             }
         }
