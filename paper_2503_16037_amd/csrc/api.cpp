@@ -462,6 +462,7 @@ void fill_default_opts(sg_solve_opts &o) {
 struct Exec {
     bool on = false;
     bool graphs = true, autotune = true;
+    int front = 0;  // SG_FRONT_NEVER, SG_FRONT_ALWAYS, or the library's choice
     hipStream_t st = nullptr;
     std::vector<hipEvent_t> ev;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> spmv;
@@ -601,15 +602,14 @@ struct SolveStats {
 // 11.5 strongest couplings per voxel: 71.5 ms whole, 72.0 over the front).
 constexpr int64_t kFrontMinNnz = 16000000;
 bool front_pays(const Scene &s) { return s.nnz - s.nnz_big >= kFrontMinNnz && s.nnz_big <= s.nnz / 2; }
+bool takes_front(int asked, bool pays) { return asked ? asked == SG_FRONT_ALWAYS : pays; }
 
 // The same for a batch, by the bytes of a sweep (the values, and the inputs and results of
 // every edge and wavelength): from 128 MB on, where a sweep takes about 30 us.  Half of that
 // made a stream of 8 x 8 x 8 to 48 x 48 x 24 scenes 5 % slower, 128 MB 2 % faster; 12 wavelengths
 // on a 71 x 53 x 29 cloud (0.6 GB) 10.3 -> 7.4 ms, 64 on a 96 x 96 x 32 plume (4.2 GB) 18.0 -> 14.7 ms.
 // (A 32-lane tile, which only a caller or the tuner asks for, takes whole sweeps.)
-bool front_pays_batched(const Scene &s) {
-    return batched_tile(s) != 32 && 4 * s.nnz + 8 * s.E * s.n_lambda >= 8 * kFrontMinNnz;
-}
+bool front_pays_batched(const Scene &s) { return 4 * s.nnz + 8 * s.E * s.n_lambda >= 8 * kFrontMinNnz; }
 // what the launches of a chunk depend on t by: the sweeps before the front's, then the
 // rotation of its marks
 int front_phase(bool front, int t) { return !front ? 0 : (t < 4 ? t : 4 + t % 3); }
@@ -630,7 +630,7 @@ sg_status neumann(Scene &s, hipStream_t st, Exec &tm, const Real *rhs, Real *&xa
     const int grid = spmv_grid<Real>(s, st, rhs, xa, xb, tm.autotune);
     std::vector<double> l1, rel;  // measures of consecutive monitored sweeps
     int chunk = 2, first = 1;
-    const bool front = front_pays(s);
+    const bool front = takes_front(tm.front, front_pays(s));
     int t = 0;  // sweeps of this series so far (the copied first iterate is none)
     stalled = 0;
     double host[64];
@@ -959,6 +959,7 @@ sg_status solve_single(Scene &s, const sg_solve_opts &o, hipStream_t st, double 
     tm.on = o.timing != 0;
     tm.graphs = !(o.flags & SG_NO_GRAPHS) && !tm.on;
     tm.autotune = !(o.flags & SG_NO_AUTOTUNE);
+    tm.front = o.flags & (SG_FRONT_NEVER | SG_FRONT_ALWAYS);
     s.qscreen = (o.flags & SG_EXACT_CELLS) ? 0 : 1;
     s.phi32 = nullptr;
     tm.st = st;
@@ -1049,7 +1050,7 @@ sg_status neumann_batched(Scene &s, hipStream_t st, Exec &tm, int grid, const fl
     std::vector<int> done(nl, 0);
     int chunk = 3, first = 1;  // the first iterate and the third: a ratio over two sweeps
     int at = 0, at_prev = 0;   // sweep index of the last measure and of the one before
-    const bool front = front_pays_batched(s);
+    const bool front = batched_tile(s) != 32 && takes_front(tm.front, front_pays_batched(s));
     int t = 0;  // sweeps of this series so far (the copied first iterate is none)
     stalled = 0;
     double *hist = s.lam_buf + 4 * nl;  // [2][nl][2]: the first iterate's and the chunk's last sweep's
@@ -1254,6 +1255,7 @@ sg_status solve_batched(Scene &s, const sg_solve_opts &o, hipStream_t st, double
     tm.on = o.timing != 0;
     tm.graphs = !(o.flags & SG_NO_GRAPHS) && !tm.on;
     tm.autotune = !(o.flags & SG_NO_AUTOTUNE);
+    tm.front = o.flags & (SG_FRONT_NEVER | SG_FRONT_ALWAYS);
     s.qscreen = (o.flags & SG_EXACT_CELLS) ? 0 : 1;
     s.phi32 = nullptr;
     tm.st = st;

@@ -73,7 +73,7 @@ __device__ __forceinline__ void stage_q(const float *__restrict__ qg, float *__r
 // kMark: the rows whose value moved for any wavelength mark their head node and this one for
 // the next sweep over the front (as the single-wavelength sweep does).
 template <int DB, class XT, class YT, class AccT, bool kResidual, bool kMark>
-__device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, float s, int nl, int monitor,
+__device__ __forceinline__ float2 wide_node(int N, int l, int lane, int lam, bool lv, float s, int nl, int monitor,
                                             float *__restrict__ qs, const long long *__restrict__ adj_ptr,
                                             const long long *__restrict__ nodeoff, const int *__restrict__ rev,
                                             const float *__restrict__ q, const float *__restrict__ qsun,
@@ -172,7 +172,10 @@ __device__ __forceinline__ float2 wide_node(int l, int lane, int lam, bool lv, f
         const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)rows);
         const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(rows >> 32));
         const unsigned long long m = ((unsigned long long)hi << 32) | lo;
-        if (lane < d && (m >> lane & 1ull)) mark[adj_idx[em]] = 1;
+        if (lane < d && (m >> lane & 1ull)) {
+            const int head = adj_idx[em];
+            if (SG_IN(head, N, 0x40b)) mark[head] = 1;
+        }
         if (m && lane == 0) mark[l] = 1;
     }
     return measures.value();
@@ -230,7 +233,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(wide_waves_
         const int bucket = (d + 7) >> 3;
         float2 part = make_float2(0.f, 0.f);
 #define SG_NODE(DB)                                                                                               \
-    part = wide_node<DB, XT, YT, AccT, kResidual, kMode != 0>(l, lane, lam, lv, s, nl, monitor, qs, adj_ptr, nodeoff, \
+    part = wide_node<DB, XT, YT, AccT, kResidual, kMode != 0>(N, l, lane, lam, lv, s, nl, monitor, qs, adj_ptr, nodeoff, \
                                                               rev, q, qsun, tau_s, tau_a, brho, bsrc, rhs, x, y,   \
                                                               adj_idx, next)
         if (bucket <= 1) { SG_NODE(8); }
@@ -462,7 +465,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
             }
             const long long from = node_ok ? edges_from(adj_ptr, l) : 0;
             for (int m = lam; m < d; m += W)
-                if ((m < 32 ? lo >> m : hi >> (m - 32)) & 1u) next[adj_idx[from + m]] = 1;
+                if ((m < 32 ? lo >> m : hi >> (m - 32)) & 1u) {
+                    const int head = adj_idx[from + m];
+                    if (SG_IN(head, N, 0x40c)) next[head] = 1;
+                }
             if ((lo | hi) && lam == 0) next[l] = 1;
         }
         if (monitor && node_ok && lam_ok) meas[(long long)l * nl + lam] = part;

@@ -476,7 +476,7 @@ __global__ __launch_bounds__(256) void k_spmv_big(int nbig, const int *__restric
                                                  const Real *__restrict__ x, Real *__restrict__ y,
                                                  double2 *__restrict__ part, int monitor,
                                                  const int *__restrict__ adj_idx, unsigned char *__restrict__ mark,
-                                                 const unsigned char *__restrict__ only) {
+                                                 const unsigned char *__restrict__ only, int n_nodes) {
     extern __shared__ unsigned char smem_raw[];
     Real *xin = reinterpret_cast<Real *>(smem_raw);
     const long long wg = blockIdx.x;
@@ -500,7 +500,8 @@ __global__ __launch_bounds__(256) void k_spmv_big(int nbig, const int *__restric
             r = fabs((double)yn - (double)xb);
             u = keep_nan(r / (fabs((double)yn) + kRelFloor));
             if (mark && moved(yn, xb)) {
-                mark[adj_idx[off + n]] = 1;
+                const int head = adj_idx[off + n];
+                if (SG_IN(head, n_nodes, 0x308)) mark[head] = 1;
                 mark[l] = 1;
             }
         }
@@ -714,7 +715,7 @@ void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y
     }
     if (s.n_big && with_big) {
         hipLaunchKernelGGL((k_spmv_big<Real>), dim3(s.n_bigrow), dim3(256), sizeof(Real) * s.dmax, st, s.n_big, s.big,
-                           s.bigrow, s.adj_ptr, s.nodeoff, s.rev, val, S, x, y, s.big_part, mon, s.adj_idx, next, only);
+                           s.bigrow, s.adj_ptr, s.nodeoff, s.rev, val, S, x, y, s.big_part, mon, s.adj_idx, next, only, s.N);
         if (out)
             hipLaunchKernelGGL(k_big_measures, dim3((s.n_big + 255) / 256), dim3(256), 0, st, s.n_big, s.big, s.bigrow,
                                s.big_part, s.meas, only);

@@ -214,12 +214,12 @@ def make_desc(scene, keep: list) -> SceneDesc:
     return d
 
 
-SG_NO_GRAPHS, SG_NO_AUTOTUNE, SG_EXACT_CELLS = 1, 2, 4
+SG_NO_GRAPHS, SG_NO_AUTOTUNE, SG_EXACT_CELLS, SG_FRONT_NEVER, SG_FRONT_ALWAYS = 1, 2, 4, 8, 16
 
 
 def make_opts(precision="fp32", solver="auto", rtol=0.0, max_sweeps=0, gmres_restart=0, scatter_order=0,
               build_col_idx=False, timing=False, graphs=True, autotune=True, lambda_tile=0,
-              screen=True) -> SolveOpts:
+              screen=True, front=None) -> SolveOpts:
     o = SolveOpts()
     o.abi_version = ABI_VERSION
     o.precision = SG_FP64 if precision in ("fp64", SG_FP64) else SG_FP32
@@ -231,7 +231,8 @@ def make_opts(precision="fp32", solver="auto", rtol=0.0, max_sweeps=0, gmres_res
     o.build_col_idx = 1 if build_col_idx else 0
     o.timing = 1 if timing else 0
     o.flags = ((0 if graphs else SG_NO_GRAPHS) | (0 if autotune else SG_NO_AUTOTUNE)
-               | (0 if screen else SG_EXACT_CELLS))
+               | (0 if screen else SG_EXACT_CELLS)
+               | (0 if front is None else SG_FRONT_ALWAYS if front else SG_FRONT_NEVER))
     o.lambda_tile = int(lambda_tile)
     return o
 
