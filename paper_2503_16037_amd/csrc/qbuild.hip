@@ -65,10 +65,10 @@ __device__ __forceinline__ int small_div(int p, float inv_n) { return (int)(((fl
 // (two tiles) a step, and the half is the out-edge's low bit.
 // Error bound, in units of v (|v| <= 1): the rotation in FP32 (one multiply and two FMAs from
 // the FP32 roundings of R and s) is off by at most 5 2^-24 per component, the halves of s
-// (rounded toward zero) by 2^-22 and those of p by 1.5 2^-24, together below sqrt(3) 10.5 2^-24
-// < 2^-19.7 in the dot product; the products are exact, and 16 additions of partial sums below
-// 2 are off by at most one unit of 2^-23 each, 2^-19 (measured: 2^-22.3 in all); the index moves
-// a value by less than 64 units in the last place, 2^-17.  So a value lies within 2^-16.1 of the
+// (rounded toward zero) by 2^-22 and those of p by 1.5 2^-24 (2^-22 too where the points are rotated),
+// together below sqrt(3) 13 2^-24 < 2^-19.5 in the dot product; the products are exact, and 16
+// additions of partial sums below 2 are taken to be off by at most one unit of 2^-23 each, 2^-19
+// (measured: 2^-22.3 in all); the index moves a value by less than 64 units in the last place, 2^-17.  So a value lies within 2^-16.1 of the
 // FP64 sequence's, and if the largest exceeds the second by more than 2^-15 (kCertified), its
 // out-edge is the FP64 argmax, with no tie.  The other slots (a few pairs in 10,000 on
 // jittered grids) are queued, and the FP64 sequence decides them, one per lane.
