@@ -594,22 +594,31 @@ struct SolveStats {
 };
 
 // Whether a series' sweeps visit only their front (the nodes that can still change).  A sweep
-// over the front has a fixed cost of about 1 us over a whole one (its marks), which a sweep
-// of a small matrix does not earn back: whole against front solves measured 507 / 536 us at
-// 1.5 M nonzeros (FP64), 393 / 401 at 3.2 M, 660 / 667 at 12.6 M, 1171 / 1117 at 20 M,
-// 2338 / 2139 at 70 M, 19.98 / 13.00 ms at 424 M.  A matrix that lies mostly in nodes of more than 64
+// over the front has a fixed cost of about 1 us over a whole one, and its marks read the previous iterate,
+// which a sweep of a small matrix does not earn back: solves by whole sweeps and over the front measured, in
+// us, in FP32 393 / 401 at 3.2 M nonzeros, 660 / 667 at 12.6 M, 705 / 695 at 16.6 M, 1375 / 1254 at 24 M,
+// 2338 / 2139 at 70 M, 19980 / 13000 at 424 M (in a homogeneous medium, whose nodes move longer, 1095 / 1135 at
+// 17.5 M, 1594 / 1659 at 34 M, 5365 / 4763 at 120 M), and in FP64 1066 / 1100 at 16.6 M, 2160 / 2174 at 24 M,
+// 1987 / 1740 at 34 M, 3880 / 3226 at 46 M.  A matrix that lies mostly in nodes of more than 64
 // couplings takes whole sweeps: each of them has an input that moves until the end (the
 // 11.5 strongest couplings per voxel: 71.5 ms whole, 72.0 over the front).
 constexpr int64_t kFrontMinNnz = 16000000;
-bool front_pays(const Scene &s) { return s.nnz - s.nnz_big >= kFrontMinNnz && s.nnz_big <= s.nnz / 2; }
+template <class Real>
+bool front_pays(const Scene &s) {
+    return s.nnz - s.nnz_big >= kFrontMinNnz * (int64_t)(sizeof(Real) / 4) && s.nnz_big <= s.nnz / 2;
+}
 bool takes_front(int asked, bool pays) { return asked ? asked == SG_FRONT_ALWAYS : pays; }
 
 // The same for a batch, by the bytes of a sweep (the values, and the inputs and results of
-// every edge and wavelength): from 128 MB on, where a sweep takes about 30 us.  Half of that
+// every edge and wavelength).  In narrow tiles from 128 MB on, where a sweep takes about 30 us: half of that
 // made a stream of 8 x 8 x 8 to 48 x 48 x 24 scenes 5 % slower, 128 MB 2 % faster; 12 wavelengths
-// on a 71 x 53 x 29 cloud (0.6 GB) 10.3 -> 7.4 ms, 64 on a 96 x 96 x 32 plume (4.2 GB) 18.0 -> 14.7 ms.
+// on a 71 x 53 x 29 cloud (0.6 GB) 10.3 -> 7.4 ms.  In full wavefronts from 384 MB on (whole / over the front,
+// in us): 1538 / 1648 at 184 MB, 1107 / 1175 at 226 MB, 2457 / 2443 at 281 MB, 1526 / 1611 at 323 MB, 2208 / 2093 at
+// 441 MB, 3677 / 3150 at 516 MB, 18.0 -> 14.7 ms for 64 wavelengths on a 96 x 96 x 32 plume (4.2 GB).
 // (A 32-lane tile, which only a caller or the tuner asks for, takes whole sweeps.)
-bool front_pays_batched(const Scene &s) { return 4 * s.nnz + 8 * s.E * s.n_lambda >= 8 * kFrontMinNnz; }
+bool front_pays_batched(const Scene &s) {
+    return 4 * s.nnz + 8 * s.E * s.n_lambda >= (batched_tile(s) == 64 ? 24 : 8) * kFrontMinNnz;
+}
 // what the launches of a chunk depend on t by: the sweeps before the front's, then the
 // rotation of its marks
 int front_phase(bool front, int t) { return !front ? 0 : (t < 4 ? t : 4 + t % 3); }
@@ -630,7 +639,7 @@ sg_status neumann(Scene &s, hipStream_t st, Exec &tm, const Real *rhs, Real *&xa
     const int grid = spmv_grid<Real>(s, st, rhs, xa, xb, tm.autotune);
     std::vector<double> l1, rel;  // measures of consecutive monitored sweeps
     int chunk = 2, first = 1;
-    const bool front = takes_front(tm.front, front_pays(s));
+    const bool front = takes_front(tm.front, front_pays<Real>(s));
     int t = 0;  // sweeps of this series so far (the copied first iterate is none)
     stalled = 0;
     double host[64];

@@ -505,18 +505,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(pack_waves_
 template <int W, class XT, class YT, class AccT, bool kRes, int kMode>
 static void launch_pack(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor, int front) {
     const int groups = batched_groups(s);
+    static std::atomic<uint64_t> kept[8];  // per degree bucket
 #define SG_PK(DD)                                                                                                  \
+    if (kMode == kFrontOn)                                                                                         \
+        grid = std::min(groups, resident_groups(k_spmm_pack<W, DD, XT, YT, AccT, kRes, kMode>, 256, 0, kept[DD / 8 - 1])); \
     hipLaunchKernelGGL((k_spmm_pack<W, DD, XT, YT, AccT, kRes, kMode>), dim3(grid), dim3(256), 0, st, s.N, s.n_lambda, \
                        groups, s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a, \
                        s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor, s.adj_idx, front_marks_of(s, front), \
                        front_marks_of(s, front + 1), (unsigned long long *)front_marks_of(s, front + 2), front_skew(grid * 4))
-    if (s.dmax <= 16) SG_PK(16);
-    else if (s.dmax <= 24) SG_PK(24);
-    else if (s.dmax <= 32) SG_PK(32);
-    else if (s.dmax <= 40) SG_PK(40);
-    else if (s.dmax <= 48) SG_PK(48);
-    else if (s.dmax <= 56) SG_PK(56);
-    else SG_PK(64);
+    if (s.dmax <= 16) { SG_PK(16); }
+    else if (s.dmax <= 24) { SG_PK(24); }
+    else if (s.dmax <= 32) { SG_PK(32); }
+    else if (s.dmax <= 40) { SG_PK(40); }
+    else if (s.dmax <= 48) { SG_PK(48); }
+    else if (s.dmax <= 56) { SG_PK(56); }
+    else { SG_PK(64); }
 #undef SG_PK
 }
 
@@ -524,9 +527,6 @@ template <class XT, class YT, class AccT, bool kRes, int kMode>
 static void launch_wide(Scene &s, hipStream_t st, int grid, const float *rhs, const XT *x, YT *y, int monitor, int front) {
     const int W = batched_tile(s);
     const int waves = wide_waves(s);
-    // over the front, the wavefronts that are resident (six per SIMD, four of the narrow tiles):
-    // each takes its share of the marks, and a second round of them would start when the first ends
-    if (kMode == kFrontOn) grid = W < 64 ? 256 * 4 : 256 * 6 * 4 / waves;
     grid = std::max(1, std::min(grid, batched_groups(s)));
     if (W == 8) return launch_pack<8, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
     if (W == 16) return launch_pack<16, XT, YT, AccT, kRes, kMode>(s, st, grid, rhs, x, y, monitor, front);
@@ -535,19 +535,23 @@ static void launch_wide(Scene &s, hipStream_t st, int grid, const float *rhs, co
     const int groups = batched_groups(s);
     dim3 gr(grid, (s.n_lambda + 63) / 64);
     const size_t shm = (size_t)waves * (s.dmax * s.dmax + 64) * sizeof(float);
+    static std::atomic<uint64_t> kept[8];  // per degree bucket
 #define SG_WIDE(DD)                                                                                                 \
+    if (kMode == kFrontOn)                                                                                          \
+        gr.x = std::max(1, std::min(groups, resident_groups(k_spmm_wide<DD, XT, YT, AccT, kRes, kMode>, 64 * waves, shm, \
+                                                            kept[DD / 8 - 1]) / (int)gr.y));                        \
     hipLaunchKernelGGL((k_spmm_wide<DD, XT, YT, AccT, kRes, kMode>), gr, dim3(64 * waves), shm, st, s.N, s.n_lambda,  \
                        groups, s.adj_ptr, s.nodeoff, s.rev, s.q, s.qsun, (const float *)s.tau_s, (const float *)s.tau_a, \
                        s.abs_scale_d, s.brho, s.bsrc, rhs, x, y, s.meas, monitor, s.dmax, s.adj_idx,                 \
                        front_marks_of(s, front), front_marks_of(s, front + 1),                                      \
-                       (unsigned long long *)front_marks_of(s, front + 2), front_skew(grid * waves))
-    if (s.dmax <= 16) SG_WIDE(16);
-    else if (s.dmax <= 24) SG_WIDE(24);
-    else if (s.dmax <= 32) SG_WIDE(32);
-    else if (s.dmax <= 40) SG_WIDE(40);
-    else if (s.dmax <= 48) SG_WIDE(48);
-    else if (s.dmax <= 56) SG_WIDE(56);
-    else SG_WIDE(64);
+                       (unsigned long long *)front_marks_of(s, front + 2), front_skew((int)gr.x * waves))
+    if (s.dmax <= 16) { SG_WIDE(16); }
+    else if (s.dmax <= 24) { SG_WIDE(24); }
+    else if (s.dmax <= 32) { SG_WIDE(32); }
+    else if (s.dmax <= 40) { SG_WIDE(40); }
+    else if (s.dmax <= 48) { SG_WIDE(48); }
+    else if (s.dmax <= 56) { SG_WIDE(56); }
+    else { SG_WIDE(64); }
 #undef SG_WIDE
 }
 

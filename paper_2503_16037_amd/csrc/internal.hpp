@@ -277,6 +277,23 @@ inline int front_of(int t) { return t >= kFrontFirst ? t : 0; }
 __host__ __device__ inline size_t front_marks(int N) { return ((size_t)N + 7) / 8 * 8; }
 // the marks of the nodes sweep t visits
 inline unsigned char *front_marks_of(const Scene &s, int t) { return s.front + front_marks(s.N) * (t % 3); }
+// Workgroups of 256 CUs that are resident at once: the grid of a sweep over the front, whose wavefronts
+// each take their share of the marks (a second round of them would start when the first ends).  The
+// runtime's answer for a kernel and its LDS, kept per kernel (last: one per instantiation).  A grid for six
+// and four wavefronts per SIMD took two rounds at the degrees above 40, which fit fewer: 12 wavelengths on
+// plain 48x48x30 (degree 42) 5581 us against 4556 by whole sweeps, 64 on 80x80x32 31.7 ms against 30.2; now
+// 5068 against 4896 and 26.8 against 30.5.
+template <class Kernel>
+int resident_groups(Kernel kernel, int threads, size_t lds, std::atomic<uint64_t> &last) {
+    uint64_t v = last.load();
+    if (v >> 32 != lds + 1) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess || n < 1) n = 1;
+        v = (uint64_t)(lds + 1) << 32 | (uint32_t)n;
+        last.store(v);
+    }
+    return 256 * (int)(uint32_t)v;
+}
 // the shift from row to row of a front's nodes over W wavefronts (front_node): 0.618 W
 inline int front_skew(int W) { return (int)(0.618 * W); }
 

@@ -686,11 +686,6 @@ static int lds_dmax(const Scene &s) { return block_lds<Real>(s) ? std::min(s.dma
 // also run persistent over fewer workgroups; the tuner measures both)
 static int default_grid(const Scene &s) { return spmv_blocks(s); }
 
-// Workgroups of a sweep over the front: the wavefronts that are resident (eight per SIMD in
-// FP32, five in FP64); a second round of them would start when the first ends
-template <class Real>
-static int front_grid(const Scene &s) { return std::min(spmv_blocks(s), 256 * (sizeof(Real) == 4 ? 8 : 5)); }
-
 template <class Real>
 void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y, double *out, int grid,
                  hipEvent_t after, bool with_big, int front) {
@@ -702,7 +697,8 @@ void launch_spmv(Scene &s, hipStream_t st, const Real *S, const Real *x, Real *y
     unsigned char *next = front ? front_marks_of(s, front + 1) : nullptr;
     const unsigned char *only = front > kFrontFirst ? front_marks_of(s, front) : nullptr;
     if (only) {
-        const int g = front_grid<Real>(s);
+        static std::atomic<uint64_t> kept{0};
+        const int g = std::min(spmv_blocks(s), resident_groups(k_spmv_front<Real>, kSpmvThreads, lds, kept));
         hipLaunchKernelGGL((k_spmv_front<Real>), dim3(g), dim3(kSpmvThreads), lds, st, s.N, s.adj_ptr, s.nodeoff, s.rev,
                            val, S, x, y, s.meas, mon, dl, s.adj_idx, only, next,
                            (unsigned long long *)front_marks_of(s, front + 2), front_skew(g * kNodesPerSpmvBlock));

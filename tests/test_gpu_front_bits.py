@@ -105,7 +105,7 @@ def test_wavelengths(ctx, what, n_lambda):
         assert info["sweeps"] > 6, "no sweep over the front"
 
 
-@pytest.mark.parametrize("opts", [dict(precision="fp32"), dict(precision="fp64"), dict(n_lambda=12)])
+@pytest.mark.parametrize("opts", [dict(precision="fp32"), dict(precision="fp64"), dict(n_lambda=12), dict(n_lambda=31)])
 def test_more_nodes_than_resident_wavefronts(ctx, opts):
     """39,960 nodes: several rows of the front's stride, the last one ragged."""
     from paper_2503_16037_amd import sgrt
