@@ -451,10 +451,15 @@ typedef struct sg_graph_desc {
 typedef struct sg_graph_info {
     int64_t candidates;      /* pairs ranked (C^2 >= threshold; in threshold mode, selected) */
     int64_t pairs_evaluated; /* couplings computed to find the ranked candidates (pairs j > i in
-                                the boxes, counted once; the fill kernel recomputes those it keeps) */
-    double threshold;        /* C^2 bound of the last candidate pass (0: every pair) */
-    int32_t streamed;        /* 1: every pair went through the streamed best-n list */
-    int32_t passes;          /* candidate passes, each a count and a fill kernel over the boxes */
+                                the boxes, counted once; the fill kernel recomputes those it keeps;
+                                with streamed = 1, every pair of every pass) */
+    double threshold;        /* C^2 bound of the last pass over boxes (0: every pair, or streamed) */
+    int32_t streamed;        /* 1: the strongest were ranked among every pair, against a sampled
+                                threshold, instead of those in boxes round the nodes (general
+                                nodes, or no box budget holds) */
+    int32_t passes;          /* candidate passes: over the boxes, a count and a fill kernel each; over
+                                every pair, one kernel each (the selection among many equal
+                                couplings takes thirteen) */
     double ms_total;         /* wall time of the call */
     double ms_pairs;         /* summed kernel time of the candidate passes (HIP events) */
     double ms_sort;          /* summed time of the ranking and adjacency sorts (HIP events) */

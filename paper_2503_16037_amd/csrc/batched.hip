@@ -332,10 +332,12 @@ void launch_bnode_coef(Scene &s, hipStream_t st) {
 int wide_waves(const Scene &s) { return (size_t)4 * (s.dmax * s.dmax + 64) * sizeof(float) <= 60 * 1024 ? 4 : 2; }
 
 // Wavelength lanes per node: 8, 16, 32 or 64 (counts above 64 use several 64-lane
-// columns of the full-wavefront kernel).  The narrow tiles read the phase-cell columns
-// through the vector cache, once per node slot; the full-wavefront kernel stages them
-// in LDS.  Measured on MI355X, 8 and 16 lanes beat the full wavefront by up to 2x while
-// 32 lanes lose to it by about 1.5x, so 32 is left to the autotuner.
+// columns of the full-wavefront kernel).  8 and 16 lanes beat the full wavefront by up to 2x.  32 lanes
+// take about its time per whole sweep (17 to 32 wavelengths, in us: 38 / 43 on 24x24x16, 51 / 67 on
+// 32x32x20, 160 / 176 on 48x48x24, 433 / 453 on 64x64x32, 980 / 1010 on 96x96x32, 171 / 235 on plain
+// 40x40x24), but have no sweeps over the front: whole solves 5940 / 5605 us on 64x64x32, 14.2 / 11.8 ms on
+// 96x96x32, against 4056 / 5163 on plain 40x40x24.  So 32 is left to the autotuner, whose choice
+// by whole sweeps was the faster solve at each of these.
 int smallest_tile(int n_lambda) { return n_lambda <= 8 ? 8 : n_lambda <= 16 ? 16 : n_lambda <= 32 ? 32 : 64; }
 int default_tile(int n_lambda) { return smallest_tile(n_lambda) <= 16 ? smallest_tile(n_lambda) : 64; }
 

@@ -347,18 +347,18 @@ __global__ __launch_bounds__(256) void k_graph_cells(Geo g, const long long *__r
     if (threadIdx.x < tests && sum[threadIdx.x]) atomicAdd(&total[threadIdx.x], sum[threadIdx.x]);
 }
 
-// Boxes of nodes n0 + r (r < n) at threshold t, stored as (lo x, lo y, lo z, extent
+// Boxes of the nodes r < n at threshold t, stored as (lo x, lo y, lo z, extent
 // x, y, z, surface row, 0), and their cell counts (volume cells + surface cells);
 // cells[n] = 0 closes the array for the exclusive scan.
 __global__ void k_graph_boxes(Geo g, const long long *__restrict__ P, const double *__restrict__ mu, double t,
-                              long long n0, long long n, int *__restrict__ box, unsigned long long *__restrict__ cells) {
+                              long long n, int *__restrict__ box, unsigned long long *__restrict__ cells) {
     const long long r = blockIdx.x * (long long)blockDim.x + threadIdx.x;
     if (r > n) return;
     if (r == n) {
         cells[n] = 0;
         return;
     }
-    const Box b = node_box(g, P, mu, n0 + r, t);
+    const Box b = node_box(g, P, mu, r, t);
     long long e[3];
     for (int a = 0; a < 3; ++a) e[a] = b.hi[a] >= b.lo[a] ? b.hi[a] - b.lo[a] + 1 : 0;
     const unsigned long long nv = (unsigned long long)e[0] * e[1] * e[2];
@@ -390,8 +390,8 @@ __device__ __forceinline__ long long owner(const unsigned long long *__restrict_
 // list stays ordered by (i, j).  bev: the evaluated pairs per workgroup (count pass).
 template <bool kFill>
 __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restrict__ q,
-                                                    const double *__restrict__ mu, double t, int strict, long long n0,
-                                                    long long n, const int *__restrict__ box,
+                                                    const double *__restrict__ mu, double t, int strict, long long n,
+                                                    const int *__restrict__ box,
                                                     const unsigned long long *__restrict__ coff, unsigned long long T,
                                                     unsigned long long *__restrict__ bcount,
                                                     const unsigned long long *__restrict__ boff,
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(256) void k_graph_eval(Geo g, const double *__restr
                 const unsigned bx = (unsigned)o[3], by = (unsigned)o[4], bz = (unsigned)o[5];
                 const unsigned nv = bx * by * bz;
                 const unsigned lc = (unsigned)(c - (staged ? scoff[r - fb] : coff[r]));
-                i = n0 + r;
+                i = r;
                 if (lc < nv) {
                     const unsigned yz = lc / bx, cx = lc - yz * bx, cz = yz / by, cy = yz - cz * by;
                     j = ((long long)o[0] + cx) + (long long)g.nx * (((long long)o[1] + cy) + (long long)g.ny * ((long long)o[2] + cz));
@@ -1008,7 +1008,7 @@ struct Builder {
         GTRY(dev.get(&box, 8 * n));
         GTRY(dev.get(&cells, n + 1));
         GTRY(dev.get(&coff, n + 1));
-        hipLaunchKernelGGL(k_graph_boxes, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, g, P, mu, t, 0ll, n, box, cells);
+        hipLaunchKernelGGL(k_graph_boxes, dim3(blocks_for(n + 1, 256)), dim3(256), 0, st, g, P, mu, t, n, box, cells);
         GHIP(hipGetLastError());
         GTRY(scan<unsigned long long>(cells, coff, n + 1, 0ull));
         unsigned long long T = 0;
@@ -1026,7 +1026,7 @@ struct Builder {
         GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
         ++passes;
         const int e0 = mark(ev_pairs);
-        hipLaunchKernelGGL((k_graph_eval<false>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, 0ll, n,
+        hipLaunchKernelGGL((k_graph_eval<false>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, n,
                            box, coff, T, bcount, nullptr, nullptr, nullptr, bev);
         end(ev_pairs, e0);
         GHIP(hipGetLastError());
@@ -1046,7 +1046,7 @@ struct Builder {
             GTRY(dev.get(&keys, total));
             GTRY(dev.get(&codes, total));
             const int e1 = mark(ev_pairs);
-            hipLaunchKernelGGL((k_graph_eval<true>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, 0ll, n,
+            hipLaunchKernelGGL((k_graph_eval<true>), dim3((unsigned)nb), dim3(256), 0, st, g, q, mu, t, strict, n,
                                box, coff, T, nullptr, boff, keys, codes, nullptr);
             end(ev_pairs, e1);
             GHIP(hipGetLastError());
