@@ -28,7 +28,8 @@
 //   otherwise every pair is evaluated against a threshold taken from a sample of the
 //   pairs (k_graph_all), so that only about n of them become candidates.
 // General nodes (the path points of the lines of sight, Sec. 2) are not tied to voxels
-// and always take the second way; its candidates are then sorted by (i, j).
+// and always take the second way; its candidates are then sorted by (i, j).  Up to 2^23
+// pairs are listed in order instead (k_graph_every), without a threshold.
 // The n best of the candidates are selected, not sorted: a radix selection finds the
 // n-th largest k, and a compaction in list order keeps the larger ones and the first of
 // the equal ones (equal couplings: the smaller pair first).  The selected pairs are the
@@ -507,21 +508,22 @@ __device__ __forceinline__ void sel_count(unsigned *bins, unsigned long long k, 
 // the nodes j of every gridDim.y-th span of kAllSpan, staged in LDS kAllTile at a time.  The
 // division is left to the pairs that mu_i mu_j >= t d2 (1 - 1e-9) lets through: the
 // products, the differences and this test, eleven FP64 operations a pair, bound the kernel.
-// Candidates are few: they collect in LDS and leave with one atomic per workgroup (a list
-// that overflows goes out by one atomic per wavefront and node j).
+// The span is the launch's: 4096, or less where that leaves fewer than 2048 workgroups (9000 nodes
+// 1.87 -> 0.68 ms by c_min).  Candidates are few: they collect in LDS and leave with one atomic per
+// 512 and workgroup (a list that overflows within a tile goes out by one atomic per wavefront and node j).
 // 119,958 nodes (7.2e9 pairs): 3.3 ms, 24 T lane-operations/s of the 30 that FP64 issues; its
 // build 1440 -> 5.6 ms (every pair written out, sorted and merged into a best-n list before).
 // Where far more pairs reach the threshold than are asked for (equal couplings), none is written:
 // kAllKeys and kAllCodes count them for a pass of the radix selection (select_hist), by the coupling
 // and then, among those equal to the n-th (kn), by the complement of the code, so that the n best are
 // known in the order of their ids; kAllTake lists just these.
-constexpr int kAllTile = 256, kAllSpan = 4096, kAllHits = 512;
+constexpr int kAllTile = 256, kAllSpan = 4096, kAllHits = 1024, kAllFlush = 512;
 enum AllMode { kAllList, kAllKeys, kAllCodes, kAllTake };
 template <AllMode kMode>
 __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restrict__ q, const double *__restrict__ mu,
                                                    double t, int strict, unsigned long long cap,
                                                    unsigned long long *__restrict__ count, double *__restrict__ keys,
-                                                   unsigned long long *__restrict__ codes, int pass,
+                                                   unsigned long long *__restrict__ codes, int span, int pass,
                                                    const unsigned long long *__restrict__ sel, unsigned long long kn) {
 #pragma clang fp contract(off)
     constexpr bool kCount = kMode == kAllKeys || kMode == kAllCodes;
@@ -571,12 +573,24 @@ __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restri
             codes[b] = code;
         }
     };
+    auto flush = [&]() {  // by the whole workgroup, between barriers; the next one publishes nhit = 0
+        const unsigned n = min(nhit, (unsigned)kAllHits);
+        if (threadIdx.x == 0) hbase = n ? atomicAdd(count, (unsigned long long)n) : 0ull;
+        __syncthreads();
+        for (unsigned h = threadIdx.x; h < n; h += 256)
+            if (hbase + h < cap) {
+                keys[hbase + h] = hkey[h];
+                codes[hbase + h] = hcode[h];
+            }
+        if (threadIdx.x == 0) nhit = 0u;
+    };
     if (threadIdx.x == 0) nhit = 0u;
-    for (long long jb = (long long)blockIdx.y * kAllSpan; jb < g.N; jb += (long long)gridDim.y * kAllSpan) {
-        const long long je = min(g.N, jb + kAllSpan);
+    for (long long jb = (long long)blockIdx.y * span; jb < g.N; jb += (long long)gridDim.y * span) {
+        const long long je = min(g.N, jb + span);
         for (long long j0 = max(jb, i0); j0 < je; j0 += kAllTile) {  // none below every i
             const int nj = (int)min((long long)kAllTile, je - j0);
             __syncthreads();
+            if (!kCount && nhit >= (unsigned)kAllFlush) flush();
             if ((int)threadIdx.x < nj) {
                 const long long j = j0 + threadIdx.x;
                 jxy[threadIdx.x] = make_double2(q[3 * j], q[3 * j + 1]);
@@ -601,14 +615,42 @@ __global__ __launch_bounds__(256) void k_graph_all(Geo g, const double *__restri
             if (bins[b]) atomicAdd(&count[b], (unsigned long long)bins[b]);
         return;
     }
-    const unsigned n = min(nhit, (unsigned)kAllHits);
-    if (threadIdx.x == 0) hbase = n ? atomicAdd(count, (unsigned long long)n) : 0ull;
-    __syncthreads();
-    for (unsigned h = threadIdx.x; h < n; h += 256)
-        if (hbase + h < cap) {
-            keys[hbase + h] = hkey[h];
-            codes[hbase + h] = hcode[h];
+    flush();
+}
+
+// The coupling and code of every pair i < j (i a volume node) in order, 0 where it is no candidate (k > 0
+// and k >= t, strict: k > t), and the candidates counted in *count: for few nodes, whose pairs
+// are soon written and need no threshold, no atomics and no sort afterwards.  A workgroup takes 256
+// nodes j and kEveryRows nodes i.
+// Up to 2^23 pairs: 800 nodes 3.44 -> 0.27 ms (two workgroups of k_graph_all and an atomic per hit before),
+// 3000 nodes with 8 couplings each 2.11 -> 0.43 ms.
+constexpr unsigned long long kEveryPairs = 1ull << 23;
+constexpr int kEveryRows = 8;
+__global__ __launch_bounds__(256) void k_graph_every(Geo g, const double *__restrict__ q, const double *__restrict__ mu,
+                                                     double t, int strict, unsigned long long *__restrict__ count,
+                                                     double *__restrict__ keys, unsigned long long *__restrict__ codes) {
+#pragma clang fp contract(off)
+    const long long j = blockIdx.x * 256ll + threadIdx.x, i0 = (long long)blockIdx.y * kEveryRows;
+    if (i0 >= blockIdx.x * 256ll + 255) return;  // no pair of this workgroup
+    __shared__ unsigned sum[4];
+    unsigned n = 0u;
+    for (long long i = i0; i < min(i0 + kEveryRows, g.nvol); ++i) {
+        double k = 0.0;
+        if (j > i && j < g.N) {
+            const double c = pair_key(q, mu, i, j);
+            if (c > 0.0 && (strict ? c > t : c >= t)) k = c;
+            const long long at = i * (2 * g.N - i - 1) / 2 + (j - i - 1);
+            keys[at] = k;
+            codes[at] = (unsigned long long)i << 32 | (unsigned long long)j;
         }
+        n += (unsigned)__popcll(__ballot(k > 0.0));
+    }
+    if ((threadIdx.x & 63) == 0) sum[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        n = sum[0] + sum[1] + sum[2] + sum[3];
+        if (n) atomicAdd(count, (unsigned long long)n);
+    }
 }
 
 // The couplings of M pairs spread over all of them (a fixed hash of the sample's number, so
@@ -945,6 +987,46 @@ __global__ __launch_bounds__(256) void k_rs_scatter(const unsigned long long *__
     }
 }
 
+// The same of few nodes and voxels on the host: the device's answer is a round trip (8x8x8 nodes above a
+// c_min: 221 -> 183 us).
+constexpr long long kHostMoments = 4096;
+void host_moments(const sg_graph_desc *d, const Geo &g, Moments &m) {
+    m = Moments{};
+    m.bad_node = ~0ull;
+    for (long long v = 0; v < g.nvox; ++v) {
+        unsigned bits;
+        std::memcpy(&bits, d->mu_s + v, sizeof(bits));
+        if (d->mu_s[v] >= 0.0f && std::isfinite(d->mu_s[v])) m.mu_max = std::max(m.mu_max, bits & 0x7fffffffu);
+        else m.bad_mu = 1u;
+    }
+    const int *pos = g.general ? d->node_pos_fx : d->vol_pos_fx;
+    for (long long l = 0; l < g.N; ++l) {
+        long long p[3] = {0, 0, 0};
+        if (l < g.nvol) {
+            const long long c[3] = {l % g.nx, (l / g.nx) % g.ny, l / ((long long)g.nx * g.ny)};
+            const long long w[3] = {g.nx * kFx, g.ny * kFx, g.nz * kFx};
+            bool in = true;
+            for (int a = 0; a < 3; ++a) {
+                p[a] = pos[3 * l + a];
+                const long long lo = g.general ? (a < 2 ? -1 : 0) : c[a] * kFx;
+                in = in && p[a] > lo && p[a] < (g.general ? w[a] : lo + kFx);
+            }
+            if (!in) m.bad_node = std::min(m.bad_node, (unsigned long long)l);
+        } else {
+            const long long c = l - g.nvol;
+            p[0] = (c % g.nx) * kFx + kFx / 2;
+            p[1] = (c / g.nx) * kFx + kFx / 2;
+            if (!(d->surf_albedo[c] >= 0.0f && d->surf_albedo[c] <= 1.0f)) m.bad_albedo = 1u;
+        }
+        for (int a = 0; a < 3; ++a) {
+            const unsigned long long sq = (unsigned long long)(p[a] * p[a]);
+            m.s1[a] += (unsigned long long)p[a];
+            m.lo[a] += sq & 0xffffffffull;
+            m.hi[a] += sq >> 32;
+        }
+    }
+}
+
 unsigned blocks_for(long long n, int threads) { return (unsigned)std::max<long long>(1, (n + threads - 1) / threads); }
 
 // ---- host driver ---------------------------------------------------------------------
@@ -1088,16 +1170,36 @@ struct Builder {
     template <AllMode kMode>
     sg_status all_pass(double t, int strict, unsigned long long cap, unsigned long long *out, double *keys,
                        unsigned long long *codes, int pass, unsigned long long kn) {
-        const dim3 grid((unsigned)((g.nvol + 511) / 512),
-                        (unsigned)std::min<long long>((g.N + kAllSpan - 1) / kAllSpan, 65535));
+        const long long gx = (g.nvol + 511) / 512;
+        const long long span = std::min<long long>(kAllSpan, (gx * g.N / 2048 / kAllTile + 1) * kAllTile);
+        const dim3 grid((unsigned)gx, (unsigned)std::min<long long>((g.N + span - 1) / span, 65535));
         if (out == scal) GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
         ++passes;
         const int e0 = mark(ev_pairs);
-        hipLaunchKernelGGL(k_graph_all<kMode>, grid, dim3(256), 0, st, g, q, mu, t, strict, cap, out, keys, codes, pass,
-                           scal + kCellTests, kn);
+        hipLaunchKernelGGL(k_graph_all<kMode>, grid, dim3(256), 0, st, g, q, mu, t, strict, cap, out, keys, codes, (int)span,
+                           pass, scal + kCellTests, kn);
         end(ev_pairs, e0);
         GHIP(hipGetLastError());
-        evals += (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
+        evals += all();
+        return SG_OK;
+    }
+    // the pairs i < j of a volume node i and any node j
+    unsigned long long all() const { return (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2; }
+
+    // every pair in order (k_graph_every); have: the candidates among them
+    sg_status every_pair(double t, int strict, double *&keys, unsigned long long *&codes, unsigned long long &have) {
+        GTRY(dev.get(&keys, all()));
+        GTRY(dev.get(&codes, all()));
+        GHIP(hipMemsetAsync(scal, 0, sizeof(unsigned long long), st));
+        ++passes;
+        const int e0 = mark(ev_pairs);
+        hipLaunchKernelGGL(k_graph_every, dim3(blocks_for(g.N, 256), (unsigned)((g.nvol + kEveryRows - 1) / kEveryRows)),
+                           dim3(256), 0, st, g, q, mu, t, strict, scal, keys, codes);
+        end(ev_pairs, e0);
+        GHIP(hipGetLastError());
+        GHIP(hipMemcpyAsync(&have, scal, sizeof(have), hipMemcpyDeviceToHost, st));
+        GHIP(hipStreamSynchronize(st));
+        evals += all();
         return SG_OK;
     }
 
@@ -1284,20 +1386,24 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     GTRY(B.dev.get(&B.mu, N));
     GTRY(B.dev.get(&B.scal, kCellTests + 2));
     GTRY(B.dev.get(&B.hist, kSelBins));
+    Moments m;
+    const bool few = std::max(N, nvox) <= kHostMoments;
+    if (few) host_moments(d, g, m);
     GHIP(hipMemsetAsync(B.hist, 0, sizeof(unsigned long long) * kSelBins, st));
-    GHIP(hipMemsetAsync(mom, 0, sizeof(Moments), st));
-    GHIP(hipMemsetAsync(&mom->bad_node, 0xff, sizeof(mom->bad_node), st));
     GHIP(hipMemcpyAsync(pos, general ? d->node_pos_fx : d->vol_pos_fx, sizeof(int) * 3 * nvol, hipMemcpyHostToDevice,
                         st));
     GHIP(hipMemcpyAsync(mus, d->mu_s, sizeof(float) * nvox, hipMemcpyHostToDevice, st));
     if (d->surface_nodes)
         GHIP(hipMemcpyAsync(alb, d->surf_albedo, sizeof(float) * d->nx * d->ny, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_graph_moments, dim3(std::min(256u, blocks_for(std::max(N, nvox), 256))), dim3(256), 0, st, g,
-                       pos, mus, alb, mom);
-    GHIP(hipGetLastError());
-    Moments m;
-    GHIP(hipMemcpyAsync(&m, mom, sizeof(m), hipMemcpyDeviceToHost, st));
-    GHIP(hipStreamSynchronize(st));
+    if (!few) {
+        GHIP(hipMemsetAsync(mom, 0, sizeof(Moments), st));
+        GHIP(hipMemsetAsync(&mom->bad_node, 0xff, sizeof(mom->bad_node), st));
+        hipLaunchKernelGGL(k_graph_moments, dim3(std::min(256u, blocks_for(std::max(N, nvox), 256))), dim3(256), 0, st, g,
+                           pos, mus, alb, mom);
+        GHIP(hipGetLastError());
+        GHIP(hipMemcpyAsync(&m, mom, sizeof(m), hipMemcpyDeviceToHost, st));
+        GHIP(hipStreamSynchronize(st));
+    }
     if (m.bad_mu) return gfail(SG_E_INVALID, "mu_s must be finite and >= 0");
     if (m.bad_albedo) return gfail(SG_E_INVALID, "surf_albedo must be in [0, 1]");
     if (m.bad_node != ~0ull)
@@ -1319,13 +1425,20 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     // candidates and selection
     double *keys = nullptr;
     unsigned long long *codes = nullptr, have = 0, n_sel = 0, ranked = 0;
+    unsigned long long listed = 0;  // keys and codes; `have` of them are candidates
     double t_used = 0.0;
     int streamed = 0;
     const unsigned long long n_want = (unsigned long long)d->n_pairs;
     if (d->n_pairs == 0) {
         t_used = d->c_min * d->c_min;
-        if (general) GTRY(B.all_pairs(t_used, 1, 1ull << 20, 0ull, keys, codes, have, ranked));
-        else GTRY(B.pairs(t_used, 1, 0ull, keys, codes, have));
+        if (general && B.all() <= kEveryPairs) {
+            GTRY(B.every_pair(t_used, 1, keys, codes, have));
+            listed = B.all();
+        } else {
+            if (general) GTRY(B.all_pairs(t_used, 1, 1ull << 20, 0ull, keys, codes, have, ranked));
+            else GTRY(B.pairs(t_used, 1, 0ull, keys, codes, have));
+            listed = have;
+        }
         n_sel = ranked = have;
     } else {
         // the lowest threshold whose boxes fit the cell budget, to a factor of sqrt 2 (any
@@ -1370,8 +1483,15 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
             }
         }
         t_used = t_fit;
-        ranked = have;
-        if (!enough) {
+        ranked = listed = have;
+        if (!enough && B.all() <= kEveryPairs) {
+            streamed = 1;
+            t_used = 0.0;
+            B.evals = 0;
+            GTRY(B.every_pair(0.0, 0, keys, codes, have));
+            ranked = have;
+            listed = B.all();
+        } else if (!enough) {
             // every pair against a threshold from a sample, lower ones while too few reach it
             streamed = 1;
             t_used = 0.0;
@@ -1380,14 +1500,13 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
                 const double want = more * (double)n_want;
                 double t = 0.0;
                 GTRY(B.sampled_threshold(want, t));
-                const unsigned long long all =
-                    (unsigned long long)g.nvol * (unsigned long long)(2 * g.N - g.nvol - 1) / 2;
-                const double room = std::min({1.25 * want + 65536.0, (double)all, 2147483647.0});
+                const double room = std::min({1.25 * want + 65536.0, (double)B.all(), 2147483647.0});
                 const size_t level = B.dev.blocks.size();
                 GTRY(B.all_pairs(t, 0, (unsigned long long)room, n_want, keys, codes, have, ranked));
                 if (have >= n_want || !(t > 0.0)) break;
                 GTRY(B.dev.drop(level));
             }
+            listed = have;
         }
         n_sel = std::min(have, n_want);
     }
@@ -1406,7 +1525,7 @@ sg_status graph_build(Ctx *ctx, const sg_graph_desc *d, hipStream_t st, int64_t 
     GTRY(B.dev.get(&up, N + 1));
     GTRY(B.dev.get(&down, N + 1));
     const int es = B.mark(B.ev_sort);
-    if (n_sel < have) GTRY(B.take(keys, codes, (long long)have, (long long)n_sel, codes));
+    if (n_sel && n_sel < listed) GTRY(B.take(keys, codes, (long long)listed, (long long)n_sel, codes));
     if (n_sel) {
         hipLaunchKernelGGL(k_graph_swap, dim3(blocks_for((long long)n_sel, 256)), dim3(256), 0, st, (long long)n_sel,
                            (const unsigned long long *)codes, rev);
