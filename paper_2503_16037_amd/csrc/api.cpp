@@ -123,8 +123,12 @@ void host_lattice(int N, std::vector<double> &p) {
 // (hx, hy) (hz, hx) (hy, hz) (lx, ly) for lanes 0..31 and (lz, lx) (ly, lz) (2^10, 0) (0, 0) for
 // lanes 32..63.  Points past the last are zero but for k = 13, -2^11, which the colouring's screen
 // multiplies by 2^10 (as rows they lose to every point) and the Voronoi cells' by zero.
+constexpr size_t kLatticeHalves = 4 * 64 * 4;  // words
+// the halves lie behind the lattice's doubles, on a 16-byte line
+size_t lattice_halves_at(int N) { return ((size_t)3 * N + 1) / 2 * 2; }
+size_t lattice_doubles(int N) { return lattice_halves_at(N) + kLatticeHalves / 2; }
 void host_lattice_halves(int N, const std::vector<double> &p, std::vector<unsigned> &out) {
-    out.assign(4 * 64 * 4, 0u);
+    out.assign(kLatticeHalves, 0u);
     auto pair = [](_Float16 a, _Float16 b) {
         unsigned short x, y;
         std::memcpy(&x, &a, 2);
@@ -1404,7 +1408,7 @@ void free_scene_impl(Scene *s) {
     if (s->ev_fork) (void)hipEventDestroy(s->ev_fork);
     if (s->ev_join) (void)hipEventDestroy(s->ev_join);
     s->ev_fork = s->ev_join = nullptr;
-    void *ptrs[] = {s->big, s->bigdir, s->bigrow, s->big_part, s->mu_s, s->mu_a, s->frac, s->albedo, s->abs_scale_d, s->pos, s->adj_ptr, s->adj_idx, s->lat, s->lat_halves,
+    void *ptrs[] = {s->big, s->bigdir, s->bigrow, s->big_part, s->mu_s, s->mu_a, s->frac, s->albedo, s->abs_scale_d, s->pos, s->adj_ptr, s->adj_idx, s->lat,
                     s->tab, s->lut, s->hull, s->rev, s->nodeoff, s->row_ptr, s->col_idx, s->scan_tmp, s->tau_s, s->tau_a, s->tsun_s,
                     s->tsun_a, s->T, s->Tsun, s->rho, s->val, s->S, s->x, s->y, s->c_rhs, s->c_a, s->c_b, s->qsun,
                     s->q, s->bS, s->bx, s->by, s->brho, s->bsrc, s->lam_buf, s->x64, s->r64, s->gm_V, s->partial, s->meas, s->meas_part, s->scal, s->J, s->pix,
@@ -1510,8 +1514,8 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
         SG_TRY(dalloc(s, &s.los_node, (size_t)n_el));
         SG_TRY(dalloc(s, &s.los_t, (size_t)n_el));
     }
-    SG_TRY(dalloc(s, &s.lat, (size_t)3 * s.n_fib));
-    SG_TRY(dalloc(s, &s.lat_halves, (size_t)4 * 64 * 4));
+    SG_TRY(dalloc(s, &s.lat, lattice_doubles(s.n_fib)));
+    s.lat_halves = reinterpret_cast<unsigned *>(s.lat + lattice_halves_at(s.n_fib));
     SG_TRY(dalloc(s, &s.tab, (size_t)(s.n_phase + 1) * s.n_fib));
     if (s.lut_n) SG_TRY(dalloc(s, &s.lut, (size_t)s.n_phase * s.lut_n));
     if (s.sigma_mode == SG_SIGMA_COLOUR) SG_TRY(dalloc(s, &s.hull, (size_t)s.n_fib * (kHullNb + 1)));
@@ -1623,10 +1627,12 @@ sg_status create_scene_impl(Ctx *ctx, const sg_scene_desc *d, hipStream_t st, Sc
         SG_TRY(upload(s, s.bigdir, bigdir.data(), sizeof(long long) * bigdir.size(), st));
         SG_TRY(upload(s, s.bigrow, bigrow.data(), sizeof(long long) * bigrow.size(), st));
     }
-    SG_TRY(upload(s, s.lat, lat.data(), sizeof(double) * lat.size(), st));
+    std::vector<double> lat_both(lattice_doubles(s.n_fib), 0.0);  // the lattice and its halves, one copy
+    std::copy(lat.begin(), lat.end(), lat_both.begin());
     std::vector<unsigned> halves;
     host_lattice_halves(s.n_fib, lat, halves);
-    SG_TRY(upload(s, s.lat_halves, halves.data(), sizeof(unsigned) * halves.size(), st));
+    std::memcpy(lat_both.data() + lattice_halves_at(s.n_fib), halves.data(), sizeof(unsigned) * halves.size());
+    SG_TRY(upload(s, s.lat, lat_both.data(), sizeof(double) * lat_both.size(), st));
     SG_TRY(upload(s, s.tab, tab.data(), sizeof(double) * tab.size(), st));
     if (s.E) {
         unsigned *bad = reinterpret_cast<unsigned *>(s.scal);
@@ -1762,7 +1768,7 @@ uint64_t reservations(const sg_scene_desc *d, const sg_solve_opts *o, bool with_
     bool table = false;
     for (int k = 0; k < d->n_phase; ++k) table = table || (d->phase_kind && d->phase_kind[k] == SG_PHASE_TABLE);
     uint64_t b = a(nvox, 4) * 2 + (np > 1 ? a(np * nvox, 4) : 0) + a(npx, 4) + a(3 * n, 4) + a(n + 1, 8) +
-                 a(e, 4) + a(3 * nf, 8) + a(4 * 64 * 4, 4) + a((np + 1) * nf, 8) + (table ? a(np * (uint64_t)d->phase_lut_n, 8) : 0) +
+                 a(e, 4) + a(lattice_doubles(d->n_fib), 8) + a((np + 1) * nf, 8) + (table ? a(np * (uint64_t)d->phase_lut_n, 8) : 0) +
                  (d->sigma_mode == SG_SIGMA_COLOUR ? a(nf * (kHullNb + 1), 4) : 0);
     if (d->n_nodes > 0)  // general nodes: their medium and the lines of sight's elements
         b += a(n_vol, 4) * 2 + (np > 1 ? a(np * n_vol, 4) : 0) + a(npx + 1, 8) + a(n_el, 4) + a(n_el, 8);

@@ -124,8 +124,8 @@ struct Scene {
     int *pos = nullptr;  // [N][3]
     long long *adj_ptr = nullptr;
     int *adj_idx = nullptr;
-    double *lat = nullptr;  // [n_fib][3]
-    unsigned *lat_halves = nullptr;  // [4][64][4]: the lattice as matrix operands of the phase cells (qbuild.hip)
+    double *lat = nullptr;  // [n_fib][3], then lat_halves
+    unsigned *lat_halves = nullptr;  // [4][64][4]: the lattice as matrix operands of the phase cells (qbuild.hip), in lat's block
     double *tab = nullptr;  // [n_phase + 1][n_fib]: HG tables, then the Lambertian cosine weights
 
     // structure
