@@ -61,20 +61,27 @@ def spmv_bytes(n_nodes: int, n_edges: int, nnz: int, real_bytes: int = 4, n_lamb
 # Lane operations per (incoming direction, out-edge, lattice point) of the phase-cell ownership
 # (Eq. 7): the algorithmic count is 5 (a 3-term dot product as one multiply and two FMAs, then
 # a compare and a select of the running argmax).  The kernel takes the dot products from the
-# matrix cores; every vector instruction it issues (counted on plume 64x64x32, its set-up and its columns
-# included) is 4.7 lane operations per triple, reported beside it
+# matrix cores, so 5 over the vector peak is a rate of work, not a share of the vector units; those
+# are busy with the instructions counted per triple (SQ_INSTS_VALU, 64 lanes each, the set-up and the
+# columns included), reported beside it for the workloads they were counted on
 QBUILD_OPS_PER_PAIR = 5
+QBUILD_OPS_ARE = ("the five algorithmic lane operations of a triple over the vector peak; three of them (the dot "
+                  "product) run on the matrix cores, so this may pass 1 and is not the vector units' utilisation")
+QBUILD_OPS_ISSUED_PER_PAIR = {"plume": 4.9, "cloud": 4.9, "slab": 4.9}
 # The nodes that a sweep over the front visits are not counted, so such sweeps count no bytes
 SWEEP_BYTES = "those of the whole sweeps, a lower bound: later sweeps visit the nodes whose inputs still move"
 
 
-def whole_sweeps(sz, launches, n_lambda):
+def whole_sweeps(sz, degrees, launches, n_lambda):
     """Of a solve's sweep launches, those that visit every node: the first three (four of a batch) where the
-    library goes over to the front (from 16 M matrix values, or 128 MB per sweep of a batch, on)."""
+    library goes over to the front: from 16 M matrix values on, without those of nodes above 64 couplings and
+    not where these hold most of the values; in a batch from 128 MB per sweep on in tiles of 8 and 16 lanes,
+    384 MB in full wavefronts (the tile a batch of more than 16 wavelengths takes here)."""
     if n_lambda == 1:
-        return min(launches, 3) if sz["nnz"] >= 16e6 else launches
-    return min(launches, 4) if 4 * sz["nnz"] + 8 * sz["n_edges"] * n_lambda >= 128e6 else launches
-QBUILD_OPS_ISSUED_PER_PAIR = 4.7
+        dense = float((degrees[degrees > 64].astype(np.float64) ** 2).sum())
+        return min(launches, 3) if sz["nnz"] - dense >= 16e6 and dense <= sz["nnz"] / 2 else launches
+    front = 4 * sz["nnz"] + 8 * sz["n_edges"] * n_lambda >= (128e6 if n_lambda <= 16 else 384e6)
+    return min(launches, 4) if front else launches
 
 
 def qbuild_pairs(scene) -> float:
@@ -399,7 +406,7 @@ def bench_graph(args):
                                   f"n = {n_pairs} strongest couplings", "parallelism": "single GPU"},
            "latency_ms": {"p50": round(float(np.percentile(lat, 50)), 4),
                           "p99": round(float(np.percentile(lat, 99)), 4)},
-           "roofline": {"kernel": "k_graph_pairs (count + fill passes)", "bound": "alu",
+           "roofline": {"kernel": "k_graph_eval (count + fill passes)", "bound": "alu",
                         "achieved": round(achieved, 3), "peak": round(ALU_PEAK_TOPS, 2), "unit": "T lane-op/s",
                         "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": None,
                         "algorithmic_per_launch": ops / 2, "avg_launch_ms": round(ms_pairs / 2, 5)},
@@ -520,7 +527,7 @@ def main():
     ap.add_argument("--couplings", type=float, default=None,
                     help="workload coupling: only this many couplings per voxel (for profiling)")
     ap.add_argument("--exact-cells", action="store_true",
-                    help="phase-cell owners by the FP64 scan alone (no FP32 screen; same results)")
+                    help="phase-cell owners by the FP64 scan alone (no screen; same results)")
     ap.add_argument("--sigma", default="voronoi", choices=["voronoi", "colour"],
                     help="phase cells: Voronoi ownership (default) or the paper's colouring with flood fill")
     args = ap.parse_args()
@@ -589,21 +596,24 @@ def main():
     # a sweep that computes the convergence measures also reads the previous iterate
     # (4 bytes per edge and wavelength): average over the timed launches
     monitored = sum(i["spmv_monitored"] for i in infos) / max(spmv_launches, 1)
-    whole = whole_sweeps(sz, spmv_launches / len(infos), g.n_lambda) / max(spmv_launches / len(infos), 1e-9)
+    whole = whole_sweeps(sz, np.diff(scene.adj_ptr), spmv_launches / len(infos), g.n_lambda) / max(spmv_launches / len(infos), 1e-9)
     sbytes = whole * (spmv_bytes(sz["n_nodes"], sz["n_edges"], sz["nnz"], n_lambda=g.n_lambda) +
                       monitored * 4 * sz["n_edges"] * g.n_lambda)
     qpairs = qbuild_pairs(scene)
     qops = QBUILD_OPS_PER_PAIR * qpairs
     if stages["ms_qbuild"] >= spmv_per_step_ms and g.n_lambda == 1:
         achieved = qops / (stages["ms_qbuild"] * 1e-3) / 1e12
-        issued = QBUILD_OPS_ISSUED_PER_PAIR * qpairs / (stages["ms_qbuild"] * 1e-3) / 1e12
+        per_pair = QBUILD_OPS_ISSUED_PER_PAIR.get(args.workload) if args.sigma != "colour" and screen else None
+        issued = per_pair and per_pair * qpairs / (stages["ms_qbuild"] * 1e-3) / 1e12
         roof = {"kernel": ("k_qcolour" if args.sigma == "colour" else "k_qbuild") + " (phase cells + K values + source)",
                 "bound": "alu",
                 "achieved": round(achieved, 3), "peak": round(ALU_PEAK_TOPS, 2), "unit": "T lane-op/s",
-                "frac": round(achieved / ALU_PEAK_TOPS, 4), "traffic": measured_traffic("k_qbuild", args.workload),
+                "frac": round(achieved / ALU_PEAK_TOPS, 4),
+                "traffic": measured_traffic("k_qbuild", args.workload) if args.sigma != "colour" and screen else None,
                 "algorithmic_per_launch": qops, "ops_per_pair": QBUILD_OPS_PER_PAIR,
                 "avg_launch_ms": round(stages["ms_qbuild"], 4),
-                "frac_issued": round(issued / ALU_PEAK_TOPS, 4), "ops_issued_per_pair": QBUILD_OPS_ISSUED_PER_PAIR}
+                "frac_is": QBUILD_OPS_ARE,
+                "frac_issued": issued and round(issued / ALU_PEAK_TOPS, 4), "ops_issued_per_pair": per_pair}
     else:
         achieved = sbytes / (spmv_avg_ms * 1e-3) / 1e9
         roof = {"kernel": "k_spmv (FP32 sweep)" if g.n_lambda == 1 else "k_spmm (FP32, all wavelengths)",
@@ -615,7 +625,7 @@ def main():
     cell_roof = {"kernel": "k_qcolour" if args.sigma == "colour" else "k_qbuild", "bound": "alu",
                  "avg_launch_ms": round(stages["ms_qbuild"], 4), "ops_per_pair": QBUILD_OPS_PER_PAIR,
                  "achieved": round(qops / (stages["ms_qbuild"] * 1e-3) / 1e12, 3), "unit": "T lane-op/s",
-                 "frac": round(qops / (stages["ms_qbuild"] * 1e-3) / 1e12 / ALU_PEAK_TOPS, 4),
+                 "frac": round(qops / (stages["ms_qbuild"] * 1e-3) / 1e12 / ALU_PEAK_TOPS, 4), "frac_is": QBUILD_OPS_ARE,
                  "owners": "FP64 scan only" if args.exact_cells else "matrix-core screen, FP64 scan where uncertified"}
     sweep_roof = {"kernel": "k_spmv", "avg_launch_ms": round(spmv_avg_ms, 5), "bytes_per_launch": round(sbytes),
                   "monitored_fraction": round(monitored, 4),

@@ -9,7 +9,7 @@
 // butterfly, then block, then one final block), so results are bit-identical
 // from run to run.
 //
-// Sweeps over the front.  From its third sweep on a series visits only the nodes that can
+// Sweeps over the front.  From its fourth sweep on a series visits only the nodes that can
 // still change: a node whose gathered inputs and own rows are the bits of the sweep before
 // gives the same bits again, so skipping it leaves every iterate as a whole sweep leaves
 // it (k_spmv_front).
